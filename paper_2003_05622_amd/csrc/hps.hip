@@ -23,6 +23,7 @@
 #include "partition.hpp"
 #include "pool.hpp"
 #include "push.hpp"
+#include "rows.hpp"
 #include "sort.hpp"
 #include "table.hpp"
 #include "mem_tier.hpp"
@@ -786,15 +787,15 @@ hps_status hps_insert(hps_table* t, const uint64_t* d_keys, uint64_t n, const fl
                       const float* d_acc, void* stream) {
   if (!t || (n && !d_keys) || (d_acc && !d_weights)) return HPS_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const unsigned blocks = grid_for(n, kProbeGroups * kProbeInFlight, kProbeMaxBlocks);
-  const unsigned lookup_blocks = grid_for(n, kLookupGroups * kProbeInFlight, kProbeMaxBlocks);
   if (n) {
-    if (d_weights)
-      lookup_keys<2><<<lookup_blocks, kProbeThreads, 0, s>>>(t->view, d_keys, n, nullptr, d_weights, d_acc,
-                                                             nullptr, nullptr, nullptr);
-    else
-      lookup_keys<1><<<lookup_blocks, kProbeThreads, 0, s>>>(t->view, d_keys, n, nullptr, nullptr, nullptr,
-                                                             nullptr, nullptr, nullptr);
+    const unsigned blocks = grid_for(n, kProbeGroups * kProbeInFlight, kProbeMaxBlocks);
+    const unsigned row_blocks = grid_for(n, kRowThreads, kRowMaxBlocks);
+    check_keys<<<grid_for(n, kRowThreads * 4, 2048), kRowThreads, 0, s>>>(d_keys, n, t->view.st);
+#define HPS_INSERT(BF16, VALUES) \
+    insert_rows<BF16, VALUES><<<row_blocks, kRowThreads, 0, s>>>(t->view, d_keys, n, d_weights, d_acc)
+    if (t->view.bf16) { if (d_weights) HPS_INSERT(true, true); else HPS_INSERT(true, false); }
+    else { if (d_weights) HPS_INSERT(false, true); else HPS_INSERT(false, false); }
+#undef HPS_INSERT
     insert_missing<<<blocks, kProbeThreads, 0, s>>>(t->view, d_keys, n, nullptr, nullptr, d_weights,
                                                     d_acc, nullptr, 0);
   }
@@ -1047,9 +1048,11 @@ hps_status hps_get(hps_table* t, const uint64_t* d_keys, uint64_t n, float* d_we
   if (!t || (n && (!d_keys || !d_weights_out || !d_acc_out || !d_found_out))) return HPS_EINVAL;
   if (n == 0) return HPS_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const unsigned blocks = grid_for(n, kLookupGroups * kProbeInFlight, kProbeMaxBlocks);
-  lookup_keys<3><<<blocks, kProbeThreads, 0, s>>>(t->view, d_keys, n, nullptr, nullptr, nullptr,
-                                                  d_weights_out, d_acc_out, d_found_out);
+  const unsigned blocks = grid_for(n, kRowThreads, kRowMaxBlocks);
+  if (t->view.bf16)
+    get_rows<true><<<blocks, kRowThreads, 0, s>>>(t->view, d_keys, n, d_weights_out, d_acc_out, d_found_out);
+  else
+    get_rows<false><<<blocks, kRowThreads, 0, s>>>(t->view, d_keys, n, d_weights_out, d_acc_out, d_found_out);
   return launch_ok() ? HPS_OK : HPS_EDEVICE;
 }
 
@@ -1058,12 +1061,13 @@ static hps_status dump_impl(hps_table* t, bool dirty, uint64_t* d_keys_out, floa
   if (!t || !h_n_rows) return HPS_EINVAL;
   if (max_rows && (!d_keys_out || !d_weights_out || !d_acc_out)) return HPS_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  const unsigned dump_blocks = grid_for(t->n_slots, kDumpSlots, kDumpMaxBlocks);
   clear_dump_count<<<1, 1, 0, s>>>(t->view.st);
   if (dirty)
-    dump_rows<true><<<4096, 256, 0, s>>>(t->view, d_keys_out, d_weights_out, d_acc_out, max_rows,
+    dump_rows<true><<<dump_blocks, kRowThreads, 0, s>>>(t->view, d_keys_out, d_weights_out, d_acc_out, max_rows,
                                          &t->view.st->dump_count);
   else
-    dump_rows<false><<<4096, 256, 0, s>>>(t->view, d_keys_out, d_weights_out, d_acc_out, max_rows,
+    dump_rows<false><<<dump_blocks, kRowThreads, 0, s>>>(t->view, d_keys_out, d_weights_out, d_acc_out, max_rows,
                                           &t->view.st->dump_count);
   if (!launch_ok()) return HPS_EDEVICE;
   unsigned long long count = 0;

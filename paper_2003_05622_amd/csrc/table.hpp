@@ -7,12 +7,13 @@
 //   w[n_slots][dim]          f32
 //   acc[n_slots][acc_len]    f32
 //
-// Looking keys up and creating the missing ones are two kernels, so that the room
-// check against the capacity is one consistent decision and no block has to hit a
-// single counter: lookup_keys counts the missing keys into sharded counters,
-// insert_missing (every block reads the same total) claims slots only if all of
-// them fit and counts the rows it creates, commit_insert adds that count to the
-// table size.
+// A lookup creates missing keys on the spot if the table has room even if every key it
+// looks up were new.  Otherwise creating them is a second kernel, so that the room check
+// against the capacity is one consistent decision and no block has to hit a single
+// counter: the lookup counts the missing keys into sharded counters, insert_missing
+// (every block reads the same total) claims slots only if all of them fit and counts
+// the rows it creates.  commit_insert adds the count of created rows to the table size.
+// rows.hpp: the entry points that move rows by key or by slot (insert, get, dump).
 #pragma once
 
 #include "common.hpp"
@@ -94,12 +95,22 @@ __device__ __forceinline__ float4 load_w4_as(const TableView& t, u64 row, u32 co
 __device__ __forceinline__ float4 load_w4(const TableView& t, u64 row, u32 col4) {
   return t.bf16 ? load_w4_as<true>(t, row, col4) : load_w4_as<false>(t, row, col4);
 }
-__device__ __forceinline__ void store_w4(const TableView& t, u64 row, u32 col4, float4 v) {
-  if (t.bf16)
+template <bool BF16>
+__device__ __forceinline__ void store_w4_as(const TableView& t, u64 row, u32 col4, float4 v) {
+  if (BF16)
     reinterpret_cast<uint2*>(w_row(t, row))[col4] = make_uint2(bf16_nearest(v.x) | (bf16_nearest(v.y) << 16),
                                                    bf16_nearest(v.z) | (bf16_nearest(v.w) << 16));
   else
     reinterpret_cast<float4*>(w_row(t, row))[col4] = v;
+}
+__device__ __forceinline__ void store_w4(const TableView& t, u64 row, u32 col4, float4 v) {
+  if (t.bf16) store_w4_as<true>(t, row, col4, v);
+  else store_w4_as<false>(t, row, col4, v);
+}
+// Elements 4*col4 .. 4*col4+3 of the initial row of the key whose mixed seed is `base`.
+__device__ __forceinline__ float4 init_weight4(u64 base, u32 col4, float range) {
+  return make_float4(init_weight(base, 4 * col4, range), init_weight(base, 4 * col4 + 1, range),
+                     init_weight(base, 4 * col4 + 2, range), init_weight(base, 4 * col4 + 3, range));
 }
 
 constexpr int kProbeThreads = 256;
@@ -377,22 +388,6 @@ __global__ void __launch_bounds__(256) commit_absent(TableState* st, HeavyRing* 
   }
 }
 
-// Walks key's probe sequence from `line` on.  Returns the slot of the key, or
-// kNoRow with `line` left at the first line that has a free slot (slot_key holds
-// this lane's slot of that line).  All 8 lanes of the group call it together.
-// No kernel that calls it changes slot keys, so plain (cacheable) loads are enough.
-__device__ __forceinline__ u32 probe_find(const TableView& t, u64 key, u32 sub, u64& line,
-                                          u64& slot_key) {
-  for (u64 step = 0; step < t.n_lines; ++step) {
-    const u32 hit = group_bits(__ballot(slot_key == key));
-    if (hit) return (u32)(line * kSlotsPerLine + (__ffs(hit) - 1));
-    if (group_bits(__ballot(slot_key == kEmptyKey))) return kNoRow;
-    line = line + 1 == t.n_lines ? 0 : line + 1;
-    slot_key = t.keys[line * kSlotsPerLine + sub];
-  }
-  return kNoRow;
-}
-
 // Where a key's probe sequence starts: an even line (n_lines is even), so that a 128-byte
 // memory line holds the first two lines of the sequence.
 __device__ __forceinline__ u64 home_line(const TableView& t, u64 key) {
@@ -406,21 +401,6 @@ __device__ __forceinline__ u32 group4_bits(u64 ballot) {
 }
 __device__ __forceinline__ ulonglong2 load_slot_pair(const TableView& t, u64 line, u32 sub) {
   return reinterpret_cast<const ulonglong2*>(t.keys)[line * (kSlotsPerLine / 2) + sub];
-}
-__device__ __forceinline__ u32 probe_find4(const TableView& t, u64 key, u32 sub, u64& line,
-                                           ulonglong2& pair) {
-  for (u64 step = 0; step < t.n_lines; ++step) {
-    // bit s: lane s's first slot, bit 4 + s: its second
-    const u32 hit = group4_bits(__ballot(pair.x == key)) | (group4_bits(__ballot(pair.y == key)) << 4);
-    if (hit) {
-      const u32 b = __ffs(hit) - 1;
-      return (u32)(line * kSlotsPerLine + 2 * (b & 3u) + (b >> 2));
-    }
-    if (group4_bits(__ballot(pair.x == kEmptyKey || pair.y == kEmptyKey))) return kNoRow;
-    line = line + 1 == t.n_lines ? 0 : line + 1;
-    pair = load_slot_pair(t, line, sub);
-  }
-  return kNoRow;
 }
 
 // Finds the key or claims a free slot for it.  *created tells which.
@@ -449,19 +429,32 @@ __device__ __forceinline__ u32 probe_find_or_claim(const TableView& t, u64 key, 
   return kNoRow;
 }
 
-// For a group of kLookupLanes lanes, after probe_find4 has returned kNoRow: claims a free slot
-// for the key, starting at `line` (whose slots `pair` holds; they may be out of date, the
-// compare-and-swap decides).  No other group creates the same key at the same time (the
-// keys of a pull are distinct), so only the free slot is raced for.  `seen` is what a first
-// compare-and-swap on slot `target` of the line returned (issued by the caller, so that
-// several keys' first attempts are in flight together).
+// For a group of kLookupLanes lanes, after search_keys has found a key absent: claims a free slot
+// for it, starting at `line` (whose slots may be out of date, the compare-and-swap decides).
+// `seen` is what a first compare-and-swap on slot `target` of the line returned (issued by the
+// caller, so that several keys' first attempts are in flight together).  *created tells whether
+// this group created the key.  DISTINCT: no other group creates the same key at the same time
+// (the keys of a pull), so only the free slot is raced for.  Otherwise another group may have put
+// the key there meanwhile: slots of a line are only ever claimed in one order (slot_of_bit) and
+// never freed, so whoever comes second meets the key before the next free slot.
+template <bool DISTINCT>
 __device__ __forceinline__ u32 claim_after4(const TableView& t, u64 key, u32 sub, u64 line, u32 target,
-                                            u64 seen) {
+                                            u64 seen, bool* created) {
+  *created = true;
   if (seen == kEmptyKey) return (u32)(line * kSlotsPerLine + target);
+  if (!DISTINCT && seen == key) { *created = false; return (u32)(line * kSlotsPerLine + target); }
   for (u64 step = 0; step < 2 * t.n_lines; ++step) {
     // another key took the slot, or the line is full: look at the line as it is now
     const u64 x = load_slot_key(&t.keys[line * kSlotsPerLine + 2 * sub]);
     const u64 y = load_slot_key(&t.keys[line * kSlotsPerLine + 2 * sub + 1]);
+    if (!DISTINCT) {
+      const u32 hit = group4_bits(__ballot(x == key)) | (group4_bits(__ballot(y == key)) << 4);
+      if (hit) {
+        const u32 h = __ffs(hit) - 1;
+        *created = false;
+        return (u32)(line * kSlotsPerLine + 2 * (h & 3u) + (h >> 2));
+      }
+    }
     const u32 free_slots = group4_bits(__ballot(x == kEmptyKey)) | (group4_bits(__ballot(y == kEmptyKey)) << 4);
     if (!free_slots) { line = line + 1 == t.n_lines ? 0 : line + 1; continue; }
     const u32 b = __ffs(free_slots) - 1;
@@ -472,76 +465,10 @@ __device__ __forceinline__ u32 claim_after4(const TableView& t, u64 key, u32 sub
                       (unsigned long long)kEmptyKey, (unsigned long long)key);
     got = __shfl(got, (int)((lane_id() & ~3u) + (b & 3u)), kWave);
     if (got == kEmptyKey) return (u32)(line * kSlotsPerLine + slot);
+    if (!DISTINCT && got == key) { *created = false; return (u32)(line * kSlotsPerLine + slot); }
   }
+  *created = false;
   return kNoRow;
-}
-
-// MODE 1  bulk insert, initial rows: missing keys counted, nothing written
-// MODE 2  bulk insert with values: present keys overwritten, missing keys counted
-// MODE 3  get: copy the row out, found flags
-// (The pull has a kernel of its own: pull_lookup.)
-template <int MODE>
-__global__ void __launch_bounds__(kProbeThreads)
-lookup_keys(TableView t, const u64* __restrict__ keys, u64 n_keys_host,
-            const u32* __restrict__ n_keys_dev,
-            const float* __restrict__ w_in, const float* __restrict__ acc_in,
-            float* __restrict__ w_out, float* __restrict__ acc_out,
-            uint8_t* __restrict__ found_out) {
-  __shared__ u32 s_missing;
-  const u64 n_keys = n_keys_dev ? (u64)*n_keys_dev : n_keys_host;
-  if (load_error(t.st) != 0) return;
-  if (threadIdx.x == 0) s_missing = 0;
-  __syncthreads();
-  const u32 sub = threadIdx.x % kLookupLanes;
-  const u64 group = (u64)blockIdx.x * kLookupGroups + threadIdx.x / kLookupLanes;
-  const u64 n_groups = (u64)gridDim.x * kLookupGroups;
-  u32 missing = 0;
-  for (u64 u0 = group; u0 < n_keys; u0 += n_groups * kProbeInFlight) {
-    u64 key[kProbeInFlight], line[kProbeInFlight];
-    ulonglong2 pair[kProbeInFlight];
-#pragma unroll
-    for (int k = 0; k < kProbeInFlight; ++k) {
-      const u64 u = u0 + (u64)k * n_groups;
-      key[k] = u < n_keys ? keys[u] : 0;
-      line[k] = home_line(t, key[k]);
-    }
-#pragma unroll
-    for (int k = 0; k < kProbeInFlight; ++k) {
-      const u64 u = u0 + (u64)k * n_groups;
-      pair[k] = u < n_keys ? load_slot_pair(t, line[k], sub) : make_ulonglong2(0, 0);
-    }
-#pragma unroll
-    for (int k = 0; k < kProbeInFlight; ++k) {
-      const u64 u = u0 + (u64)k * n_groups;
-      if (u >= n_keys) continue;
-      if (key[k] == kEmptyKey) {
-        if (MODE != 3) raise_error(t.st, kErrReserved);
-        if (MODE == 3 && sub == 0) found_out[u] = 0;
-        continue;
-      }
-      const u32 row = probe_find4(t, key[k], sub, line[k], pair[k]);
-      if (row == kNoRow && MODE != 3) ++missing;
-      if (MODE == 2 && row != kNoRow) {
-        for (u32 j = sub; j < t.dim; j += kLookupLanes) store_w(t, row, j, w_in[u * t.dim + j]);
-        float* ar = acc_row(t, row);
-        for (u32 j = sub; j < t.acc_len; j += kLookupLanes)
-          ar[j] = acc_in ? acc_value(acc_in[u * t.acc_len + j]) : t.init_acc;
-      }
-      if (MODE == 3) {
-        if (sub == 0) found_out[u] = row != kNoRow;
-        if (row != kNoRow) {
-          for (u32 j = sub; j < t.dim; j += kLookupLanes) w_out[u * t.dim + j] = load_w(t, row, j);
-          const float* ar = acc_row(t, row);
-          for (u32 j = sub; j < t.acc_len; j += kLookupLanes) acc_out[u * t.acc_len + j] = acc_value(ar[j]);
-        }
-      }
-    }
-  }
-  if (MODE == 1 || MODE == 2) {
-    if (sub == 0 && missing) atomicAdd(&s_missing, missing);
-    __syncthreads();
-    if (threadIdx.x == 0 && s_missing) atomicAdd(&t.st->miss_shard[blockIdx.x % kCountShards], s_missing);
-  }
 }
 
 // ---- the pull's lookup -------------------------------------------------------------------
@@ -591,6 +518,78 @@ __device__ __forceinline__ u32 bucket_bits(const BucketSlots& s, u64 key, u32 su
   m |= (s.b.x == key ? lo << 16 : 0u) | (s.b.y == key ? hi << 16 : 0u);
   m |= (s.b.x == kEmptyKey ? lo << 24 : 0u) | (s.b.y == kEmptyKey ? hi << 24 : 0u);
   return quad_or(m);
+}
+
+// Searches for the K keys a group of four lanes has in flight.  Key k is owned by lane k % 4 (as
+// its number k / 4): that lane keeps the key and, here, where its search stands (line) and what
+// came of it (row, or kNoRow); the group fetches them from it when needed.  Every phase runs for
+// all K keys before the next phase starts: a wave waits for memory once per round, not once per
+// key (16 groups share a wave, and nearly always one of them has a key that needs another
+// bucket).  Keys equal to kEmptyKey are not searched for.  Returns a mask: bit k = key k is absent,
+// and its owner's `line` and `free_at` name the first free slot for it (free_at: bit 3 = in the
+// line after `line`, bits 0..2 the slot).  The slots are read with plain (cacheable) loads: they
+// may be out of date where the same kernel creates keys, and the compare-and-swap decides.
+template <int K>
+__device__ __forceinline__ u32 search_keys(const TableView& t, const u64* my_key, u64* my_line, u32* my_row,
+                                           u32* my_free, u32 sub) {
+  constexpr int OWN = K / kLookupLanes;
+#pragma unroll
+  for (int o = 0; o < OWN; ++o) {
+    my_line[o] = home_line(t, my_key[o]);
+    my_row[o] = kNoRow;
+    my_free[o] = 0;
+  }
+  u32 open = 0;                 // bit k: key k is still being searched for
+  BucketSlots slots[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const u64 key = quad_lane(my_key[k / kLookupLanes], k % kLookupLanes);
+    const u64 line = quad_lane(my_line[k / kLookupLanes], k % kLookupLanes);
+    if (key != kEmptyKey) {
+      open |= 1u << k;
+      slots[k] = load_bucket(t, line, sub);
+    }
+  }
+  // rounds: look at the buckets at hand, fetch the next ones for the keys not settled
+  u32 to_create = 0;            // bit k: key k is absent; its owner's my_free names the slot for it
+  for (u64 step = 0; step < t.n_lines; step += 2) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (!(open >> k & 1u)) continue;
+      const int o = k / kLookupLanes;
+      const bool mine = sub == (u32)(k % kLookupLanes);
+      const u64 key = quad_lane(my_key[o], k % kLookupLanes);
+      const u32 bits = bucket_bits(slots[k], key, sub);
+      const u32 hit_a = bits & 0xFFu, free_a = (bits >> 8) & 0xFFu;
+      const u32 hit_b = (bits >> 16) & 0xFFu, free_b = bits >> 24;
+      // (a key sits in the first line of its sequence that had a free slot when it came: if
+      // the even line has a free slot the key is not in the odd one)
+      if (hit_a) {
+        if (mine) my_row[o] = (u32)(my_line[o] * kSlotsPerLine + slot_of_bit(__ffs(hit_a) - 1));
+        open &= ~(1u << k);
+      } else if (free_a) {
+        if (mine) my_free[o] = slot_of_bit(__ffs(free_a) - 1);
+        to_create |= 1u << k;
+        open &= ~(1u << k);
+      } else if (hit_b) {
+        if (mine) my_row[o] = (u32)((my_line[o] + 1) * kSlotsPerLine + slot_of_bit(__ffs(hit_b) - 1));
+        open &= ~(1u << k);
+      } else if (free_b) {
+        if (mine) my_free[o] = 8u | slot_of_bit(__ffs(free_b) - 1);
+        to_create |= 1u << k;
+        open &= ~(1u << k);
+      } else if (mine) {
+        my_line[o] = my_line[o] + 2 >= t.n_lines ? 0 : my_line[o] + 2;
+      }
+    }
+    if (!__any(open != 0)) break;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const u64 line = quad_lane(my_line[k / kLookupLanes], k % kLookupLanes);
+      if (open >> k & 1u) slots[k] = load_bucket(t, line, sub);
+    }
+  }
+  return to_create;
 }
 
 // rows[u] = the slot of unique key u, for u < *n_keys_dev.  Keys the table does not hold:
@@ -660,62 +659,7 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ n
       my_len[o] = u < n_keys ? often.seg_off[u + 1] - often.seg_off[u] : 0u;
       if (u < n_keys && my_key[o] == kEmptyKey) raise_error(t.st, kErrReserved);
     }
-#pragma unroll
-    for (int o = 0; o < OWN; ++o) {
-      my_line[o] = home_line(t, my_key[o]);
-      my_row[o] = kNoRow;
-      my_free[o] = 0;
-    }
-    u32 open = 0;                 // bit k: key k is still being searched for
-    BucketSlots slots[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const u64 key = quad_lane(my_key[k / kLookupLanes], k % kLookupLanes);
-      const u64 line = quad_lane(my_line[k / kLookupLanes], k % kLookupLanes);
-      if (key != kEmptyKey) {
-        open |= 1u << k;
-        slots[k] = load_bucket(t, line, sub);
-      }
-    }
-    // rounds: look at the buckets at hand, fetch the next ones for the keys not settled
-    u32 to_create = 0;            // bit k: key k is absent; its owner's my_free names the slot for it
-    for (u64 step = 0; step < t.n_lines; step += 2) {
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        if (!(open >> k & 1u)) continue;
-        const int o = k / kLookupLanes;
-        const bool mine = sub == (u32)(k % kLookupLanes);
-        const u64 key = quad_lane(my_key[o], k % kLookupLanes);
-        const u32 bits = bucket_bits(slots[k], key, sub);
-        const u32 hit_a = bits & 0xFFu, free_a = (bits >> 8) & 0xFFu;
-        const u32 hit_b = (bits >> 16) & 0xFFu, free_b = bits >> 24;
-        // (a key sits in the first line of its sequence that had a free slot when it came: if
-        // the even line has a free slot the key is not in the odd one)
-        if (hit_a) {
-          if (mine) my_row[o] = (u32)(my_line[o] * kSlotsPerLine + slot_of_bit(__ffs(hit_a) - 1));
-          open &= ~(1u << k);
-        } else if (free_a) {
-          if (mine) my_free[o] = slot_of_bit(__ffs(free_a) - 1);
-          to_create |= 1u << k;
-          open &= ~(1u << k);
-        } else if (hit_b) {
-          if (mine) my_row[o] = (u32)((my_line[o] + 1) * kSlotsPerLine + slot_of_bit(__ffs(hit_b) - 1));
-          open &= ~(1u << k);
-        } else if (free_b) {
-          if (mine) my_free[o] = 8u | slot_of_bit(__ffs(free_b) - 1);
-          to_create |= 1u << k;
-          open &= ~(1u << k);
-        } else if (mine) {
-          my_line[o] = my_line[o] + 2 >= t.n_lines ? 0 : my_line[o] + 2;
-        }
-      }
-      if (!__any(open != 0)) break;
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        const u64 line = quad_lane(my_line[k / kLookupLanes], k % kLookupLanes);
-        if (open >> k & 1u) slots[k] = load_bucket(t, line, sub);
-      }
-    }
+    const u32 to_create = search_keys<K>(t, my_key, my_line, my_row, my_free, sub);
     // keys to create: all first attempts in flight together, then whatever is left of each
     if (create_here && __any(to_create != 0)) {
       u64 seen[K];
@@ -740,7 +684,8 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ n
         const u32 slot = quad_lane(my_free[o], k % kLookupLanes) & 7u;
         if (!(to_create >> k & 1u)) continue;
         const u64 got = __shfl(seen[k], (int)(lane0 + (slot >> 1)), kWave);
-        const u32 row = claim_after4(t, key, sub, line, slot, got);
+        bool created;
+        const u32 row = claim_after4<true>(t, key, sub, line, slot, got, &created);
         if (row == kNoRow) {
           raise_error(t.st, kErrInternal);            // (cannot happen: the table has room)
           continue;
@@ -823,9 +768,7 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ n
   for (u32 e = threadIdx.x; e < n_new * dim4; e += kProbeThreads) {
     const u32 i = e / dim4, col = e % dim4;
     const u64 base = mix64(s_new_key[i] ^ t.init_seed);
-    store_w4(t, s_new_row[i], col,
-             make_float4(init_weight(base, 4 * col, t.init_range), init_weight(base, 4 * col + 1, t.init_range),
-                         init_weight(base, 4 * col + 2, t.init_range), init_weight(base, 4 * col + 3, t.init_range)));
+    store_w4(t, s_new_row[i], col, init_weight4(base, col, t.init_range));
   }
   for (u32 e = threadIdx.x; e < n_new * t.acc_len; e += kProbeThreads)
     acc_row(t, s_new_row[e / t.acc_len])[e % t.acc_len] = t.init_acc;
@@ -851,8 +794,8 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ n
   for (u32 i = threadIdx.x; i < cnt; i += kProbeThreads) dst[i] = s_list[i];
 }
 
-// Creates the keys lookup_keys found missing, if the table has room for all of them
-// (a key that occurs twice in a bulk insert is counted twice for this check).
+// Creates the keys that pull_lookup or insert_rows found missing and left to it, if the table has room for
+// all of them (a key that occurs twice in a bulk insert is counted twice for this check).
 // rows != null (pull): the listed missing keys are visited (or, after a list overflow,
 // all keys with rows[u] == kNoRow); rows[u] is set.
 // rows == null (bulk insert): every key is probed again.
@@ -919,39 +862,6 @@ insert_missing(TableView t, const u64* __restrict__ keys, u64 n_keys_host,
   if (sub == 0 && made) atomicAdd(&s_made, made);
   __syncthreads();
   if (threadIdx.x == 0 && s_made) atomicAdd(&t.st->made_shard[block % kCountShards], s_made);
-}
-
-// dump: every occupied slot (DIRTY: every occupied slot whose row is marked as
-// updated; the mark of a row that is written out is cleared), compacted through one
-// counter per block of slots (order unspecified).
-template <bool DIRTY>
-__global__ void __launch_bounds__(256)
-dump_rows(TableView t, u64* __restrict__ keys_out, float* __restrict__ w_out,
-          float* __restrict__ acc_out, u64 max_rows, unsigned long long* __restrict__ counter) {
-  __shared__ u32 scratch[256 / kWave + 1];
-  __shared__ unsigned long long s_base;
-  const u64 n_slots = t.n_lines * kSlotsPerLine;
-  const u64 n_rounds = (n_slots + 255) / 256;
-  for (u64 round = blockIdx.x; round < n_rounds; round += gridDim.x) {
-    const u64 s = round * 256 + threadIdx.x;
-    const u64 key = s < n_slots ? t.keys[s] : kEmptyKey;
-    bool used = key != kEmptyKey;
-    if (DIRTY && used) used = acc_is_marked(*acc_row(t, s));
-    u32 total;
-    const u32 before = block_excl_sum<256>(used ? 1u : 0u, scratch, &total);
-    if (threadIdx.x == 0 && total) s_base = atomicAdd(counter, (unsigned long long)total);
-    __syncthreads();
-    if (used) {
-      const u64 o = s_base + before;
-      if (o < max_rows) {
-        keys_out[o] = key;
-        for (u32 j = 0; j < t.dim; ++j) w_out[o * t.dim + j] = load_w(t, s, j);
-        for (u32 j = 0; j < t.acc_len; ++j) acc_out[o * t.acc_len + j] = acc_value(acc_row(t, s)[j]);
-        if (DIRTY) *acc_row(t, s) = acc_value(*acc_row(t, s));
-      }
-    }
-    __syncthreads();
-  }
 }
 
 // How many buckets (pairs of lines: 128 bytes) a lookup reads to find each stored key (1 = the
