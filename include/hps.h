@@ -56,17 +56,18 @@
  *   - The key dedup has two forms with identical results; the library picks one per call
  *     from the mini-batch's size and the table's history.  A table's third and later dedups
  *     use the keys that earlier lookups found frequent and run without any waits between
- *     workgroups (counts per tile, a scan, a scatter; then every region of the array is put
- *     in order inside one workgroup).  The lookups report back, into pinned host memory that
+ *     workgroups (counts per tile, a scan, a scatter into buckets; then every bucket's keys are
+ *     grouped inside one workgroup).  The lookups report back, into pinned host memory that
  *     nobody waits for, when the keys did not suit that form, and the next dedups then take
  *     the plain form (radix passes with look-back between tiles), sorting by all 64 key
- *     bits if need be: hps_stats().n_plain_fallbacks, .n_full_fallbacks.
+ *     bits if need be: hps_stats().n_plain_fallbacks, .n_full_fallbacks.  What a pull needs of
+ *     a dedup is the occurrences grouped by key; the ascending order of the unique keys is
+ *     worked out when hps_last_unique asks for it.
  *   - Environment variables, read by hps_create, for tests and comparison runs:
  *     HPS_DEDUP = "radix" | "bucket" pins the dedup's form; HPS_RANK = "ballot" ranks the
  *     elements of a sort tile with wave ballots even where the GPU's LDS atomics would
  *     serve (the faster way; hps_create checks on every GPU that they answer the lanes of
- *     an instruction in lane order, and uses ballots where they do not); HPS_POOL = "lds"
- *     makes the pooling kernel keep the most frequent keys' rows in LDS (measured slower);
+ *     an instruction in lane order, and uses ballots where they do not);
  *     HPS_ROWS = "apart" keeps weights and accumulators in arrays of their own also where
  *     the library would put them side by side (float32 rows, elementwise Adagrad);
  *     HPS_LOOKUP_NEW_LIST = n makes the pull's lookup use only n entries of the list in

@@ -24,11 +24,6 @@ constexpr int kErrInternal = -5;   // HPS_EDEVICE: a dedup's cross-workgroup wai
 // fix_mixed_runs can note; beyond that one workgroup puts the whole array in order.
 constexpr u32 kMaxEvidence = 1024;
 
-// Rows of the mini-batch's most frequent keys that every workgroup of the pooling kernel keeps
-// in LDS: at most kHotBytes of them (as float32) and at most kMaxHot keys.
-constexpr u32 kHotBytes = 16384;
-constexpr u32 kMaxHot = 512;
-
 constexpr int kCountShards = 64;   // counters that many blocks add to are spread over this many words
 
 // Lives in the table's storage for the table's whole life.
@@ -42,73 +37,62 @@ struct TableState {
   // over shards so that blocks do not all hit one address.
   u32 miss_shard[kCountShards];
   u32 made_shard[kCountShards];
-  u32 miss_overflow;            // the list of missing keys did not fit: scan instead
+  u32 pad;
   u32 probe_bad;                // result word of probe_lane_order (written once, at creation)
   // hps_probe_lengths: lines looked at to find each stored key, summed / the most for one key
   unsigned long long probe_sum;
   unsigned long long probe_max;
 };
 
-// Where a mini-batch's keys lie, estimated from a sample of them (sort_prepare).  The
-// dedup orders keys by rel = clamp(key - lo, 0, span) instead of by the key itself, which
+// Where a mini-batch's keys lie, estimated from a sample of them by the dedup's first kernel.
+// The dedup orders keys by rel = clamp(key - lo, 0, span) instead of by the key itself, which
 // is the same order, but raw ids that all share their leading bits spread over the
-// buckets / digits like hashed keys do (sort.hpp: range_rel, natural_bucket).
+// buckets / digits like hashed keys do (sort.hpp: range_rel; partition.hpp: bucket_of).
 struct KeyRange {
   u64 lo;
   u64 span;      // largest rel
-  u32 mult;      // bucket form: natural bucket = ((rel >> pre) * mult) >> 32
+  u32 mult;      // bucket form: bucket = ((rel >> pre) * mult) >> 32
   u32 pre;       //   (rel >> pre fits 32 bits)
-  u32 direct;    // bucket form: span is below the number of natural buckets, natural bucket = rel
+  u32 direct;    // bucket form: span is below the number of buckets, bucket = rel
   u32 base;      // plain form: the sorted digits start at this bit of rel
 };
 
 // Lives in the workspace; describes the outstanding pull.
 struct PullCtx {
-  u32 n_unique;        // U
+  u32 n_unique;        // plain form: number of distinct keys (bucket form: the sum of uniq_shard)
   u32 n_long;          // keys the push handles chunk by chunk
-  u32 n_slow;          // bucket form: occurrences in regions that did not fit LDS
+  u32 n_slow;          // bucket form: occurrences in buckets that were grouped through global memory
   u32 n_chunk_items;   // (key, chunk) work items of the push
-  u32 n_evidence;      // sorted positions where a run of equal sorted bits mixes keys
+  u32 n_evidence;      // plain form: sorted positions where a run of equal sorted bits mixes keys
   u32 sort_error;      // set if a look-back wait gave up (never expected)
   u32 n_total;         // occurrences of this dedup
   u32 by_id;           // 1: this dedup took the bucket form
-  u32 med_count[kCountShards];   // keys the push handles with one wave each, per list shard
-  KeyRange range;                // written by the dedup's first kernel for the later ones
-  u32 n_slow_one_key;            // ... of n_slow, in regions that one key fills at least half of
-  u32 n_hot;                     // keys listed for the pooling kernel's LDS-resident rows (pool.hpp)
+  u32 n_med;           // keys the push handles with one wave each
+  u32 n_heavy;         // bucket form: frequent keys with a bucket of their own
+  u32 ticket;          // bucket form: blocks of scan_buckets that are done
+  u32 n_slow_one_key;  // ... of n_slow, in buckets that one key fills at least half of
+  KeyRange range;      // plain form: for the kernels after the first
+  u32 uniq_shard[kCountShards];   // bucket form: distinct keys, spread over shards
 };
 
-// Keys that make up a large share of a mini-batch (bucket.hpp).  HeavySet: ascending,
-// padded with all-ones.  HeavyRaw: the keys the last lookup saw often, in arrival
-// order; only a hint, readers cope with any content.
-constexpr int kMaxHeavy = 4095;
-constexpr int kSmallHeavy = 1023;    // lists up to this long are copied to LDS by the kernels that look keys up in them
-constexpr int kHeavyTopBits = 10;
-struct HeavySet {
-  u32 count;
-  u32 pad;
-  u64 keys[kMaxHeavy + 1];
-  // per value of a key's top kHeavyTopBits bits: index of the first heavy key with these
-  // top bits (low half) and how many there are (high half)
-  u32 span[1 << kHeavyTopBits];
-};
+// Keys that make up a large share of a mini-batch ("heavy" keys): the bucket form gives each
+// of them a bucket of its own.  Which ones they are is a hint, taken from an earlier lookup,
+// which lists the keys it sees often in arrival order; readers cope with any content.
+// Lookup s (s = 1, 2, ...) fills raw[s % 3] and empties raw[(s + 1) % 3] for the next one.  A dedup
+// issued when s lookups have been issued reads raw[(s - 1) % 3]: lookup s - 1 is certainly
+// complete (the dedup waits for the push that released its context, which is push s - 1 or a
+// later one) and nobody appends to that list again before lookup s + 2, which comes after this
+// dedup's pull.  So every block of a dedup sees the same, unchanging list, whatever
+// streams the calls were issued on.
+constexpr int kMaxHeavy = 2047;
 struct HeavyRaw {
   u32 count;
   u32 pad;
   u64 keys[kMaxHeavy + 1];
 };
-// Lookup s (s = 1, 2, ...) fills raw[s % 3]; the push of the same pull (an extra block of
-// its kernel; for an accumulate the kernel after the lookup) puts that list in order as
-// set[s % 3] and empties raw[(s + 1) % 3] for the next lookup.  A dedup issued when s
-// lookups have been issued reads set[(s - 1) % 3]: the push of pull s - 1 is certainly
-// complete (the dedup waits for the push that released its context, which is that push or a
-// later one) and nobody writes the slot again before push s + 2, which comes after this
-// dedup's pull.  So every kernel of a dedup sees the same, unchanging list, whatever
-// streams the calls were issued on.
 constexpr u32 kHeavyRing = 3;
 struct HeavyRing {
   HeavyRaw raw[kHeavyRing];
-  HeavySet set[kHeavyRing];
 };
 
 // SplitMix64 output function for state x (Steele, Lea, Flood 2014).  The row
@@ -150,39 +134,42 @@ __device__ __forceinline__ u64 lanemask_lt() {
   return l == 0 ? 0ull : (~0ull >> (64 - l));
 }
 
+// One step of a wave-wide scan or reduction in the data-parallel-primitive form: lane l receives
+// lane l - 1, - 2, - 4 or - 8 of its row of 16 (CTRL 0x110 + distance), or the last lane of the row
+// / of the half before (0x142, 0x143, masked to the rows that need it); zero where there is none.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ u32 dpp_or_zero(u32 v) {
+  return (u32)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+
 // Inclusive sum over the 64 lanes of a wave.
 __device__ __forceinline__ u32 wave_incl_sum(u32 v) {
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const u32 o = __shfl_up(v, d, kWave);
-    if ((int)lane_id() >= d) v += o;
-  }
+  v += dpp_or_zero<0x111, 0xF>(v);
+  v += dpp_or_zero<0x112, 0xF>(v);
+  v += dpp_or_zero<0x114, 0xF>(v);
+  v += dpp_or_zero<0x118, 0xF>(v);
+  v += dpp_or_zero<0x142, 0xA>(v);
+  v += dpp_or_zero<0x143, 0xC>(v);
   return v;
 }
 
 // Exclusive sum over a block of THREADS threads (multiple of 64, at most 1024).
-// `scratch` needs THREADS/64 + 1 words of LDS.  Returns the exclusive prefix of v
+// `scratch` needs THREADS/64 words of LDS.  Returns the exclusive prefix of v
 // and the block total in *total.  Contains __syncthreads().
 template <int THREADS>
 __device__ __forceinline__ u32 block_excl_sum(u32 v, u32* scratch, u32* total) {
   constexpr int NW = THREADS / kWave;
   const u32 incl = wave_incl_sum(v);
-  const u32 w = threadIdx.x / kWave;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   __syncthreads();   // scratch may still be in use by a previous call
   if (lane_id() == kWave - 1) scratch[w] = incl;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    u32 run = 0;
-    for (int i = 0; i < NW; ++i) {
-      const u32 c = scratch[i];
-      scratch[i] = run;
-      run += c;
-    }
-    scratch[NW] = run;
-  }
-  __syncthreads();
-  *total = scratch[NW];
-  return scratch[w] + incl - v;
+  // every wave adds up the waves' sums for itself
+  const u32 c = lane_id() < (u32)NW ? scratch[lane_id()] : 0u;
+  const u32 upto = wave_incl_sum(c);
+  *total = (u32)__builtin_amdgcn_readlane((int)upto, kWave - 1);
+  const u32 before = (u32)__builtin_amdgcn_readlane((int)upto, w) - (u32)__builtin_amdgcn_readlane((int)c, w);
+  return before + incl - v;
 }
 
 __device__ __forceinline__ int load_error(const TableState* st) {

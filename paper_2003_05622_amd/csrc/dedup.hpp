@@ -3,8 +3,8 @@
 // (skeys[j], spay[j]; payload = occurrence index | bag << 32) to
 //   uniq[U]      ascending unique keys
 //   inverse[N]   rank of each occurrence's key among them
-//   bagperm[N]   bag of each occurrence, occurrences grouped by key (ascending key)
-//   seg_off[U+1] start of each key's group in bagperm
+//   bags[N]      bag of each occurrence, occurrences grouped by key (ascending key)
+//   seg_off[U+1] start of each key's group in bags
 //
 //   unique_emit     group heads, their running count across tiles by decoupled
 //                   look-back, and all outputs.  It also records "evidence": positions
@@ -167,7 +167,7 @@ fix_mixed_runs(u64* __restrict__ skeys, u64* __restrict__ sidx, u64* __restrict_
 // Heads of the key groups, their ranks, and every output of the dedup.
 //   head_rows [n_tiles] and head_groups [n_groups]: status words of the tiles' and
 //   tile groups' head counts (see sort.hpp), ticket: tile tickets
-//   bagperm[j] = bag of the occurrence at sorted position j, bit 31 set on group heads
+//   bags[j] = bag of the occurrence at sorted position j
 // REDO = false: the first instance; counts evidence.  REDO = true: the instance after
 // fix_mixed_runs; returns at once unless there was evidence.
 template <bool REDO>
@@ -176,13 +176,13 @@ unique_emit(const u64* __restrict__ skeys, const u64* __restrict__ spay, u32 n,
             u32* __restrict__ head_rows, u32* __restrict__ head_groups, u32 group,
             u32* __restrict__ ticket, u32 epoch,
             u32 n_bags, u64* __restrict__ uniq,
-            i32* __restrict__ inverse, u32* __restrict__ bagperm, u32* __restrict__ seg_off,
+            i32* __restrict__ inverse, u32* __restrict__ bags, u32* __restrict__ seg_off,
             PullCtx* __restrict__ ctx, u32* __restrict__ evidence, TableState* __restrict__ st) {
   __shared__ u32 scratch[kHeadThreads / kWave + 1];
   __shared__ u32 s_tile, s_earlier;
   __shared__ u64 lds_key[kHeadTile];     // the tile, read coalesced, handed out in runs of 8
   __shared__ u64 lds_pay[kHeadTile];
-  __shared__ u32 lds_out[kHeadTile];     // the bagperm words going out
+  __shared__ u32 lds_out[kHeadTile];     // the bags going out
   if (REDO && ctx->n_evidence == 0) return;
   const KeyRange range = ctx->range;
   if (threadIdx.x == 0) s_tile = atomicAdd(ticket, 1u);
@@ -260,7 +260,7 @@ unique_emit(const u64* __restrict__ skeys, const u64* __restrict__ spay, u32 n,
         if (key[k] == kEmptyKey) raise_error(st, kErrReserved);
         ++rank;
       }
-      lds_out[threadIdx.x * kHeadItems + k] = bag[k] | (head[k] ? 0x80000000u : 0u);
+      lds_out[threadIdx.x * kHeadItems + k] = bag[k];
       inverse[idx[k]] = (i32)(rank - 1);
     }
   }
@@ -268,7 +268,7 @@ unique_emit(const u64* __restrict__ skeys, const u64* __restrict__ spay, u32 n,
 #pragma unroll
   for (int k = 0; k < kHeadItems; ++k) {
     const u32 p = k * kHeadThreads + threadIdx.x;
-    if (tile_base + p < n) bagperm[tile_base + p] = lds_out[p];
+    if (tile_base + p < n) bags[tile_base + p] = lds_out[p];
   }
 }
 

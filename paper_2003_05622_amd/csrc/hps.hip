@@ -97,40 +97,105 @@ StorageLayout storage_layout(uint64_t n_slots, uint32_t dim, uint32_t acc_len, i
   return L;
 }
 
+// Bucket form of the dedup by number of occurrences: tiles (threads x items), number and mean size of
+// the natural buckets, heavy keys at most, threads of a bucket's workgroup (which holds
+// 8 * threads occurrences).  Small mini-batches take small tiles and buckets, so that they
+// spread over the GPU; large ones large tiles and buckets, so that a tile's run per bucket stays
+// long (large: 12288 / 2400 buckets = five occurrences, 40 bytes of keys).
+struct BucketSizes {
+  uint64_t max_n;
+  uint32_t threads, items, max_nat, mean, max_heavy, group_threads;
+};
+constexpr BucketSizes kBucketSizes[] = {
+    {1u << 16, 256, 4, 256, 256, 255, 256},
+    {1u << 20, 512, 8, 1024, 256, 1023, 256},
+    {3u << 20, 1024, 8, 1536, 2048, 2047, 512},
+    {12u << 20, 1024, 12, 3072, 4096, 2047, 1024},
+};
+constexpr int kBucketClasses = 4;
+constexpr int kMaxBuckets[kBucketClasses] = {512, 2048, 4096, 5120};
+constexpr bool bucket_sizes_ok() {
+  for (int k = 0; k < kBucketClasses; ++k) {
+    const BucketSizes& z = kBucketSizes[k];
+    if (z.max_nat + z.max_heavy > (uint32_t)kMaxBuckets[k] || z.max_nat + z.max_heavy > 8191) return false;
+    if (z.max_nat < z.max_n / z.mean && k != 1) return false;
+    if (k == 0 && z.max_n > kDirectTiles * z.threads * z.items) return false;
+    if (z.max_n > 1024u * z.threads * z.items) return false;       // scan_buckets: at most 64 tiles per wave
+  }
+  return true;
+}
+static_assert(bucket_sizes_ok(), "the kernels' limits");
+// Largest dedup the bucket form takes.
+constexpr uint64_t kBucketPathMaxKeys = kBucketSizes[kBucketClasses - 1].max_n;
+
+int bucket_class(uint64_t n) {
+  int k = 0;
+  while (k + 1 < kBucketClasses && n > kBucketSizes[k].max_n) ++k;
+  return k;
+}
+// A key with at least this many occurrences in a mini-batch of n is listed as heavy: an eighth of
+// what a bucket's workgroup holds, so that a few such keys the hint misses still fit one.
+uint32_t heavy_min(uint64_t n) {
+  const uint64_t share = n / kHeavyShare, eighth = kBucketSizes[bucket_class(n)].group_threads;
+  return (uint32_t)(share > eighth ? share : eighth);
+}
+BucketPlan bucket_plan(uint64_t n) {
+  const BucketSizes& z = kBucketSizes[bucket_class(n)];
+  BucketPlan p;
+  uint64_t nat = (n + z.mean - 1) / z.mean;
+  p.n_nat = (u32)(nat < 1 ? 1 : nat > z.max_nat ? z.max_nat : nat);
+  p.max_heavy = z.max_heavy;
+  p.stride = (p.n_nat + p.max_heavy + 63) / 64 * 64;
+  p.n_tiles = (u32)((n + z.threads * z.items - 1) / (z.threads * z.items));
+  return p;
+}
+// Counts a dedup of at most n occurrences keeps per (tile, bucket).
+uint64_t max_counts(uint64_t n) {
+  uint64_t most = 0;
+  for (int k = 0; k < kBucketClasses; ++k) {
+    const BucketPlan p = bucket_plan(n < kBucketSizes[k].max_n ? n : kBucketSizes[k].max_n);
+    const uint64_t c = (uint64_t)p.n_tiles * p.stride;
+    if (c > most) most = c;
+    if (n <= kBucketSizes[k].max_n) break;
+  }
+  return most;
+}
+
 // Per pull context (two of them, so that the dedup of the next mini-batch can run
 // while the current one is still between pull and push).
 struct ContextLayout {
-  size_t ctx, uniq, rows, inverse, bagperm, seg_off, inv_len, hot_list;
+  size_t ctx, uniq, rows, bags, seg_off, inv_len;
+  size_t code, from, upos, bucket_start, count;      // bucket form
+  size_t inverse;                                    // plain form (shares its memory with `code`)
 };
 
 struct WorkspaceLayout {
-  size_t keys_a, keys_b, keys_c, idx_a, idx_b, idx_c, id16, dig, part_hist, part_tot, borders, heavy_raw, ghist,
-      tickets, tile_rows, group_rows, head_rows, head_groups, evidence, bag_of, miss_list, med_list, long_list,
-      chunk_items, partials, total;
+  size_t keys_a, keys_b, keys_c, idx_a, idx_b, idx_c, hist, prefix, total, tile_bag, heavy_raw, ghist,
+      tickets, tile_rows, group_rows, head_rows, head_groups, evidence, bag_of, id16, by_pos, by_heavy, row_of,
+      bucket_total, med_list, long_list, chunk_items, partials, end;
   ContextLayout c[2];
-  uint64_t med_cap, max_long, max_items, sort_tiles, head_tiles, shard_cap;
+  uint64_t max_long, max_items, sort_tiles, head_tiles;
 };
 
 WorkspaceLayout workspace_layout(uint64_t n, uint64_t bags, uint32_t dim) {
   WorkspaceLayout L;
   const uint64_t n1 = n ? n : 1;
+  const uint64_t buckets = (uint64_t)kMaxBuckets[kBucketClasses - 1] + 1;
   L.sort_tiles = (n1 + kSortTile - 1) / kSortTile;
   L.head_tiles = (n1 + kHeadTile - 1) / kHeadTile;
-  L.med_cap = n1 / kCountShards + 2048;     // per shard: no shard's blocks see more keys
   L.max_long = n1 / (kMedSeg + 1) + 1;      // keys with more than kMedSeg occurrences
   L.max_items = n1 / kChunk + L.max_long + 1;
   size_t o = 0;
   L.keys_a = o;      o = align_up(o + n1 * 8);
   L.keys_b = o;      o = align_up(o + n1 * 8);
-  L.keys_c = o;      o = align_up(o + n1 * 8);    // scratch of a region ordered the slow way
+  L.keys_c = o;      o = align_up(o + n1 * 8);    // scratch of a bucket ordered the slow way
   L.idx_a = o;       o = align_up(o + n1 * 8);    // payloads: occurrence index | bag << 32
   L.idx_b = o;       o = align_up(o + n1 * 8);
   L.idx_c = o;       o = align_up(o + n1 * 8);
-  L.id16 = o;        o = align_up(o + n1 * 2);    // bucket id of every occurrence
-  L.dig = o;         o = align_up(o + n1 + 4);    // the ids' high bytes, ordered by the low bytes
-  L.part_hist = o;   o = align_up(o + (size_t)kRadix * L.sort_tiles * 4);   // [digit][tile] counts of a pass
-  L.part_tot = o;    o = align_up(o + kRadix * 4);
-  L.borders = o;     o = align_up(o + (n1 / kRegionSpan + 3) * 4);
+  L.hist = o;        o = align_up(o + max_counts(n1) * 2);    // bucket form: counts per (tile, bucket)
+  L.prefix = o;      o = align_up(o + max_counts(n1) * 4);    // ... and those of the tiles before
+  L.total = o;       o = align_up(o + buckets * 4);
+  L.tile_bag = o;    o = align_up(o + 1025 * 4);
   // from here to `evidence`: cleared at creation, never again (see sort.hpp)
   L.ghist = o;       o = align_up(o + 2 * (size_t)kHistWords * 4);
   L.tickets = o;     o = align_up(o + (kMaxPasses + 2) * 4);
@@ -140,24 +205,29 @@ WorkspaceLayout workspace_layout(uint64_t n, uint64_t bags, uint32_t dim) {
   L.head_groups = o; o = align_up(o + 2 * (L.head_tiles / kMinTileGroup + 1) * 4);
   L.evidence = o;    o = align_up(o + kMaxEvidence * 4);
   L.heavy_raw = o;   o = align_up(o + sizeof(HeavyRing));
-  L.bag_of = o;      o = align_up(o + n1 * 4);
-  L.shard_cap = n1 / kCountShards + kMissLdsCap;
-  L.miss_list = o;   o = align_up(o + (size_t)kCountShards * L.shard_cap * 4);
+  L.bag_of = L.id16 = o; o = align_up(o + n1 * 4);    // plain: bag of every occurrence; buckets: its bucket (16 bits)
   for (int k = 0; k < 2; ++k) {
     L.c[k].ctx = o;     o = align_up(o + sizeof(PullCtx));
     L.c[k].uniq = o;    o = align_up(o + n1 * 8);
     L.c[k].rows = o;    o = align_up(o + n1 * 4);
-    L.c[k].inverse = o; o = align_up(o + n1 * 4);
-    L.c[k].bagperm = o; o = align_up(o + n1 * 4);
+    L.c[k].bags = o;    o = align_up(o + n1 * 4);
     L.c[k].seg_off = o; o = align_up(o + (n1 + 1) * 4);
     L.c[k].inv_len = o; o = align_up(o + (bags ? bags : 1) * 4);    // mean pooling: 1 / bag length
-    L.c[k].hot_list = o; o = align_up(o + kMaxHot * 8);             // (unique index, row) of the most frequent keys
+    L.c[k].code = L.c[k].inverse = o; o = align_up(o + n1 * 4);
+    L.c[k].from = o;    o = align_up(o + n1 * 2);
+    L.c[k].upos = o;    o = align_up(o + n1 * 4);
+    L.c[k].bucket_start = o; o = align_up(o + (buckets + 1) * 4);
+    L.c[k].count = o;   o = align_up(o + buckets * 4);
   }
-  L.med_list = o;    o = align_up(o + (size_t)kCountShards * L.med_cap * 4);
+  L.by_pos = o;      o = align_up(o + n1 * 4);      // row of the key at every position
+  L.by_heavy = o;    o = align_up(o + (kMaxHeavy + 1) * 4);
+  L.row_of = o;      o = align_up(o + n1 * 4);      // row of every occurrence
+  L.bucket_total = o; o = align_up(o + buckets * 4);
+  L.med_list = o;    o = align_up(o + (n1 / (kShortSeg + 1) + kMaxHeavy + 64) * 4);
   L.long_list = o;   o = align_up(o + L.max_long * 8);
   L.chunk_items = o; o = align_up(o + L.max_items * 8);
   L.partials = o;    o = align_up(o + L.max_items * (size_t)dim * 4);
-  L.total = o;
+  L.end = o;
   return L;
 }
 
@@ -168,36 +238,8 @@ uint32_t tile_group(uint64_t n_tiles) {
   return g;
 }
 
-// Largest dedup the bucket path takes: beyond it a heavy key the hint misses could
-// hold more occurrences than a region has room for.
-constexpr uint64_t kBucketPathMaxKeys = 12ull << 20;
 constexpr uint64_t kPlainHold = 32;      // dedups in the plain form after the bucket form disappointed
 constexpr uint64_t kHintLag = 3;         // ... after a surprise that the next lists of frequent keys will cover
-static_assert(kChunkSpan + 2 * kNaturalBucket + kBucketPathMaxKeys / kHeavyShare + 64 <= kChunkThreads * kChunkItems,
-              "a region must have room for its span, a natural bucket and one heavy key the hint missed");
-
-// Bucket path: enough leading key bits that a natural bucket holds kNaturalBucket
-// occurrences on average at most; the passes sort by the bytes of the bucket id.  Up to
-// kOnePassMaxKeys occurrences 7 leading bits and 63 heavy keys do: ids below 256, one pass.
-constexpr uint64_t kOnePassMaxKeys = 1ull << 16;
-
-SortPlan bucket_plan(uint64_t n) {
-  SortPlan p;
-  int bits = 1;
-  while (bits < 15 && ((n + kNaturalBucket - 1) / kNaturalBucket) > (1ull << bits)) ++bits;
-  p.max_heavy = kMaxHeavy;
-  p.n_pass = 2;      // ids stay below 2^16 for every n the bucket path takes
-  if (n <= kOnePassMaxKeys) {
-    if (bits > 7) bits = 7;
-    p.max_heavy = 63;
-    p.n_pass = 1;
-  }
-  p.low_shift = 0;
-  p.group = tile_group((n + kSortTile - 1) / kSortTile);
-  p.by_id = 1;
-  p.nat_shift = 64 - bits;
-  return p;
-}
 
 // Plain form.  How many 8-bit digits to sort for n occurrences: enough that two different
 // keys rarely agree in all sorted bits.  With b sorted bits about n^2 / 2^(b+1) pairs of
@@ -206,9 +248,6 @@ SortPlan bucket_plan(uint64_t n) {
 // all_bits: every bit of the keys is sorted (eight passes), whatever the keys look like.
 SortPlan sort_plan(uint64_t n, bool all_bits) {
   SortPlan p;
-  p.by_id = 0;
-  p.nat_shift = 0;
-  p.max_heavy = 0;
   int log2n = 1;
   while ((1ull << log2n) < n) ++log2n;
   int want = (2 * log2n - 2 + 7) / 8;
@@ -264,10 +303,6 @@ struct hps_table {
   // How much of pull_lookup's per-block list of created keys is used: all of it, unless
   // HPS_LOOKUP_NEW_LIST says less (tests of what happens when it is full).
   u32 lookup_new_cap;
-  // The pooling kernel keeps the most frequent keys' rows in LDS (HPS_POOL=lds).  Off unless
-  // asked for: measured slower than reading them through L2 on every workload (the hash probe
-  // per occurrence costs more than the L2 hits it saves, and the LDS halves the occupancy).
-  bool hot_rows;
   uint64_t serial;     // number of dedups so far (status words carry it modulo kEpochMod)
   uint64_t plain_serial;   // ... of them in the plain form
   // Pinned host word the lookups report into (table.hpp: OftenLists::report).  When a dedup
@@ -292,6 +327,9 @@ struct hps_table {
     uint64_t n_keys, n_bags;
     const int32_t* d_offsets;
     bool mean;            // pooling of this pull (fixed when it is prepared)
+    bool buckets;         // its dedup took the bucket form ...
+    BucketPlan plan;      // ... with these sizes ...
+    u32 heavy_slot;       // ... and this list of frequent keys (common.hpp: HeavyRing)
     hipEvent_t ready;     // recorded after the dedup kernels
     hipEvent_t released;  // recorded after the push that used the context
     bool ready_set, released_set;
@@ -326,43 +364,70 @@ void stage_mark(hps_table* t, int stage, hipStream_t s) {
 }
 }  // namespace
 
-// Rows of frequent keys the pooling kernel keeps in LDS: as many as fit kHotBytes.  A key is
-// listed by the lookup if it has at least n / (8 * cap) occurrences, so that at most 8 * cap
-// keys can qualify and usually far fewer do.
-static u32 hot_capacity(uint32_t dim) {
-  const u32 cap = kHotBytes / (dim * 4);
-  return cap < kMaxHot ? cap : kMaxHot;
+static UniqueSpans unique_spans(const hps_table* t, int c, uint64_t n) {
+  const hps_table::Context& cx = t->cx[c];
+  UniqueSpans u;
+  if (cx.buckets) {
+    u.bucket_start = t->w<u32>(t->wl.c[c].bucket_start);
+    u.count = t->w<u32>(t->wl.c[c].count);
+    u.n_spans = cx.plan.n_nat;
+    u.max_heavy = cx.plan.max_heavy;
+    u.plain_span = 0;
+  } else {
+    u.bucket_start = u.count = nullptr;
+    // about 2000 blocks, however few keys there are (a few dozen keys per block still fill its waves)
+    u.plain_span = 32;
+    while (u.plain_span < 1024 && (uint64_t)u.plain_span * 2048 < n) u.plain_span *= 2;
+    u.n_spans = (u32)((n + u.plain_span - 1) / u.plain_span);
+    u.max_heavy = 0;
+  }
+  return u;
 }
 
+// spread (partition.hpp) with the tiles of a bucket-form dedup of n occurrences.
+static void launch_spread(const u32* code, const uint16_t* from, u32 n, u32 n_tiles, const u32* by_pos,
+                          const u32* by_heavy, u32* out, hipStream_t s) {
+#define HPS_SPREAD(K) \
+  spread<kBucketSizes[K].threads, kBucketSizes[K].items><<<n_tiles, kBucketSizes[K].threads, 0, s>>>(code, from, n, by_pos, by_heavy, out)
+  switch (bucket_class(n)) {
+    case 0: HPS_SPREAD(0); break;
+    case 1: HPS_SPREAD(1); break;
+    case 2: HPS_SPREAD(2); break;
+    default: HPS_SPREAD(3); break;
+  }
+#undef HPS_SPREAD
+}
+
+// Rows per occurrence (row_of), then the bags' sums.
 template <int LPR>
 static void launch_pool(hps_table* t, int c, float* d_pooled, hipStream_t s) {
   const hps_table::Context& cx = t->cx[c];
+  const ContextLayout& C = t->wl.c[c];
+  u32* row_of = t->w<u32>(t->wl.row_of);
+  if (cx.n_keys) {
+    const u32 n = (u32)cx.n_keys;
+    if (cx.buckets)
+      launch_spread(t->w<u32>(C.code), t->w<uint16_t>(C.from), n, cx.plan.n_tiles, t->w<u32>(t->wl.by_pos),
+                    t->w<u32>(t->wl.by_heavy), row_of, s);
+    else
+      rows_by_rank<<<grid_for(n, kPoolThreads * 4, 4096), kPoolThreads, 0, s>>>(t->view.st, t->w<i32>(C.inverse), t->w<u32>(C.rows), n, row_of);
+  }
   // (a block has 256 / LPR lane groups with eight rows in flight each: wide rows need more
   // blocks for as many rows in flight; d = 64: 0.293 ms with 1024 blocks, 0.247 with 4096, while
   // d = 16 runs the same with 1024 to 3072)
   const unsigned blocks = grid_for(cx.n_bags, kPoolThreads / LPR, kPoolMaxBlocks * (LPR > 4 ? LPR / 4 : 1));
-  float* inv_len = cx.mean ? t->w<float>(t->wl.c[c].inv_len) : nullptr;
-  const u32 cap = hot_capacity(t->dim);
-  const bool hot = t->hot_rows && cap >= 8;
-#define HPS_POOL(COLS, HOT)                                                                     \
-  pool_bags<LPR, COLS, HOT><<<blocks, kPoolThreads, 0, s>>>(                                    \
-      t->view, cx.d_offsets, (u32)cx.n_bags, (u32)cx.n_keys, t->w<i32>(t->wl.c[c].inverse),     \
-      t->w<u32>(t->wl.c[c].rows), d_pooled, inv_len, t->w<uint2>(t->wl.c[c].hot_list),          \
-      &t->ctx(c)->n_hot, cap)
-  if (t->dim <= (uint32_t)LPR * 4) {
-    if (hot) HPS_POOL(1, true); else HPS_POOL(1, false);
-  } else {
-    if (hot) HPS_POOL(4, true); else HPS_POOL(4, false);
-  }
-#undef HPS_POOL
+  float* inv_len = cx.mean ? t->w<float>(C.inv_len) : nullptr;
+  if (t->dim <= (uint32_t)LPR * 4)
+    pool_bags<LPR, 1><<<blocks, kPoolThreads, 0, s>>>(t->view, cx.d_offsets, (u32)cx.n_bags, (u32)cx.n_keys, row_of, d_pooled, inv_len);
+  else
+    pool_bags<LPR, 4><<<blocks, kPoolThreads, 0, s>>>(t->view, cx.d_offsets, (u32)cx.n_bags, (u32)cx.n_keys, row_of, d_pooled, inv_len);
 }
 
 template <int LPR>
 static void launch_push(hps_table* t, uint64_t n, PushArgs& a, hipStream_t s) {
-  a.short_blocks = grid_for(n, kPushThreads / LPR, kPushShortBlocks);
   a.medium_blocks = kPushMediumBlocks;
   const unsigned chunk_blocks = grid_for(n / kChunk + 1, 1, kPushChunkBlocks);
-  const unsigned main_blocks = a.short_blocks + a.medium_blocks + chunk_blocks + (a.ring ? 1 : 0);
+  const unsigned main_blocks = span_blocks(a.spans) + a.medium_blocks + chunk_blocks;
   const unsigned long_blocks = grid_for(n / (kMedSeg + 1) + 1, 1, kPushLongBlocks);
   if (t->dim <= (uint32_t)LPR * 4) {
     push_main<LPR, 1><<<main_blocks, kPushThreads, 0, s>>>(t->view, a);
@@ -373,13 +438,59 @@ static void launch_push(hps_table* t, uint64_t n, PushArgs& a, hipStream_t s) {
   }
 }
 
-// a1 for context c: the kernels that turn (keys, offsets) into uniq / inverse / bagperm /
-// seg_off.  d_offsets == nullptr: every occurrence is its own bag.
+// The bucket form's kernels for context c (partition.hpp, bucket.hpp), size class K.
+template <int K>
+static void launch_buckets(hps_table* t, int c, const uint64_t* d_keys, u32 n, const int32_t* d_offsets, u32 n_bags,
+                           const HeavyRaw* heavy, hipStream_t s) {
+  constexpr int kThreads = kBucketSizes[K].threads, kItems = kBucketSizes[K].items, kGroup = kBucketSizes[K].group_threads;
+  constexpr bool kDirect = K == 0;
+  const WorkspaceLayout& L = t->wl;
+  const ContextLayout& C = L.c[c];
+  const BucketPlan plan = t->cx[c].plan;
+  PullCtx* ctx = t->ctx(c);
+  uint16_t* id16 = t->w<uint16_t>(L.id16);
+  uint16_t* hist = t->w<uint16_t>(L.hist);
+  u32* prefix = t->w<u32>(L.prefix);
+  u32* tile_bag = t->w<u32>(L.tile_bag);
+  u32* bucket_start = t->w<u32>(C.bucket_start);
+  u64* keys = t->w<u64>(L.keys_a);
+  u32* bags = t->w<u32>(C.bags);
+  const unsigned bag_blocks = d_offsets ? grid_for(n_bags, kThreads * 4, 256) : 0;
+  bucket_count<kThreads, kItems, kMaxBuckets[K]><<<plan.n_tiles + bag_blocks, kThreads, 0, s>>>(
+      d_keys, n, plan, ctx, d_offsets, n_bags, tile_bag, heavy, id16, hist);
+  if (!kDirect) {
+    const unsigned blocks = (plan.n_nat + plan.max_heavy + kWave - 1) / kWave;
+#define HPS_SCAN(PER) scan_buckets<PER><<<blocks, kScanThreads, 0, s>>>(hist, plan, prefix, t->w<u32>(L.total), bucket_start, ctx)
+    if (plan.n_tiles <= 16 * kScanWaves) HPS_SCAN(16);
+    else if (plan.n_tiles <= 32 * kScanWaves) HPS_SCAN(32);
+    else HPS_SCAN(64);
+#undef HPS_SCAN
+  }
+#define HPS_ORDERED(ORDERED)                                                                                      \
+  do {                                                                                                            \
+    bucket_scatter<kThreads, kItems, kMaxBuckets[K], ORDERED, kDirect><<<plan.n_tiles, kThreads, 0, s>>>(         \
+        d_keys, id16, d_offsets, n_bags, tile_bag, n, plan, ctx, hist, prefix, bucket_start, keys, bags,          \
+        t->w<u32>(C.code), t->w<uint16_t>(C.from));                                                               \
+    stage_mark(t, HPS_STAGE_SORT, s);                                                                             \
+    stage_mark(t, HPS_STAGE_UNIQUE, s);                                                                           \
+    group_bucket<kGroup, ORDERED><<<plan.n_nat, kGroup, 0, s>>>(                                                  \
+        keys, bucket_start, t->w<u64>(C.uniq), t->w<u32>(C.seg_off), bags, t->w<u32>(C.upos),                     \
+        t->w<u32>(C.count), slow, ctx, t->view.st);                                                               \
+  } while (0)
+  const SlowScratch slow = {t->w<u64>(L.idx_a), t->w<u64>(L.keys_b), t->w<u64>(L.idx_b), t->w<u64>(L.keys_c), t->w<u64>(L.idx_c)};
+  if (t->ordered_rank) HPS_ORDERED(true);
+  else HPS_ORDERED(false);
+#undef HPS_ORDERED
+}
+
+// a1 for context c: the kernels that turn (keys, offsets) into the distinct keys and the
+// occurrences' bags grouped by key.  d_offsets == nullptr: every occurrence is its own bag.
 static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
                          const int32_t* d_offsets, u32 n_bags, hipStream_t s) {
   const WorkspaceLayout& L = t->wl;
   const ContextLayout& C = L.c[c];
   PullCtx* ctx = t->ctx(c);
+  t->cx[c].buckets = false;
   if (n == 0) {
     set_ctx_empty<<<1, 64, 0, s>>>(ctx, t->w<u32>(C.seg_off));
   } else {
@@ -419,70 +530,27 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
     }
     const bool buckets = n <= kBucketPathMaxKeys && t->dedup_mode != 1 &&
                          (t->dedup_mode == 2 || (t->lookup_serial >= 2 && t->serial >= t->plain_until));
-    const SortPlan plan = buckets ? bucket_plan(n) : sort_plan(n, t->dedup_mode != 2 && t->serial < t->full_until);
-    u64* kcur = t->w<u64>(L.keys_a);
-    u64* kalt = t->w<u64>(L.keys_b);
-    u64* pcur = t->w<u64>(L.idx_a);
-    u64* palt = t->w<u64>(L.idx_b);
-    u32* tickets = t->w<u32>(L.tickets);
-    const unsigned n_tiles = (n + kSortTile - 1) / kSortTile;
-    const unsigned bag_blocks = grid_for(d_offsets ? n_bags : n, kPrepThreads, 256);
+    t->cx[c].buckets = buckets;
     if (buckets) {
+      t->cx[c].plan = bucket_plan(n);
       // the most recent list of frequent keys that is certainly complete (common.hpp)
-      const HeavySet* heavy =
-          &t->w<HeavyRing>(L.heavy_raw)->set[(t->lookup_serial + kHeavyRing - 1) % kHeavyRing];
-      const unsigned count_blocks = n_tiles < 1024 ? n_tiles : 1024;
-      const unsigned n_regions = (n + kRegionSpan - 1) / kRegionSpan;
-      u32* hist = t->w<u32>(L.part_hist);
-      u32* tot = t->w<u32>(L.part_tot);
-      uint8_t* dig = plan.n_pass == 2 ? t->w<uint8_t>(L.dig) : nullptr;
-      bucket_count<<<count_blocks + bag_blocks, kPrepThreads, 0, s>>>(
-          d_keys, n, plan, tickets, ctx, d_offsets, n_bags, t->w<i32>(L.bag_of), heavy,
-          t->w<uint16_t>(L.id16), hist, n_tiles, count_blocks);
-      // (the first scan also clears the status words of region_sort_emit: one per region and
-      // one per group of regions, laid out back to back)
-      scan_tiles<<<kRadix, kPartThreads, 0, s>>>(hist, n_tiles, tot, t->w<u32>(L.head_rows),
-                                                 (u32)((L.evidence - L.head_rows) / 4));
-#define HPS_SCATTER(FIRST, ...)                                                          \
-  do {                                                                                  \
-    if (t->ordered_rank) scatter_pass<FIRST, true><<<n_tiles, kPartThreads, 0, s>>>(__VA_ARGS__);  \
-    else scatter_pass<FIRST, false><<<n_tiles, kPartThreads, 0, s>>>(__VA_ARGS__);      \
-  } while (0)
-      HPS_SCATTER(true, d_keys, nullptr, t->w<i32>(L.bag_of), t->w<uint16_t>(L.id16), nullptr, kcur, pcur,
-                  dig, n, hist, n_tiles, tot);
-      if (plan.n_pass == 2) {
-        digit_count<<<n_tiles, kPartThreads, 0, s>>>(dig, n, hist, n_tiles);
-        scan_tiles<<<kRadix, kPartThreads, 0, s>>>(hist, n_tiles, tot, nullptr, 0);
-        HPS_SCATTER(false, kcur, pcur, nullptr, nullptr, dig, kalt, palt, nullptr, n, hist, n_tiles, tot);
-        u64* tk = kcur; kcur = kalt; kalt = tk;
-        tk = pcur; pcur = palt; palt = tk;
+      t->cx[c].heavy_slot = (u32)((t->lookup_serial + kHeavyRing - 1) % kHeavyRing);
+      const HeavyRaw* heavy = &t->w<HeavyRing>(L.heavy_raw)->raw[t->cx[c].heavy_slot];
+      switch (bucket_class(n)) {
+        case 0: launch_buckets<0>(t, c, d_keys, n, d_offsets, n_bags, heavy, s); break;
+        case 1: launch_buckets<1>(t, c, d_keys, n, d_offsets, n_bags, heavy, s); break;
+        case 2: launch_buckets<2>(t, c, d_keys, n, d_offsets, n_bags, heavy, s); break;
+        default: launch_buckets<3>(t, c, d_keys, n, d_offsets, n_bags, heavy, s); break;
       }
-      stage_mark(t, HPS_STAGE_SORT, s);
-      // a1: unique keys, ranks, grouping
-      stage_mark(t, HPS_STAGE_UNIQUE, s);
-      u32* borders = t->w<u32>(L.borders);
-      region_borders<<<(n_regions + 1 + kPartWaves - 1) / kPartWaves, kPartThreads, 0, s>>>(
-          kcur, n, n_regions, plan.max_heavy, heavy, ctx, borders);
-#undef HPS_SCATTER
-      // region_sort's notes for region_emit: heads per region and per group of regions (the
-      // status words the first scan cleared), how each region was ordered, and the order itself
-      // (in bag_of, which the first scatter has finished with)
-      u32* region_heads = t->w<u32>(L.head_rows);
-      u32* region_kind = t->w<u32>(L.head_rows) + L.head_tiles;
-      u32* group_heads = t->w<u32>(L.head_groups);
-      u32* order = t->w<u32>(L.bag_of);
-#define HPS_REGIONS(ORDERED)                                                                       \
-  region_sort<kChunkItems, ORDERED><<<n_regions, kChunkThreads, 0, s>>>(                           \
-      kcur, pcur, kalt, palt, t->w<u64>(L.keys_c), t->w<u64>(L.idx_c), n, borders, region_kind,    \
-      region_heads, group_heads, order, ctx)
-      if (t->ordered_rank) HPS_REGIONS(true);
-      else HPS_REGIONS(false);
-#undef HPS_REGIONS
-      region_emit<<<n_regions, kChunkThreads, 0, s>>>(
-          kcur, pcur, kalt, palt, t->w<u64>(L.keys_c), t->w<u64>(L.idx_c), n, borders, region_kind,
-          region_heads, group_heads, order, n_bags, t->w<u64>(C.uniq), t->w<i32>(C.inverse),
-          t->w<u32>(C.bagperm), t->w<u32>(C.seg_off), ctx, t->view.st);
     } else {
+      const SortPlan plan = sort_plan(n, t->dedup_mode != 2 && t->serial < t->full_until);
+      u64* kcur = t->w<u64>(L.keys_a);
+      u64* kalt = t->w<u64>(L.keys_b);
+      u64* pcur = t->w<u64>(L.idx_a);
+      u64* palt = t->w<u64>(L.idx_b);
+      u32* tickets = t->w<u32>(L.tickets);
+      const unsigned n_tiles = (n + kSortTile - 1) / kSortTile;
+      const unsigned bag_blocks = grid_for(d_offsets ? n_bags : n, kPrepThreads, 256);
       // two sets of digit histograms: a plain dedup counts into one and clears the other for
       // the next plain dedup
       ++t->plain_serial;
@@ -517,66 +585,71 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
       unique_emit<false><<<head_tiles, kHeadThreads, 0, s>>>(
           kcur, pcur, n, t->w<u32>(L.head_rows), t->w<u32>(L.head_groups), head_group,
           tickets + kMaxPasses, epoch, n_bags, t->w<u64>(C.uniq),
-          t->w<i32>(C.inverse), t->w<u32>(C.bagperm), t->w<u32>(C.seg_off), ctx, evidence, t->view.st);
+          t->w<i32>(C.inverse), t->w<u32>(C.bags), t->w<u32>(C.seg_off), ctx, evidence, t->view.st);
       fix_mixed_runs<<<1, kFixThreads, 0, s>>>(kcur, pcur, kalt, palt, n, ctx, evidence);
       unique_emit<true><<<head_tiles, kHeadThreads, 0, s>>>(
           kcur, pcur, n, t->w<u32>(L.head_rows) + L.head_tiles,
           t->w<u32>(L.head_groups) + (L.head_tiles / kMinTileGroup + 1), head_group,
           tickets + kMaxPasses + 1, epoch, n_bags, t->w<u64>(C.uniq),
-          t->w<i32>(C.inverse), t->w<u32>(C.bagperm), t->w<u32>(C.seg_off), ctx, evidence, t->view.st);
+          t->w<i32>(C.inverse), t->w<u32>(C.bags), t->w<u32>(C.seg_off), ctx, evidence, t->view.st);
     }
     stage_mark(t, HPS_STAGE_UNIQUE, s);
   }
 }
 
-// a2 without creating anything, for context c: rows of the unique keys (kNoRow for a
-// key the table does not hold) and the push's work lists.
+// What a lookup of context c hands on besides rows[]: the rows by position (bucket form, for the
+// pooling; an accumulate has none).
+static RowsByPosition rows_by_position_args(const hps_table* t, int c, bool pull) {
+  const hps_table::Context& cx = t->cx[c];
+  RowsByPosition out;
+  out.upos = pull && cx.buckets ? t->w<u32>(t->wl.c[c].upos) : nullptr;
+  out.by_pos = t->w<u32>(t->wl.by_pos);
+  out.by_heavy = t->w<u32>(t->wl.by_heavy);
+  out.heavy_keys = cx.buckets ? t->w<HeavyRing>(t->wl.heavy_raw)->raw[cx.heavy_slot].keys : nullptr;
+  return out;
+}
+
+// a2 for context c: rows of the distinct keys (kNoRow for a key the table does not hold and, unless
+// `create`, does not get) and the push's work lists.
 static void launch_lookup(hps_table* t, int c, uint64_t n_keys, bool create, hipStream_t s) {
   const ContextLayout& C = t->wl.c[c];
   PullCtx* ctx = t->ctx(c);
+  HeavyRing* ring = t->w<HeavyRing>(t->wl.heavy_raw);
   OftenLists often;
-  often.seg_off = t->w<u32>(C.seg_off);
   often.ctx = ctx;
   often.med_list = t->w<u32>(t->wl.med_list);
-  often.med_cap = (u32)t->wl.med_cap;
   often.long_list = t->w<uint2>(t->wl.long_list);
   often.chunk_items = t->w<uint2>(t->wl.chunk_items);
   ++t->lookup_serial;
-  often.heavy_raw = &t->w<HeavyRing>(t->wl.heavy_raw)->raw[t->lookup_serial % kHeavyRing];
-  often.heavy_min = (u32)(n_keys / kHeavyShare > kHeavyMin ? n_keys / kHeavyShare : kHeavyMin);
-  often.hot_list = t->w<uint2>(C.hot_list);
-  often.hot_cap = hot_capacity(t->dim);
-  // at most 8 * cap keys can have this many occurrences; 0 occurrences never qualify
-  often.hot_min = ~0u;                       // nothing is listed
-  if (t->hot_rows && often.hot_cap >= 8)
-    often.hot_min = (u32)(n_keys / (8ull * often.hot_cap) > 8 ? n_keys / (8ull * often.hot_cap) : 8);
+  often.heavy_raw = &ring->raw[t->lookup_serial % kHeavyRing];
+  often.heavy_next = &ring->raw[(t->lookup_serial + 1) % kHeavyRing];
+  often.heavy_min = heavy_min(n_keys);
   often.report = t->report;
   often.serial = (u32)t->lookup_serial;
-  const unsigned probe_blocks = grid_for(n_keys, kLookupGroups * kPullInFlight, kProbeMaxBlocks);
-  pull_lookup<<<probe_blocks, kProbeThreads, 0, s>>>(
-      t->view, t->w<u64>(C.uniq), &ctx->n_unique, t->w<u32>(C.rows), t->w<u32>(t->wl.miss_list),
-      (u32)t->wl.shard_cap, create ? 1u : 0u, t->lookup_new_cap, often);
-
+  const UniqueSpans spans = unique_spans(t, c, n_keys);
+  const RowsByPosition out = rows_by_position_args(t, c, create);
+  pull_lookup<<<span_blocks(spans), kProbeThreads, 0, s>>>(t->view, t->w<u64>(C.uniq), t->w<u32>(C.seg_off), spans,
+                                                           t->w<u32>(C.rows), out, create ? 1u : 0u, t->lookup_new_cap, often);
+  if (create)
+    pull_missing<<<span_blocks(spans), kProbeThreads, 0, s>>>(t->view, t->w<u64>(C.uniq), spans, ctx, t->w<u32>(C.rows), out);
 }
 
-static void fill_push_args(hps_table* t, int c, const float* d_rows, int kind, PushArgs& a) {
+static void fill_push_args(hps_table* t, int c, uint64_t n_keys, const float* d_rows, int kind, PushArgs& a) {
   const WorkspaceLayout& L = t->wl;
+  a.spans = unique_spans(t, c, n_keys);
   a.seg_off = t->w<u32>(L.c[c].seg_off);
-  a.bagperm = t->w<u32>(L.c[c].bagperm);
+  a.bags = t->w<u32>(L.c[c].bags);
   a.rows = t->w<u32>(L.c[c].rows);
   a.grads = d_rows;
   a.inv_len = nullptr;
   a.ctx = t->ctx(c);
   a.med_list = t->w<u32>(L.med_list);
-  a.med_cap = (u32)L.med_cap;
   a.long_list = t->w<uint2>(L.long_list);
   a.chunk_items = t->w<uint2>(L.chunk_items);
   a.partials = t->w<float>(L.partials);
   a.lr = t->opt.lr;
   a.eps = t->opt.eps;
   a.kind = kind;
-  a.ring = nullptr;
-  a.ring_slot = 0;
 }
 
 // Whether the GPU's LDS atomics serve the lanes of one instruction in ascending lane order
@@ -586,8 +659,8 @@ static void fill_push_args(hps_table* t, int c, const float* d_rows, int kind, P
 static int g_lane_order[64];
 
 static bool lane_order_holds(TableState* st, hipStream_t s) {
-  static_assert(offsetof(TableState, miss_overflow) % 8 == 0 &&
-                    offsetof(TableState, probe_bad) == offsetof(TableState, miss_overflow) + 4,
+  static_assert(offsetof(TableState, pad) % 8 == 0 &&
+                    offsetof(TableState, probe_bad) == offsetof(TableState, pad) + 4,
                 "the two words are cleared as one");
   u32* word = &st->probe_bad;
   const char* force = std::getenv("HPS_RANK");
@@ -597,7 +670,7 @@ static bool lane_order_holds(TableState* st, hipStream_t s) {
   int state = __atomic_load_n(&g_lane_order[dev], __ATOMIC_ACQUIRE);
   if (state == 0) {
     u32 bad = 1;
-    fill_u64<<<1, 64, 0, s>>>(reinterpret_cast<u64*>(&st->miss_overflow), 1, 0);
+    fill_u64<<<1, 64, 0, s>>>(reinterpret_cast<u64*>(&st->pad), 1, 0);
     probe_lane_order<<<256, kSortThreads, 0, s>>>(64, word);
     if (hipMemcpyAsync(&bad, word, sizeof(bad), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess) {
@@ -645,7 +718,7 @@ size_t hps_table_bytes(uint64_t capacity_keys, uint32_t dim, const hps_optimizer
 size_t hps_workspace_bytes(uint64_t max_keys, uint64_t max_bags, uint32_t dim) {
   if (max_keys >= (1ull << 30) || max_bags >= (1ull << 31) || dim < 4 || dim > 1024 || dim % 4)
     return 0;
-  return workspace_layout(max_keys, max_bags, dim).total;
+  return workspace_layout(max_keys, max_bags, dim).end;
 }
 
 hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
@@ -662,7 +735,7 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   const uint64_t n_slots = slots_for(capacity_keys);
   const StorageLayout sl = storage_layout(n_slots, dim, acc_len, opt->row_format);
   const WorkspaceLayout wl = workspace_layout(max_keys, max_bags, dim);
-  if (storage_bytes < sl.total || workspace_bytes < wl.total) return HPS_ENOMEM;
+  if (storage_bytes < sl.total || workspace_bytes < wl.end) return HPS_ENOMEM;
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); return HPS_EDEVICE; }
 
@@ -700,6 +773,7 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   for (int k = 0; k < 2; ++k) {
     t->cx[k].n_keys = t->cx[k].n_bags = 0;
     t->cx[k].d_offsets = nullptr;
+    t->cx[k].buckets = false;
     t->cx[k].ready_set = t->cx[k].released_set = false;
     events_ok = events_ok &&
                 hipEventCreateWithFlags(&t->cx[k].ready, hipEventDisableTiming) == hipSuccess &&
@@ -738,17 +812,11 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
     const unsigned n = (unsigned)std::strtoul(cap, nullptr, 10);
     t->lookup_new_cap = n < kNewLdsCap ? n : kNewLdsCap;
   }
-  {
-    const char* pool = std::getenv("HPS_POOL");
-    t->hot_rows = pool && std::strcmp(pool, "lds") == 0;
-  }
   hipStream_t s = static_cast<hipStream_t>(stream);
   t->ordered_rank = lane_order_holds(t->view.st, s);
   fill_u64<<<4096, 256, 0, s>>>(t->view.keys, n_slots, kEmptyKey);
-  // look-back status words and digit histograms start at zero
+  // look-back status words, digit histograms and the lists of frequent keys start at zero
   fill_u64<<<1024, 256, 0, s>>>(t->w<u64>(wl.ghist), (wl.bag_of - wl.ghist) / 8, 0);
-  for (u32 k = 0; k < kHeavyRing; ++k)
-    init_heavy_set<<<1, 256, 0, s>>>(&t->w<HeavyRing>(wl.heavy_raw)->set[k]);
   reset_state<<<1, 64, 0, s>>>(t->view.st);
   for (int k = 0; k < 2; ++k)
     set_ctx_empty<<<1, 64, 0, s>>>(t->ctx(k), t->w<u32>(wl.c[k].seg_off));
@@ -788,7 +856,7 @@ hps_status hps_insert(hps_table* t, const uint64_t* d_keys, uint64_t n, const fl
   if (!t || (n && !d_keys) || (d_acc && !d_weights)) return HPS_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (n) {
-    const unsigned blocks = grid_for(n, kProbeGroups * kProbeInFlight, kProbeMaxBlocks);
+    const unsigned blocks = grid_for(n, kProbeGroups, kProbeMaxBlocks);
     const unsigned row_blocks = grid_for(n, kRowThreads, kRowMaxBlocks);
     check_keys<<<grid_for(n, kRowThreads * 4, 2048), kRowThreads, 0, s>>>(d_keys, n, t->view.st);
 #define HPS_INSERT(BF16, VALUES) \
@@ -796,8 +864,7 @@ hps_status hps_insert(hps_table* t, const uint64_t* d_keys, uint64_t n, const fl
     if (t->view.bf16) { if (d_weights) HPS_INSERT(true, true); else HPS_INSERT(true, false); }
     else { if (d_weights) HPS_INSERT(false, true); else HPS_INSERT(false, false); }
 #undef HPS_INSERT
-    insert_missing<<<blocks, kProbeThreads, 0, s>>>(t->view, d_keys, n, nullptr, nullptr, d_weights,
-                                                    d_acc, nullptr, 0);
+    insert_missing<<<blocks, kProbeThreads, 0, s>>>(t->view, d_keys, n, d_weights, d_acc);
   }
   commit_insert<<<1, 64, 0, s>>>(t->view.st);
   return launch_ok() ? HPS_OK : HPS_EDEVICE;
@@ -847,8 +914,6 @@ hps_status hps_pull_prepared(hps_table* t, float* d_pooled, void* stream) {
   if (cx.n_bags && !d_pooled) return HPS_EINVAL;
   if ((uintptr_t)d_pooled % 16) return HPS_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const ContextLayout& C = t->wl.c[c];
-  PullCtx* ctx = t->ctx(c);
   if (hipStreamWaitEvent(s, cx.ready, 0) != hipSuccess) return HPS_EDEVICE;
   // the lookup rewrites the work lists that both contexts share and the pooling reads rows: order
   // them after the push of the mini-batch before, should that have run on another stream
@@ -856,15 +921,7 @@ hps_status hps_pull_prepared(hps_table* t, float* d_pooled, void* stream) {
   if (other.released_set && hipStreamWaitEvent(s, other.released, 0) != hipSuccess) return HPS_EDEVICE;
   // a2: look up every unique key, create the missing ones
   stage_mark(t, HPS_STAGE_LOOKUP, s);
-  if (cx.n_keys) {
-    const unsigned probe_blocks = grid_for(cx.n_keys, kProbeGroups * kProbeInFlight, kProbeMaxBlocks);
-    u32* miss_list = t->w<u32>(t->wl.miss_list);
-    const u32 shard_cap = (u32)t->wl.shard_cap;
-    launch_lookup(t, c, cx.n_keys, true, s);
-    insert_missing<<<probe_blocks, kProbeThreads, 0, s>>>(t->view, t->w<u64>(C.uniq), 0,
-                                                          &ctx->n_unique, t->w<u32>(C.rows), nullptr,
-                                                          nullptr, miss_list, shard_cap);
-  }
+  if (cx.n_keys) launch_lookup(t, c, cx.n_keys, true, s);
   if (!cx.n_bags) commit_insert<<<1, 64, 0, s>>>(t->view.st);   // else the pooling kernel does it
   stage_mark(t, HPS_STAGE_LOOKUP, s);
   // a3: gather rows and pool per bag
@@ -904,11 +961,9 @@ hps_status hps_push(hps_table* t, const float* d_pooled_grads, void* stream) {
   t->current = -1;
   if (cx.n_keys && cx.n_bags) {
     PushArgs a;
-    fill_push_args(t, c, d_pooled_grads,
+    fill_push_args(t, c, cx.n_keys, d_pooled_grads,
                    t->opt.kind == HPS_OPT_ADAGRAD_ELEMENTWISE ? kStepElementwise : kStepRowwise, a);
     if (cx.mean) a.inv_len = t->w<float>(t->wl.c[c].inv_len);
-    a.ring = t->w<HeavyRing>(t->wl.heavy_raw);       // the pull's lookup listed the frequent keys
-    a.ring_slot = (u32)(t->lookup_serial % kHeavyRing);
     stage_mark(t, HPS_STAGE_PUSH, s);
 #define CALL(LPR) launch_push<LPR>(t, cx.n_keys, a, s)
     HPS_DISPATCH_LPR(t->lpr, CALL)
@@ -937,15 +992,14 @@ static hps_status accumulate_launches(hps_table* t, const uint64_t* d_keys, uint
   launch_dedup(t, c, d_keys, (u32)n, nullptr, (u32)n, s);
   if (n) {
     launch_lookup(t, c, n, false, s);
-    commit_absent<<<1, 256, 0, s>>>(t->view.st, t->w<HeavyRing>(t->wl.heavy_raw),
-                                   (u32)(t->lookup_serial % kHeavyRing));
+    commit_absent<<<1, 64, 0, s>>>(t->view.st);
     PushArgs a;
-    fill_push_args(t, c, d_values, kStepAdd, a);
+    fill_push_args(t, c, n, d_values, kStepAdd, a);
 #define CALL(LPR) launch_push<LPR>(t, n, a, s)
     HPS_DISPATCH_LPR(t->lpr, CALL)
 #undef CALL
   } else {
-    commit_absent<<<1, 256, 0, s>>>(t->view.st, nullptr, 0);
+    commit_absent<<<1, 64, 0, s>>>(t->view.st);
   }
   return launch_ok() ? HPS_OK : HPS_EDEVICE;
 }
@@ -975,7 +1029,7 @@ hps_status hps_accumulate_static(hps_table* t, const uint64_t* d_keys, uint64_t 
   if (n > HPS_STATIC_MAX_KEYS || (uintptr_t)d_keys % 8 || (uintptr_t)d_values % 16) return HPS_EINVAL;
   if (t->current >= 0 || t->prepared >= 0) return HPS_ESTATE;
   const WorkspaceLayout wl = workspace_layout(HPS_STATIC_MAX_KEYS, HPS_STATIC_MAX_KEYS, t->dim);
-  if (wl.total > kStaticScratchBytes) return HPS_EINVAL;       // rows too wide for the static array
+  if (wl.end > kStaticScratchBytes) return HPS_EINVAL;       // rows too wide for the static array
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) { (void)hipGetLastError(); return HPS_EDEVICE; }
   StaticScratch& ss = g_static[dev];
@@ -1006,8 +1060,6 @@ hps_status hps_accumulate_static(hps_table* t, const uint64_t* d_keys, uint64_t 
   fill_u64<<<256, 256, 0, s>>>(t->w<u64>(wl.ghist), (wl.heavy_raw - wl.ghist) / 8, 0);
   if (!ss.ring_ready) {
     fill_u64<<<64, 256, 0, s>>>(t->w<u64>(wl.heavy_raw), (wl.bag_of - wl.heavy_raw) / 8, 0);
-    for (u32 k = 0; k < kHeavyRing; ++k)
-      init_heavy_set<<<1, 256, 0, s>>>(&t->w<HeavyRing>(wl.heavy_raw)->set[k]);
     ss.ring_ready = true;
   }
   set_ctx_empty<<<1, 64, 0, s>>>(t->ctx(0), t->w<u32>(wl.c[0].seg_off));
@@ -1030,9 +1082,28 @@ hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_invers
   if (!t) return HPS_EINVAL;
   if (t->current < 0) return HPS_ESTATE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const ContextLayout& C = t->wl.c[t->current];
-  const uint64_t n = t->cx[t->current].n_keys;
-  if (n == 0) return HPS_OK;
+  const int c = t->current;
+  const ContextLayout& C = t->wl.c[c];
+  const hps_table::Context& cx = t->cx[c];
+  const uint64_t n = cx.n_keys;
+  if (n == 0 || (!d_uniq_out && !d_inverse_out)) return HPS_OK;
+  if (cx.buckets) {
+    // the pooling is done with by_pos, by_heavy and row_of (calls that touch the table follow each other)
+    u32* local_rank = t->w<u32>(t->wl.row_of);
+    u32* bucket_total = t->w<u32>(t->wl.bucket_total);
+    u32* by_pos = d_inverse_out ? t->w<u32>(t->wl.by_pos) : nullptr;
+    u32* by_heavy = d_inverse_out ? t->w<u32>(t->wl.by_heavy) : nullptr;
+    const u32* start = t->w<u32>(C.bucket_start);
+    const u32* count = t->w<u32>(C.count);
+    order_uniques<<<cx.plan.n_nat, kOrderThreads, 0, s>>>(t->w<u64>(C.uniq), start, count, cx.plan.n_nat, t->ctx(c), t->view.st,
+                                                          local_rank, bucket_total);
+    emit_uniques<<<cx.plan.n_nat, kOrderThreads, 0, s>>>(t->w<u64>(C.uniq), start, count, t->w<u32>(C.upos), cx.plan.n_nat,
+                                                         t->ctx(c), t->view.st, local_rank, bucket_total, d_uniq_out, by_pos, by_heavy);
+    if (d_inverse_out)
+      launch_spread(t->w<u32>(C.code), t->w<uint16_t>(C.from), (u32)n, cx.plan.n_tiles, by_pos, by_heavy,
+                    reinterpret_cast<u32*>(d_inverse_out), s);
+    return launch_ok() ? HPS_OK : HPS_EDEVICE;
+  }
   // U <= n is only known on the device: copy n entries, the caller reads the first U.
   if (d_uniq_out &&
       hipMemcpyAsync(d_uniq_out, t->w<u64>(C.uniq), n * 8, hipMemcpyDeviceToDevice, s) != hipSuccess)
@@ -1105,6 +1176,10 @@ hps_status hps_stats(hps_table* t, hps_stats_t* h_out, void* stream) {
   h_out->n_slots = t->n_slots;
   h_out->last_n_keys = t->last_n_keys;
   h_out->last_n_unique = ctx.n_unique;
+  if (ctx.by_id) {
+    h_out->last_n_unique = 0;
+    for (int k = 0; k < kCountShards; ++k) h_out->last_n_unique += ctx.uniq_shard[k];
+  }
   h_out->last_n_inserted = st.inserted;
   h_out->last_n_absent = (uint64_t)st.absent;
   h_out->n_plain_fallbacks = t->n_fallbacks;

@@ -1,24 +1,29 @@
-// Key dedup, bucket form, part 1: ordering the key occurrences by bucket id without any
-// workgroup waiting for another.
+// Key dedup, bucket form, part 1: the key occurrences are dealt into buckets in one stable pass,
+// without any workgroup waiting for another.
 //
-// A key's bucket id (sort.hpp: bucket_id) has at most 16 bits; the occurrences are ordered by
-// it with one or two stable 8-bit passes, least significant byte first.  Each pass is three
-// launches, none of which waits for anything but its own input:
+// A bucket is one of n_nat equal parts of the mini-batch's key range (sampled; for hashed keys: of
+// all 64 bits), a few hundred to a few thousand occurrences each, or one frequent ("heavy") key, which a hint from an
+// earlier lookup names (common.hpp): those would make single buckets too large for bucket.hpp,
+// and their occurrences need no grouping.  Buckets 0 .. n_nat-1 are in key order, the heavy
+// ones follow in the order of the hint.  Three launches (two for few tiles):
 //
-//   bucket_count / digit_count   every tile (kPartTile consecutive occurrences) counts its
-//                                digits; the counts go to a digit-major matrix
-//                                hist[digit][tile];
-//   scan_tiles                   one workgroup per digit: exclusive prefix over the tiles
-//                                (in place) and the digit's total;
-//   scatter_pass                 a tile ranks its elements (wave ballots: stable), adds the
-//                                tile's prefix and the digit's base, stages the tile in LDS
-//                                and writes every digit's run contiguously.
+//   bucket_count     a tile of consecutive occurrences per block: bucket of every key (id16), counts
+//                    per bucket (hist[tile][bucket]); further blocks note which bag every tile
+//                    starts in;
+//   scan_buckets     counts -> for every tile and bucket the occurrences in earlier tiles
+//                    (prefix[tile][bucket]), and where every bucket starts (bucket_start); left out
+//                    for up to kDirectTiles tiles, where every block of the scatter adds the counts up itself;
+//   bucket_scatter   a tile ranks its occurrences per bucket in occurrence order, stages them in LDS
+//                    and writes every bucket's run contiguously: the key (not for heavy
+//                    buckets), the bag.  It also leaves, per tile in the order of the
+//                    destinations, where each occurrence went (code) and which of the tile's it was
+//                    (from): what spread() needs to bring per-position results back into
+//                    occurrence order with whole runs read, a tile's worth of LDS scattered and whole lines
+//                    written (an occurrence's index does not travel with the pair).
 //
-// bucket_count also works out the mini-batch's key range (from samples), every key's bucket
-// id (id16, read again by the first scatter) and bag_of[i]; the first scatter of a two-pass
-// plan leaves the ids' high bytes in sorted order (dig), so that the second pass's count
-// reads one byte per occurrence.  region_borders then cuts the ordered array into the
-// regions that bucket.hpp finishes.
+// One pass with thousands of buckets instead of two 8-bit passes: what a scatter pays for is
+// write requests, and a run of five occurrences (one or two requests for its keys, one for its
+// bags) costs two requests where the second pass cost a read and a write of every pair.
 #pragma once
 
 #include "common.hpp"
@@ -26,285 +31,415 @@
 
 namespace hps {
 
-constexpr int kPartThreads = 256;
-constexpr int kPartWaves = kPartThreads / kWave;
-constexpr int kPartItems = 12;                          // per thread
-constexpr int kPartTile = kPartThreads * kPartItems;    // 3072 occurrences
-constexpr int kPartWaveSpan = kWave * kPartItems;       // 768 consecutive occurrences per wave
-constexpr u32 kRegionSpan = 2048;                       // positions between nominal region cuts
-static_assert(kPartTile == kSortTile, "the workspace is sized in tiles of kSortTile");
-static_assert(kRadix == kPartThreads, "thread d owns digit d");
+struct BucketPlan {
+  u32 n_nat;        // natural buckets
+  u32 max_heavy;    // heavy keys that get buckets of their own, at most
+  u32 stride;       // words from one tile's counts to the next, >= n_nat + max_heavy
+  u32 n_tiles;
+};
 
-// First kernel of a bucket-form dedup.  The first count_blocks blocks loop over the tiles:
-// bucket id of every key (id16) and the tile's counts of the ids' low bytes
-// (hist[digit * n_tiles + tile]); the blocks behind them write bag_of.  Block 0 also resets
-// the pull context and the tickets and leaves the key range in ctx->range.
-__global__ void __launch_bounds__(kPrepThreads)
-bucket_count(const u64* __restrict__ keys, u32 n, SortPlan plan, u32* __restrict__ tickets,
-             PullCtx* __restrict__ ctx, const i32* __restrict__ offsets, u32 n_bags,
-             i32* __restrict__ bag_of, const HeavySet* __restrict__ heavy_set,
-             uint16_t* __restrict__ id16, u32* __restrict__ hist, u32 n_tiles, u32 count_blocks) {
-  if (blockIdx.x >= count_blocks) {
-    expand_bags(offsets, n_bags, n, bag_of, blockIdx.x - count_blocks, gridDim.x - count_blocks);
+constexpr u32 kHeavyCode = 0x80000000u;   // code of an occurrence in heavy bucket h: kHeavyCode | h, else its position
+constexpr u32 kDirectTiles = 64;
+constexpr int kHeavySlots = 4096;         // hash slots for the heavy keys (a power of two)
+constexpr u32 kNoHeavy = ~0u;
+
+// Which part of the key range a key lies in.
+__device__ __forceinline__ u32 bucket_of(u64 key, const KeyRange& r) {
+  const u64 rel = range_rel(key, r);
+  return r.direct ? (u32)rel : (u32)(((rel >> r.pre) * r.mult) >> 32);
+}
+__device__ __forceinline__ KeyRange bucket_range(u64 lo, u64 hi, u32 n_nat) {
+  KeyRange r = widened_range(lo, hi);
+  r.direct = r.span < n_nat;
+  // span >= n_nat here, so the quotient is below 2^32, and parts are numbered below n_nat
+  r.mult = r.direct ? 0u : (u32)(((u64)n_nat << 32) / ((r.span >> r.pre) + 1));
+  return r;
+}
+__device__ __forceinline__ u32 key_hash(u64 key) {
+  return (u32)((key * 0x9E3779B97F4A7C15ull) >> 32);
+}
+
+// The heavy keys in LDS: an open-addressing hash from key to its index in the list.
+struct HeavyLds {
+  u64 keys[kMaxHeavy + 1];
+  u32 slot[kHeavySlots];
+};
+// Step 1 of 2 (a barrier after each): all threads copy the list and clear the slots.
+template <int THREADS>
+__device__ __forceinline__ void heavy_copy(HeavyLds& H, const HeavyRaw* raw, u32 count) {
+  for (u32 i = threadIdx.x; i < count; i += THREADS) H.keys[i] = raw->keys[i];
+  if (count)
+    for (u32 i = threadIdx.x; i < (u32)kHeavySlots; i += THREADS) H.slot[i] = kNoHeavy;
+}
+// Step 2: a key that is listed twice goes by its first index, in every block.
+template <int THREADS>
+__device__ __forceinline__ void heavy_index(HeavyLds& H, u32 count) {
+  for (u32 i = threadIdx.x; i < count; i += THREADS) {
+    const u64 key = H.keys[i];
+    u32 s = key_hash(key) >> 20;
+    while (true) {       // (at most kMaxHeavy of the kHeavySlots slots are ever taken)
+      const u32 old = atomicCAS(&H.slot[s], kNoHeavy, i);
+      if (old == kNoHeavy) break;
+      if (H.keys[old] == key) { atomicMin(&H.slot[s], i); break; }
+      s = (s + 1) & (kHeavySlots - 1);
+    }
+  }
+}
+__device__ __forceinline__ u32 heavy_find(const HeavyLds& H, u64 key) {
+  u32 s = key_hash(key) >> 20;
+  while (true) {
+    const u32 i = H.slot[s];
+    if (i == kNoHeavy || H.keys[i] == key) return i;
+    s = (s + 1) & (kHeavySlots - 1);
+  }
+}
+static_assert(kHeavySlots == 1 << 12, "a slot is the top 12 bits of the hash");
+
+// First kernel of a bucket-form dedup, one tile of THREADS * ITEMS occurrences per block for the
+// first plan.n_tiles blocks; the blocks behind them look through the bag offsets and leave in
+// tile_bag[t] the bag that holds occurrence t * tile (offsets == null: every occurrence is its
+// own bag, nothing to do).  Block 0 also resets the pull context.
+template <int THREADS, int ITEMS, int MAX_BUCKETS>
+__global__ void __launch_bounds__(THREADS, 8)
+bucket_count(const u64* __restrict__ keys, u32 n, BucketPlan plan, PullCtx* __restrict__ ctx,
+             const i32* __restrict__ offsets, u32 n_bags, u32* __restrict__ tile_bag,
+             const HeavyRaw* __restrict__ heavy, uint16_t* __restrict__ id16, uint16_t* __restrict__ hist) {
+  constexpr u32 kTile = THREADS * ITEMS;
+  if (blockIdx.x >= plan.n_tiles) {
+    const u32 first = (blockIdx.x - plan.n_tiles) * THREADS + threadIdx.x, step = (gridDim.x - plan.n_tiles) * THREADS;
+    for (u32 b = first; b < n_bags; b += step) {
+      const u32 lo = (u32)max(offsets[b], 0), hi = min((u32)max(offsets[b + 1], 0), n);
+      for (u32 t = (lo + kTile - 1) / kTile; t < plan.n_tiles && t * kTile < hi; ++t) tile_bag[t] = b;
+    }
     return;
   }
-  __shared__ u32 h[kRadix];
+  __shared__ u32 h[MAX_BUCKETS];
   __shared__ HeavyLds hv;
-  __shared__ u64 s_lo[kPrepThreads / kWave], s_hi[kPrepThreads / kWave];
-  // The block's first tile is requested before anything waits for the samples, so that the
-  // two round trips to memory overlap (count_blocks <= n_tiles: every block has a tile).
-  u64 first_keys[kPartItems];
+  __shared__ u64 s_lo[THREADS / kWave], s_hi[THREADS / kWave];
+  __shared__ KeyRange s_range;
+  // the tile is requested before anything waits for the samples and the list
+  const u32 base = blockIdx.x * kTile;
+  u64 key[ITEMS];
 #pragma unroll
-  for (int k = 0; k < kPartItems; ++k) {
-    const u32 i = blockIdx.x * kPartTile + k * kPrepThreads + threadIdx.x;
-    first_keys[k] = i < n ? keys[i] : 0;
-  }
-  sample_key_range(keys, n, s_lo, s_hi);
-  load_heavy(hv, heavy_set, plan.max_heavy);
-  h[threadIdx.x] = 0;
-  if (blockIdx.x == 0) {
-    if (threadIdx.x < kMaxPasses + 2) tickets[threadIdx.x] = 0;
-    reset_ctx(ctx, n, 1u);
-  }
+  for (int k = 0; k < ITEMS; ++k) key[k] = keys[min(base + k * THREADS + threadIdx.x, n - 1)];
+  const u32 n_heavy = min(heavy->count, plan.max_heavy);
+  sample_key_range<THREADS>(keys, n, s_lo, s_hi);
+  heavy_copy<THREADS>(hv, heavy, n_heavy);
+  const u32 n_buckets = plan.n_nat + n_heavy;
+  for (u32 b = threadIdx.x; b < n_buckets; b += THREADS) h[b] = 0;
+  if (blockIdx.x == 0) reset_ctx(ctx, n, 1u, n_heavy);
   __syncthreads();
+  heavy_index<THREADS>(hv, n_heavy);
   if (threadIdx.x == 0) {
-    u64 lo = s_lo[0], hi = s_hi[0];
-    for (int w = 1; w < kPrepThreads / kWave; ++w) { lo = min(lo, s_lo[w]); hi = max(hi, s_hi[w]); }
-    if (lo > hi) lo = hi = 0;            // n == 0
-    hv.range = make_range(lo, hi, plan);
-    if (blockIdx.x == 0) ctx->range = hv.range;
+    u64 lo, hi;
+    sampled_ends<THREADS>(s_lo, s_hi, &lo, &hi);
+    s_range = bucket_range(lo, hi, plan.n_nat);
+    if (blockIdx.x == 0) ctx->range = s_range;
   }
   __syncthreads();
-  for (u32 tile = blockIdx.x; tile < n_tiles; tile += count_blocks) {
-    const u32 base = tile * kPartTile;
+  const KeyRange range = s_range;
 #pragma unroll
-    for (int k = 0; k < kPartItems; ++k) {
-      const u32 i = base + k * kPrepThreads + threadIdx.x;
-      if (i < n) {
-        const u64 key = tile == blockIdx.x ? first_keys[k] : keys[i];
-        bool heavy;
-        const u32 id = bucket_id(key, hv, &heavy);
-        id16[i] = (uint16_t)id;
-        atomicAdd(&h[id & (kRadix - 1)], 1u);
+  for (int k = 0; k < ITEMS; ++k) {
+    const u32 i = base + k * THREADS + threadIdx.x;
+    if (i < n) {
+      u32 id = bucket_of(key[k], range);
+      if (n_heavy) {
+        const u32 at = heavy_find(hv, key[k]);
+        if (at != kNoHeavy) id = plan.n_nat + at;
+      }
+      id16[i] = (uint16_t)id;
+      atomicAdd(&h[id], 1u);
+    }
+  }
+  __syncthreads();
+  uint16_t* row = hist + (u64)blockIdx.x * plan.stride;
+  for (u32 b = threadIdx.x; b < n_buckets; b += THREADS) row[b] = (uint16_t)h[b];
+}
+
+// prefix[tile][bucket] and bucket_start[0 .. n_nat + max_heavy].  A block takes 64 buckets, its waves
+// share the tiles (PER tiles each, kept in registers between the two halves of the scan); the block
+// that is done last scans the buckets' totals.
+constexpr int kScanThreads = 1024;
+constexpr int kScanWaves = kScanThreads / kWave;
+template <int PER>
+__global__ void __launch_bounds__(kScanThreads)
+scan_buckets(const uint16_t* __restrict__ hist, BucketPlan plan, u32* __restrict__ prefix,
+             u32* __restrict__ total, u32* __restrict__ bucket_start, PullCtx* __restrict__ ctx) {
+  __shared__ u32 sums[kScanWaves][kWave];
+  __shared__ u32 scratch[kScanThreads / kWave + 1];
+  __shared__ u32 s_last;
+  const u32 lane = lane_id(), wave = threadIdx.x / kWave;
+  const u32 n_buckets = plan.n_nat + ctx->n_heavy, n_all = plan.n_nat + plan.max_heavy;
+  const u32 b = blockIdx.x * kWave + lane;
+  const u32 t0 = wave * PER;
+  u32 v[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k)
+    v[k] = b < n_buckets && t0 + k < plan.n_tiles ? (u32)hist[(u64)(t0 + k) * plan.stride + b] : 0u;
+  u32 mine = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) mine += v[k];
+  sums[wave][lane] = mine;
+  __syncthreads();
+  u32 run = 0;
+  for (u32 w = 0; w < wave; ++w) run += sums[w][lane];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    if (b < n_buckets && t0 + k < plan.n_tiles) prefix[(u64)(t0 + k) * plan.stride + b] = run;
+    run += v[k];
+  }
+  if (wave == kScanWaves - 1 && b < n_all)
+    __hip_atomic_store(total + b, run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __threadfence();
+  __syncthreads();
+  if (threadIdx.x == 0) s_last = atomicAdd(&ctx->ticket, 1u) + 1 == gridDim.x ? 1u : 0u;
+  __syncthreads();
+  if (!s_last) return;
+  __threadfence();
+  u32 before = 0;
+  for (u32 base = 0; base < n_all; base += 4 * kScanThreads) {
+    u32 c[4], sum = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const u32 at = base + 4 * threadIdx.x + q;
+      c[q] = at < n_all ? __hip_atomic_load(total + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+      sum += c[q];
+    }
+    u32 all;
+    u32 at_start = before + block_excl_sum<kScanThreads>(sum, scratch, &all);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const u32 at = base + 4 * threadIdx.x + q;
+      if (at < n_all) bucket_start[at] = at_start;
+      if (at >= plan.n_nat && c[q]) atomicAdd(&ctx->uniq_shard[at % kCountShards], 1u);    // a heavy key that occurs
+      at_start += c[q];
+    }
+    before += all;
+  }
+  if (threadIdx.x == 0) bucket_start[n_all] = before;
+}
+
+// Deals one tile per block out to the buckets.  DIRECT: scan_buckets was left out, hist holds all
+// there is; block 0 then writes bucket_start.
+template <int THREADS, int ITEMS, int MAX_BUCKETS, bool ORDERED, bool DIRECT>
+__global__ void __launch_bounds__(THREADS)
+bucket_scatter(const u64* __restrict__ keys, const uint16_t* __restrict__ id16, const i32* __restrict__ offsets,
+               u32 n_bags, const u32* __restrict__ tile_bag, u32 n, BucketPlan plan, PullCtx* __restrict__ ctx,
+               const uint16_t* __restrict__ hist, const u32* __restrict__ prefix, u32* __restrict__ bucket_start,
+               u64* __restrict__ keys_out, u32* __restrict__ bags_out, u32* __restrict__ code,
+               uint16_t* __restrict__ from) {
+  constexpr u32 kTile = THREADS * ITEMS;
+  constexpr int kWaves = THREADS / kWave;
+  constexpr int kPer = (MAX_BUCKETS + THREADS - 1) / THREADS;    // buckets a thread scans
+  constexpr int kIdBits = 13;
+  static_assert(MAX_BUCKETS <= 1 << kIdBits && kTile <= 1 << 16, "packed below");
+  __shared__ u64 stage[kTile];
+  __shared__ u32 first[kPer * THREADS];      // per bucket: count, then first staged place
+  __shared__ u32 out[kPer * THREADS];        // per bucket: destination of a staged element - its staged place
+  __shared__ u32 scratch[kWaves + 1];
+  __shared__ u32 wave_last[kWaves];
+  const u32 tid = threadIdx.x, wave = tid / kWave, lane = tid & (kWave - 1);
+  const u32 tile = blockIdx.x, base = tile * kTile;
+  const u32 tile_n = min(kTile, n - base);
+  const u32 wave_first = wave * (kWave * ITEMS);        // element e of the tile: wave_first + r * 64 + lane
+  const u32 n_buckets = plan.n_nat + ctx->n_heavy;
+
+  u64 key[ITEMS];
+  u32 id[ITEMS];
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const u32 i = min(base + wave_first + r * kWave + lane, n - 1);
+    key[r] = keys[i];
+    id[r] = id16[i];
+  }
+  // every non-empty bag that starts inside the tile marks its first occurrence
+  u32* mark = reinterpret_cast<u32*>(stage);
+  for (u32 e = tid; e < kTile; e += THREADS) mark[e] = 0;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) first[q * THREADS + tid] = 0;
+  u32 bag0 = 0;
+  __syncthreads();
+  if (offsets) {
+    const u32 last = n_bags - 1;
+    bag0 = min(tile_bag[tile], last);
+    const u32 end = tile + 1 < plan.n_tiles ? min(tile_bag[tile + 1], last) : last;
+    for (u32 b = bag0 + 1 + tid; b <= end; b += THREADS) {
+      const u32 lo = (u32)offsets[b], hi = (u32)offsets[b + 1];
+      if (lo < hi && lo - base < kTile) mark[lo - base] = b;      // (lo >= base, or the difference is huge)
+    }
+  }
+  // ranks: the waves take turns, so that a bucket's counter is counted up in occurrence order
+  u32 rank[ITEMS];
+  const u64 lt = lanemask_lt();
+  for (int w = 0; w < kWaves; ++w) {
+    if (wave == (u32)w) {
+#pragma unroll
+      for (int r = 0; r < ITEMS; ++r)
+        rank[r] = digit_rank<ORDERED, kIdBits>(&first[id[r]], id[r], wave_first + r * kWave + lane < tile_n, lt);
+    }
+    __syncthreads();
+  }
+  // bags: the bag of the last mark at or before the element, in this wave or an earlier one
+  u32 bag[ITEMS];
+  if (offsets) {
+    u32 carry = 0;
+    u32 m[ITEMS];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) m[r] = mark[wave_first + r * kWave + lane];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+      const u64 set = __ballot(m[r] != 0);
+      const u64 upto = set & (lt | (1ull << lane));
+      const u32 v = (u32)__shfl((int)m[r], upto ? 63 - __clzll((long long)upto) : 0, kWave);
+      bag[r] = upto ? v : carry;                 // 0: none in this wave so far
+      if (set) carry = (u32)__builtin_amdgcn_readlane((int)m[r], 63 - __clzll((long long)set));
+    }
+    if (lane == 0) wave_last[wave] = carry;
+    __syncthreads();
+    u32 before = bag0;
+    for (u32 w = 0; w < wave; ++w) before = wave_last[w] ? wave_last[w] : before;
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) bag[r] = bag[r] ? bag[r] : before;
+  } else {
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) bag[r] = base + wave_first + r * kWave + lane;
+  }
+  // per bucket (thread t: buckets kPer * t ...): its first staged place, its run's destination
+  {
+    u32 c[kPer], g[kPer], p[kPer], sum = 0, gsum = 0, all;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const u32 b = kPer * tid + q;
+      c[q] = first[b];
+      sum += c[q];
+      g[q] = p[q] = 0;
+      if (DIRECT) {
+        if (b < n_buckets)
+          for (u32 t = 0; t < plan.n_tiles; ++t) {
+            const u32 v = hist[(u64)t * plan.stride + b];
+            g[q] += v;
+            if (t < tile) p[q] += v;
+          }
+        gsum += g[q];
+      } else if (b < n_buckets) {
+        g[q] = bucket_start[b];
+        p[q] = prefix[(u64)tile * plan.stride + b];
       }
     }
-    __syncthreads();
-    hist[(u64)threadIdx.x * n_tiles + tile] = h[threadIdx.x];
-    h[threadIdx.x] = 0;
-    __syncthreads();
-  }
-}
-
-// Counts of the second pass: dig[j] is the id's high byte of the occurrence at position j
-// after the first pass.  One tile per block.
-__global__ void __launch_bounds__(kPartThreads)
-digit_count(const uint8_t* __restrict__ dig, u32 n, u32* __restrict__ hist, u32 n_tiles) {
-  __shared__ u32 h[kRadix];
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  const u32 tile = blockIdx.x;
-  // four consecutive digits per load (tiles start at multiples of four)
-  const u32* dig4 = reinterpret_cast<const u32*>(dig);
-  const u32 base4 = tile * (kPartTile / 4);
+    u32 at = block_excl_sum<THREADS>(sum, scratch, &all);
+    if (DIRECT) {
+      u32 start = block_excl_sum<THREADS>(gsum, scratch, &all);
+      u32 count[kPer];
 #pragma unroll
-  for (int k = 0; k < kPartItems / 4; ++k) {
-    const u32 q = base4 + k * kPartThreads + threadIdx.x;
-    const u32 i = q * 4;
-    if (i + 3 < n) {
-      const u32 v = dig4[q];
-      atomicAdd(&h[v & 255u], 1u);
-      atomicAdd(&h[(v >> 8) & 255u], 1u);
-      atomicAdd(&h[(v >> 16) & 255u], 1u);
-      atomicAdd(&h[v >> 24], 1u);
-    } else {
-      for (u32 e = i; e < n; ++e) atomicAdd(&h[dig[e]], 1u);
+      for (int q = 0; q < kPer; ++q) { count[q] = g[q]; g[q] = start; start += count[q]; }
+      if (tile == 0) {
+        const u32 n_all = plan.n_nat + plan.max_heavy;
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+          const u32 b = kPer * tid + q;
+          if (b < n_all) bucket_start[b] = g[q];
+          if (b >= plan.n_nat && count[q]) atomicAdd(&ctx->uniq_shard[b % kCountShards], 1u);    // a heavy key that occurs
+        }
+        if (tid == 0) bucket_start[n_all] = all;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const u32 b = kPer * tid + q;
+      first[b] = at;
+      out[b] = g[q] + p[q] - at;
+      at += c[q];
     }
   }
   __syncthreads();
-  hist[(u64)threadIdx.x * n_tiles + tile] = h[threadIdx.x];
-}
-
-// One workgroup per digit: hist[digit][0 .. n_tiles) becomes its own exclusive prefix, tot[digit]
-// the digit's total.  The launch also clears `n_clear` words at `clear` (status words of the
-// kernel that finishes the dedup: nothing of an earlier dedup may be left in them).
-__global__ void __launch_bounds__(kPartThreads)
-scan_tiles(u32* __restrict__ hist, u32 n_tiles, u32* __restrict__ tot, u32* __restrict__ clear,
-           u32 n_clear) {
-  __shared__ u32 scratch[kPartThreads / kWave + 1];
-  for (u32 i = blockIdx.x * kPartThreads + threadIdx.x; i < n_clear; i += gridDim.x * kPartThreads)
-    clear[i] = 0;
-  u32* row = hist + (u64)blockIdx.x * n_tiles;
-  u32 running = 0;
-  for (u32 base = 0; base < n_tiles; base += kPartThreads) {
-    const u32 t = base + threadIdx.x;
-    const u32 v = t < n_tiles ? row[t] : 0;
-    u32 total;
-    const u32 ex = block_excl_sum<kPartThreads>(v, scratch, &total);
-    if (t < n_tiles) row[t] = running + ex;
-    running += total;
-  }
-  if (threadIdx.x == 0) tot[blockIdx.x] = running;
-}
-
-// One stable pass over (key, payload) pairs by one byte of the bucket id; payload =
-// occurrence index | bag << 32.  One tile per block.
-//   FIRST: reads keys / id16 / bag_of in arrival order, sorts by the id's low byte and, if
-//          dig_out is not null (two-pass plan), leaves the high byte of every occurrence at
-//          its new position there.
-//   else:  reads the pairs and dig_in (the first pass's dig_out), sorts by that byte.
-//   hist   [digit][tile] exclusive prefixes and tot[digit] totals of this pass (scan_tiles)
-//   ORDERED: how the elements are ranked (sort.hpp: digit_rank)
-template <bool FIRST, bool ORDERED>
-__global__ void __launch_bounds__(kPartThreads)
-scatter_pass(const u64* __restrict__ keys_in, const u64* __restrict__ pay_in,
-             const i32* __restrict__ bag_of, const uint16_t* __restrict__ id16,
-             const uint8_t* __restrict__ dig_in, u64* __restrict__ keys_out,
-             u64* __restrict__ pay_out, uint8_t* __restrict__ dig_out, u32 n,
-             const u32* __restrict__ hist, u32 n_tiles, const u32* __restrict__ tot) {
-  __shared__ u32 wave_cnt[kPartWaves][kRadix];   // per-wave digit counts, then wave offsets
-  __shared__ u32 local_start[kRadix];            // first staged position of each digit
-  __shared__ u32 out_base[kRadix];               // global position of the digit's run - local_start
-  __shared__ u32 scratch[kPartThreads / kWave + 1];
-  __shared__ u64 stage[kPartTile];               // keys first, then the payloads
-  __shared__ uint8_t stage_digit[kPartTile];     // digit of each staged element
-  __shared__ uint8_t stage_next[kPartTile];      // FIRST: its id's high byte
-
-  const u32 tid = threadIdx.x;
-  const u32 tile = blockIdx.x;
-  const u32 wave = tid / kWave, lane = tid & (kWave - 1);
-  const u32 tile_base = tile * kPartTile;
-  const u32 tile_n = min((u32)kPartTile, n - tile_base);
-  const u32 wave_base = tile_base + wave * kPartWaveSpan;
+  // destinations
 #pragma unroll
-  for (int w = 0; w < kPartWaves; ++w) wave_cnt[w][tid] = 0;
-  // what thread d needs about digit d, requested early
-  const u32 tile_prefix = hist[(u64)tid * n_tiles + tile];
-  const u32 digit_count_all = tot[tid];
-
-  u64 key[kPartItems];
-  u64 pay[kPartItems];
-  u32 dg[kPartItems];      // digit | next digit << 8
-#pragma unroll
-  for (int r = 0; r < kPartItems; ++r) {
-    const u32 i = wave_base + r * kWave + lane;
-    key[r] = (i < n) ? keys_in[i] : ~0ull;
-    if (FIRST) {
-      pay[r] = (i < n) ? ((u64)i | ((u64)(u32)bag_of[i] << 32)) : 0ull;
-      dg[r] = (i < n) ? (u32)id16[i] : 0u;
-    } else {
-      pay[r] = (i < n) ? pay_in[i] : 0ull;
-      dg[r] = (i < n) ? (u32)dig_in[i] : 0u;
+  for (int r = 0; r < ITEMS; ++r) {
+    const u32 e = wave_first + r * kWave + lane;
+    if (e < tile_n) {
+      rank[r] += first[id[r]];                   // now the staged place
+      const u32 dest = out[id[r]] + rank[r];
+      const u32 c = id[r] >= plan.n_nat ? kHeavyCode | (id[r] - plan.n_nat) : dest;
+      stage[rank[r]] = (u64)dest | ((u64)c << 32);
     }
   }
   __syncthreads();
-  u32 rank[kPartItems];
-  {
-    const u64 lt = lanemask_lt();
+  u32 dest[ITEMS];
+  u32 heavy = 0;
 #pragma unroll
-    for (int r = 0; r < kPartItems; ++r) {
-      const u32 i = wave_base + r * kWave + lane;
-      const u32 d = dg[r] & (kRadix - 1);
-      rank[r] = digit_rank<ORDERED>(&wave_cnt[wave][d], d, i < n, lt);
-    }
-  }
-  __syncthreads();
-  // Thread d owns digit d: the waves' offsets inside the run, the run's place.
-  u32 digit_total = 0;
-#pragma unroll
-  for (int w = 0; w < kPartWaves; ++w) {
-    const u32 c = wave_cnt[w][tid];
-    wave_cnt[w][tid] = digit_total;
-    digit_total += c;
-  }
-  u32 total;
-  const u32 gbase = block_excl_sum<kPartThreads>(digit_count_all, scratch, &total);
-  const u32 start = block_excl_sum<kPartThreads>(digit_total, scratch, &total);
-  local_start[tid] = start;
-  out_base[tid] = gbase + tile_prefix - start;
-  __syncthreads();
-
-  u32 pos[kPartItems];
-#pragma unroll
-  for (int r = 0; r < kPartItems; ++r) {
-    const u32 i = wave_base + r * kWave + lane;
-    pos[r] = 0;
-    if (i < n) {
-      const u32 d = dg[r] & (kRadix - 1);
-      pos[r] = local_start[d] + wave_cnt[wave][d] + rank[r];
-      stage[pos[r]] = key[r];
-      stage_digit[pos[r]] = (uint8_t)d;
-      if (FIRST) stage_next[pos[r]] = (uint8_t)(dg[r] >> kRadixBits);
-    }
-  }
-  __syncthreads();
-  u32 dest[kPartItems];
-#pragma unroll
-  for (int k = 0; k < kPartItems; ++k) {
-    const u32 p = k * kPartThreads + tid;
+  for (int k = 0; k < ITEMS; ++k) {
+    const u32 j = k * THREADS + tid;
     dest[k] = 0;
-    if (p < tile_n) {
-      dest[k] = out_base[stage_digit[p]] + p;
-      keys_out[dest[k]] = stage[p];
-      if (FIRST && dig_out) dig_out[dest[k]] = stage_next[p];
+    if (j < tile_n) {
+      const u64 v = stage[j];
+      dest[k] = (u32)v;
+      code[base + j] = (u32)(v >> 32);
+      if (v >> 63) heavy |= 1u << k;
     }
   }
   __syncthreads();
 #pragma unroll
-  for (int r = 0; r < kPartItems; ++r) {
-    const u32 i = wave_base + r * kWave + lane;
-    if (i < n) stage[pos[r]] = pay[r];
+  for (int r = 0; r < ITEMS; ++r)
+    if (wave_first + r * kWave + lane < tile_n) stage[rank[r]] = key[r];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const u32 j = k * THREADS + tid;
+    if (j < tile_n && !(heavy >> k & 1u)) keys_out[dest[k]] = stage[j];
   }
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < kPartItems; ++k) {
-    const u32 p = k * kPartThreads + tid;
-    if (p < tile_n) pay_out[dest[k]] = stage[p];
+  for (int r = 0; r < ITEMS; ++r) {
+    const u32 e = wave_first + r * kWave + lane;
+    if (e < tile_n) stage[rank[r]] = (u64)bag[r] | ((u64)e << 32);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const u32 j = k * THREADS + tid;
+    if (j < tile_n) {
+      const u64 v = stage[j];
+      bags_out[dest[k]] = (u32)v;
+      from[base + j] = (uint16_t)(v >> 32);
+    }
   }
 }
 
-// ---- regions ---------------------------------------------------------------------------
-// A region may start where the bucket id changes, or anywhere inside a heavy key's bucket
-// (it holds one key).  border(p0) = the first such position >= p0, n if there is none; region
-// c is [border(c * kRegionSpan), border((c + 1) * kRegionSpan)), border(0) = 0.  One wave per
-// border, 256 positions per round; borders[0 .. n_regions] out.
-__global__ void __launch_bounds__(kPartThreads)
-region_borders(const u64* __restrict__ skeys, u32 n, u32 n_regions, u32 max_heavy,
-               const HeavySet* __restrict__ heavy_set, const PullCtx* __restrict__ ctx,
-               u32* __restrict__ borders) {
-  __shared__ HeavyLds hv;
-  load_heavy(hv, heavy_set, max_heavy);
-  if (threadIdx.x == 0) hv.range = ctx->range;
+// Brings a value per position (by_pos) or heavy bucket (by_heavy) back into occurrence order:
+// out[i] = the value of the position or heavy bucket that occurrence i went to.  One tile per block.
+template <int THREADS, int ITEMS>
+__device__ __forceinline__ void spread_tile(const u32* __restrict__ code, const uint16_t* __restrict__ from, u32 n,
+                                            u32 tile, const u32* __restrict__ by_pos,
+                                            const u32* __restrict__ by_heavy, u32* __restrict__ out, u32* lds) {
+  constexpr u32 kTile = THREADS * ITEMS;
+  const u32 base = tile * kTile, tile_n = min(kTile, n - base);
+  u32 c[ITEMS], at[ITEMS];
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const u32 j = min(base + k * THREADS + threadIdx.x, n - 1);
+    c[k] = code[j];
+    at[k] = from[j];
+  }
+  u32 v[ITEMS];
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) v[k] = c[k] & kHeavyCode ? by_heavy[c[k] & ~kHeavyCode] : by_pos[c[k]];
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k)
+    if (k * THREADS + threadIdx.x < tile_n) lds[at[k]] = v[k];
   __syncthreads();
-  const u32 lane = lane_id();
-  const u32 c = blockIdx.x * kPartWaves + threadIdx.x / kWave;
-  if (c > n_regions) return;
-  if (c == 0 || c == n_regions) {
-    if (lane == 0) borders[c] = c == 0 ? 0u : n;
-    return;
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const u32 e = k * THREADS + threadIdx.x;
+    if (e < tile_n) out[base + e] = lds[e];
   }
-  const u32 p0 = c * kRegionSpan;       // 0 < p0 < n
-  u32 found = n;
-  for (u32 base = p0; base < n && found == n; base += 4 * kWave) {
-    // positions base + 4 * lane + q, q = 0..3, and the one before them
-    u32 id[5];
-    bool heavy[5];
-#pragma unroll
-    for (int q = 0; q < 5; ++q) {
-      const u32 p = base + 4 * lane + q - 1;       // >= p0 - 1 >= 0
-      const u64 key = skeys[min(p, n - 1)];
-      id[q] = bucket_id(key, hv, &heavy[q]);
-    }
-    u32 mine = n;
-#pragma unroll
-    for (int q = 3; q >= 0; --q) {
-      const u32 p = base + 4 * lane + q;
-      if (p < n && (id[q + 1] != id[q] || (p == p0 && heavy[q + 1]))) mine = p;
-    }
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) mine = min(mine, (u32)__shfl_xor((int)mine, d, kWave));
-    found = mine;
-  }
-  if (lane == 0) borders[c] = found;
+}
+
+template <int THREADS, int ITEMS>
+__global__ void __launch_bounds__(THREADS)
+spread(const u32* __restrict__ code, const uint16_t* __restrict__ from, u32 n, const u32* __restrict__ by_pos,
+       const u32* __restrict__ by_heavy, u32* __restrict__ out) {
+  __shared__ u32 lds[THREADS * ITEMS];
+  spread_tile<THREADS, ITEMS>(code, from, n, blockIdx.x, by_pos, by_heavy, out, lds);
 }
 
 }  // namespace hps

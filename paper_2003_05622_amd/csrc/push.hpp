@@ -1,15 +1,15 @@
 // Gradient reduce-by-key fused with the Adagrad row update.
 //
-// The dedup left the occurrences grouped by unique key: seg_off[u] .. seg_off[u+1]
-// are the sorted positions of key u, and bagperm[j] is the bag of the occurrence at
-// sorted position j.  The gradient of a sum-pooled bag reaches every occurrence
-// unchanged, so the gradient of key u is the sum of grads[bagperm[j]] over its
+// The dedup left the occurrences grouped by distinct key: seg_off[u] .. seg_off[u+1]
+// are the positions of key u, and bags[j] is the bag of the occurrence at
+// position j.  The gradient of a sum-pooled bag reaches every occurrence
+// unchanged, so the gradient of key u is the sum of grads[bags[j]] over its
 // positions.  Keys are handled by how often they occur; the pull's lookup already
 // sorted the frequent ones into work lists (table.hpp, OftenLists):
 //
 //   push_main   one launch, blocks take one of three roles:
-//                 short   a group of LPR lanes per key with at most kShortSeg
-//                         occurrences: reduced and updated on the spot;
+//                 short   a span of distinct keys per block, a group of LPR lanes per key with
+//                         at most kShortSeg occurrences: reduced and updated on the spot;
 //                 medium  one wave per listed key (up to kMedSeg occurrences): its
 //                         lane groups stride over the positions, then add up;
 //                 chunks  one block per listed chunk (kChunk positions of a still more
@@ -25,36 +25,32 @@
 namespace hps {
 
 constexpr int kPushThreads = 256;
-constexpr int kPushShortBlocks = 1024;   // fixed grids: groups, waves and blocks loop (more short blocks measured slower)
-constexpr int kPushMediumBlocks = 512;   // a multiple of kCountShards
+constexpr int kPushMediumBlocks = 512;   // fixed grids: waves and blocks loop
 // (one block per chunk, as many as the mini-batch could have, up to this: with 512 the skewed
 // workload, most of whose occurrences are chunks of very frequent keys, ran its push at two
 // waves per SIMD, 0.55 ms instead of 0.32; blocks without a chunk return at once)
 constexpr int kPushChunkBlocks = 4096;
 constexpr int kPushLongBlocks = 256;
 constexpr int kPushInFlight = 8;  // gradient rows a lane group has in flight
-constexpr u32 kBagMask = 0x7FFFFFFFu;
 constexpr int kStepRowwise = 0;      // Adagrad, one accumulator per row
 constexpr int kStepElementwise = 1;  // Adagrad, one accumulator per element
 constexpr int kStepAdd = 2;          // Section 4.1 accumulate: the summed values are added
 
 struct PushArgs {
+  UniqueSpans spans;
   const u32* seg_off;
-  const u32* bagperm;
+  const u32* bags;
   const u32* rows;
   const float* grads;
   const float* inv_len;   // != null (mean pooling): per bag, the share of its gradient an occurrence gets
   const PullCtx* ctx;
-  const u32* med_list;  // unique indices, kCountShards shards of med_cap entries
-  u32 med_cap;
+  const u32* med_list;        // unique indices
   const uint2* long_list;     // (unique index, first chunk item)
   const uint2* chunk_items;   // (unique index, chunk number)
-  u32 short_blocks, medium_blocks;   // roles of push_main's blocks: short, medium, chunks
+  u32 medium_blocks;          // roles of push_main's blocks: short (one per span), medium, chunks
   float* partials;      // [chunk item][dim]
   float lr, eps;
   int kind;   // what a touched row takes: kStepRowwise, kStepElementwise or kStepAdd
-  HeavyRing* ring;   // != null: one more block puts the pull's list of frequent keys in order
-  u32 ring_slot;
 };
 
 // One step on row r with the row's summed gradient (or summed values) held as
@@ -130,7 +126,7 @@ __device__ __forceinline__ void add_positions(float4* g, const PushArgs& a, u32 
     for (int k = 0; k < kPushInFlight; ++k) {
       const u32 j = j0 + k * stride;
       on[k] = j < hi;
-      bag[k] = on[k] ? (a.bagperm[j] & kBagMask) : 0u;
+      bag[k] = on[k] ? a.bags[j] : 0u;
     }
     float4 v[kPushInFlight][COLS];
     float share[kPushInFlight];
@@ -169,12 +165,19 @@ __device__ __forceinline__ void add_positions(float4* g, const PushArgs& a, u32 
 }
 
 template <int LPR, int COLS>
-__device__ __forceinline__ void push_short_role(const TableView& t, const PushArgs& a, u32 block,
-                                                u32 n_blocks) {
+__device__ __forceinline__ void push_short_role(const TableView& t, const PushArgs& a, u32 span) {
   const u32 sub = threadIdx.x % LPR;
-  const u32 n_unique = a.ctx->n_unique;
-  const u32 n_groups = n_blocks * (kPushThreads / LPR);
-  for (u32 u = (block * kPushThreads + threadIdx.x) / LPR; u < n_unique; u += n_groups) {
+  const bool heavies = span >= a.spans.n_spans;
+  const u32 h0 = heavies ? (span - a.spans.n_spans) * kHeavyGroup : 0u;
+  u32 first = 0, count;
+  if (heavies) count = a.ctx->n_heavy > h0 ? min(kHeavyGroup, a.ctx->n_heavy - h0) : 0u;
+  else unique_span(a.spans, a.ctx, span, &first, &count);
+  for (u32 k = threadIdx.x / LPR; k < count; k += kPushThreads / LPR) {
+    u32 u = first + k;
+    if (heavies) {
+      u = a.spans.bucket_start[a.spans.n_spans + h0 + k];
+      if (a.spans.bucket_start[a.spans.n_spans + h0 + k + 1] == u) continue;
+    }
     const u32 lo = a.seg_off[u], hi = a.seg_off[u + 1];
     if (hi - lo > kShortSeg) continue;      // on one of the lists
     const u32 r = a.rows[u];
@@ -188,19 +191,13 @@ __device__ __forceinline__ void push_short_role(const TableView& t, const PushAr
 }
 
 template <int LPR, int COLS>
-__device__ __forceinline__ void push_medium_role(const TableView& t, const PushArgs& a, u32 block,
-                                                 u32 n_blocks) {
+__device__ __forceinline__ void push_medium_role(const TableView& t, const PushArgs& a, u32 block) {
   constexpr u32 kGroups = kWave / LPR;
   constexpr u32 kWavesPerBlock = kPushThreads / kWave;
   const u32 group = lane_id() / LPR, sub = lane_id() % LPR;
-  // block b serves list shard b % 64, together with the other blocks of that residue
-  const u32 shard = block % kCountShards;
-  const u32 shard_blocks = (n_blocks - shard + kCountShards - 1) / kCountShards;
-  const u32 count = min(a.ctx->med_count[shard], a.med_cap);
-  const u32* list = a.med_list + (u64)shard * a.med_cap;
-  for (u32 m = (block / kCountShards) * kWavesPerBlock + threadIdx.x / kWave; m < count;
-       m += shard_blocks * kWavesPerBlock) {
-    const u32 u = list[m];
+  const u32 count = a.ctx->n_med;
+  for (u32 m = block * kWavesPerBlock + threadIdx.x / kWave; m < count; m += a.medium_blocks * kWavesPerBlock) {
+    const u32 u = a.med_list[m];
     float4 g[COLS];
 #pragma unroll
     for (int c = 0; c < COLS; ++c) g[c] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -270,23 +267,13 @@ template <int LPR, int COLS>
 __global__ void __launch_bounds__(kPushThreads) push_main(TableView t, PushArgs a) {
   __shared__ float4 lds[kPushThreads];
   if (load_error(t.st) != 0) return;
-  if (a.ring && blockIdx.x == 0) {
-    // Not part of the push: the list of frequent keys the pull's lookup left (common.hpp) is
-    // put in order here, where it costs nothing -- the next dedup that reads it starts after
-    // this push, and the push takes several times longer than this block.  (The first block,
-    // so that it starts at once: behind thousands of others it would end the kernel late.)
-    finalize_heavy(a.ring, a.ring_slot);
-    return;
-  }
-  const u32 b = a.ring ? blockIdx.x - 1 : blockIdx.x;
-  const u32 role_blocks = a.ring ? gridDim.x - 1 : gridDim.x;
-  if (b < a.short_blocks) {
-    push_short_role<LPR, COLS>(t, a, b, a.short_blocks);
-  } else if (b < a.short_blocks + a.medium_blocks) {
-    push_medium_role<LPR, COLS>(t, a, b - a.short_blocks, a.medium_blocks);
+  const u32 b = blockIdx.x, n_short = span_blocks(a.spans);
+  if (b < n_short) {
+    push_short_role<LPR, COLS>(t, a, b);
+  } else if (b < n_short + a.medium_blocks) {
+    push_medium_role<LPR, COLS>(t, a, b - n_short);
   } else {
-    push_chunks_role<LPR, COLS>(t, a, b - a.short_blocks - a.medium_blocks,
-                          role_blocks - a.short_blocks - a.medium_blocks, lds);
+    push_chunks_role<LPR, COLS>(t, a, b - n_short - a.medium_blocks, gridDim.x - n_short - a.medium_blocks, lds);
   }
 }
 

@@ -18,9 +18,8 @@
 // Mini-batch keys are hashed feature ids, so these bits separate almost all distinct keys;
 // the rare runs that still mix different keys are found and put right afterwards
 // (dedup.hpp).  With eight passes every bit is sorted and nothing is left to put right.
-// The usual form, by bucket ids (bucket_id below), has passes of its own without any waits
-// between workgroups (partition.hpp) and finishes per region (bucket.hpp); it shares this
-// file's key range, bucket ids and ranking helpers.
+// The usual form, by buckets, has kernels of its own without any waits between workgroups
+// (partition.hpp, bucket.hpp); it shares this file's key range and ranking helpers.
 // Either way the dedup's result is exact for any input.
 //
 // Cross-tile counts without a serial chain: tiles are grouped, `group` consecutive
@@ -60,7 +59,7 @@ constexpr int kHistWords = kHistShards * kMaxPasses * kRadix;   // one pull's hi
 // the counts of tiles with smaller tickets, which are running and need microseconds each
 // (the bucket form has no waits between workgroups at all).
 constexpr u64 kWaitTicks = 500000000ull;
-constexpr u32 kRangeSamples = 2048;    // keys sampled for the key range (sort_prepare)
+constexpr u32 kRangeSamples = 512;     // keys sampled for the key range
 constexpr u32 kEpochMod = 4095;        // epochs run 1..4095
 constexpr u32 kMaxTileGroup = 64;      // tiles per group at most (count fits 19 bits)
 constexpr int kLookChunk = 8;          // status rows read per round trip
@@ -70,11 +69,8 @@ static_assert(kRadix == 4 * kWave, "each look-back lane owns four digits");
 
 struct SortPlan {
   int n_pass;       // digits sorted
-  int low_shift;    // plain mode: 64 - 8 * n_pass: so many low bits stay unsorted if keys fill 64 bits
+  int low_shift;    // 64 - 8 * n_pass: so many low bits stay unsorted if keys fill 64 bits
   u32 group;        // tiles per group
-  int by_id;        // 1: the passes sort by the bucket id of the key (see bucket_id) instead
-  int nat_shift;    // by_id: 64 - log2 of the number of natural buckets
-  u32 max_heavy;    // by_id: heavy keys that get buckets of their own, at most
 };
 
 __device__ __forceinline__ u32 key_digit(u64 k, int shift) {
@@ -92,17 +88,11 @@ __device__ __forceinline__ u64 range_rel(u64 key, const KeyRange& r) {
 __device__ __forceinline__ u64 sorted_prefix(u64 key, const KeyRange& r) {
   return range_rel(key, r) >> r.base;
 }
-// Bucket form: the range cut into 2^nat_bits equal parts.
-__device__ __forceinline__ u32 natural_bucket(u64 key, const KeyRange& r) {
-  const u64 rel = range_rel(key, r);
-  return r.direct ? (u32)rel : (u32)(((rel >> r.pre) * r.mult) >> 32);
-}
-// From the smallest and largest sampled key.  The range is widened by 1/256 of its length
-// at both ends: with kRangeSamples samples of evenly spread keys, the share of keys
-// beyond the widened ends (they all land in the first / last part) is then far below one
-// part's share.
-__device__ __forceinline__ KeyRange make_range(u64 lo, u64 hi, const SortPlan& plan) {
-  const u64 widen = (hi - lo) >> 8;
+// The range from the smallest and largest sampled key, widened by 1/64 of its length at both ends:
+// with kRangeSamples samples of evenly spread keys, the share of keys beyond the widened ends
+// (they all land in the first / last part) is then far below one part's share.
+__device__ __forceinline__ KeyRange widened_range(u64 lo, u64 hi) {
+  const u64 widen = (hi - lo) >> 6;
   lo = lo > widen ? lo - widen : 0;
   hi = hi + widen >= hi ? hi + widen : ~0ull;
   KeyRange r;
@@ -110,80 +100,24 @@ __device__ __forceinline__ KeyRange make_range(u64 lo, u64 hi, const SortPlan& p
   r.span = hi - lo;
   const u32 bits = r.span ? 64 - __clzll((long long)r.span) : 0;
   r.pre = bits > 32 ? bits - 32 : 0;
-  const u32 nat_bits = plan.by_id ? 64 - plan.nat_shift : 0;
-  r.direct = (r.span >> nat_bits) == 0;
-  // span >= 2^nat_bits here, so the quotient is below 2^32 and parts are numbered below 2^nat_bits
-  r.mult = r.direct ? 0u : (u32)((1ull << (32 + nat_bits)) / ((r.span >> r.pre) + 1));
-  if (plan.by_id) {
-    r.base = 0;
-    return r;
-  }
-  // Plain form: the passes order sorted_bits bits of rel from bit `base` up, so every key with
-  // rel < 2^(base + sorted_bits) is placed exactly, not only those inside the sampled range:
-  // the range that is covered reaches that far, with the sampled range in its middle (a
-  // long-tailed set of raw ids has many keys beyond its largest sample; clamped to one
-  // place they would all have to be put in order afterwards).
+  r.mult = r.direct = r.base = 0;
+  return r;
+}
+// Plain form: the passes order sorted_bits bits of rel from bit `base` up, so every key with
+// rel < 2^(base + sorted_bits) is placed exactly, not only those inside the sampled range:
+// the range that is covered reaches that far, with the sampled range in its middle (a
+// long-tailed set of raw ids has many keys beyond its largest sample; clamped to one
+// place they would all have to be put in order afterwards).
+__device__ __forceinline__ KeyRange plain_range(u64 lo, u64 hi, const SortPlan& plan) {
+  KeyRange r = widened_range(lo, hi);
+  const u32 bits = r.span ? 64 - __clzll((long long)r.span) : 0;
   const u32 sorted_bits = 64 - plan.low_shift;
   r.base = bits > sorted_bits ? bits - sorted_bits : 0;
   const u64 cover = r.base + sorted_bits >= 64 ? ~0ull : (1ull << (r.base + sorted_bits)) - 1;
   const u64 spare = (cover - r.span) / 2;
-  r.lo = lo > spare ? lo - spare : 0;
+  r.lo = r.lo > spare ? r.lo - spare : 0;
   r.span = cover;
   return r;
-}
-
-// ---- bucket ids ---------------------------------------------------------------------
-// Keys that make up a large share of a mini-batch ("heavy" keys; found from a sample,
-// bucket.hpp) get buckets of their own, so that every other bucket stays small enough
-// to be sorted inside one workgroup.  With the heavy keys h_0 < h_1 < ... the id of a
-// key is
-//     natural(key) + 2 * #{i : h_i < key} + (key is heavy ? 1 : 0),
-// natural(key) = which of 2^(64 - nat_shift) equal parts of the mini-batch's key range the
-// key lies in (natural_bucket; for hashed keys: the key's leading bits),
-// which is monotone in the key; keys share an id only if they share the part and no
-// heavy key lies between them, and a heavy key shares its id with nothing.
-
-// The heavy keys in LDS, with their spans per value of the top bits, so that a lookup
-// costs one LDS read unless heavy keys share the key's top bits.  A list of more than
-// kSmallHeavy keys (rare) stays in global memory: `keys` points to it instead of `lds_keys`.
-struct HeavyLds {
-  u64 lds_keys[kSmallHeavy + 1];
-  const u64* keys;
-  u32 span[1 << kHeavyTopBits];
-  KeyRange range;
-  u32 max_heavy;     // only the max_heavy smallest heavy keys get buckets of their own
-};
-
-// All threads of the block; the caller's next barrier makes the copy visible.  H.range is
-// the caller's to fill.
-__device__ __forceinline__ void load_heavy(HeavyLds& H, const HeavySet* set, u32 max_heavy) {
-  // (only the listed keys are ever looked at: the spans index nothing behind them)
-  const u32 count = min(set->count, (u32)kMaxHeavy);
-  const bool small = count <= (u32)kSmallHeavy;
-  if (small)
-    for (u32 i = threadIdx.x; i < count; i += blockDim.x) H.lds_keys[i] = set->keys[i];
-  for (u32 i = threadIdx.x; i < (1u << kHeavyTopBits); i += blockDim.x) H.span[i] = set->span[i];
-  if (threadIdx.x == 0) {
-    H.max_heavy = max_heavy;
-    H.keys = small ? H.lds_keys : set->keys;
-  }
-}
-
-// *heavy tells whether the key is one of the heavy keys (that count: see max_heavy;
-// limiting them keeps the ids of a small dedup below 256, one pass, and the id monotone).
-__device__ __forceinline__ u32 bucket_id(u64 key, const HeavyLds& H, bool* heavy) {
-  const u32 sp = H.span[(u32)(key >> (64 - kHeavyTopBits))];
-  u32 m = sp & 0xFFFFu;
-  const u32 end = m + (sp >> 16);
-  bool is_heavy = false;
-  if (m < end) {                       // (most keys: no heavy key shares their top bits)
-    const u64* hk = H.keys;
-    while (m < end && hk[m] < key) ++m;
-    is_heavy = m < end && m < H.max_heavy && hk[m] == key;
-  }
-  *heavy = is_heavy;
-  m = min(m, H.max_heavy);
-  return natural_bucket(key, H.range) + 2 * m + (is_heavy ? 1u : 0u);
 }
 
 // ---- status words -------------------------------------------------------------------
@@ -278,11 +212,12 @@ __device__ __forceinline__ u32 wave_sum_words(const u32* words, u32 first, u32 l
   return c;
 }
 
-// The lanes of the wave (among `valid` ones) whose digit equals this lane's.
+// The lanes of the wave (among `valid` ones) whose digit (of BITS bits) equals this lane's.
+template <int BITS = kRadixBits>
 __device__ __forceinline__ u64 match_mask(u32 d, bool valid) {
   u64 same = __ballot(valid);
 #pragma unroll
-  for (int b = 0; b < kRadixBits; ++b) {
+  for (int b = 0; b < BITS; ++b) {
     const bool bit = (d >> b) & 1;
     const u64 bb = __ballot(bit);
     same &= bit ? bb : ~bb;
@@ -303,10 +238,10 @@ __device__ __forceinline__ u64 match_mask(u32 d, bool valid) {
 // instruction that hit the same address in ascending lane order -- which the instruction
 // set manual does not promise, so the library measures it (probe_lane_order below, once per
 // GPU when the first table is created there) and uses this form only where it holds.
-template <bool ORDERED>
+template <bool ORDERED, int BITS = kRadixBits>
 __device__ __forceinline__ u32 digit_rank(u32* counter, u32 d, bool valid, u64 lt) {
   if (ORDERED) return valid ? atomicAdd(counter, 1u) : 0u;
-  const u64 same = match_mask(d, valid);
+  const u64 same = match_mask<BITS>(d, valid);
   const u32 before = __popcll(same & lt);
   u32 old = 0;
   if (valid && before == 0) old = atomicAdd(counter, (u32)__popcll(same));
@@ -361,7 +296,7 @@ __device__ __forceinline__ void match_digit(u32 d, bool valid, u64 lt, u32* befo
 }
 
 // Resets of the pull context, shared by the first kernel of either dedup form.
-__device__ __forceinline__ void reset_ctx(PullCtx* ctx, u32 n, u32 by_id) {
+__device__ __forceinline__ void reset_ctx(PullCtx* ctx, u32 n, u32 by_id, u32 n_heavy) {
   if (threadIdx.x == 0) {
     ctx->n_unique = 0;
     ctx->n_long = 0;
@@ -370,11 +305,13 @@ __device__ __forceinline__ void reset_ctx(PullCtx* ctx, u32 n, u32 by_id) {
     ctx->sort_error = 0;
     ctx->n_slow = 0;
     ctx->n_slow_one_key = 0;
-    ctx->n_hot = 0;
+    ctx->n_med = 0;
+    ctx->n_heavy = n_heavy;
+    ctx->ticket = 0;
     ctx->n_total = n;
     ctx->by_id = by_id;
   }
-  if (threadIdx.x < kCountShards) ctx->med_count[threadIdx.x] = 0;
+  if (threadIdx.x < kCountShards) ctx->uniq_shard[threadIdx.x] = 0;
 }
 
 // bag_of[i] = bag of occurrence i, by the blocks of a launch that are given this role:
@@ -407,17 +344,19 @@ __device__ __forceinline__ void expand_bags(const i32* __restrict__ offsets, u32
   }
 }
 
-// Smallest and largest of kRangeSamples sampled keys, to every thread of the block (kPrepThreads
-// threads; contains barriers; s_lo / s_hi: kPrepThreads / kWave words of LDS each).  The samples
-// are kRangeSamples / 8 evenly spaced runs of 8 consecutive keys (a 64-byte line each, the first
-// and the last included), so that a wave's request is 8 lines and not 64: every block asks for
-// the same lines, and the caches serve requests, not bytes.
+// Smallest and largest of kRangeSamples sampled keys: thread 0 of each wave leaves its wave's in
+// s_lo / s_hi (THREADS / kWave words of LDS each), after the caller's next barrier
+// sampled_ends() puts them together.  The samples are kRangeSamples / 8 evenly spaced runs of 8
+// consecutive keys (a 64-byte line each, the first and the last included), so that a wave's
+// request is 8 lines and not 64: every block asks for the same lines, and the caches serve
+// requests, not bytes.
+template <int THREADS>
 __device__ __forceinline__ void sample_key_range(const u64* __restrict__ keys, u32 n, u64* s_lo,
                                                  u64* s_hi) {
   u64 lo = ~0ull, hi = 0;
   const u32 n_samples = min(n, kRangeSamples);
   const u32 n_lines = n >> 3;
-  for (u32 j = threadIdx.x; j < n_samples; j += kPrepThreads) {
+  for (u32 j = threadIdx.x; j < n_samples; j += THREADS) {
     const u32 at = n > kRangeSamples
                        ? (u32)(((u64)(j >> 3) * (n_lines - 1)) / (kRangeSamples / 8 - 1)) * 8 + (j & 7)
                        : j;
@@ -431,6 +370,12 @@ __device__ __forceinline__ void sample_key_range(const u64* __restrict__ keys, u
     hi = max(hi, (u64)__shfl_xor((unsigned long long)hi, d, kWave));
   }
   if (lane_id() == 0) { s_lo[threadIdx.x / kWave] = lo; s_hi[threadIdx.x / kWave] = hi; }
+}
+template <int THREADS>
+__device__ __forceinline__ void sampled_ends(const u64* s_lo, const u64* s_hi, u64* lo, u64* hi) {
+  *lo = s_lo[0]; *hi = s_hi[0];
+  for (int w = 1; w < THREADS / kWave; ++w) { *lo = min(*lo, s_lo[w]); *hi = max(*hi, s_hi[w]); }
+  if (*lo > *hi) *lo = *hi = 0;            // n == 0
 }
 
 // First kernel of a plain-form dedup: histograms of every pass's digit over all keys (the
@@ -461,21 +406,20 @@ sort_prepare(const u64* __restrict__ keys, u32 n, SortPlan plan, u32* __restrict
     const u32 i = blockIdx.x * kSortTile + k * kPrepThreads + threadIdx.x;
     first_keys[k] = i < n ? keys[i] : 0;
   }
-  sample_key_range(keys, n, s_lo, s_hi);
+  sample_key_range<kPrepThreads>(keys, n, s_lo, s_hi);
   for (u32 sh = blockIdx.x; sh < (u32)kHistShards; sh += hist_blocks)     // the next pull's counters
     for (int i = threadIdx.x; i < kMaxPasses * kRadix; i += kPrepThreads)
       ghist_next[sh * kMaxPasses * kRadix + i] = 0;
   for (int i = threadIdx.x; i < kMaxPasses * kRadix; i += kPrepThreads) (&h[0][0])[i] = 0;
   if (blockIdx.x == 0) {
     if (threadIdx.x < kMaxPasses + 2) tickets[threadIdx.x] = 0;
-    reset_ctx(ctx, n, 0u);
+    reset_ctx(ctx, n, 0u, 0u);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    u64 lo = s_lo[0], hi = s_hi[0];
-    for (int w = 1; w < kPrepThreads / kWave; ++w) { lo = min(lo, s_lo[w]); hi = max(hi, s_hi[w]); }
-    if (lo > hi) lo = hi = 0;            // n == 0
-    s_range = make_range(lo, hi, plan);
+    u64 lo, hi;
+    sampled_ends<kPrepThreads>(s_lo, s_hi, &lo, &hi);
+    s_range = plain_range(lo, hi, plan);
     if (blockIdx.x == 0) ctx->range = s_range;
   }
   __syncthreads();

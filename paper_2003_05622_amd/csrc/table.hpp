@@ -128,7 +128,6 @@ static_assert(kPullInFlight % kLookupLanes == 0, "every lane of a group owns the
 constexpr int kLookupGroups = kProbeThreads / kLookupLanes;
 constexpr int kProbeMaxBlocks = 1024;
 constexpr u32 kNoSlot = ~0u;
-constexpr u32 kMissLdsCap = 2048;        // missing keys a block can list per lookup
 constexpr u32 kNewLdsCap = 1024;         // created keys a block lists for its common initialisation
 constexpr u32 kLongLdsCap = 64;          // very frequent keys whose chunk items a block writes together
 constexpr u32 kMedLdsCap = 512;          // medium keys a block buffers before it appends
@@ -136,25 +135,48 @@ constexpr u32 kShortSeg = 16;            // occurrences handled serially by one 
 constexpr u32 kMedSeg = 512;             // occurrences handled by one wave
 constexpr u32 kChunk = 1024;             // occurrences per queued chunk of a longer key
 
-// What the pull leaves for the push about keys that occur often (push.hpp): keys with
-// kShortSeg < occurrences <= kMedSeg go to a sharded list (shard b % 64 for block b,
-// med_cap entries per shard), keys with more are cut into chunks of kChunk positions.
+// Where the distinct keys of a mini-batch lie in uniq / seg_off / rows.  Bucket form (bucket.hpp): natural
+// bucket c's in [bucket_start[c], + count[c]), heavy key h at bucket_start[n_spans + h] if that
+// bucket is not empty.  Plain form (bucket_start == null): all in [0, ctx->n_unique), taken in
+// spans of plain_span.  A block of the kernels that go through the distinct keys takes one span,
+// or (blocks from n_spans on) up to kHeavyGroup heavy keys.
+struct UniqueSpans {
+  const u32* bucket_start;
+  const u32* count;
+  u32 n_spans;
+  u32 max_heavy;         // bucket form: heavy buckets there may be
+  u32 plain_span;        // plain form
+};
+constexpr u32 kHeavyGroup = 256;
+__host__ __device__ __forceinline__ u32 span_blocks(const UniqueSpans& s) {
+  return s.n_spans + (s.max_heavy + kHeavyGroup - 1) / kHeavyGroup;
+}
+__device__ __forceinline__ void unique_span(const UniqueSpans& s, const PullCtx* ctx, u32 c, u32* first, u32* count) {
+  if (s.bucket_start) {
+    *first = s.bucket_start[c];
+    *count = s.count[c] & 0x7FFFFFFFu;
+  } else {
+    const u32 u = ctx->n_unique;
+    *first = c * s.plain_span;
+    *count = u > *first ? min(s.plain_span, u - *first) : 0u;
+  }
+}
+
+// What the lookup leaves for the push about keys that occur often (push.hpp): keys with
+// kShortSeg < occurrences <= kMedSeg are listed, keys with more are cut into
+// chunks of kChunk positions.
 struct OftenLists {
-  const u32* seg_off;
   PullCtx* ctx;
   u32* med_list;
-  u32 med_cap;
   uint2* long_list;     // (unique index, first chunk item)
   uint2* chunk_items;   // (unique index, chunk number)
   HeavyRaw* heavy_raw;  // keys with at least heavy_min occurrences are listed for the next dedup
   u32 heavy_min;
-  uint2* hot_list;      // (unique index, row) of keys with at least hot_min occurrences, for the pooling kernel
-  u32 hot_min;
-  u32 hot_cap;
+  HeavyRaw* heavy_next; // the list the next lookup will fill: emptied
   // Host memory (or null) that receives serial | flags << 32 about the dedup before this
   // lookup: kReportBucket = it took the bucket form, kReportSlow = and more than 1/8 of
-  // the occurrences lay in regions that had to be ordered through global memory,
-  // kReportOneKey = most of them in regions that one key fills at least half of (keys
+  // the occurrences lay in buckets that had to be ordered through global memory,
+  // kReportOneKey = most of them in buckets that one key fills at least half of (keys
   // that turned frequent without warning, which the next hint will list; otherwise the
   // keys do not suit the buckets); kReportMixed = it took the plain form and more places
   // than fix_mixed_runs can note had different keys agreeing in all sorted bits (keys in
@@ -175,138 +197,6 @@ __device__ __forceinline__ float acc_marked(float value) {
 }
 __device__ __forceinline__ bool acc_is_marked(float stored) {
   return (__float_as_uint(stored) & 0x80000000u) != 0;
-}
-
-// One step of a bitonic sorting network over words[0, size), size a power of two; all threads
-// of a block of 256, a barrier before every step.  GLOBAL: the words live in global memory
-// and are read and written with device-scope accesses, so that what one wave wrote before the
-// barrier is what another reads after it.
-template <bool GLOBAL>
-__device__ __forceinline__ void bitonic_sort_256(u64* words, u32 size) {
-  const u32 tid = threadIdx.x;
-  for (u32 k = 2; k <= size; k <<= 1) {
-    for (u32 j = k >> 1; j > 0; j >>= 1) {
-      if (GLOBAL) __threadfence();
-      __syncthreads();
-      for (u32 i = tid; i < size; i += 256) {
-        const u32 partner = i ^ j;
-        if (partner > i) {
-          u64 x, y;
-          if (GLOBAL) {
-            x = __hip_atomic_load(words + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            y = __hip_atomic_load(words + partner, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          } else {
-            x = words[i];
-            y = words[partner];
-          }
-          const bool up = (i & k) == 0;
-          if ((x > y) == up) {
-            if (GLOBAL) {
-              __hip_atomic_store(words + i, y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              __hip_atomic_store(words + partner, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            } else {
-              words[i] = y;
-              words[partner] = x;
-            }
-          }
-        }
-      }
-    }
-  }
-  if (GLOBAL) __threadfence();
-  __syncthreads();
-}
-
-// Called by all threads of one block (exactly 256) once lookup `slot`'s list of frequent
-// keys is complete: orders it into the ring's set and empties the next list.  A list of fewer
-// than kHalfHeavy keys (nearly always) is put in order in LDS in one go; a longer one as two halves,
-// each ordered in LDS and parked in the raw list's own storage (which nobody reads again before
-// it is refilled), then merged: every element finds its place by a binary search in the other
-// half.
-constexpr u32 kHalfHeavy = (kMaxHeavy + 1) / 2;
-__device__ __forceinline__ void finalize_heavy(HeavyRing* ring, u32 slot) {
-  constexpr u32 kSize = kMaxHeavy + 1;             // a power of two
-  __shared__ u64 sorted[kHalfHeavy];
-  const u32 tid = threadIdx.x;
-  HeavyRaw& raw = ring->raw[slot];
-  HeavySet& set = ring->set[slot];
-  const u32 count = min(raw.count, (u32)kMaxHeavy);
-  const bool small = count < kHalfHeavy;
-  if (small) {
-    // the smallest power of two that holds the listed keys (the order of equal keys does not
-    // matter; everything behind is all-ones already)
-    u32 size = 2;
-    while (size < count) size <<= 1;
-    for (u32 i = tid; i < kHalfHeavy; i += 256) sorted[i] = i < count ? raw.keys[i] : ~0ull;
-    bitonic_sort_256<false>(sorted, size);
-    for (u32 i = tid; i < kSize; i += 256) set.keys[i] = i < kHalfHeavy ? sorted[i] : ~0ull;
-  } else {
-    for (u32 half = 0; half < 2; ++half) {
-      u64* part = raw.keys + half * kHalfHeavy;
-      for (u32 i = tid; i < kHalfHeavy; i += 256) sorted[i] = half * kHalfHeavy + i < count ? part[i] : ~0ull;
-      bitonic_sort_256<false>(sorted, kHalfHeavy);
-      for (u32 i = tid; i < kHalfHeavy; i += 256) part[i] = sorted[i];
-      __syncthreads();
-    }
-    __threadfence();
-    __syncthreads();
-    // merge: an element's place = its index in its own half + the number of elements of the
-    // other half before it (equal elements: those of the first half first)
-    for (u32 e = tid; e < kSize; e += 256) {
-      const bool second = e >= kHalfHeavy;
-      const u32 i = second ? e - kHalfHeavy : e;
-      const u64* mine = raw.keys + (second ? kHalfHeavy : 0);
-      const u64* other = raw.keys + (second ? 0 : kHalfHeavy);
-      const u64 x = __hip_atomic_load(mine + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      u32 m = 0;
-#pragma unroll
-      for (u32 step = kHalfHeavy / 2; step >= 1; step >>= 1) {
-        const u64 y = __hip_atomic_load(other + m + step - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (second ? y <= x : y < x) m += step;
-      }
-      // (m counts the elements other[0 .. m) that go before x; at most kHalfHeavy - 1 can be
-      // found this way, the last one is looked at separately)
-      const u64 last = __hip_atomic_load(other + kHalfHeavy - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (m == kHalfHeavy - 1 && (second ? last <= x : last < x)) m = kHalfHeavy;
-      set.keys[i + m] = x;
-    }
-    __threadfence();
-    __syncthreads();
-  }
-  // spans: thread t takes top-bit values 4t .. 4t+3
-  u32 first[5];
-#pragma unroll
-  for (int e = 0; e < 5; ++e) {
-    const u32 v = 4 * tid + e;
-    u32 m = count;
-    if (v < (1u << kHeavyTopBits)) {
-      const u64 bound = (u64)v << (64 - kHeavyTopBits);
-      m = 0;
-      if (small) {
-#pragma unroll
-        for (u32 step = kHalfHeavy / 2; step >= 1; step >>= 1)     // the all-ones padding is never below
-          if (sorted[m + step - 1] < bound) m += step;
-      } else {
-#pragma unroll
-        for (u32 step = kSize / 2; step >= 1; step >>= 1)
-          if (__hip_atomic_load(set.keys + m + step - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < bound) m += step;
-      }
-    }
-    first[e] = m;
-  }
-#pragma unroll
-  for (int e = 0; e < 4; ++e) set.span[4 * tid + e] = first[e] | ((first[e + 1] - first[e]) << 16);
-  if (tid == 0) {
-    set.count = count;
-    ring->raw[(slot + 1) % kHeavyRing].count = 0;
-  }
-}
-
-// No mini-batch seen yet: no heavy keys.
-__global__ void __launch_bounds__(256) init_heavy_set(HeavySet* set) {
-  for (u32 i = threadIdx.x; i <= (u32)kMaxHeavy; i += 256) set->keys[i] = ~0ull;
-  for (u32 i = threadIdx.x; i < (1u << kHeavyTopBits); i += 256) set->span[i] = 0;
-  if (threadIdx.x == 0) set->count = 0;
 }
 
 // Bits of a wave-wide ballot that belong to this lane's 8-lane group.
@@ -332,10 +222,9 @@ __global__ void __launch_bounds__(64) reset_state(TableState* st) {
     st->dump_count = 0;
   }
   if (threadIdx.x < kCountShards) st->miss_shard[threadIdx.x] = st->made_shard[threadIdx.x] = 0;
-  if (threadIdx.x == 0) st->miss_overflow = 0;
 }
 __global__ void __launch_bounds__(64) clear_error(TableState* st) {
-  if (threadIdx.x == 0) { st->error = 0; st->miss_overflow = 0; }
+  if (threadIdx.x == 0) st->error = 0;
   if (threadIdx.x < kCountShards) st->miss_shard[threadIdx.x] = st->made_shard[threadIdx.x] = 0;
 }
 __global__ void clear_dump_count(TableState* st) { st->dump_count = 0; }
@@ -348,12 +237,13 @@ __global__ void __launch_bounds__(64) set_ctx_empty(PullCtx* ctx, u32* seg_off) 
     ctx->sort_error = 0;
     ctx->n_slow = 0;
     ctx->n_slow_one_key = 0;
-    ctx->n_hot = 0;
+    ctx->n_med = 0;
+    ctx->n_heavy = 0;
     ctx->n_total = 0;
     ctx->by_id = 0;
     seg_off[0] = 0;
   }
-  if (threadIdx.x < kCountShards) ctx->med_count[threadIdx.x] = 0;
+  if (threadIdx.x < kCountShards) ctx->uniq_shard[threadIdx.x] = 0;
 }
 
 // Adds the rows insert_missing created to the table size and clears the counters.
@@ -367,25 +257,19 @@ __device__ __forceinline__ void commit_insert_wave(TableState* st) {
   if (lane == 0) {
     st->size += made;
     st->inserted = made;
-    st->miss_overflow = 0;
   }
 }
 __global__ void __launch_bounds__(64) commit_insert(TableState* st) { commit_insert_wave(st); }
 
 // After a lookup that creates nothing (accumulate): the number of keys not found
 // goes to st->absent, the counters are cleared.
-__global__ void __launch_bounds__(256) commit_absent(TableState* st, HeavyRing* ring, u32 slot) {
-  if (ring) finalize_heavy(ring, slot);
-  if (threadIdx.x >= kWave) return;
+__global__ void __launch_bounds__(64) commit_absent(TableState* st) {
   const u32 lane = lane_id();
   u32 missing = lane < kCountShards ? st->miss_shard[lane] : 0;
 #pragma unroll
   for (int d = 1; d < kWave; d <<= 1) missing += __shfl_xor(missing, d, kWave);
   if (lane < kCountShards) st->miss_shard[lane] = 0;
-  if (lane == 0) {
-    st->absent = (int)missing;
-    st->miss_overflow = 0;
-  }
+  if (lane == 0) st->absent = (int)missing;
 }
 
 // Where a key's probe sequence starts: an even line (n_lines is even), so that a 128-byte
@@ -592,98 +476,136 @@ __device__ __forceinline__ u32 search_keys(const TableView& t, const u64* my_key
   return to_create;
 }
 
-// rows[u] = the slot of unique key u, for u < *n_keys_dev.  Keys the table does not hold:
+// Bucket form: what the lookup needs besides the spans to hand the rows on by position
+// (partition.hpp: spread).
+struct RowsByPosition {
+  const u32* upos;       // null (plain form, accumulate): nothing is handed on
+  u32* by_pos;
+  u32* by_heavy;
+  const u64* heavy_keys; // the heavy keys this dedup went by
+};
+
+__device__ __forceinline__ void rows_by_position(const UniqueSpans& spans, const RowsByPosition& out, u32 c,
+                                                 u32 first, const u32* rows) {
+  const u32 end = spans.bucket_start[c + 1];
+  const bool wide = (spans.count[c] & 0x80000000u) != 0;       // (bucket.hpp: upos_at)
+  const uint16_t* up = reinterpret_cast<const uint16_t*>(out.upos + first);
+  for (u32 e = threadIdx.x; e < end - first; e += kProbeThreads)
+    out.by_pos[first + e] = rows[first + (wide ? out.upos[first + e] : (u32)up[e])];
+}
+
+// rows[u] = the slot of distinct key u.  Keys the table does not hold:
 //  - create == 0 (accumulate): rows[u] = kNoRow, counted in st->miss_shard;
 //  - create != 0 and the table has room for all the keys even if every one of them is new: the
 //    key is created right here, with its initial row (the line is at hand, and so are its free
 //    slots), counted in st->made_shard;
-//  - create != 0 otherwise (a pull that might overfill the table): rows[u] = kNoRow and the key
-//    is listed for insert_missing, which creates all the listed keys or none: block b appends to
-//    shard b % 64 of miss_list (shard_cap entries each); if a list does not fit, the overflow
-//    flag makes insert_missing scan all keys instead.
-// Also sorts the keys into the push's work lists by their number of occurrences.
+//  - create != 0 otherwise (a pull that might overfill the table): rows[u] = kNoRow, counted in
+//    st->miss_shard, for insert_missing, which creates all of them or none.
+// Also sorts the keys into the push's work lists by their number of occurrences, and (bucket form)
+// hands the rows on by position.  One span of distinct keys or group of heavy keys per block.
 //
-// A group of four lanes looks at a bucket at once and has four keys in flight, one per lane:
+// A group of four lanes looks at a bucket of the table at once and has four keys in flight, one per lane:
 // each lane loads and hashes its own key and, at the end, stores its own key's row and lists it
-// (one key per lane: full waves); in between the group goes through its four keys together.
-// Every phase runs for all four keys before the next phase starts: a wave waits for memory once
-// per phase and round, not once per key (16 groups share a wave, and nearly always one of them
-// has a key that needs the next bucket, or has to be created).
+// (one key per lane: full waves); in between the group goes through its four keys together
+// (search_keys).
 __global__ void __launch_bounds__(kProbeThreads)
-pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ n_keys_dev,
-            u32* __restrict__ rows, u32* __restrict__ miss_list, u32 shard_cap, u32 create,
-            u32 new_cap, OftenLists often) {
+pull_lookup(TableView t, u64* __restrict__ keys, u32* __restrict__ seg_off, UniqueSpans spans,
+            u32* __restrict__ rows, RowsByPosition out, u32 create, u32 new_cap, OftenLists often) {
   // new_cap <= kNewLdsCap: how much of the block's list of created keys is used (all of it,
   // except in tests of what happens when it is full)
   constexpr int K = kPullInFlight;            // keys a group has in flight
-  constexpr int OWN = K / kLookupLanes;       // of which each lane owns this many
-  __shared__ u32 s_missing, s_base, s_med, s_med_base, s_made, s_new, s_long;
+  static_assert(K == kLookupLanes, "one key per lane");
+  __shared__ u32 s_missing, s_med, s_med_base, s_made, s_new, s_long, s_unique;
   __shared__ uint4 s_long_list[kLongLdsCap];  // (key, first chunk item, chunks) of the block's very frequent keys
-  __shared__ u32 s_list[kMissLdsCap];
   __shared__ u32 s_med_list[kMedLdsCap];
   __shared__ u64 s_new_key[kNewLdsCap];       // keys created by this block, and their rows
   __shared__ u32 s_new_row[kNewLdsCap];
-  const u64 n_keys = *n_keys_dev;
-  if (often.report && blockIdx.x == 0 && threadIdx.x == 0) {
-    const PullCtx* c = often.ctx;
-    const u32 flags = (c->by_id ? kReportBucket : 0u) | ((u64)c->n_slow * 8 > c->n_total ? kReportSlow : 0u) |
-                      ((u64)c->n_slow_one_key * 2 >= c->n_slow ? kReportOneKey : 0u) |
-                      (!c->by_id && c->n_evidence > kMaxEvidence ? kReportMixed : 0u);
-    __hip_atomic_store(often.report, (unsigned long long)often.serial | ((unsigned long long)flags << 32),
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  PullCtx* ctx = often.ctx;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    often.heavy_next->count = 0;
+    if (often.report) {
+      const u32 flags = (ctx->by_id ? kReportBucket : 0u) | ((u64)ctx->n_slow * 8 > ctx->n_total ? kReportSlow : 0u) |
+                        ((u64)ctx->n_slow_one_key * 2 >= ctx->n_slow ? kReportOneKey : 0u) |
+                        (!ctx->by_id && ctx->n_evidence > kMaxEvidence ? kReportMixed : 0u);
+      __hip_atomic_store(often.report, (unsigned long long)often.serial | ((unsigned long long)flags << 32),
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
   }
-  if (often.ctx->sort_error != 0) {     // the dedup before this lookup failed
+  if (ctx->sort_error != 0) {     // the dedup before this lookup failed
     if (threadIdx.x == 0) raise_error(t.st, kErrInternal);
     return;
   }
   if (load_error(t.st) != 0) return;
+  const u32 c = blockIdx.x;
+  const bool heavies = c >= spans.n_spans;
+  u32 first = 0, count;
+  if (heavies) {
+    const u32 h0 = (c - spans.n_spans) * kHeavyGroup;
+    count = ctx->n_heavy > h0 ? min(kHeavyGroup, ctx->n_heavy - h0) : 0u;
+  } else {
+    unique_span(spans, ctx, c, &first, &count);
+  }
+  if (count == 0) return;
   if (threadIdx.x == 0) { s_missing = 0; s_med = 0; s_made = 0; s_new = 0; s_long = 0; }
+  if (threadIdx.x < kWave) {
+    // (kCountShards == kWave) distinct keys of the whole mini-batch
+    const u32 u = wave_incl_sum(ctx->uniq_shard[threadIdx.x]);
+    if (threadIdx.x == kWave - 1) s_unique = ctx->by_id ? u : ctx->n_unique;
+  }
   __syncthreads();
   // (the size does not change while this kernel runs: every thread decides the same)
-  const bool create_here = create && t.st->size + n_keys <= t.capacity;
+  const bool create_here = create && t.st->size + s_unique <= t.capacity;
   const u32 sub = threadIdx.x % kLookupLanes;
   const u32 lane0 = lane_id() & ~3u;          // the group's first lane
-  const u64 group = (u64)blockIdx.x * kLookupGroups + threadIdx.x / kLookupLanes;
-  const u64 n_groups = (u64)gridDim.x * kLookupGroups;
-  u32 made = 0;
+  u32 made = 0, missing = 0;
   // (the bound is the same for all lanes of a group, so a group stays together)
-  for (u64 u0 = group; u0 < n_keys; u0 += n_groups * K) {
-    // Key k of the group's K is owned by lane k % 4 (as its number k / 4): that lane keeps the
-    // key, where its search stands and its row; the group fetches them from it when needed.
-    u64 my_key[OWN], my_line[OWN];
-    u32 my_len[OWN], my_row[OWN], my_free[OWN];
-#pragma unroll
-    for (int o = 0; o < OWN; ++o) {
-      const u64 u = u0 + (u64)(o * kLookupLanes + sub) * n_groups;
-      my_key[o] = u < n_keys ? keys[u] : kEmptyKey;
-      my_len[o] = u < n_keys ? often.seg_off[u + 1] - often.seg_off[u] : 0u;
-      if (u < n_keys && my_key[o] == kEmptyKey) raise_error(t.st, kErrReserved);
+  for (u32 k0 = threadIdx.x & ~3u; k0 < count; k0 += kProbeThreads) {
+    const u32 k = k0 + sub;
+    u64 my_key = kEmptyKey, my_line;
+    u32 my_len = 0, my_row, my_free, u = 0;
+    bool on = k < count;
+    if (heavies) {
+      const u32 h = (c - spans.n_spans) * kHeavyGroup + k;
+      if (on) {
+        u = spans.bucket_start[spans.n_spans + h];
+        const u32 end = spans.bucket_start[spans.n_spans + h + 1];
+        my_len = end - u;
+        on = my_len != 0;                      // a key the hint named and the mini-batch does not hold
+        if (on) {
+          my_key = out.heavy_keys[h];
+          keys[u] = my_key;
+          seg_off[u] = u;
+          seg_off[u + 1] = end;
+        }
+      }
+    } else if (on) {
+      u = first + k;
+      my_key = keys[u];
+      my_len = seg_off[u + 1] - seg_off[u];
+      if (my_key == kEmptyKey) raise_error(t.st, kErrReserved);
     }
-    const u32 to_create = search_keys<K>(t, my_key, my_line, my_row, my_free, sub);
+    const u32 to_create = search_keys<K>(t, &my_key, &my_line, &my_row, &my_free, sub);
     // keys to create: all first attempts in flight together, then whatever is left of each
     if (create_here && __any(to_create != 0)) {
       u64 seen[K];
+      my_line += my_free >> 3;        // the line of the free slot
 #pragma unroll
-      for (int o = 0; o < OWN; ++o) my_line[o] += my_free[o] >> 3;        // the line of the free slot
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        const int o = k / kLookupLanes;
-        const u64 key = quad_lane(my_key[o], k % kLookupLanes);
-        const u64 line = quad_lane(my_line[o], k % kLookupLanes);
-        const u32 slot = quad_lane(my_free[o], k % kLookupLanes) & 7u;
-        seen[k] = 0;
-        if ((to_create >> k & 1u) && sub == slot >> 1)
-          seen[k] = atomicCAS((unsigned long long*)&t.keys[line * kSlotsPerLine + slot],
+      for (int q = 0; q < K; ++q) {
+        const u64 key = quad_lane(my_key, q);
+        const u64 line = quad_lane(my_line, q);
+        const u32 slot = quad_lane(my_free, q) & 7u;
+        seen[q] = 0;
+        if ((to_create >> q & 1u) && sub == slot >> 1)
+          seen[q] = atomicCAS((unsigned long long*)&t.keys[line * kSlotsPerLine + slot],
                               (unsigned long long)kEmptyKey, (unsigned long long)key);
       }
 #pragma unroll
-      for (int k = 0; k < K; ++k) {
-        const int o = k / kLookupLanes;
-        const u64 key = quad_lane(my_key[o], k % kLookupLanes);
-        const u64 line = quad_lane(my_line[o], k % kLookupLanes);
-        const u32 slot = quad_lane(my_free[o], k % kLookupLanes) & 7u;
-        if (!(to_create >> k & 1u)) continue;
-        const u64 got = __shfl(seen[k], (int)(lane0 + (slot >> 1)), kWave);
+      for (int q = 0; q < K; ++q) {
+        const u64 key = quad_lane(my_key, q);
+        const u64 line = quad_lane(my_line, q);
+        const u32 slot = quad_lane(my_free, q) & 7u;
+        if (!(to_create >> q & 1u)) continue;
+        const u64 got = __shfl(seen[q], (int)(lane0 + (slot >> 1)), kWave);
         bool created;
         const u32 row = claim_after4<true>(t, key, sub, line, slot, got, &created);
         if (row == kNoRow) {
@@ -694,13 +616,13 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ n
         // the block share the work (here four lanes of the wave would do it while sixty wait);
         // only a key that finds the block's list full gets them right away.
         u32 at = 0;
-        if (sub == (u32)(k % kLookupLanes)) {
-          my_row[o] = row;
+        if (sub == (u32)q) {
+          my_row = row;
           ++made;
           at = atomicAdd(&s_new, 1u);
           if (at < new_cap) { s_new_key[at] = key; s_new_row[at] = row; }
         }
-        if (quad_lane(at, k % kLookupLanes) >= new_cap) {
+        if (quad_lane(at, q) >= new_cap) {
           const u64 base = mix64(key ^ t.init_seed);
           for (u32 j = sub; j < t.dim; j += kLookupLanes) store_w(t, row, j, init_weight(base, j, t.init_range));
           float* ar = acc_row(t, row);
@@ -708,58 +630,47 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ n
         }
       }
     }
-    // every lane: the rows of its own keys, and the push's work lists
-#pragma unroll
-    for (int o = 0; o < OWN; ++o) {
-      const u64 u = u0 + (u64)(o * kLookupLanes + sub) * n_groups;
-      if (u >= n_keys) continue;
-      rows[u] = my_row[o];
-      if (my_key[o] == kEmptyKey) continue;
-      if (my_row[o] == kNoRow) {
-        const u32 at = atomicAdd(&s_missing, 1u);
-        if (at < kMissLdsCap) s_list[at] = (u32)u;
+    // every lane: the row of its own key, and the push's work lists
+    if (!on) continue;
+    rows[u] = my_row;
+    if (heavies && out.upos) out.by_heavy[(c - spans.n_spans) * kHeavyGroup + k] = my_row;
+    if (my_row == kNoRow) ++missing;
+    if (my_len >= often.heavy_min && my_key != kEmptyKey) {
+      const u32 at = atomicAdd(&often.heavy_raw->count, 1u);
+      if (at < (u32)kMaxHeavy) often.heavy_raw->keys[at] = my_key;
+    }
+    if (my_len > kMedSeg) {
+      const u32 n_chunks = (my_len + kChunk - 1) / kChunk;
+      const u32 item = atomicAdd(&ctx->n_chunk_items, n_chunks);
+      often.long_list[atomicAdd(&ctx->n_long, 1u)] = make_uint2(u, item);
+      // the key's chunk items are written at the end of the kernel by all lanes of the block
+      // (a key that fills thousands of chunks would keep this lane, and its wave, for long)
+      const u32 at = atomicAdd(&s_long, 1u);
+      if (at < kLongLdsCap) {
+        s_long_list[at] = make_uint4(u, item, n_chunks, 0u);
+      } else {
+        for (u32 i = 0; i < n_chunks; ++i) often.chunk_items[item + i] = make_uint2(u, i);
       }
-      const u32 len = my_len[o];
-      if (len >= often.heavy_min) {
-        const u32 at = atomicAdd(&often.heavy_raw->count, 1u);
-        if (at < (u32)kMaxHeavy) often.heavy_raw->keys[at] = my_key[o];
-      }
-      if (len >= often.hot_min && my_row[o] != kNoRow) {
-        const u32 at = atomicAdd(&often.ctx->n_hot, 1u);
-        if (at < often.hot_cap) often.hot_list[at] = make_uint2((u32)u, my_row[o]);
-      }
-      if (len > kMedSeg) {
-        const u32 n_chunks = (len + kChunk - 1) / kChunk;
-        const u32 first = atomicAdd(&often.ctx->n_chunk_items, n_chunks);
-        often.long_list[atomicAdd(&often.ctx->n_long, 1u)] = make_uint2((u32)u, first);
-        // the key's chunk items are written at the end of the kernel by all lanes of the block
-        // (a key that fills thousands of chunks would keep this lane, and its wave, for long)
-        const u32 at = atomicAdd(&s_long, 1u);
-        if (at < kLongLdsCap) {
-          s_long_list[at] = make_uint4((u32)u, first, n_chunks, 0u);
-        } else {
-          for (u32 c = 0; c < n_chunks; ++c) often.chunk_items[first + c] = make_uint2((u32)u, c);
-        }
-      } else if (len > kShortSeg) {
-        const u32 at = atomicAdd(&s_med, 1u);
-        if (at < kMedLdsCap) {
-          s_med_list[at] = (u32)u;
-        } else {      // buffer full: append straight to the shard
-          const u32 shard = blockIdx.x % kCountShards;
-          const u32 pos = atomicAdd(&often.ctx->med_count[shard], 1u);
-          if (pos < often.med_cap) often.med_list[(u64)shard * often.med_cap + pos] = (u32)u;
-        }
-      }
+    } else if (my_len > kShortSeg) {
+      const u32 at = atomicAdd(&s_med, 1u);
+      if (at < kMedLdsCap) s_med_list[at] = u;
+      else often.med_list[atomicAdd(&ctx->n_med, 1u)] = u;      // buffer full: append straight to the list
     }
   }
   if (made) atomicAdd(&s_made, made);
+  if (missing) atomicAdd(&s_missing, missing);
   __syncthreads();
-  if (threadIdx.x == 0 && s_made) atomicAdd(&t.st->made_shard[blockIdx.x % kCountShards], s_made);
+  if (threadIdx.x == 0) {
+    if (s_made) atomicAdd(&t.st->made_shard[c % kCountShards], s_made);
+    if (s_missing) atomicAdd(&t.st->miss_shard[c % kCountShards], s_missing);
+    if (s_med) s_med_base = atomicAdd(&ctx->n_med, min(s_med, kMedLdsCap));
+  }
+  if (out.upos && !heavies) rows_by_position(spans, out, c, first, rows);      // (this block's own rows[])
   {
     const u32 n_long_here = min(s_long, kLongLdsCap);
     for (u32 e = 0; e < n_long_here; ++e) {
       const uint4 it = s_long_list[e];
-      for (u32 c = threadIdx.x; c < it.z; c += kProbeThreads) often.chunk_items[it.y + c] = make_uint2(it.x, c);
+      for (u32 i = threadIdx.x; i < it.z; i += kProbeThreads) often.chunk_items[it.y + i] = make_uint2(it.x, i);
     }
   }
   // the initial rows of the keys created above: one float4 of one row per lane and turn
@@ -767,101 +678,102 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ n
   const u32 dim4 = t.dim >> 2;
   for (u32 e = threadIdx.x; e < n_new * dim4; e += kProbeThreads) {
     const u32 i = e / dim4, col = e % dim4;
-    const u64 base = mix64(s_new_key[i] ^ t.init_seed);
-    store_w4(t, s_new_row[i], col, init_weight4(base, col, t.init_range));
+    store_w4(t, s_new_row[i], col, init_weight4(mix64(s_new_key[i] ^ t.init_seed), col, t.init_range));
   }
   for (u32 e = threadIdx.x; e < n_new * t.acc_len; e += kProbeThreads)
     acc_row(t, s_new_row[e / t.acc_len])[e % t.acc_len] = t.init_acc;
   const u32 n_med = min(s_med, kMedLdsCap);
   if (n_med) {
-    const u32 shard = blockIdx.x % kCountShards;
-    if (threadIdx.x == 0) s_med_base = atomicAdd(&often.ctx->med_count[shard], n_med);
     __syncthreads();
-    for (u32 i = threadIdx.x; i < n_med; i += kProbeThreads)
-      if (s_med_base + i < often.med_cap)
-        often.med_list[(u64)shard * often.med_cap + s_med_base + i] = s_med_list[i];
+    for (u32 i = threadIdx.x; i < n_med; i += kProbeThreads) often.med_list[s_med_base + i] = s_med_list[i];
   }
-  const u32 cnt = s_missing;
-  if (cnt == 0) return;
-  if (threadIdx.x == 0) s_base = atomicAdd(&t.st->miss_shard[blockIdx.x % kCountShards], cnt);
-  __syncthreads();
-  const u32 base = s_base;
-  if (cnt > kMissLdsCap || base + cnt > shard_cap) {
-    if (threadIdx.x == 0) t.st->miss_overflow = 1;
-    return;
-  }
-  u32* dst = miss_list + (u64)(blockIdx.x % kCountShards) * shard_cap + base;
-  for (u32 i = threadIdx.x; i < cnt; i += kProbeThreads) dst[i] = s_list[i];
 }
 
-// Creates the keys that pull_lookup or insert_rows found missing and left to it, if the table has room for
-// all of them (a key that occurs twice in a bulk insert is counted twice for this check).
-// rows != null (pull): the listed missing keys are visited (or, after a list overflow,
-// all keys with rows[u] == kNoRow); rows[u] is set.
-// rows == null (bulk insert): every key is probed again.
-// w_in == null: new rows get the deterministic initial row; else the given values.
-__global__ void __launch_bounds__(kProbeThreads)
-insert_missing(TableView t, const u64* __restrict__ keys, u64 n_keys_host,
-               const u32* __restrict__ n_keys_dev, u32* __restrict__ rows,
-               const float* __restrict__ w_in, const float* __restrict__ acc_in,
-               const u32* __restrict__ miss_list, u32 shard_cap) {
-  __shared__ u32 s_total, s_made, s_mine;
-  const u32 block = blockIdx.x, n_blocks = gridDim.x;
-  if (load_error(t.st) != 0) return;
+// Whether the keys a lookup found missing (st->miss_shard) may be created: 0 there are none, 1 yes,
+// 2 no (the table would overflow; the error is raised).  All threads of the block.
+__device__ __forceinline__ u32 may_create(const TableView& t, u32* s_word) {
   if (threadIdx.x < kWave) {
-    const u32 mine = threadIdx.x < kCountShards ? t.st->miss_shard[threadIdx.x] : 0;
-    u32 c = mine;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) c += __shfl_xor(c, d, kWave);
-    if (threadIdx.x == 0) { s_total = c; s_made = 0; }
-    if (threadIdx.x == block % kCountShards) s_mine = mine;
+    const u32 total = wave_incl_sum(threadIdx.x < kCountShards ? t.st->miss_shard[threadIdx.x] : 0);
+    if (threadIdx.x == kWave - 1) *s_word = total;
   }
   __syncthreads();
-  const u32 total = s_total;
-  if (total == 0) return;
+  const u32 total = *s_word;
+  if (total == 0) return 0;
   // st->size does not change while this kernel runs: every block decides the same
-  if (t.st->size + total > t.capacity) {
-    if (threadIdx.x == 0) raise_error(t.st, kErrFull);
-    return;
-  }
-  const u64 n_keys = n_keys_dev ? (u64)*n_keys_dev : n_keys_host;
+  if (t.st->size + total <= t.capacity) return 1;
+  if (threadIdx.x == 0) raise_error(t.st, kErrFull);
+  return 2;
+}
+
+// Finds or creates `key` (all eight lanes of a group); a new row is given w / acc (null: the
+// deterministic initial values / init_acc).
+__device__ __forceinline__ u32 find_or_create(const TableView& t, u64 key, u32 sub, const float* w, const float* acc,
+                                              bool* created) {
+  const u64 line = home_line(t, key);
+  const u64 slot_key = load_slot_key(&t.keys[line * kSlotsPerLine + sub]);
+  const u32 row = probe_find_or_claim(t, key, sub, line, slot_key, created);
+  if (!*created) return row;
+  const u64 base = mix64(key ^ t.init_seed);
+  for (u32 j = sub; j < t.dim; j += 8) store_w(t, row, j, w ? w[j] : init_weight(base, j, t.init_range));
+  float* ar = acc_row(t, row);
+  for (u32 j = sub; j < t.acc_len; j += 8) ar[j] = acc ? acc_value(acc[j]) : t.init_acc;
+  return row;
+}
+
+// Creates the keys that insert_rows found missing and left to it, if the table has room for all of them (a
+// key that occurs twice in a bulk insert is counted twice for this check).
+__global__ void __launch_bounds__(kProbeThreads)
+insert_missing(TableView t, const u64* __restrict__ keys, u64 n_keys, const float* __restrict__ w_in,
+               const float* __restrict__ acc_in) {
+  __shared__ u32 s_word, s_made;
+  if (load_error(t.st) != 0) return;
+  if (threadIdx.x == 0) s_made = 0;
+  if (may_create(t, &s_word) != 1) return;
   const u32 sub = threadIdx.x & 7;
-  const u64 group = (u64)block * kProbeGroups + (threadIdx.x >> 3);
-  const u64 n_groups = (u64)n_blocks * kProbeGroups;
   u32 made = 0;
-  const bool listed = rows != nullptr && t.st->miss_overflow == 0;
-  // listed: this block's share of its shard's list; else every key
-  const u32 shard = block % kCountShards;
-  const u32 shard_blocks = (n_blocks - shard + kCountShards - 1) / kCountShards;
-  const u64 first = listed ? (u64)(block / kCountShards) * kProbeGroups + (threadIdx.x >> 3) : group;
-  const u64 stride = listed ? (u64)shard_blocks * kProbeGroups : n_groups;
-  const u64 count = listed ? (u64)s_mine : n_keys;
-  for (u64 e = first; e < count; e += stride) {
-    const u64 u = listed ? (u64)miss_list[(u64)shard * shard_cap + e] : e;
-    if (!listed && rows && rows[u] != kNoRow) continue;
-    const u64 key = keys[u];
-    if (key == kEmptyKey) continue;
-    const u64 line = home_line(t, key);
-    const u64 slot_key = load_slot_key(&t.keys[line * kSlotsPerLine + sub]);
+  for (u64 u = (u64)blockIdx.x * kProbeGroups + (threadIdx.x >> 3); u < n_keys; u += (u64)gridDim.x * kProbeGroups) {
     bool created;
-    const u32 row = probe_find_or_claim(t, key, sub, line, slot_key, &created);
-    if (rows && sub == 0) rows[u] = row;
-    if (!created) continue;
-    ++made;
-    float* ar = acc_row(t, row);
-    if (w_in) {
-      for (u32 j = sub; j < t.dim; j += 8) store_w(t, row, j, w_in[u * t.dim + j]);
-      for (u32 j = sub; j < t.acc_len; j += 8)
-        ar[j] = acc_in ? acc_value(acc_in[u * t.acc_len + j]) : t.init_acc;
-    } else {
-      const u64 base = mix64(key ^ t.init_seed);
-      for (u32 j = sub; j < t.dim; j += 8) store_w(t, row, j, init_weight(base, j, t.init_range));
-      for (u32 j = sub; j < t.acc_len; j += 8) ar[j] = t.init_acc;
+    (void)find_or_create(t, keys[u], sub, w_in ? w_in + u * t.dim : nullptr,
+                         acc_in ? acc_in + u * t.acc_len : nullptr, &created);
+    if (created) ++made;
+  }
+  if (sub == 0 && made) atomicAdd(&s_made, made);
+  __syncthreads();
+  if (threadIdx.x == 0 && s_made) atomicAdd(&t.st->made_shard[blockIdx.x % kCountShards], s_made);
+}
+
+// The same for a pull, whose lookup left rows[u] == kNoRow; hands the rows on by position again.  One span
+// of distinct keys or group of heavy keys per block, as the lookup.
+__global__ void __launch_bounds__(kProbeThreads)
+pull_missing(TableView t, const u64* __restrict__ keys, UniqueSpans spans, const PullCtx* __restrict__ ctx,
+             u32* __restrict__ rows, RowsByPosition out) {
+  __shared__ u32 s_word, s_made;
+  if (load_error(t.st) != 0) return;
+  if (threadIdx.x == 0) s_made = 0;
+  if (may_create(t, &s_word) != 1) return;
+  const u32 sub = threadIdx.x & 7;
+  const u32 c = blockIdx.x;
+  const bool heavies = c >= spans.n_spans;
+  const u32 h0 = heavies ? (c - spans.n_spans) * kHeavyGroup : 0u;
+  u32 first = 0, count, made = 0;
+  if (heavies) count = ctx->n_heavy > h0 ? min(kHeavyGroup, ctx->n_heavy - h0) : 0u;
+  else unique_span(spans, ctx, c, &first, &count);
+  for (u32 k = threadIdx.x >> 3; k < count; k += kProbeGroups) {
+    const u32 u = heavies ? spans.bucket_start[spans.n_spans + h0 + k] : first + k;
+    if (heavies && spans.bucket_start[spans.n_spans + h0 + k + 1] == u) continue;
+    if (rows[u] != kNoRow) continue;
+    bool created;
+    const u32 row = find_or_create(t, keys[u], sub, nullptr, nullptr, &created);
+    if (created) ++made;
+    if (sub == 0) {
+      rows[u] = row;
+      if (heavies && out.upos) out.by_heavy[h0 + k] = row;
     }
   }
   if (sub == 0 && made) atomicAdd(&s_made, made);
   __syncthreads();
-  if (threadIdx.x == 0 && s_made) atomicAdd(&t.st->made_shard[block % kCountShards], s_made);
+  if (threadIdx.x == 0 && s_made) atomicAdd(&t.st->made_shard[c % kCountShards], s_made);
+  if (out.upos && !heavies) rows_by_position(spans, out, c, first, rows);
 }
 
 // How many buckets (pairs of lines: 128 bytes) a lookup reads to find each stored key (1 = the

@@ -1,0 +1,68 @@
+"""The bucket form of the dedup at the sizes where it changes shape: one tile and one more or less of each
+size class, the largest and smallest mini-batch of a class, with bags that start in the middle of tiles, empty
+bags, bags longer than a tile, and heavy keys the hint names, misses, or names in vain.  Unique keys and ranks
+are compared bit for bit, pooled rows and the rows after the push within the float32 tolerance (at most 2^14
+terms of one sign per sum would be off by 2^14 * 2^-24 = 1e-3 relative if added in a chain; the sums here are trees of
+eight-term chains, below 1e-5)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2003_05622_amd as hps
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.uint64).view(np.int64)).cuda()
+
+
+def close(got, want, what):
+    err = np.abs(got.astype(np.float64) - want) - (1e-6 + 1e-5 * np.abs(want))
+    assert err.max(initial=-1) <= 0, "%s: excess %g" % (what, err.max())
+
+
+# tiles of 1024 (up to 2^16 occurrences), 4096 (up to 2^20), 8192 (up to 3 * 2^20)
+@pytest.mark.parametrize("n", [1, 1023, 1025, 65535, 65537, 4096 * 17 + 1, (1 << 20) + 1])
+@pytest.mark.parametrize("bags", ["one", "ragged"])
+def test_shapes(n, bags, monkeypatch):
+    monkeypatch.setenv("HPS_DEDUP", "bucket")
+    rng = np.random.default_rng(n)
+    dim = 4
+    n_bags = 1 if bags == "one" else max(3, n // 3)
+    pool = synth.mix64(rng.integers(0, 2**40, size=max(2, n // 2)).astype(np.uint64))
+    gt = hps.HpsTable(4 * n + 100, dim, n, n_bags, lr=0.05)
+    ot = oracle.OracleTable(4 * n + 100, dim, lr=0.05)
+    gt.set_pooling(bags == "one")            # (a bag of a million rows: its mean stays small)
+    ot.set_pooling(bags == "one")
+    hot = pool[:3]
+    for step in range(4):
+        keys = pool[rng.integers(0, pool.size, size=n)]
+        # a hot key nobody has announced, the same again, another one, none
+        if step < 3:
+            keys[rng.random(n) < 0.3] = hot[step // 2]
+        if bags == "one":
+            offsets = np.array([0, n], np.int32)
+        else:
+            # many empty bags, a few very long ones
+            cuts = np.sort(rng.integers(0, n + 1, size=n_bags - 1))
+            cuts[: n_bags // 2] = cuts[n_bags // 2]
+            offsets = np.concatenate([[0], np.sort(cuts), [n]]).astype(np.int32)
+        pooled = gt.pull(dev(keys), torch.from_numpy(offsets).cuda(), n_bags, 1)
+        want = ot.pull(keys, offsets)
+        uniq, inv = gt.last_unique()
+        ou, oi = ot.last_unique()
+        assert np.array_equal(uniq.cpu().numpy().view(np.uint64), ou), "unique keys, step %d" % step
+        assert np.array_equal(inv.cpu().numpy(), oi), "ranks, step %d" % step
+        if step == 0 and bags != "one":
+            long = np.diff(offsets) > 4096                 # the oracle sums in double, the library in float32
+            close(pooled.cpu().numpy()[~long], want[~long], "pooled")
+        grads = (rng.integers(-8, 9, size=(n_bags, dim)) / 4096).astype(np.float32)     # sums of these are exact
+        gt.push(torch.from_numpy(grads).cuda())
+        ot.push(grads)
+        st = gt.stats()
+        assert st.error == 0 and st.size == ot.size and st.last_n_unique == ou.size
+    sample = np.unique(rng.choice(pool, size=min(2000, pool.size)))
+    close(gt.get(dev(sample))[1].cpu().numpy(), ot.get(sample)[1], "accumulators")
