@@ -69,7 +69,7 @@ struct PullCtx {
   u32 by_id;           // 1: this dedup took the bucket form
   u32 n_med;           // keys the push handles with one wave each
   u32 n_heavy;         // bucket form: frequent keys with a bucket of their own
-  u32 ticket;          // bucket form: blocks of scan_buckets that are done
+  u32 pad;
   u32 n_slow_one_key;  // ... of n_slow, in buckets that one key fills at least half of
   KeyRange range;      // plain form: for the kernels after the first
   u32 uniq_shard[kCountShards];   // bucket form: distinct keys, spread over shards
@@ -170,6 +170,15 @@ __device__ __forceinline__ u32 block_excl_sum(u32 v, u32* scratch, u32* total) {
   *total = (u32)__builtin_amdgcn_readlane((int)upto, kWave - 1);
   const u32 before = (u32)__builtin_amdgcn_readlane((int)upto, w) - (u32)__builtin_amdgcn_readlane((int)c, w);
   return before + incl - v;
+}
+
+// Which of n consecutive pieces of work block b of n takes, so that neighbours stay together: the GPU
+// deals blocks out over its 8 XCDs in turn, each with an L2 of its own, so block b takes the
+// (b / 8)-th piece of part b % 8.
+constexpr u32 kXcds = 8;
+__device__ __forceinline__ u32 xcd_piece(u32 b, u32 n) {
+  const u32 part = b % kXcds;
+  return part * (n / kXcds) + min(part, n % kXcds) + b / kXcds;
 }
 
 __device__ __forceinline__ int load_error(const TableState* st) {

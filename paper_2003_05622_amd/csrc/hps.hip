@@ -120,7 +120,7 @@ constexpr bool bucket_sizes_ok() {
     if (z.max_nat + z.max_heavy > (uint32_t)kMaxBuckets[k] || z.max_nat + z.max_heavy > 8191) return false;
     if (z.max_nat < z.max_n / z.mean && k != 1) return false;
     if (k == 0 && z.max_n > kDirectTiles * z.threads * z.items) return false;
-    if (z.max_n > 1024u * z.threads * z.items) return false;       // scan_buckets: at most 64 tiles per wave
+    if (z.max_n > 1024u * z.threads * z.items) return false;       // scan_buckets: at most 16 tiles per group of lanes
   }
   return true;
 }
@@ -459,17 +459,17 @@ static void launch_buckets(hps_table* t, int c, const uint64_t* d_keys, u32 n, c
   bucket_count<kThreads, kItems, kMaxBuckets[K]><<<plan.n_tiles + bag_blocks, kThreads, 0, s>>>(
       d_keys, n, plan, ctx, d_offsets, n_bags, tile_bag, heavy, id16, hist);
   if (!kDirect) {
-    const unsigned blocks = (plan.n_nat + plan.max_heavy + kWave - 1) / kWave;
-#define HPS_SCAN(PER) scan_buckets<PER><<<blocks, kScanThreads, 0, s>>>(hist, plan, prefix, t->w<u32>(L.total), bucket_start, ctx)
-    if (plan.n_tiles <= 16 * kScanWaves) HPS_SCAN(16);
-    else if (plan.n_tiles <= 32 * kScanWaves) HPS_SCAN(32);
-    else HPS_SCAN(64);
+    const unsigned blocks = (plan.n_nat + plan.max_heavy + kScanBuckets - 1) / kScanBuckets;
+#define HPS_SCAN(PER) scan_buckets<PER><<<blocks, kScanThreads, 0, s>>>(hist, plan, prefix, t->w<u32>(L.total), ctx)
+    if (plan.n_tiles <= 4 * kScanChunks) HPS_SCAN(4);
+    else if (plan.n_tiles <= 8 * kScanChunks) HPS_SCAN(8);
+    else HPS_SCAN(16);
 #undef HPS_SCAN
   }
 #define HPS_ORDERED(ORDERED)                                                                                      \
   do {                                                                                                            \
     bucket_scatter<kThreads, kItems, kMaxBuckets[K], ORDERED, kDirect><<<plan.n_tiles, kThreads, 0, s>>>(         \
-        d_keys, id16, d_offsets, n_bags, tile_bag, n, plan, ctx, hist, prefix, bucket_start, keys, bags,          \
+        d_keys, id16, d_offsets, n_bags, tile_bag, n, plan, ctx, hist, prefix, t->w<u32>(L.total), bucket_start, keys, bags,          \
         t->w<u32>(C.code), t->w<uint16_t>(C.from));                                                               \
     stage_mark(t, HPS_STAGE_SORT, s);                                                                             \
     stage_mark(t, HPS_STAGE_UNIQUE, s);                                                                           \

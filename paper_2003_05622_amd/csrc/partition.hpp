@@ -11,7 +11,7 @@
 //                    per bucket (hist[tile][bucket]); further blocks note which bag every tile
 //                    starts in;
 //   scan_buckets     counts -> for every tile and bucket the occurrences in earlier tiles
-//                    (prefix[tile][bucket]), and where every bucket starts (bucket_start); left out
+//                    (prefix[tile][bucket]), and how many every bucket holds (total); left out
 //                    for up to kDirectTiles tiles, where every block of the scatter adds the counts up itself;
 //   bucket_scatter   a tile ranks its occurrences per bucket in occurrence order, stages them in LDS
 //                    and writes every bucket's run contiguously: the key (not for heavy
@@ -156,22 +156,24 @@ bucket_count(const u64* __restrict__ keys, u32 n, BucketPlan plan, PullCtx* __re
   for (u32 b = threadIdx.x; b < n_buckets; b += THREADS) row[b] = (uint16_t)h[b];
 }
 
-// prefix[tile][bucket] and bucket_start[0 .. n_nat + max_heavy].  A block takes 64 buckets, its waves
-// share the tiles (PER tiles each, kept in registers between the two halves of the scan); the block
-// that is done last scans the buckets' totals.
+// prefix[tile][bucket] and total[bucket].  A block takes 16 buckets and shares the tiles out over
+// 64 groups of 16 lanes, PER tiles each, kept in registers between the two halves of the scan.  What bounds it
+// is latency: few blocks, each with all its loads in flight at once.  The starts of the buckets (a
+// scan of the totals) are left to every block of the scatter: the block that is done last
+// here could scan them too, but the device-scope fence that takes costs each block a write-back of
+// its L2 (9.8 M occurrences: 139 us with it).
 constexpr int kScanThreads = 1024;
-constexpr int kScanWaves = kScanThreads / kWave;
+constexpr int kScanBuckets = 16;
+constexpr int kScanChunks = kScanThreads / kScanBuckets;
 template <int PER>
 __global__ void __launch_bounds__(kScanThreads)
 scan_buckets(const uint16_t* __restrict__ hist, BucketPlan plan, u32* __restrict__ prefix,
-             u32* __restrict__ total, u32* __restrict__ bucket_start, PullCtx* __restrict__ ctx) {
-  __shared__ u32 sums[kScanWaves][kWave];
-  __shared__ u32 scratch[kScanThreads / kWave + 1];
-  __shared__ u32 s_last;
-  const u32 lane = lane_id(), wave = threadIdx.x / kWave;
-  const u32 n_buckets = plan.n_nat + ctx->n_heavy, n_all = plan.n_nat + plan.max_heavy;
-  const u32 b = blockIdx.x * kWave + lane;
-  const u32 t0 = wave * PER;
+             u32* __restrict__ total, const PullCtx* __restrict__ ctx) {
+  __shared__ u32 sums[kScanThreads / kWave][kScanBuckets];
+  const u32 lane = lane_id(), wave = threadIdx.x / kWave, col = lane % kScanBuckets;
+  const u32 n_buckets = plan.n_nat + ctx->n_heavy;
+  const u32 b = blockIdx.x * kScanBuckets + col;
+  const u32 t0 = (threadIdx.x / kScanBuckets) * PER;
   u32 v[PER];
 #pragma unroll
   for (int k = 0; k < PER; ++k)
@@ -179,53 +181,40 @@ scan_buckets(const uint16_t* __restrict__ hist, BucketPlan plan, u32* __restrict
   u32 mine = 0;
 #pragma unroll
   for (int k = 0; k < PER; ++k) mine += v[k];
-  sums[wave][lane] = mine;
+  // prefix over the wave's four groups, then over the waves
+  u32 incl = mine;
+  u32 up = (u32)__shfl_up((int)incl, kScanBuckets, kWave);
+  if (lane >= kScanBuckets) incl += up;
+  up = (u32)__shfl_up((int)incl, 2 * kScanBuckets, kWave);
+  if (lane >= 2 * kScanBuckets) incl += up;
+  if (lane >= kWave - kScanBuckets) sums[wave][col] = incl;
   __syncthreads();
-  u32 run = 0;
-  for (u32 w = 0; w < wave; ++w) run += sums[w][lane];
+  u32 run = incl - mine, all = 0;
+#pragma unroll
+  for (u32 w = 0; w < kScanThreads / kWave; ++w) {
+    const u32 c = sums[w][col];
+    if (w < wave) run += c;
+    all += c;
+  }
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     if (b < n_buckets && t0 + k < plan.n_tiles) prefix[(u64)(t0 + k) * plan.stride + b] = run;
     run += v[k];
   }
-  if (wave == kScanWaves - 1 && b < n_all)
-    __hip_atomic_store(total + b, run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __threadfence();
-  __syncthreads();
-  if (threadIdx.x == 0) s_last = atomicAdd(&ctx->ticket, 1u) + 1 == gridDim.x ? 1u : 0u;
-  __syncthreads();
-  if (!s_last) return;
-  __threadfence();
-  u32 before = 0;
-  for (u32 base = 0; base < n_all; base += 4 * kScanThreads) {
-    u32 c[4], sum = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const u32 at = base + 4 * threadIdx.x + q;
-      c[q] = at < n_all ? __hip_atomic_load(total + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
-      sum += c[q];
-    }
-    u32 all;
-    u32 at_start = before + block_excl_sum<kScanThreads>(sum, scratch, &all);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const u32 at = base + 4 * threadIdx.x + q;
-      if (at < n_all) bucket_start[at] = at_start;
-      if (at >= plan.n_nat && c[q]) atomicAdd(&ctx->uniq_shard[at % kCountShards], 1u);    // a heavy key that occurs
-      at_start += c[q];
-    }
-    before += all;
-  }
-  if (threadIdx.x == 0) bucket_start[n_all] = before;
+  if (threadIdx.x < kScanBuckets && b < n_buckets) total[b] = all;
 }
 
-// Deals one tile per block out to the buckets.  DIRECT: scan_buckets was left out, hist holds all
-// there is; block 0 then writes bucket_start.
+// Deals one tile per block out to the buckets.  What bounds it is the write requests of short runs (9.8 M
+// occurrences, 2400 buckets: five occurrences a run, 40 bytes of keys, 20 of bags), which start and end
+// in the middle of memory lines.  Neighbouring tiles' runs lie side by side, so tiles that follow each other
+// go to the same XCD (xcd_piece), whose L2 then puts the pieces of a line together before it
+// writes it: 143 -> 107 us (and 46 -> 37 us for spread, which reads the same runs).  Block 0 also writes bucket_start[0 .. n_nat +
+// max_heavy].  DIRECT: scan_buckets was left out, hist holds all there is.
 template <int THREADS, int ITEMS, int MAX_BUCKETS, bool ORDERED, bool DIRECT>
 __global__ void __launch_bounds__(THREADS)
 bucket_scatter(const u64* __restrict__ keys, const uint16_t* __restrict__ id16, const i32* __restrict__ offsets,
                u32 n_bags, const u32* __restrict__ tile_bag, u32 n, BucketPlan plan, PullCtx* __restrict__ ctx,
-               const uint16_t* __restrict__ hist, const u32* __restrict__ prefix, u32* __restrict__ bucket_start,
+               const uint16_t* __restrict__ hist, const u32* __restrict__ prefix, const u32* __restrict__ total, u32* __restrict__ bucket_start,
                u64* __restrict__ keys_out, u32* __restrict__ bags_out, u32* __restrict__ code,
                uint16_t* __restrict__ from) {
   constexpr u32 kTile = THREADS * ITEMS;
@@ -239,11 +228,30 @@ bucket_scatter(const u64* __restrict__ keys, const uint16_t* __restrict__ id16, 
   __shared__ u32 scratch[kWaves + 1];
   __shared__ u32 wave_last[kWaves];
   const u32 tid = threadIdx.x, wave = tid / kWave, lane = tid & (kWave - 1);
-  const u32 tile = blockIdx.x, base = tile * kTile;
+  const u32 tile = xcd_piece(blockIdx.x, plan.n_tiles), base = tile * kTile;
   const u32 tile_n = min(kTile, n - base);
   const u32 wave_first = wave * (kWave * ITEMS);        // element e of the tile: wave_first + r * 64 + lane
   const u32 n_buckets = plan.n_nat + ctx->n_heavy;
 
+  // Everything the tile needs from memory is requested up front, what is needed last after what is needed
+  // first (loads come back in order): bag starts, the buckets' counts, keys and bucket numbers.
+  const u32 last_bag = n_bags - 1;
+  u32 bag0 = 0, bag_end = 0, bag_lo = 0, bag_hi = 0;
+  if (offsets) {
+    bag0 = min(tile_bag[tile], last_bag);
+    bag_end = tile + 1 < plan.n_tiles ? min(tile_bag[tile + 1], last_bag) : last_bag;
+    if (bag0 + 1 + tid <= bag_end) { bag_lo = (u32)offsets[bag0 + 1 + tid]; bag_hi = (u32)offsets[bag0 + 2 + tid]; }
+  }
+  u32 in_bucket[kPer], in_earlier[kPer];       // of this thread's buckets: occurrences in all tiles, in the tiles before
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const u32 b = kPer * tid + q;
+    in_bucket[q] = in_earlier[q] = 0;
+    if (!DIRECT && b < n_buckets) {
+      in_bucket[q] = total[b];
+      in_earlier[q] = prefix[(u64)tile * plan.stride + b];
+    }
+  }
   u64 key[ITEMS];
   u32 id[ITEMS];
 #pragma unroll
@@ -252,20 +260,28 @@ bucket_scatter(const u64* __restrict__ keys, const uint16_t* __restrict__ id16, 
     key[r] = keys[i];
     id[r] = id16[i];
   }
+  if (DIRECT) {
+#pragma unroll 8
+    for (u32 t = 0; t < plan.n_tiles; ++t) {
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) {
+        const u32 b = kPer * tid + q;
+        const u32 v = b < n_buckets ? (u32)hist[(u64)t * plan.stride + b] : 0u;
+        in_bucket[q] += v;
+        if (t < tile) in_earlier[q] += v;
+      }
+    }
+  }
   // every non-empty bag that starts inside the tile marks its first occurrence
   u32* mark = reinterpret_cast<u32*>(stage);
   for (u32 e = tid; e < kTile; e += THREADS) mark[e] = 0;
 #pragma unroll
   for (int q = 0; q < kPer; ++q) first[q * THREADS + tid] = 0;
-  u32 bag0 = 0;
   __syncthreads();
   if (offsets) {
-    const u32 last = n_bags - 1;
-    bag0 = min(tile_bag[tile], last);
-    const u32 end = tile + 1 < plan.n_tiles ? min(tile_bag[tile + 1], last) : last;
-    for (u32 b = bag0 + 1 + tid; b <= end; b += THREADS) {
-      const u32 lo = (u32)offsets[b], hi = (u32)offsets[b + 1];
-      if (lo < hi && lo - base < kTile) mark[lo - base] = b;      // (lo >= base, or the difference is huge)
+    for (u32 b = bag0 + 1 + tid; b <= bag_end; b += THREADS) {
+      if (bag_lo < bag_hi && bag_lo - base < kTile) mark[bag_lo - base] = b;      // (before the tile: the difference is huge)
+      if (b + THREADS <= bag_end) { bag_lo = (u32)offsets[b + THREADS]; bag_hi = (u32)offsets[b + THREADS + 1]; }
     }
   }
   // ranks: the waves take turns, so that a bucket's counter is counted up in occurrence order
@@ -306,48 +322,32 @@ bucket_scatter(const u64* __restrict__ keys, const uint16_t* __restrict__ id16, 
   }
   // per bucket (thread t: buckets kPer * t ...): its first staged place, its run's destination
   {
-    u32 c[kPer], g[kPer], p[kPer], sum = 0, gsum = 0, all;
+    u32 c[kPer], start[kPer], sum = 0, bucket_sum = 0, all;
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
-      const u32 b = kPer * tid + q;
-      c[q] = first[b];
+      c[q] = first[kPer * tid + q];
       sum += c[q];
-      g[q] = p[q] = 0;
-      if (DIRECT) {
-        if (b < n_buckets)
-          for (u32 t = 0; t < plan.n_tiles; ++t) {
-            const u32 v = hist[(u64)t * plan.stride + b];
-            g[q] += v;
-            if (t < tile) p[q] += v;
-          }
-        gsum += g[q];
-      } else if (b < n_buckets) {
-        g[q] = bucket_start[b];
-        p[q] = prefix[(u64)tile * plan.stride + b];
-      }
+      bucket_sum += in_bucket[q];
     }
     u32 at = block_excl_sum<THREADS>(sum, scratch, &all);
-    if (DIRECT) {
-      u32 start = block_excl_sum<THREADS>(gsum, scratch, &all);
-      u32 count[kPer];
+    u32 at_all = block_excl_sum<THREADS>(bucket_sum, scratch, &all);
 #pragma unroll
-      for (int q = 0; q < kPer; ++q) { count[q] = g[q]; g[q] = start; start += count[q]; }
-      if (tile == 0) {
-        const u32 n_all = plan.n_nat + plan.max_heavy;
+    for (int q = 0; q < kPer; ++q) { start[q] = at_all; at_all += in_bucket[q]; }
+    if (tile == 0) {
+      const u32 n_all = plan.n_nat + plan.max_heavy;
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-          const u32 b = kPer * tid + q;
-          if (b < n_all) bucket_start[b] = g[q];
-          if (b >= plan.n_nat && count[q]) atomicAdd(&ctx->uniq_shard[b % kCountShards], 1u);    // a heavy key that occurs
-        }
-        if (tid == 0) bucket_start[n_all] = all;
+      for (int q = 0; q < kPer; ++q) {
+        const u32 b = kPer * tid + q;
+        if (b < n_all) bucket_start[b] = start[q];
+        if (b >= plan.n_nat && in_bucket[q]) atomicAdd(&ctx->uniq_shard[b % kCountShards], 1u);    // a heavy key that occurs
       }
+      if (tid == 0) bucket_start[n_all] = all;
     }
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
       const u32 b = kPer * tid + q;
       first[b] = at;
-      out[b] = g[q] + p[q] - at;
+      out[b] = start[q] + in_earlier[q] - at;
       at += c[q];
     }
   }
@@ -439,7 +439,7 @@ __global__ void __launch_bounds__(THREADS)
 spread(const u32* __restrict__ code, const uint16_t* __restrict__ from, u32 n, const u32* __restrict__ by_pos,
        const u32* __restrict__ by_heavy, u32* __restrict__ out) {
   __shared__ u32 lds[THREADS * ITEMS];
-  spread_tile<THREADS, ITEMS>(code, from, n, blockIdx.x, by_pos, by_heavy, out, lds);
+  spread_tile<THREADS, ITEMS>(code, from, n, xcd_piece(blockIdx.x, gridDim.x), by_pos, by_heavy, out, lds);
 }
 
 }  // namespace hps
