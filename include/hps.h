@@ -276,6 +276,11 @@ hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_invers
 hps_status hps_get(hps_table* t, const uint64_t* d_keys, uint64_t n, float* d_weights_out,
                    float* d_acc_out, uint8_t* d_found_out, void* stream);
 
+/* The same, with rows and accumulators of absent keys written as zeros (of all keys while the
+ * sticky device status is set): for callers that would have to clear the arrays first. */
+hps_status hps_get_or_zero(hps_table* t, const uint64_t* d_keys, uint64_t n, float* d_weights_out,
+                           float* d_acc_out, uint8_t* d_found_out, void* stream);
+
 /* Algorithm 1 pull_updates_HBM-PS: writes every stored (key, row, accumulator) in
  * unspecified order, at most max_rows of them; *h_n_rows (host) gets the number of
  * stored keys.  Waits for the stream.  HPS_ENOMEM if max_rows was too small (the

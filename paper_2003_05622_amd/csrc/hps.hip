@@ -1114,17 +1114,28 @@ hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_invers
   return HPS_OK;
 }
 
-hps_status hps_get(hps_table* t, const uint64_t* d_keys, uint64_t n, float* d_weights_out,
-                   float* d_acc_out, uint8_t* d_found_out, void* stream) {
+static hps_status get_impl(hps_table* t, bool zero, const uint64_t* d_keys, uint64_t n, float* d_weights_out,
+                           float* d_acc_out, uint8_t* d_found_out, void* stream) {
   if (!t || (n && (!d_keys || !d_weights_out || !d_acc_out || !d_found_out))) return HPS_EINVAL;
   if (n == 0) return HPS_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const unsigned blocks = grid_for(n, kRowThreads, kRowMaxBlocks);
-  if (t->view.bf16)
-    get_rows<true><<<blocks, kRowThreads, 0, s>>>(t->view, d_keys, n, d_weights_out, d_acc_out, d_found_out);
-  else
-    get_rows<false><<<blocks, kRowThreads, 0, s>>>(t->view, d_keys, n, d_weights_out, d_acc_out, d_found_out);
+#define HPS_GET(BF16, ZERO) \
+  get_rows<BF16, ZERO><<<blocks, kRowThreads, 0, s>>>(t->view, d_keys, n, d_weights_out, d_acc_out, d_found_out)
+  if (t->view.bf16) { if (zero) HPS_GET(true, true); else HPS_GET(true, false); }
+  else { if (zero) HPS_GET(false, true); else HPS_GET(false, false); }
+#undef HPS_GET
   return launch_ok() ? HPS_OK : HPS_EDEVICE;
+}
+
+hps_status hps_get(hps_table* t, const uint64_t* d_keys, uint64_t n, float* d_weights_out,
+                   float* d_acc_out, uint8_t* d_found_out, void* stream) {
+  return get_impl(t, false, d_keys, n, d_weights_out, d_acc_out, d_found_out, stream);
+}
+
+hps_status hps_get_or_zero(hps_table* t, const uint64_t* d_keys, uint64_t n, float* d_weights_out,
+                           float* d_acc_out, uint8_t* d_found_out, void* stream) {
+  return get_impl(t, true, d_keys, n, d_weights_out, d_acc_out, d_found_out, stream);
 }
 
 static hps_status dump_impl(hps_table* t, bool dirty, uint64_t* d_keys_out, float* d_weights_out,

@@ -50,8 +50,9 @@ struct FlatWalk {
 
 // Calls load(row, key, col) and store(value, row, key, col) for every word of the rows of the
 // wave's 64 keys, kRowInFlight loads before their stores; my_row: lane l's row number of key l
-// (kNoRow: skipped).
-template <typename V, typename LOAD, typename STORE>
+// (kSkipRow: nothing; kNoRow: nothing either, or with ZERO a store of V()).
+constexpr u32 kSkipRow = kNoRow - 1;       // (above any row number: hps.hip, kMaxSlots)
+template <bool ZERO, typename V, typename LOAD, typename STORE>
 __device__ __forceinline__ void move_rows(u32 my_row, u32 words, LOAD load, STORE store) {
   FlatWalk at(words);
   for (u32 i0 = 0; i0 < words; i0 += kRowInFlight) {       // 64 * words words, 64 per step
@@ -59,46 +60,59 @@ __device__ __forceinline__ void move_rows(u32 my_row, u32 words, LOAD load, STOR
     u32 row[kRowInFlight], key[kRowInFlight], col[kRowInFlight];
 #pragma unroll
     for (int q = 0; q < kRowInFlight; ++q) {
-      row[q] = i0 + q < words ? (u32)__shfl((int)my_row, (int)at.key, kWave) : kNoRow;
+      row[q] = i0 + q < words ? (u32)__shfl((int)my_row, (int)at.key, kWave) : kSkipRow;
       key[q] = at.key; col[q] = at.col;
-      if (row[q] != kNoRow) v[q] = load(row[q], key[q], col[q]);
+      v[q] = V();
+      if (row[q] < kSkipRow) v[q] = load(row[q], key[q], col[q]);
       at.next(words);
     }
 #pragma unroll
     for (int q = 0; q < kRowInFlight; ++q)
-      if (row[q] != kNoRow) store(v[q], row[q], key[q], col[q]);
+      if (row[q] < kSkipRow || (ZERO && row[q] == kNoRow)) store(v[q], row[q], key[q], col[q]);
   }
 }
 
-// rows by key, nothing created: w_out / acc_out of keys the table does not hold are left
-// unwritten, found_out[u] tells.
-template <bool BF16>
+// rows by key, nothing created; found_out[u] tells whether the table holds the key.  w_out / acc_out
+// of a key it does not hold are left unwritten, or with ZERO set to zero (while the sticky status
+// is set, all of them: then nothing is looked up).
+template <bool BF16, bool ZERO>
 __global__ void __launch_bounds__(kRowThreads)
 get_rows(TableView t, const u64* __restrict__ keys, u64 n_keys, float* __restrict__ w_out,
          float* __restrict__ acc_out, uint8_t* __restrict__ found_out) {
-  if (load_error(t.st) != 0) return;
+  const bool failed = load_error(t.st) != 0;
+  if (failed && !ZERO) return;
   const u32 lane = lane_id(), sub = lane % kLookupLanes;
   const u64 n_waves = (u64)gridDim.x * (kRowThreads / kWave);
   const bool aligned = aligned16(w_out) && aligned16(acc_out);
   for (u64 first = ((u64)blockIdx.x * (kRowThreads / kWave) + threadIdx.x / kWave) * kWave; first < n_keys;
        first += n_waves * kWave) {
     const u64 u = first + lane;
-    u64 key = u < n_keys ? keys[u] : kEmptyKey, line;
+    u64 key = u < n_keys && !failed ? keys[u] : kEmptyKey, line;
     u32 row, free_at;
     search_keys<kLookupLanes>(t, &key, &line, &row, &free_at, sub);
     if (u < n_keys) found_out[u] = row != kNoRow;
+    else row = kSkipRow;
     float* w_first = w_out + first * t.dim;
-    if (t.acc_len == 1 && row != kNoRow) acc_out[u] = acc_value(*acc_row(t, row));
-    move_rows<StoredW4<BF16>>(
+    if (t.acc_len == 1) {
+      if (row < kSkipRow) acc_out[u] = acc_value(*acc_row(t, row));
+      else if (ZERO && row == kNoRow) acc_out[u] = 0.f;
+    }
+    move_rows<ZERO, StoredW4<BF16>>(
         row, t.dim >> 2, [&](u32 r, u32, u32 col) { return load_stored_w4<BF16>(t, r, col); },
         [&](const StoredW4<BF16>& v, u32, u32 k, u32 col) {
           store_caller4(w_first + k * t.dim + 4 * col, aligned, v.value());
         });
     if (t.acc_len != 1) {
       float* acc_first = acc_out + first * t.acc_len;
-      move_rows<float4>(
-          row, t.acc_len >> 2, [&](u32 r, u32, u32 col) { return reinterpret_cast<const float4*>(acc_row(t, r))[col]; },
-          [&](float4 v, u32, u32 k, u32 col) {
+      move_rows<ZERO, StoredW4<false>>(
+          row, t.acc_len >> 2,
+          [&](u32 r, u32, u32 col) {
+            StoredW4<false> s;
+            s.raw = reinterpret_cast<const float4*>(acc_row(t, r))[col];
+            return s;
+          },
+          [&](const StoredW4<false>& s, u32, u32 k, u32 col) {
+            float4 v = s.raw;
             v.x = acc_value(v.x); v.y = acc_value(v.y); v.z = acc_value(v.z); v.w = acc_value(v.w);
             store_caller4(acc_first + k * t.acc_len + 4 * col, aligned, v);
           });
@@ -176,7 +190,7 @@ insert_rows(TableView t, const u64* __restrict__ keys, u64 n_keys, const float* 
     }
     if (VALUES) {
       const float* w_first = w_in + first * t.dim;
-      move_rows<float4>(
+      move_rows<false, float4>(
           write, t.dim >> 2,
           [&](u32, u32 k, u32 col) { return load_caller4(w_first + k * t.dim + 4 * col, aligned); },
           [&](float4 v, u32 r, u32, u32 col) { store_w4_as<BF16>(t, r, col, v); });
@@ -196,7 +210,7 @@ insert_rows(TableView t, const u64* __restrict__ keys, u64 n_keys, const float* 
       if (write != kNoRow) *acc_row(t, write) = given ? acc_value(acc_in[u]) : t.init_acc;
     } else {
       const float* acc_first = acc_in + first * t.acc_len;
-      move_rows<float4>(
+      move_rows<false, float4>(
           write, t.acc_len >> 2,
           [&](u32, u32 k, u32 col) {
             return given ? load_caller4(acc_first + k * t.acc_len + 4 * col, aligned)

@@ -68,5 +68,15 @@ def test_rows_in_and_out(n, dim, rows, opt):
     assert L.hps_get(gt._h, dev(keys).data_ptr(), 3 * n, out.data_ptr() + 4, acc.data_ptr() + 4, flags.data_ptr(), 0) == hps.OK
     torch.cuda.synchronize()
     want = ot.get(keys)
+    # hps_get leaves absent keys' rows alone
+    absent = dev(synth.mix64(np.arange(10**6, 10**6 + n, dtype=np.uint64)))
+    rows, accs = torch.full((n, dim), 7.0, device="cuda"), torch.full((n, acc_len), 7.0, device="cuda")
+    left = torch.ones(n, dtype=torch.uint8, device="cuda")
+    assert L.hps_get(gt._h, absent.data_ptr(), n, rows.data_ptr(), accs.data_ptr(), left.data_ptr(), 0) == hps.OK
+    assert (rows == 7).all() and (accs == 7).all() and not left.any()
+    # while the sticky status is set nothing is found
+    gt.insert(dev(np.array([2**64 - 1], dtype=np.uint64)))
+    w0, a0, f0 = gt.get(dev(keys))
+    assert not w0.any() and not a0.any() and not f0.any() and gt.stats().error == hps.ERESERVED
     assert np.array_equal(out[1:].cpu().numpy().reshape(3 * n, dim), want[0]) and flags.all()
     assert np.array_equal(acc[1:].cpu().numpy().reshape(3 * n, acc_len), want[1])
