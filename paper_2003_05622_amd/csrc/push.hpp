@@ -165,10 +165,10 @@ __device__ __forceinline__ void add_positions(float4* g, const PushArgs& a, u32 
 }
 
 template <int LPR, int COLS>
-__device__ __forceinline__ void push_short_role(const TableView& t, const PushArgs& a, u32 span) {
+__device__ __forceinline__ void push_short_role(const TableView& t, const PushArgs& a, u32 block) {
   const u32 sub = threadIdx.x % LPR;
-  const bool heavies = span >= a.spans.n_spans;
-  const u32 h0 = heavies ? (span - a.spans.n_spans) * kHeavyGroup : 0u;
+  const bool heavies = block < heavy_blocks(a.spans);
+  const u32 span = block - heavy_blocks(a.spans), h0 = block * kHeavyGroup;
   u32 first = 0, count;
   if (heavies) count = a.ctx->n_heavy > h0 ? min(kHeavyGroup, a.ctx->n_heavy - h0) : 0u;
   else unique_span(a.spans, a.ctx, span, &first, &count);

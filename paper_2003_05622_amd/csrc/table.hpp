@@ -129,7 +129,7 @@ constexpr int kLookupGroups = kProbeThreads / kLookupLanes;
 constexpr int kProbeMaxBlocks = 1024;
 constexpr u32 kNoSlot = ~0u;
 constexpr u32 kNewLdsCap = 1024;         // created keys a block lists for its common initialisation
-constexpr u32 kLongLdsCap = 64;          // very frequent keys whose chunk items a block writes together
+constexpr u32 kLongLdsCap = 64;          // very frequent keys whose chunk items whole waves write (>= kHeavyGroup)
 constexpr u32 kMedLdsCap = 512;          // medium keys a block buffers before it appends
 constexpr u32 kShortSeg = 16;            // occurrences handled serially by one lane group
 constexpr u32 kMedSeg = 512;             // occurrences handled by one wave
@@ -138,8 +138,8 @@ constexpr u32 kChunk = 1024;             // occurrences per queued chunk of a lo
 // Where the distinct keys of a mini-batch lie in uniq / seg_off / rows.  Bucket form (bucket.hpp): natural
 // bucket c's in [bucket_start[c], + count[c]), heavy key h at bucket_start[n_spans + h] if that
 // bucket is not empty.  Plain form (bucket_start == null): all in [0, ctx->n_unique), taken in
-// spans of plain_span.  A block of the kernels that go through the distinct keys takes one span,
-// or (blocks from n_spans on) up to kHeavyGroup heavy keys.
+// spans of plain_span.  A block of the kernels that go through the distinct keys takes up to kHeavyGroup
+// heavy keys (the first blocks: theirs is the longest work) or one span.
 struct UniqueSpans {
   const u32* bucket_start;
   const u32* count;
@@ -147,10 +147,9 @@ struct UniqueSpans {
   u32 max_heavy;         // bucket form: heavy buckets there may be
   u32 plain_span;        // plain form
 };
-constexpr u32 kHeavyGroup = 256;
-__host__ __device__ __forceinline__ u32 span_blocks(const UniqueSpans& s) {
-  return s.n_spans + (s.max_heavy + kHeavyGroup - 1) / kHeavyGroup;
-}
+constexpr u32 kHeavyGroup = 64;
+__host__ __device__ __forceinline__ u32 heavy_blocks(const UniqueSpans& s) { return (s.max_heavy + kHeavyGroup - 1) / kHeavyGroup; }
+__host__ __device__ __forceinline__ u32 span_blocks(const UniqueSpans& s) { return heavy_blocks(s) + s.n_spans; }
 __device__ __forceinline__ void unique_span(const UniqueSpans& s, const PullCtx* ctx, u32 c, u32* first, u32* count) {
   if (s.bucket_start) {
     *first = s.bucket_start[c];
@@ -536,15 +535,12 @@ pull_lookup(TableView t, u64* __restrict__ keys, u32* __restrict__ seg_off, Uniq
     return;
   }
   if (load_error(t.st) != 0) return;
-  const u32 c = blockIdx.x;
-  const bool heavies = c >= spans.n_spans;
+  const bool heavies = blockIdx.x < heavy_blocks(spans);
+  const u32 c = blockIdx.x - heavy_blocks(spans);        // the span
+  const u32 h0 = blockIdx.x * kHeavyGroup;               // or the first heavy key
   u32 first = 0, count;
-  if (heavies) {
-    const u32 h0 = (c - spans.n_spans) * kHeavyGroup;
-    count = ctx->n_heavy > h0 ? min(kHeavyGroup, ctx->n_heavy - h0) : 0u;
-  } else {
-    unique_span(spans, ctx, c, &first, &count);
-  }
+  if (heavies) count = ctx->n_heavy > h0 ? min(kHeavyGroup, ctx->n_heavy - h0) : 0u;
+  else unique_span(spans, ctx, c, &first, &count);
   if (count == 0) return;
   if (threadIdx.x == 0) { s_missing = 0; s_med = 0; s_made = 0; s_new = 0; s_long = 0; }
   if (threadIdx.x < kWave) {
@@ -565,7 +561,7 @@ pull_lookup(TableView t, u64* __restrict__ keys, u32* __restrict__ seg_off, Uniq
     u32 my_len = 0, my_row, my_free, u = 0;
     bool on = k < count;
     if (heavies) {
-      const u32 h = (c - spans.n_spans) * kHeavyGroup + k;
+      const u32 h = h0 + k;
       if (on) {
         u = spans.bucket_start[spans.n_spans + h];
         const u32 end = spans.bucket_start[spans.n_spans + h + 1];
@@ -633,7 +629,7 @@ pull_lookup(TableView t, u64* __restrict__ keys, u32* __restrict__ seg_off, Uniq
     // every lane: the row of its own key, and the push's work lists
     if (!on) continue;
     rows[u] = my_row;
-    if (heavies && out.upos) out.by_heavy[(c - spans.n_spans) * kHeavyGroup + k] = my_row;
+    if (heavies && out.upos) out.by_heavy[h0 + k] = my_row;
     if (my_row == kNoRow) ++missing;
     if (my_len >= often.heavy_min && my_key != kEmptyKey) {
       const u32 at = atomicAdd(&often.heavy_raw->count, 1u);
@@ -643,7 +639,7 @@ pull_lookup(TableView t, u64* __restrict__ keys, u32* __restrict__ seg_off, Uniq
       const u32 n_chunks = (my_len + kChunk - 1) / kChunk;
       const u32 item = atomicAdd(&ctx->n_chunk_items, n_chunks);
       often.long_list[atomicAdd(&ctx->n_long, 1u)] = make_uint2(u, item);
-      // the key's chunk items are written at the end of the kernel by all lanes of the block
+      // the key's chunk items are written at the end of the kernel by all lanes of a wave
       // (a key that fills thousands of chunks would keep this lane, and its wave, for long)
       const u32 at = atomicAdd(&s_long, 1u);
       if (at < kLongLdsCap) {
@@ -661,16 +657,16 @@ pull_lookup(TableView t, u64* __restrict__ keys, u32* __restrict__ seg_off, Uniq
   if (missing) atomicAdd(&s_missing, missing);
   __syncthreads();
   if (threadIdx.x == 0) {
-    if (s_made) atomicAdd(&t.st->made_shard[c % kCountShards], s_made);
-    if (s_missing) atomicAdd(&t.st->miss_shard[c % kCountShards], s_missing);
+    if (s_made) atomicAdd(&t.st->made_shard[blockIdx.x % kCountShards], s_made);
+    if (s_missing) atomicAdd(&t.st->miss_shard[blockIdx.x % kCountShards], s_missing);
     if (s_med) s_med_base = atomicAdd(&ctx->n_med, min(s_med, kMedLdsCap));
   }
   if (out.upos && !heavies) rows_by_position(spans, out, c, first, rows);      // (this block's own rows[])
   {
     const u32 n_long_here = min(s_long, kLongLdsCap);
-    for (u32 e = 0; e < n_long_here; ++e) {
+    for (u32 e = threadIdx.x / kWave; e < n_long_here; e += kProbeThreads / kWave) {
       const uint4 it = s_long_list[e];
-      for (u32 i = threadIdx.x; i < it.z; i += kProbeThreads) often.chunk_items[it.y + i] = make_uint2(it.x, i);
+      for (u32 i = lane_id(); i < it.z; i += kWave) often.chunk_items[it.y + i] = make_uint2(it.x, i);
     }
   }
   // the initial rows of the keys created above: one float4 of one row per lane and turn
@@ -743,36 +739,52 @@ insert_missing(TableView t, const u64* __restrict__ keys, u64 n_keys, const floa
 }
 
 // The same for a pull, whose lookup left rows[u] == kNoRow; hands the rows on by position again.  One span
-// of distinct keys or group of heavy keys per block, as the lookup.
+// of distinct keys or group of heavy keys per block, as the lookup.  The keys to create are
+// gathered in LDS first, so that all groups have one at a time (one key in six is a new one: 0.49 M new
+// keys of 2.8 M, 140 us; 278 with every group looking for its own).
 __global__ void __launch_bounds__(kProbeThreads)
 pull_missing(TableView t, const u64* __restrict__ keys, UniqueSpans spans, const PullCtx* __restrict__ ctx,
              u32* __restrict__ rows, RowsByPosition out) {
-  __shared__ u32 s_word, s_made;
+  constexpr u32 kList = 1024;
+  __shared__ u32 s_word, s_made, s_n;
+  __shared__ u32 s_list[kList];
   if (load_error(t.st) != 0) return;
   if (threadIdx.x == 0) s_made = 0;
   if (may_create(t, &s_word) != 1) return;
   const u32 sub = threadIdx.x & 7;
-  const u32 c = blockIdx.x;
-  const bool heavies = c >= spans.n_spans;
-  const u32 h0 = heavies ? (c - spans.n_spans) * kHeavyGroup : 0u;
+  const bool heavies = blockIdx.x < heavy_blocks(spans);
+  const u32 c = blockIdx.x - heavy_blocks(spans), h0 = blockIdx.x * kHeavyGroup;
   u32 first = 0, count, made = 0;
   if (heavies) count = ctx->n_heavy > h0 ? min(kHeavyGroup, ctx->n_heavy - h0) : 0u;
   else unique_span(spans, ctx, c, &first, &count);
-  for (u32 k = threadIdx.x >> 3; k < count; k += kProbeGroups) {
-    const u32 u = heavies ? spans.bucket_start[spans.n_spans + h0 + k] : first + k;
-    if (heavies && spans.bucket_start[spans.n_spans + h0 + k + 1] == u) continue;
-    if (rows[u] != kNoRow) continue;
-    bool created;
-    const u32 row = find_or_create(t, keys[u], sub, nullptr, nullptr, &created);
-    if (created) ++made;
-    if (sub == 0) {
-      rows[u] = row;
-      if (heavies && out.upos) out.by_heavy[h0 + k] = row;
+  const u32* start = spans.bucket_start + spans.n_spans + h0;       // (heavy keys)
+  u32 k0 = 0;
+  while (k0 < count) {
+    __syncthreads();
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    for (; k0 < count && s_n <= kList - kProbeThreads; k0 += kProbeThreads) {       // (s_n: read between barriers)
+      const u32 k = k0 + threadIdx.x;
+      __syncthreads();
+      if (k < count && !(heavies && start[k] == start[k + 1]) && rows[heavies ? start[k] : first + k] == kNoRow)
+        s_list[atomicAdd(&s_n, 1u)] = k;
+      __syncthreads();
+    }
+    const u32 n = s_n;
+    for (u32 e = threadIdx.x >> 3; e < n; e += kProbeGroups) {
+      const u32 k = s_list[e], u = heavies ? start[k] : first + k;
+      bool created;
+      const u32 row = find_or_create(t, keys[u], sub, nullptr, nullptr, &created);
+      if (created) ++made;
+      if (sub == 0) {
+        rows[u] = row;
+        if (heavies && out.upos) out.by_heavy[h0 + k] = row;
+      }
     }
   }
   if (sub == 0 && made) atomicAdd(&s_made, made);
   __syncthreads();
-  if (threadIdx.x == 0 && s_made) atomicAdd(&t.st->made_shard[c % kCountShards], s_made);
+  if (threadIdx.x == 0 && s_made) atomicAdd(&t.st->made_shard[blockIdx.x % kCountShards], s_made);
   if (out.upos && !heavies) rows_by_position(spans, out, c, first, rows);
 }
 
