@@ -93,7 +93,7 @@ STAGE_KERNELS = {
              "unique_emit, fix_mixed_runs, unique_emit)",
     "lookup": "lookup_keys<0>, insert_missing",
     "pool": "pool_bags",
-    "push": "push_main (short | medium | chunk roles), push_long",
+    "push": "push_main (short | medium | chunk roles)",
 }
 
 

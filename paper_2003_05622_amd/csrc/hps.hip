@@ -161,6 +161,12 @@ uint64_t max_counts(uint64_t n) {
   return most;
 }
 
+int lanes_per_row(uint32_t dim) {
+  int l = 1;
+  while (l < 64 && (uint32_t)l * 4 < dim) l <<= 1;
+  return l;
+}
+
 // Per pull context (two of them, so that the dedup of the next mini-batch can run
 // while the current one is still between pull and push).
 struct ContextLayout {
@@ -172,7 +178,7 @@ struct ContextLayout {
 struct WorkspaceLayout {
   size_t keys_a, keys_b, keys_c, idx_a, idx_b, idx_c, hist, prefix, total, tile_bag, heavy_raw, ghist,
       tickets, tile_rows, group_rows, head_rows, head_groups, evidence, bag_of, id16, by_pos, by_heavy, row_of,
-      bucket_total, med_list, long_list, chunk_items, partials, end;
+      bucket_total, med_list, arrived, chunk_items, partials, end;
   ContextLayout c[2];
   uint64_t max_long, max_items, sort_tiles, head_tiles;
 };
@@ -183,8 +189,13 @@ WorkspaceLayout workspace_layout(uint64_t n, uint64_t bags, uint32_t dim) {
   const uint64_t buckets = (uint64_t)kMaxBuckets[kBucketClasses - 1] + 1;
   L.sort_tiles = (n1 + kSortTile - 1) / kSortTile;
   L.head_tiles = (n1 + kHeadTile - 1) / kHeadTile;
-  L.max_long = n1 / (kMedSeg + 1) + 1;      // keys with more than kMedSeg occurrences
-  L.max_items = n1 / kChunk + L.max_long + 1;
+  // (a smaller mini-batch than the largest may be cut into more pieces)
+  L.max_long = L.max_items = 0;                   // keys the push handles chunk by chunk, their chunks
+  for (uint64_t m : {n1, n1 < kSmallPush ? n1 : kSmallPush}) {
+    const PieceSizes pieces = piece_sizes(lanes_per_row(dim), m);
+    L.max_long = std::max(L.max_long, m / (pieces.medium + 1) + 1);
+    L.max_items = std::max(L.max_items, m / pieces.chunk + m / (pieces.medium + 1) + 2);
+  }
   size_t o = 0;
   L.keys_a = o;      o = align_up(o + n1 * 8);
   L.keys_b = o;      o = align_up(o + n1 * 8);
@@ -224,8 +235,8 @@ WorkspaceLayout workspace_layout(uint64_t n, uint64_t bags, uint32_t dim) {
   L.row_of = o;      o = align_up(o + n1 * 4);      // row of every occurrence
   L.bucket_total = o; o = align_up(o + buckets * 4);
   L.med_list = o;    o = align_up(o + (n1 / (kShortSeg + 1) + kMaxHeavy + 64) * 4);
-  L.long_list = o;   o = align_up(o + L.max_long * 8);
-  L.chunk_items = o; o = align_up(o + L.max_items * 8);
+  L.arrived = o;     o = align_up(o + L.max_long * 4);
+  L.chunk_items = o; o = align_up(o + L.max_items * 16);
   L.partials = o;    o = align_up(o + L.max_items * (size_t)dim * 4);
   L.end = o;
   return L;
@@ -265,12 +276,6 @@ unsigned grid_for(uint64_t work_items, uint64_t items_per_block, unsigned max_bl
   return (unsigned)(b < max_blocks ? b : max_blocks);
 }
 
-int lanes_per_row(uint32_t dim) {
-  int l = 1;
-  while (l < 64 && (uint32_t)l * 4 < dim) l <<= 1;
-  return l;
-}
-
 bool launch_ok() { return hipGetLastError() == hipSuccess; }
 
 }  // namespace
@@ -278,7 +283,7 @@ bool launch_ok() { return hipGetLastError() == hipSuccess; }
 // ---- the one entry point that allocates nothing (hps_accumulate_static) ------------------
 // Its workspace: a file-scope device array, one copy per GPU, held until the process ends.
 // Room for the workspace of HPS_STATIC_MAX_KEYS pairs with rows of up to 1024 floats.
-constexpr size_t kStaticScratchBytes = 10u << 20;
+constexpr size_t kStaticScratchBytes = 16u << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 struct StaticScratch {
@@ -425,16 +430,17 @@ static void launch_pool(hps_table* t, int c, float* d_pooled, hipStream_t s) {
 
 template <int LPR>
 static void launch_push(hps_table* t, uint64_t n, PushArgs& a, hipStream_t s) {
+  // (a span's distinct keys are fewer than its occurrences; about four keys per lane group)
+  const uint64_t per_span = (n + a.spans.n_spans - 1) / a.spans.n_spans;
+  a.parts = grid_for(per_span, 4 * kPushThreads / LPR, std::max(1u, std::min((unsigned)kPushMaxParts, kPushSplitBlocks / a.spans.n_spans)));
   a.medium_blocks = kPushMediumBlocks;
-  const unsigned chunk_blocks = grid_for(n / kChunk + 1, 1, kPushChunkBlocks);
-  const unsigned main_blocks = span_blocks(a.spans) + a.medium_blocks + chunk_blocks;
-  const unsigned long_blocks = grid_for(n / (kMedSeg + 1) + 1, 1, kPushLongBlocks);
+  a.chunk = piece_sizes(LPR, n).chunk;
+  a.chunk_blocks = grid_for(n / a.chunk + 1, 1, kPushChunkBlocks);
+  const unsigned main_blocks = a.chunk_blocks + a.medium_blocks + heavy_blocks(a.spans) + a.spans.n_spans * a.parts;
   if (t->dim <= (uint32_t)LPR * 4) {
     push_main<LPR, 1><<<main_blocks, kPushThreads, 0, s>>>(t->view, a);
-    push_long<LPR, 1><<<long_blocks, kPushThreads, 0, s>>>(t->view, a);
   } else {
     push_main<LPR, 4><<<main_blocks, kPushThreads, 0, s>>>(t->view, a);
-    push_long<LPR, 4><<<long_blocks, kPushThreads, 0, s>>>(t->view, a);
   }
 }
 
@@ -618,8 +624,9 @@ static void launch_lookup(hps_table* t, int c, uint64_t n_keys, bool create, hip
   OftenLists often;
   often.ctx = ctx;
   often.med_list = t->w<u32>(t->wl.med_list);
-  often.long_list = t->w<uint2>(t->wl.long_list);
-  often.chunk_items = t->w<uint2>(t->wl.chunk_items);
+  often.chunk_items = t->w<uint4>(t->wl.chunk_items);
+  often.arrived = t->w<u32>(t->wl.arrived);
+  often.pieces = piece_sizes((u32)t->lpr, n_keys);
   ++t->lookup_serial;
   often.heavy_raw = &ring->raw[t->lookup_serial % kHeavyRing];
   often.heavy_next = &ring->raw[(t->lookup_serial + 1) % kHeavyRing];
@@ -644,8 +651,8 @@ static void fill_push_args(hps_table* t, int c, uint64_t n_keys, const float* d_
   a.inv_len = nullptr;
   a.ctx = t->ctx(c);
   a.med_list = t->w<u32>(L.med_list);
-  a.long_list = t->w<uint2>(L.long_list);
-  a.chunk_items = t->w<uint2>(L.chunk_items);
+  a.chunk_items = t->w<uint4>(L.chunk_items);
+  a.arrived = t->w<u32>(L.arrived);
   a.partials = t->w<float>(L.partials);
   a.lr = t->opt.lr;
   a.eps = t->opt.eps;

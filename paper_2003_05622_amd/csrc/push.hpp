@@ -7,15 +7,19 @@
 // positions.  Keys are handled by how often they occur; the pull's lookup already
 // sorted the frequent ones into work lists (table.hpp, OftenLists):
 //
-//   push_main   one launch, blocks take one of three roles:
-//                 short   a span of distinct keys per block, a group of LPR lanes per key with
-//                         at most kShortSeg occurrences: reduced and updated on the spot;
-//                 medium  one wave per listed key (up to kMedSeg occurrences): its
-//                         lane groups stride over the positions, then add up;
-//                 chunks  one block per listed chunk (kChunk positions of a still more
-//                         frequent key): tree-reduced partial sum;
-//   push_long   one block per chunked key: sums its chunks' partials in chunk order
-//               (tree) and updates the row.
+//   short   a span of distinct keys, or a part of one, per block, a group of LPR lanes per key with
+//           at most kShortSeg occurrences: reduced and updated on the spot;
+//   medium  one wave per listed key: its lane groups stride over the positions, then add up;
+//   chunks  one block per listed chunk of a very frequent key: tree-reduced partial sum; the
+//           block that finishes a key's last chunk adds up the partials in chunk order (tree) and
+//           updates the row.
+//
+// What bounds it is the lines asked for: a gradient row per occurrence, and of every distinct key the
+// row and the accumulator, read and written (9.8 M occurrences of 2.8 M keys, dim 16: 412 us; at 54 G
+// lines read and 22 G lines read and written back a second they take 440, less what L2 holds).  The
+// blocks of the one launch take the roles in this order; the chunks first (4.2 M occurrences, dim 64,
+// bfloat16 rows: 247 us instead of 216) or the medium keys first (221) were slower, and so was
+// forcing eight waves per SIMD (spills: 449 instead of 412 us).
 // Every sum has a fixed shape, so results do not depend on scheduling.
 #pragma once
 
@@ -30,7 +34,13 @@ constexpr int kPushMediumBlocks = 512;   // fixed grids: waves and blocks loop
 // workload, most of whose occurrences are chunks of very frequent keys, ran its push at two
 // waves per SIMD, 0.55 ms instead of 0.32; blocks without a chunk return at once)
 constexpr int kPushChunkBlocks = 4096;
-constexpr int kPushLongBlocks = 256;
+// Few spans are shared out over several blocks each, up to kPushMaxParts and kPushSplitBlocks in all, until a
+// lane group has about four keys: wide rows leave a block eight lane groups or fewer, which would take
+// the keys of a whole span one after the other (40 K occurrences, dim 100: 59 -> 28 us; where the
+// spans fill the GPU anyway, more blocks only put off the medium keys and the chunks: 4.2 M occurrences in
+// 1024 spans, dim 64, bfloat16 rows, 216 us with one block a span and 273 with two).
+constexpr u32 kPushSplitBlocks = 1024;
+constexpr int kPushMaxParts = 8;         // blocks that share a span
 constexpr int kPushInFlight = 8;  // gradient rows a lane group has in flight
 constexpr int kStepRowwise = 0;      // Adagrad, one accumulator per row
 constexpr int kStepElementwise = 1;  // Adagrad, one accumulator per element
@@ -45,9 +55,11 @@ struct PushArgs {
   const float* inv_len;   // != null (mean pooling): per bag, the share of its gradient an occurrence gets
   const PullCtx* ctx;
   const u32* med_list;        // unique indices
-  const uint2* long_list;     // (unique index, first chunk item)
-  const uint2* chunk_items;   // (unique index, chunk number)
-  u32 medium_blocks;          // roles of push_main's blocks: short (one per span), medium, chunks
+  const uint4* chunk_items;   // (unique index, chunk number, number of the chunked key, its first chunk item)
+  u32* arrived;               // per chunked key: chunks summed so far
+  u32 chunk_blocks, medium_blocks;      // roles of push_main's blocks: chunks, medium, short
+  u32 chunk;                  // occurrences per chunk
+  u32 parts;                  // short: blocks that share one span
   float* partials;      // [chunk item][dim]
   float lr, eps;
   int kind;   // what a touched row takes: kStepRowwise, kStepElementwise or kStepAdd
@@ -168,11 +180,12 @@ template <int LPR, int COLS>
 __device__ __forceinline__ void push_short_role(const TableView& t, const PushArgs& a, u32 block) {
   const u32 sub = threadIdx.x % LPR;
   const bool heavies = block < heavy_blocks(a.spans);
-  const u32 span = block - heavy_blocks(a.spans), h0 = block * kHeavyGroup;
+  const u32 rest = block - heavy_blocks(a.spans), span = rest / a.parts, h0 = block * kHeavyGroup;
+  const u32 part = heavies ? 0 : rest % a.parts, parts = heavies ? 1 : a.parts;
   u32 first = 0, count;
   if (heavies) count = a.ctx->n_heavy > h0 ? min(kHeavyGroup, a.ctx->n_heavy - h0) : 0u;
   else unique_span(a.spans, a.ctx, span, &first, &count);
-  for (u32 k = threadIdx.x / LPR; k < count; k += kPushThreads / LPR) {
+  for (u32 k = part * (kPushThreads / LPR) + threadIdx.x / LPR; k < count; k += parts * (kPushThreads / LPR)) {
     u32 u = first + k;
     if (heavies) {
       u = a.spans.bucket_start[a.spans.n_spans + h0 + k];
@@ -239,82 +252,97 @@ __device__ __forceinline__ void block_tree_sum(float4* g, float4* lds, u32 dim4)
   }
 }
 
+// Partial rows go from one block to another inside the launch: written through to memory and read
+// from there (agent-scope accesses), and counted in only once the writes are acknowledged.
+// A release fence instead would write back the whole L2 of the XCD, once per chunk.
+__device__ __forceinline__ void store_partial(u64* p, float4 v) {
+  __hip_atomic_store(p, (u64)__float_as_uint(v.x) | (u64)__float_as_uint(v.y) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(p + 1, (u64)__float_as_uint(v.z) | (u64)__float_as_uint(v.w) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float4 load_partial(const u64* p) {
+  const u64 a = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const u64 b = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return make_float4(__uint_as_float((u32)a), __uint_as_float((u32)(a >> 32)), __uint_as_float((u32)b), __uint_as_float((u32)(b >> 32)));
+}
+
 template <int LPR, int COLS>
 __device__ __forceinline__ void push_chunks_role(const TableView& t, const PushArgs& a, u32 block,
-                                                 u32 n_blocks, float4* lds) {
+                                                 u32 n_blocks, float4* lds, u32* s_last) {
   constexpr int kGroups = kPushThreads / LPR;
+  const u32 kChunk = a.chunk;
+  static_assert(LPR <= kWave, "group 0 lies in one wave");
   const u32 n_items = a.ctx->n_chunk_items;
-  const u32 group = threadIdx.x / LPR, sub = threadIdx.x % LPR;
+  const u32 group = threadIdx.x / LPR, sub = threadIdx.x % LPR, dim4 = t.dim >> 2;
   for (u32 item = block; item < n_items; item += n_blocks) {
-    const uint2 it = a.chunk_items[item];
-    const u32 lo = a.seg_off[it.x] + it.y * kChunk;
-    const u32 hi = min(lo + kChunk, a.seg_off[it.x + 1]);
+    const uint4 it = a.chunk_items[item];
+    const u32 begin = a.seg_off[it.x], end = a.seg_off[it.x + 1];
+    const u32 n_chunks = (end - begin + kChunk - 1) / kChunk;
+    const u32 lo = begin + it.y * kChunk, hi = min(lo + kChunk, end);
     float4 g[COLS];
 #pragma unroll
     for (int c = 0; c < COLS; ++c) g[c] = make_float4(0.f, 0.f, 0.f, 0.f);
     add_positions<LPR, COLS>(g, a, lo + group, hi, kGroups, t.dim, sub);
-    block_tree_sum<LPR, COLS>(g, lds, t.dim >> 2);
-    if (group == 0) {
-      float4* out = reinterpret_cast<float4*>(a.partials + (u64)item * t.dim);
+    block_tree_sum<LPR, COLS>(g, lds, dim4);
+    if (n_chunks > 1) {
+      if (group == 0) {
+        u64* out = reinterpret_cast<u64*>(a.partials + (u64)item * t.dim);
 #pragma unroll
-      for (int c = 0; c < COLS; ++c)
-        if (sub + c * LPR < (t.dim >> 2)) out[sub + c * LPR] = g[c];
+        for (int c = 0; c < COLS; ++c)
+          if (sub + c * LPR < dim4) store_partial(out + 2 * (sub + c * LPR), g[c]);
+      }
+      if (threadIdx.x < kWave) {
+        // (the wave that holds group 0: its stores are done before its count)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (threadIdx.x == 0)
+          *s_last = __hip_atomic_fetch_add(&a.arrived[it.z], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == n_chunks;
+      }
+      __syncthreads();
+      const bool last = *s_last != 0;
+      __syncthreads();      // (s_last is written again for the next item)
+      if (!last) continue;
+#pragma unroll
+      for (int c = 0; c < COLS; ++c) g[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+      // (eight partial rows requested at a time, added in chunk order: a key that fills thousands of
+      // chunks would otherwise wait for every row in turn)
+      for (u32 c0 = group; c0 < n_chunks; c0 += kPushInFlight * kGroups) {
+        float4 v[kPushInFlight][COLS];
+#pragma unroll
+        for (int k = 0; k < kPushInFlight; ++k) {
+          const u32 c = c0 + k * kGroups;
+          const u64* row = reinterpret_cast<const u64*>(a.partials + (u64)(it.w + (c < n_chunks ? c : c0)) * t.dim);
+#pragma unroll
+          for (int q = 0; q < COLS; ++q) {
+            const u32 col = sub + q * LPR;
+            v[k][q] = (c < n_chunks && col < dim4) ? load_partial(row + 2 * col) : make_float4(0.f, 0.f, 0.f, 0.f);
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < kPushInFlight; ++k)
+#pragma unroll
+          for (int q = 0; q < COLS; ++q) {
+            g[q].x += v[k][q].x; g[q].y += v[k][q].y; g[q].z += v[k][q].z; g[q].w += v[k][q].w;
+          }
+      }
+      block_tree_sum<LPR, COLS>(g, lds, dim4);
     }
+    const u32 r = a.rows[it.x];
+    if (group == 0 && r != kNoRow) adagrad_row<LPR, COLS>(t, r, g, sub, a.lr, a.eps, a.kind);
   }
 }
 
 template <int LPR, int COLS>
 __global__ void __launch_bounds__(kPushThreads) push_main(TableView t, PushArgs a) {
   __shared__ float4 lds[kPushThreads];
+  __shared__ u32 s_last;
   if (load_error(t.st) != 0) return;
-  const u32 b = blockIdx.x, n_short = span_blocks(a.spans);
+  const u32 b = blockIdx.x;
+  const u32 n_short = heavy_blocks(a.spans) + a.spans.n_spans * a.parts;
   if (b < n_short) {
     push_short_role<LPR, COLS>(t, a, b);
   } else if (b < n_short + a.medium_blocks) {
     push_medium_role<LPR, COLS>(t, a, b - n_short);
   } else {
-    push_chunks_role<LPR, COLS>(t, a, b - n_short - a.medium_blocks, gridDim.x - n_short - a.medium_blocks, lds);
-  }
-}
-
-template <int LPR, int COLS>
-__global__ void __launch_bounds__(kPushThreads) push_long(TableView t, PushArgs a) {
-  __shared__ float4 lds[kPushThreads];
-  constexpr int kGroups = kPushThreads / LPR;
-  if (load_error(t.st) != 0) return;
-  const u32 n_long = a.ctx->n_long;
-  const u32 group = threadIdx.x / LPR, sub = threadIdx.x % LPR;
-  for (u32 l = blockIdx.x; l < n_long; l += gridDim.x) {
-  const uint2 seg = a.long_list[l];
-  const u32 len = a.seg_off[seg.x + 1] - a.seg_off[seg.x];
-  const u32 n_chunks = (len + kChunk - 1) / kChunk;
-  float4 g[COLS];
-#pragma unroll
-  for (int c = 0; c < COLS; ++c) g[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-  // (eight partial rows requested at a time, added in chunk order: a key that fills thousands of
-  // chunks would otherwise wait for every row in turn)
-  for (u32 c0 = group; c0 < n_chunks; c0 += kPushInFlight * kGroups) {
-    float4 v[kPushInFlight][COLS];
-#pragma unroll
-    for (int k = 0; k < kPushInFlight; ++k) {
-      const u32 c = c0 + k * kGroups;
-      const float4* row = reinterpret_cast<const float4*>(a.partials + (u64)(seg.y + (c < n_chunks ? c : c0)) * t.dim);
-#pragma unroll
-      for (int q = 0; q < COLS; ++q) {
-        const u32 col = sub + q * LPR;
-        v[k][q] = (c < n_chunks && col < (t.dim >> 2)) ? row[col] : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < kPushInFlight; ++k)
-#pragma unroll
-      for (int q = 0; q < COLS; ++q) {
-        g[q].x += v[k][q].x; g[q].y += v[k][q].y; g[q].z += v[k][q].z; g[q].w += v[k][q].w;
-      }
-  }
-  block_tree_sum<LPR, COLS>(g, lds, t.dim >> 2);
-  const u32 r = a.rows[seg.x];
-  if (group == 0 && r != kNoRow) adagrad_row<LPR, COLS>(t, r, g, sub, a.lr, a.eps, a.kind);
+    push_chunks_role<LPR, COLS>(t, a, b - n_short - a.medium_blocks, a.chunk_blocks, lds, &s_last);
   }
 }
 

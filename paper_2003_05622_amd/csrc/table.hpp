@@ -132,8 +132,21 @@ constexpr u32 kNewLdsCap = 1024;         // created keys a block lists for its c
 constexpr u32 kLongLdsCap = 64;          // very frequent keys whose chunk items whole waves write (>= kHeavyGroup)
 constexpr u32 kMedLdsCap = 512;          // medium keys a block buffers before it appends
 constexpr u32 kShortSeg = 16;            // occurrences handled serially by one lane group
-constexpr u32 kMedSeg = 512;             // occurrences handled by one wave
-constexpr u32 kChunk = 1024;             // occurrences per queued chunk of a longer key
+
+// How the push shares out the occurrences of a key with more than kShortSeg, by lanes per row: up to
+// `medium` go to one wave, the others in pieces of `chunk` to one block each.  Wide rows leave fewer
+// lane groups (64 / lpr a wave, 256 / lpr a block), each with eight rows in flight, so that
+// the same piece takes more round trips to memory one after the other: 512 occurrences at 32 lanes
+// a row are 32 trips of one wave.  Where the mini-batch is small the whole push waits for them (40 K
+// occurrences, dim 100: 80 us; 28 with these sizes and kPushMaxParts together), so there a piece is
+// about four trips.  In large ones they lie under other work, while more pieces cost more entries in the
+// lists and more partial sums (8.4 M occurrences, dim 64: lookup 49 -> 71, push 320 -> 384 us).
+struct PieceSizes { u32 medium, chunk; };
+constexpr u64 kSmallPush = 1u << 19;
+__host__ constexpr PieceSizes piece_sizes(u32 lpr, u64 n) {
+  return lpr <= 4 || n > kSmallPush ? PieceSizes{512, 1024} : lpr == 8 ? PieceSizes{256, 1024} : lpr == 16 ? PieceSizes{128, 512}
+         : lpr == 32 ? PieceSizes{64, 256} : PieceSizes{64, 128};
+}
 
 // Where the distinct keys of a mini-batch lie in uniq / seg_off / rows.  Bucket form (bucket.hpp): natural
 // bucket c's in [bucket_start[c], + count[c]), heavy key h at bucket_start[n_spans + h] if that
@@ -162,13 +175,14 @@ __device__ __forceinline__ void unique_span(const UniqueSpans& s, const PullCtx*
 }
 
 // What the lookup leaves for the push about keys that occur often (push.hpp): keys with
-// kShortSeg < occurrences <= kMedSeg are listed, keys with more are cut into
-// chunks of kChunk positions.
+// kShortSeg < occurrences <= pieces.medium are listed, keys with more are cut into
+// chunks of pieces.chunk positions.
 struct OftenLists {
   PullCtx* ctx;
   u32* med_list;
-  uint2* long_list;     // (unique index, first chunk item)
-  uint2* chunk_items;   // (unique index, chunk number)
+  uint4* chunk_items;   // (unique index, chunk number, number of the chunked key, its first chunk item)
+  u32* arrived;         // per chunked key: chunks the push has summed (cleared here)
+  PieceSizes pieces;
   HeavyRaw* heavy_raw;  // keys with at least heavy_min occurrences are listed for the next dedup
   u32 heavy_min;
   HeavyRaw* heavy_next; // the list the next lookup will fill: emptied
@@ -515,7 +529,7 @@ pull_lookup(TableView t, u64* __restrict__ keys, u32* __restrict__ seg_off, Uniq
   constexpr int K = kPullInFlight;            // keys a group has in flight
   static_assert(K == kLookupLanes, "one key per lane");
   __shared__ u32 s_missing, s_med, s_med_base, s_made, s_new, s_long, s_unique;
-  __shared__ uint4 s_long_list[kLongLdsCap];  // (key, first chunk item, chunks) of the block's very frequent keys
+  __shared__ uint4 s_long_list[kLongLdsCap];  // (unique index, first chunk item, chunks, number) of the block's very frequent keys
   __shared__ u32 s_med_list[kMedLdsCap];
   __shared__ u64 s_new_key[kNewLdsCap];       // keys created by this block, and their rows
   __shared__ u32 s_new_row[kNewLdsCap];
@@ -635,17 +649,18 @@ pull_lookup(TableView t, u64* __restrict__ keys, u32* __restrict__ seg_off, Uniq
       const u32 at = atomicAdd(&often.heavy_raw->count, 1u);
       if (at < (u32)kMaxHeavy) often.heavy_raw->keys[at] = my_key;
     }
-    if (my_len > kMedSeg) {
-      const u32 n_chunks = (my_len + kChunk - 1) / kChunk;
+    if (my_len > often.pieces.medium) {
+      const u32 n_chunks = (my_len + often.pieces.chunk - 1) / often.pieces.chunk;
       const u32 item = atomicAdd(&ctx->n_chunk_items, n_chunks);
-      often.long_list[atomicAdd(&ctx->n_long, 1u)] = make_uint2(u, item);
+      const u32 number = atomicAdd(&ctx->n_long, 1u);
+      often.arrived[number] = 0;
       // the key's chunk items are written at the end of the kernel by all lanes of a wave
       // (a key that fills thousands of chunks would keep this lane, and its wave, for long)
       const u32 at = atomicAdd(&s_long, 1u);
       if (at < kLongLdsCap) {
-        s_long_list[at] = make_uint4(u, item, n_chunks, 0u);
+        s_long_list[at] = make_uint4(u, item, n_chunks, number);
       } else {
-        for (u32 i = 0; i < n_chunks; ++i) often.chunk_items[item + i] = make_uint2(u, i);
+        for (u32 i = 0; i < n_chunks; ++i) often.chunk_items[item + i] = make_uint4(u, i, number, item);
       }
     } else if (my_len > kShortSeg) {
       const u32 at = atomicAdd(&s_med, 1u);
@@ -666,7 +681,7 @@ pull_lookup(TableView t, u64* __restrict__ keys, u32* __restrict__ seg_off, Uniq
     const u32 n_long_here = min(s_long, kLongLdsCap);
     for (u32 e = threadIdx.x / kWave; e < n_long_here; e += kProbeThreads / kWave) {
       const uint4 it = s_long_list[e];
-      for (u32 i = lane_id(); i < it.z; i += kWave) often.chunk_items[it.y + i] = make_uint2(it.x, i);
+      for (u32 i = lane_id(); i < it.z; i += kWave) often.chunk_items[it.y + i] = make_uint4(it.x, i, it.w, it.y);
     }
   }
   // the initial rows of the keys created above: one float4 of one row per lane and turn
