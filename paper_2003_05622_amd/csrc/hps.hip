@@ -1150,14 +1150,13 @@ static hps_status dump_impl(hps_table* t, bool dirty, uint64_t* d_keys_out, floa
   if (!t || !h_n_rows) return HPS_EINVAL;
   if (max_rows && (!d_keys_out || !d_weights_out || !d_acc_out)) return HPS_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const unsigned dump_blocks = grid_for(t->n_slots, kDumpSlots, kDumpMaxBlocks);
   clear_dump_count<<<1, 1, 0, s>>>(t->view.st);
-  if (dirty)
-    dump_rows<true><<<dump_blocks, kRowThreads, 0, s>>>(t->view, d_keys_out, d_weights_out, d_acc_out, max_rows,
-                                         &t->view.st->dump_count);
-  else
-    dump_rows<false><<<dump_blocks, kRowThreads, 0, s>>>(t->view, d_keys_out, d_weights_out, d_acc_out, max_rows,
-                                          &t->view.st->dump_count);
+#define HPS_DUMP(DIRTY, ROUNDS)                                                                                     \
+  dump_rows<DIRTY, ROUNDS><<<grid_for(t->n_slots, kDumpSlots * ROUNDS, kDumpMaxBlocks), kRowThreads, 0, s>>>(        \
+      t->view, d_keys_out, d_weights_out, d_acc_out, max_rows, &t->view.st->dump_count)
+  if (t->n_slots < kDumpSmall) { if (dirty) HPS_DUMP(true, 1); else HPS_DUMP(false, 1); }
+  else { if (dirty) HPS_DUMP(true, kDumpRounds); else HPS_DUMP(false, kDumpRounds); }
+#undef HPS_DUMP
   if (!launch_ok()) return HPS_EDEVICE;
   unsigned long long count = 0;
   if (hipMemcpyAsync(&count, &t->view.st->dump_count, sizeof(count), hipMemcpyDeviceToHost, s) != hipSuccess)

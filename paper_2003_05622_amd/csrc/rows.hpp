@@ -9,7 +9,7 @@
 //   get, 2.05 M keys, dim 32: 199 us (439), 5.3 TB/s of lines in and rows out;
 //   insert with values, 1.3 M new keys, dim 16: 149 us (247 in two kernels that each probed), which is
 //   what two random partial-line writes per key (row, accumulator) cost at 22 G/s;
-//   dump of 0.16 M changed rows out of 6 M slots, dim 32: 85 us (302, one thread per row).
+//   dump of 0.16 M changed rows out of 6 M slots, dim 32: 38 us (302, one thread per row).
 #pragma once
 
 #include "common.hpp"
@@ -232,54 +232,85 @@ insert_rows(TableView t, const u64* __restrict__ keys, u64 n_keys, const float* 
 }
 
 // dump: every occupied slot (DIRTY: every occupied slot whose row is marked as updated; the mark
-// of a row that is written out is cleared), order unspecified.  A block looks at kDumpSlots slots
-// at a time, lists the rows to go out in LDS, takes places for them from one counter and
+// of a row that is written out is cleared), order unspecified.  A block looks at kDumpSlots * ROUNDS
+// slots at a time, lists the rows to go out in LDS, takes places for them from one counter and
 // moves them with all lanes.
+//
+// What bounds it is the read of every slot's key or mark, and the one counter, whose additions the memory
+// side takes one after the other: kDumpRounds = 4 keeps them few.  Where the accumulators lie in an array
+// of their own, one per row, the marks are read first, and keys only of marked slots (an empty slot's
+// accumulator may hold anything).  0.16 M changed rows out of 6 M slots, dim 32: 85 us with one round
+// a block and keys first, 38 now.
 constexpr int kDumpItems = 4;
 constexpr int kDumpSlots = kRowThreads * kDumpItems;
 constexpr int kDumpMaxBlocks = 4096;
-template <bool DIRTY>
+constexpr int kDumpRounds = 4;
+constexpr u64 kDumpSmall = 1u << 20;      // fewer slots: one round a block, so that all CUs have a block
+template <bool DIRTY, int ROUNDS>
 __global__ void __launch_bounds__(kRowThreads)
 dump_rows(TableView t, u64* __restrict__ keys_out, float* __restrict__ w_out,
           float* __restrict__ acc_out, u64 max_rows, unsigned long long* __restrict__ counter) {
   __shared__ u32 scratch[kRowThreads / kWave + 1];
   __shared__ unsigned long long s_base;
-  __shared__ u32 s_slot[kDumpSlots];
-  __shared__ u64 s_key[kDumpSlots];
+  __shared__ u32 s_slot[kDumpSlots * ROUNDS];
   const u64 n_slots = t.n_lines * kSlotsPerLine;          // a multiple of 16
-  const u64 n_rounds = (n_slots + kDumpSlots - 1) / kDumpSlots;
+  const u64 n_rounds = (n_slots + kDumpSlots * ROUNDS - 1) / (kDumpSlots * ROUNDS);
   const bool aligned = aligned16(w_out) && aligned16(acc_out);
   const u32 words = t.dim >> 2, acc_words = t.acc_len >> 2;
+  const bool marks_first = DIRTY && t.acc_pitch == sizeof(float);
   for (u64 round = blockIdx.x; round < n_rounds; round += gridDim.x) {
-    const u64 s0 = round * kDumpSlots + threadIdx.x * kDumpItems;
-    u64 key[kDumpItems];
-    float mark[kDumpItems];
-    u32 mine = 0;
-    if (s0 < n_slots) {
-      const ulonglong2 a = reinterpret_cast<const ulonglong2*>(t.keys + s0)[0];
-      const ulonglong2 b = reinterpret_cast<const ulonglong2*>(t.keys + s0)[1];
-      key[0] = a.x; key[1] = a.y; key[2] = b.x; key[3] = b.y;
+    const u64 first = round * (kDumpSlots * ROUNDS) + threadIdx.x * kDumpItems;
+    u32 out = 0;                                          // bit: the slot goes out
+    if (marks_first) {
+      float4 m[ROUNDS];
+#pragma unroll
+      for (int k = 0; k < ROUNDS; ++k) {
+        const u64 s0 = first + k * kDumpSlots;
+        m[k] = s0 < n_slots ? *reinterpret_cast<const float4*>(t.acc + s0 * sizeof(float)) : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+#pragma unroll
+      for (int k = 0; k < ROUNDS; ++k)
+        out |= ((acc_is_marked(m[k].x) ? 1u : 0u) | (acc_is_marked(m[k].y) ? 2u : 0u) | (acc_is_marked(m[k].z) ? 4u : 0u) |
+                (acc_is_marked(m[k].w) ? 8u : 0u)) << (kDumpItems * k);
+      u64 key[ROUNDS * kDumpItems];
+#pragma unroll
+      for (int q = 0; q < ROUNDS * kDumpItems; ++q)
+        key[q] = out >> q & 1u ? t.keys[first + q / kDumpItems * kDumpSlots + q % kDumpItems] : kEmptyKey;
+#pragma unroll
+      for (int q = 0; q < ROUNDS * kDumpItems; ++q)
+        if (key[q] == kEmptyKey) out &= ~(1u << q);
     } else {
-      key[0] = key[1] = key[2] = key[3] = kEmptyKey;
-    }
 #pragma unroll
-    for (int q = 0; q < kDumpItems; ++q) mark[q] = DIRTY && key[q] != kEmptyKey ? *acc_row(t, s0 + q) : 0.f;
+      for (int k = 0; k < ROUNDS; ++k) {
+        const u64 s0 = first + k * kDumpSlots;
+        if (s0 >= n_slots) continue;
+        const ulonglong2 a = reinterpret_cast<const ulonglong2*>(t.keys + s0)[0];
+        const ulonglong2 b = reinterpret_cast<const ulonglong2*>(t.keys + s0)[1];
+        out |= ((a.x != kEmptyKey ? 1u : 0u) | (a.y != kEmptyKey ? 2u : 0u) | (b.x != kEmptyKey ? 4u : 0u) |
+                (b.y != kEmptyKey ? 8u : 0u)) << (kDumpItems * k);
+      }
+      if (DIRTY) {
+        float mark[ROUNDS * kDumpItems];
 #pragma unroll
-    for (int q = 0; q < kDumpItems; ++q) {
-      if (DIRTY && !acc_is_marked(mark[q])) key[q] = kEmptyKey;
-      mine += key[q] != kEmptyKey ? 1u : 0u;
+        for (int q = 0; q < ROUNDS * kDumpItems; ++q)
+          mark[q] = out >> q & 1u ? *acc_row(t, first + q / kDumpItems * kDumpSlots + q % kDumpItems) : 0.f;
+#pragma unroll
+        for (int q = 0; q < ROUNDS * kDumpItems; ++q)
+          if (!acc_is_marked(mark[q])) out &= ~(1u << q);
+      }
     }
     u32 total;
-    u32 at = block_excl_sum<kRowThreads>(mine, scratch, &total);
-#pragma unroll
-    for (int q = 0; q < kDumpItems; ++q)
-      if (key[q] != kEmptyKey) { s_slot[at] = (u32)(s0 + q); s_key[at] = key[q]; ++at; }
+    u32 at = block_excl_sum<kRowThreads>((u32)__popc(out), scratch, &total);
+    for (u32 left = out; left; left &= left - 1) {
+      const u32 q = __ffs(left) - 1;
+      s_slot[at++] = (u32)(first + q / kDumpItems * kDumpSlots + q % kDumpItems);
+    }
     if (threadIdx.x == 0 && total) s_base = atomicAdd(counter, (unsigned long long)total);
     __syncthreads();
     if (total) {
       const u64 base = s_base;
       const u32 count = base >= max_rows ? 0u : (u32)min((u64)total, max_rows - base);
-      for (u32 i = threadIdx.x; i < count; i += kRowThreads) keys_out[base + i] = s_key[i];
+      for (u32 i = threadIdx.x; i < count; i += kRowThreads) keys_out[base + i] = t.keys[s_slot[i]];
       if (t.acc_len == 1)
         for (u32 i = threadIdx.x; i < count; i += kRowThreads) {
           float* a = acc_row(t, s_slot[i]);
@@ -288,6 +319,7 @@ dump_rows(TableView t, u64* __restrict__ keys_out, float* __restrict__ w_out,
           if (DIRTY) *a = v;
         }
       float* w_first = w_out + base * t.dim;
+#pragma unroll 4
       for (u32 e = threadIdx.x; e < count * words; e += kRowThreads)
         store_caller4(w_first + 4 * e, aligned, load_w4(t, s_slot[e / words], e % words));
       if (t.acc_len != 1) {
