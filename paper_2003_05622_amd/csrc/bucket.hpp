@@ -329,7 +329,7 @@ constexpr u32 kOrderCells = 4096;
 constexpr u32 kOrderCellMax = 32;
 __global__ void __launch_bounds__(kOrderThreads)
 order_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start, const u32* __restrict__ count,
-              u32 n_nat, const PullCtx* __restrict__ ctx, const TableState* __restrict__ st,
+              u32 n_nat, const u64* __restrict__ border, const PullCtx* __restrict__ ctx, const TableState* __restrict__ st,
               u32* __restrict__ local_rank, u32* __restrict__ bucket_total) {
   constexpr int kPer = kOrderCap / kOrderThreads, kWaves = kOrderThreads / kWave;
   __shared__ u64 key[kOrderCap];
@@ -351,7 +351,7 @@ order_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start
     const u32 at = bucket_start[n_nat + h];
     if (bucket_start[n_nat + h + 1] == at) continue;
     const u64 k = uniq[at];
-    if (bucket_of(k, range) != c) continue;
+    if (!in_bucket(k, c, range, border, n_nat)) continue;
     const u32 i = atomicAdd(&s_n, 1u);
     key[i] = k;
     num[i] = at;
@@ -464,7 +464,7 @@ order_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start
 // wanted): every position's and heavy bucket's rank, for spread().
 __global__ void __launch_bounds__(kOrderThreads)
 emit_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start, const u32* __restrict__ count,
-             const u32* __restrict__ upos, u32 n_nat, const PullCtx* __restrict__ ctx,
+             const u32* __restrict__ upos, u32 n_nat, const u64* __restrict__ border, const PullCtx* __restrict__ ctx,
              const TableState* __restrict__ st, const u32* __restrict__ local_rank, const u32* __restrict__ bucket_total, u64* __restrict__ uniq_out,
              u32* __restrict__ rank_by_pos, u32* __restrict__ rank_by_heavy) {
   __shared__ u32 scratch[kOrderThreads / kWave + 1];
@@ -485,7 +485,7 @@ emit_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start,
     const u32 at = bucket_start[n_nat + h];
     if (bucket_start[n_nat + h + 1] == at) continue;
     const u64 k = uniq[at];
-    if (bucket_of(k, range) != c) continue;
+    if (!in_bucket(k, c, range, border, n_nat)) continue;
     const u32 rank = base + local_rank[at];
     if (uniq_out) uniq_out[rank] = k;
     if (rank_by_heavy) rank_by_heavy[h] = rank;

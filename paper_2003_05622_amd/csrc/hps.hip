@@ -124,6 +124,8 @@ constexpr bool bucket_sizes_ok() {
   }
   return true;
 }
+static_assert(kBucketSizes[0].max_nat <= kMaxBorders && kBucketSizes[1].max_nat <= kMaxBorders &&
+                  kBorderMaxKeys <= kBucketSizes[1].max_n, "buckets by sampled borders");
 static_assert(bucket_sizes_ok(), "the kernels' limits");
 // Largest dedup the bucket form takes.
 constexpr uint64_t kBucketPathMaxKeys = kBucketSizes[kBucketClasses - 1].max_n;
@@ -171,7 +173,7 @@ int lanes_per_row(uint32_t dim) {
 // while the current one is still between pull and push).
 struct ContextLayout {
   size_t ctx, uniq, rows, bags, seg_off, inv_len;
-  size_t code, from, upos, bucket_start, count;      // bucket form
+  size_t code, from, upos, bucket_start, count, border;      // bucket form
   size_t inverse;                                    // plain form (shares its memory with `code`)
 };
 
@@ -229,6 +231,7 @@ WorkspaceLayout workspace_layout(uint64_t n, uint64_t bags, uint32_t dim) {
     L.c[k].upos = o;    o = align_up(o + n1 * 4);
     L.c[k].bucket_start = o; o = align_up(o + (buckets + 1) * 4);
     L.c[k].count = o;   o = align_up(o + buckets * 4);
+    L.c[k].border = o;  o = align_up(o + kMaxBorders * 8);
   }
   L.by_pos = o;      o = align_up(o + n1 * 4);      // row of the key at every position
   L.by_heavy = o;    o = align_up(o + (kMaxHeavy + 1) * 4);
@@ -320,6 +323,11 @@ struct hps_table {
   uint32_t strikes;
   uint64_t plain_until;     // dedups numbered below this take the plain form
   uint64_t n_fallbacks;     // times plain_until was pushed out
+  // What takes the place of the bucket form until then: where `bunched` keys were the cause and the
+  // mini-batch is small enough, buckets by sampled borders, unless those have disappointed
+  // too (dedups numbered below borders_from); else the plain form.
+  bool bunched;
+  uint64_t borders_from;
   // The same for the plain form itself: after a dedup whose keys agreed in all the bits the
   // plain form sorts by (table.hpp: kReportMixed), the following ones sort by all 64 bits.
   uint32_t full_strikes;
@@ -333,6 +341,7 @@ struct hps_table {
     const int32_t* d_offsets;
     bool mean;            // pooling of this pull (fixed when it is prepared)
     bool buckets;         // its dedup took the bucket form ...
+    bool borders;         // ... by sampled borders
     BucketPlan plan;      // ... with these sizes ...
     u32 heavy_slot;       // ... and this list of frequent keys (common.hpp: HeavyRing)
     hipEvent_t ready;     // recorded after the dedup kernels
@@ -445,7 +454,7 @@ static void launch_push(hps_table* t, uint64_t n, PushArgs& a, hipStream_t s) {
 }
 
 // The bucket form's kernels for context c (partition.hpp, bucket.hpp), size class K.
-template <int K>
+template <int K, bool BORDERS>
 static void launch_buckets(hps_table* t, int c, const uint64_t* d_keys, u32 n, const int32_t* d_offsets, u32 n_bags,
                            const HeavyRaw* heavy, hipStream_t s) {
   constexpr int kThreads = kBucketSizes[K].threads, kItems = kBucketSizes[K].items, kGroup = kBucketSizes[K].group_threads;
@@ -462,8 +471,13 @@ static void launch_buckets(hps_table* t, int c, const uint64_t* d_keys, u32 n, c
   u64* keys = t->w<u64>(L.keys_a);
   u32* bags = t->w<u32>(C.bags);
   const unsigned bag_blocks = d_offsets ? grid_for(n_bags, kThreads * 4, 256) : 0;
-  bucket_count<kThreads, kItems, kMaxBuckets[K]><<<plan.n_tiles + bag_blocks, kThreads, 0, s>>>(
-      d_keys, n, plan, ctx, d_offsets, n_bags, tile_bag, heavy, id16, hist);
+  u64* border = t->w<u64>(C.border);
+  if constexpr (BORDERS) {
+    constexpr u32 kSamples = border_samples(kBucketSizes[K].max_nat);
+    sample_borders<kSamples><<<kSamples / kWave, kBorderThreads, 0, s>>>(d_keys, n, plan.n_nat, border);
+  }
+  bucket_count<kThreads, kItems, kMaxBuckets[K], BORDERS><<<plan.n_tiles + bag_blocks, kThreads, 0, s>>>(
+      d_keys, n, plan, border, ctx, d_offsets, n_bags, tile_bag, heavy, id16, hist);
   if (!kDirect) {
     const unsigned blocks = (plan.n_nat + plan.max_heavy + kScanBuckets - 1) / kScanBuckets;
 #define HPS_SCAN(PER) scan_buckets<PER><<<blocks, kScanThreads, 0, s>>>(hist, plan, prefix, t->w<u32>(L.total), ctx)
@@ -516,40 +530,58 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
         if ((flags & kReportBucket) && (flags & kReportSlow) && (flags & kReportOneKey)) {
           // a few keys turned frequent without warning: plain until the hint has caught up
           t->plain_until = t->serial + kHintLag;
+          t->bunched = false;
           ++t->n_fallbacks;
         } else if ((flags & kReportBucket) && (flags & kReportSlow)) {
           t->plain_until = t->serial + ((uint64_t)kPlainHold << (t->strikes < 7 ? t->strikes : 7));
           ++t->strikes;
+          t->bunched = true;
           ++t->n_fallbacks;
         } else if (flags & kReportBucket) {
           t->strikes = 0;
+        } else if ((flags & kReportBorders) && (flags & kReportSlow)) {
+          t->borders_from = t->serial + ((flags & kReportOneKey) ? kHintLag : kPlainHold);
         }
         if (flags & kReportMixed) {
           // the plain form's sorted bits did not tell the keys apart: all 64 bits for a while
           t->full_until = t->serial + ((uint64_t)kPlainHold << (t->full_strikes < 7 ? t->full_strikes : 7));
           ++t->full_strikes;
           ++t->n_full_fallbacks;
-        } else if (!(flags & kReportBucket) && t->serial >= t->full_until) {
+        } else if (!(flags & (kReportBucket | kReportBorders)) && t->serial >= t->full_until) {
           t->full_strikes = 0;       // the plain form with its usual passes did well
         }
       }
     }
-    const bool buckets = n <= kBucketPathMaxKeys && t->dedup_mode != 1 &&
-                         (t->dedup_mode == 2 || (t->lookup_serial >= 2 && t->serial >= t->plain_until));
+    // For small mini-batches buckets by sampled borders, one more launch, are the better stand-in for the
+    // plain form's ten (40 K occurrences, raw ids with the frequent ones side by side, dim 100, a
+    // step with its push and lookup: 109 instead of 154 us).  Larger ones would need more samples than one kernel of a few
+    // microseconds can rank.
+    const bool hinted = n <= kBucketPathMaxKeys && t->dedup_mode != 1 && (t->dedup_mode >= 2 || t->lookup_serial >= 2);
+    const bool by_range = hinted && (t->dedup_mode >= 2 || t->serial >= t->plain_until);
+    const bool borders = hinted && n <= kBorderMaxKeys &&
+                         (t->dedup_mode == 3 || (!by_range && t->bunched && t->serial >= t->borders_from));
+    const bool buckets = by_range || borders;
     t->cx[c].buckets = buckets;
+    t->cx[c].borders = borders;
     if (buckets) {
       t->cx[c].plan = bucket_plan(n);
       // the most recent list of frequent keys that is certainly complete (common.hpp)
       t->cx[c].heavy_slot = (u32)((t->lookup_serial + kHeavyRing - 1) % kHeavyRing);
       const HeavyRaw* heavy = &t->w<HeavyRing>(L.heavy_raw)->raw[t->cx[c].heavy_slot];
       switch (bucket_class(n)) {
-        case 0: launch_buckets<0>(t, c, d_keys, n, d_offsets, n_bags, heavy, s); break;
-        case 1: launch_buckets<1>(t, c, d_keys, n, d_offsets, n_bags, heavy, s); break;
-        case 2: launch_buckets<2>(t, c, d_keys, n, d_offsets, n_bags, heavy, s); break;
-        default: launch_buckets<3>(t, c, d_keys, n, d_offsets, n_bags, heavy, s); break;
+        case 0:
+          if (borders) launch_buckets<0, true>(t, c, d_keys, n, d_offsets, n_bags, heavy, s);
+          else launch_buckets<0, false>(t, c, d_keys, n, d_offsets, n_bags, heavy, s);
+          break;
+        case 1:
+          if (borders) launch_buckets<1, true>(t, c, d_keys, n, d_offsets, n_bags, heavy, s);
+          else launch_buckets<1, false>(t, c, d_keys, n, d_offsets, n_bags, heavy, s);
+          break;
+        case 2: launch_buckets<2, false>(t, c, d_keys, n, d_offsets, n_bags, heavy, s); break;
+        default: launch_buckets<3, false>(t, c, d_keys, n, d_offsets, n_bags, heavy, s); break;
       }
     } else {
-      const SortPlan plan = sort_plan(n, t->dedup_mode != 2 && t->serial < t->full_until);
+      const SortPlan plan = sort_plan(n, t->dedup_mode < 2 && t->serial < t->full_until);
       u64* kcur = t->w<u64>(L.keys_a);
       u64* kalt = t->w<u64>(L.keys_b);
       u64* pcur = t->w<u64>(L.idx_a);
@@ -794,6 +826,8 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   t->plain_serial = 0;
   t->mean_pooling = false;
   t->lookup_serial = 0;
+  t->bunched = false;
+  t->borders_from = 0;
   t->report_seen = 0;
   t->strikes = 0;
   t->plain_until = 0;
@@ -809,9 +843,10 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   }
   *t->report = 0;
   {
-    // HPS_DEDUP=radix / bucket pins the dedup to one of its two forms (comparison runs, tests)
+    // HPS_DEDUP=radix / bucket / borders pins the dedup to one of its forms (comparison runs, tests)
     const char* mode = std::getenv("HPS_DEDUP");
-    t->dedup_mode = !mode ? 0 : std::strcmp(mode, "radix") == 0 ? 1 : std::strcmp(mode, "bucket") == 0 ? 2 : 0;
+    t->dedup_mode = !mode ? 0 : std::strcmp(mode, "radix") == 0 ? 1 : std::strcmp(mode, "bucket") == 0 ? 2
+                    : std::strcmp(mode, "borders") == 0 ? 3 : 0;
   }
 
   t->lookup_new_cap = kNewLdsCap;
@@ -1102,10 +1137,11 @@ hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_invers
     u32* by_heavy = d_inverse_out ? t->w<u32>(t->wl.by_heavy) : nullptr;
     const u32* start = t->w<u32>(C.bucket_start);
     const u32* count = t->w<u32>(C.count);
-    order_uniques<<<cx.plan.n_nat, kOrderThreads, 0, s>>>(t->w<u64>(C.uniq), start, count, cx.plan.n_nat, t->ctx(c), t->view.st,
+    const u64* border = cx.borders ? t->w<u64>(C.border) : nullptr;
+    order_uniques<<<cx.plan.n_nat, kOrderThreads, 0, s>>>(t->w<u64>(C.uniq), start, count, cx.plan.n_nat, border, t->ctx(c), t->view.st,
                                                           local_rank, bucket_total);
     emit_uniques<<<cx.plan.n_nat, kOrderThreads, 0, s>>>(t->w<u64>(C.uniq), start, count, t->w<u32>(C.upos), cx.plan.n_nat,
-                                                         t->ctx(c), t->view.st, local_rank, bucket_total, d_uniq_out, by_pos, by_heavy);
+                                                         border, t->ctx(c), t->view.st, local_rank, bucket_total, d_uniq_out, by_pos, by_heavy);
     if (d_inverse_out)
       launch_spread(t->w<u32>(C.code), t->w<uint16_t>(C.from), (u32)n, cx.plan.n_tiles, by_pos, by_heavy,
                     reinterpret_cast<u32*>(d_inverse_out), s);

@@ -7,6 +7,7 @@
 // and their occurrences need no grouping.  Buckets 0 .. n_nat-1 are in key order, the heavy
 // ones follow in the order of the hint.  Three launches (two for few tiles):
 //
+//   sample_borders   (only where the keys bunch) the borders of buckets of equal shares;
 //   bucket_count     a tile of consecutive occurrences per block: bucket of every key (id16), counts
 //                    per bucket (hist[tile][bucket]); further blocks note which bag every tile
 //                    starts in;
@@ -55,6 +56,57 @@ __device__ __forceinline__ KeyRange bucket_range(u64 lo, u64 hi, u32 n_nat) {
   r.mult = r.direct ? 0u : (u32)(((u64)n_nat << 32) / ((r.span >> r.pre) + 1));
   return r;
 }
+
+// Sampled borders, for keys that bunch in parts of their range (raw ids, whose frequent ones are often
+// neighbours): bucket b holds the keys from border[b - 1] up to border[b], the quantiles of
+// evenly spaced samples, so that every bucket gets about the same share wherever the keys lie.  n_nat - 1 borders in ascending order, some perhaps equal (a frequent key).
+// Eight samples a bucket: one of four times the mean, which is what LDS holds in the worst case (2^19
+// occurrences in 1024 buckets), has a chance of about 1e-9.
+constexpr u64 kBorderMaxKeys = 1u << 19;
+constexpr u32 kMaxBorders = 1024;
+constexpr u32 border_samples(u32 max_nat) { return 8 * max_nat; }
+__device__ __forceinline__ u32 bucket_by_border(u64 key, const u64* border, u32 n_borders) {
+  u32 at = 0;
+#pragma unroll
+  for (u32 step = kMaxBorders / 2; step; step >>= 1)
+    if (at + step <= n_borders && border[at + step - 1] <= key) at += step;
+  return at;
+}
+static_assert(kMaxBorders / 2 * 2 - 1 >= kMaxBorders - 1, "the steps add up to the most borders there are");
+// Whether a key lies in natural bucket c (border == null: equal parts of the range).
+__device__ __forceinline__ bool in_bucket(u64 key, u32 c, const KeyRange& r, const u64* border, u32 n_nat) {
+  if (!border) return bucket_of(key, r) == c;
+  return (c == 0 || border[c - 1] <= key) && (c + 1 == n_nat || key < border[c]);
+}
+
+// Puts the borders down.  A block holds all samples in LDS and ranks 64 of them, one per lane of each
+// wave, against a sixteenth of all per wave (every lane reads the same word: no conflicts); equal keys
+// go by their number.  The sample of rank r is border b where b * SAMPLES / n_nat == r.  Ranking takes SAMPLES
+// squared comparisons: 28 us for 8192 samples, 9 for the 2048 of up to 2^16 occurrences.
+constexpr int kBorderThreads = 1024;
+template <u32 SAMPLES>
+__global__ void __launch_bounds__(kBorderThreads)
+sample_borders(const u64* __restrict__ keys, u32 n, u32 n_nat, u64* __restrict__ border) {
+  constexpr u32 kPart = SAMPLES / (kBorderThreads / kWave);
+  __shared__ u64 key[SAMPLES];
+  __shared__ u32 rank[kWave];
+#pragma unroll
+  for (u32 j = threadIdx.x; j < SAMPLES; j += kBorderThreads) key[j] = keys[(u64)j * n / SAMPLES];
+  if (threadIdx.x < kWave) rank[threadIdx.x] = 0;
+  __syncthreads();
+  const u32 me = blockIdx.x * kWave + lane_id(), first = threadIdx.x / kWave * kPart;
+  const u64 mine = key[me];
+  u32 before = 0;
+#pragma unroll 8
+  for (u32 j = first; j < first + kPart; ++j) before += key[j] < mine || (key[j] == mine && j < me) ? 1u : 0u;
+  atomicAdd(&rank[lane_id()], before);
+  __syncthreads();
+  if (threadIdx.x < kWave) {
+    const u32 r = rank[threadIdx.x], b = (r * n_nat + SAMPLES - 1) / SAMPLES;
+    if (b >= 1 && b < n_nat && b * SAMPLES / n_nat == r) border[b - 1] = mine;
+  }
+}
+
 __device__ __forceinline__ u32 key_hash(u64 key) {
   return (u32)((key * 0x9E3779B97F4A7C15ull) >> 32);
 }
@@ -99,9 +151,10 @@ static_assert(kHeavySlots == 1 << 12, "a slot is the top 12 bits of the hash");
 // first plan.n_tiles blocks; the blocks behind them look through the bag offsets and leave in
 // tile_bag[t] the bag that holds occurrence t * tile (offsets == null: every occurrence is its
 // own bag, nothing to do).  Block 0 also resets the pull context.
-template <int THREADS, int ITEMS, int MAX_BUCKETS>
+// BORDERS: by sampled borders.
+template <int THREADS, int ITEMS, int MAX_BUCKETS, bool BORDERS>
 __global__ void __launch_bounds__(THREADS, 8)
-bucket_count(const u64* __restrict__ keys, u32 n, BucketPlan plan, PullCtx* __restrict__ ctx,
+bucket_count(const u64* __restrict__ keys, u32 n, BucketPlan plan, const u64* __restrict__ border, PullCtx* __restrict__ ctx,
              const i32* __restrict__ offsets, u32 n_bags, u32* __restrict__ tile_bag,
              const HeavyRaw* __restrict__ heavy, uint16_t* __restrict__ id16, uint16_t* __restrict__ hist) {
   constexpr u32 kTile = THREADS * ITEMS;
@@ -117,20 +170,25 @@ bucket_count(const u64* __restrict__ keys, u32 n, BucketPlan plan, PullCtx* __re
   __shared__ HeavyLds hv;
   __shared__ u64 s_lo[THREADS / kWave], s_hi[THREADS / kWave];
   __shared__ KeyRange s_range;
+  __shared__ u64 s_border[BORDERS ? kMaxBorders : 1];
   // the tile is requested before anything waits for the samples and the list
   const u32 base = blockIdx.x * kTile;
   u64 key[ITEMS];
 #pragma unroll
   for (int k = 0; k < ITEMS; ++k) key[k] = keys[min(base + k * THREADS + threadIdx.x, n - 1)];
   const u32 n_heavy = min(heavy->count, plan.max_heavy);
-  sample_key_range<THREADS>(keys, n, s_lo, s_hi);
+  if (BORDERS) {
+    for (u32 b = threadIdx.x; b + 1 < plan.n_nat; b += THREADS) s_border[b] = border[b];
+  } else {
+    sample_key_range<THREADS>(keys, n, s_lo, s_hi);
+  }
   heavy_copy<THREADS>(hv, heavy, n_heavy);
   const u32 n_buckets = plan.n_nat + n_heavy;
   for (u32 b = threadIdx.x; b < n_buckets; b += THREADS) h[b] = 0;
-  if (blockIdx.x == 0) reset_ctx(ctx, n, 1u, n_heavy);
+  if (blockIdx.x == 0) reset_ctx(ctx, n, BORDERS ? 2u : 1u, n_heavy);
   __syncthreads();
   heavy_index<THREADS>(hv, n_heavy);
-  if (threadIdx.x == 0) {
+  if (!BORDERS && threadIdx.x == 0) {
     u64 lo, hi;
     sampled_ends<THREADS>(s_lo, s_hi, &lo, &hi);
     s_range = bucket_range(lo, hi, plan.n_nat);
@@ -142,7 +200,7 @@ bucket_count(const u64* __restrict__ keys, u32 n, BucketPlan plan, PullCtx* __re
   for (int k = 0; k < ITEMS; ++k) {
     const u32 i = base + k * THREADS + threadIdx.x;
     if (i < n) {
-      u32 id = bucket_of(key[k], range);
+      u32 id = BORDERS ? bucket_by_border(key[k], s_border, plan.n_nat - 1) : bucket_of(key[k], range);
       if (n_heavy) {
         const u32 at = heavy_find(hv, key[k]);
         if (at != kNoHeavy) id = plan.n_nat + at;

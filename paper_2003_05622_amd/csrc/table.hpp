@@ -187,7 +187,7 @@ struct OftenLists {
   u32 heavy_min;
   HeavyRaw* heavy_next; // the list the next lookup will fill: emptied
   // Host memory (or null) that receives serial | flags << 32 about the dedup before this
-  // lookup: kReportBucket = it took the bucket form, kReportSlow = and more than 1/8 of
+  // lookup: kReportBucket = it took the bucket form, kReportBorders = it did, by sampled borders, kReportSlow = and more than 1/8 of
   // the occurrences lay in buckets that had to be ordered through global memory,
   // kReportOneKey = most of them in buckets that one key fills at least half of (keys
   // that turned frequent without warning, which the next hint will list; otherwise the
@@ -198,7 +198,7 @@ struct OftenLists {
   unsigned long long* report;
   u32 serial;
 };
-constexpr u32 kReportBucket = 1, kReportSlow = 2, kReportOneKey = 4, kReportMixed = 8;
+constexpr u32 kReportBucket = 1, kReportSlow = 2, kReportOneKey = 4, kReportMixed = 8, kReportBorders = 16;
 
 // "Updated since the last dirty dump" is kept in the sign bit of a row's first
 // accumulator element: accumulators are sums of squares, never negative, so the bit
@@ -537,7 +537,7 @@ pull_lookup(TableView t, u64* __restrict__ keys, u32* __restrict__ seg_off, Uniq
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     often.heavy_next->count = 0;
     if (often.report) {
-      const u32 flags = (ctx->by_id ? kReportBucket : 0u) | ((u64)ctx->n_slow * 8 > ctx->n_total ? kReportSlow : 0u) |
+      const u32 flags = (ctx->by_id == 1 ? kReportBucket : ctx->by_id ? kReportBorders : 0u) | ((u64)ctx->n_slow * 8 > ctx->n_total ? kReportSlow : 0u) |
                         ((u64)ctx->n_slow_one_key * 2 >= ctx->n_slow ? kReportOneKey : 0u) |
                         (!ctx->by_id && ctx->n_evidence > kMaxEvidence ? kReportMixed : 0u);
       __hip_atomic_store(often.report, (unsigned long long)often.serial | ((unsigned long long)flags << 32),

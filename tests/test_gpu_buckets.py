@@ -66,3 +66,36 @@ def test_shapes(n, bags, monkeypatch):
         assert st.error == 0 and st.size == ot.size and st.last_n_unique == ou.size
     sample = np.unique(rng.choice(pool, size=min(2000, pool.size)))
     close(gt.get(dev(sample))[1].cpu().numpy(), ot.get(sample)[1], "accumulators")
+
+
+# the sampled borders: mini-batches below and above the number of samples, both size classes that use them (up to
+# 2^16 and up to 2^19 occurrences), the first size beyond; keys the equal parts of a range cannot deal out
+@pytest.mark.parametrize("n", [1, 255, 8191, 20_000, 65_536, 65_537, 1 << 19, (1 << 19) + 1])
+@pytest.mark.parametrize("form", ["borders", "auto"])
+def test_bunched_keys(n, form, monkeypatch):
+    monkeypatch.setenv("HPS_DEDUP", form)
+    rng = np.random.default_rng(n)
+    gt = hps.HpsTable(8 * n + 100, 4, n, n, lr=0.05)
+    ot = oracle.OracleTable(8 * n + 100, 4, lr=0.05)
+    offsets = np.arange(n + 1, dtype=np.int32)
+    # long-tailed raw ids (half of all keys within a thousandth of the range), two crowded places at the
+    # ends of the 64 bits, one key over and over, all keys apart
+    kinds = [lambda: np.minimum(rng.pareto(1.0, size=n) * 100.0, 1e15).astype(np.uint64),
+             lambda: np.where(rng.random(n) < 0.5, rng.integers(0, n + 1, size=n), -2 - rng.integers(0, n + 1, size=n)).astype(np.int64).view(np.uint64),
+             lambda: np.full(n, 77, np.uint64),
+             lambda: rng.permutation(n).astype(np.uint64)]
+    for step, kind in enumerate([0, 0, 0, 0, 0, 0, 1, 2, 3, 0, 1]):
+        keys = kinds[kind]()
+        gt.pull(dev(keys), torch.from_numpy(offsets).cuda(), n, 1)
+        ot.pull(keys, offsets)
+        uniq, inv = gt.last_unique()
+        ou, oi = ot.last_unique()
+        assert np.array_equal(uniq.cpu().numpy().view(np.uint64), ou), "unique keys, step %d" % step
+        assert np.array_equal(inv.cpu().numpy(), oi), "ranks, step %d" % step
+        grads = (rng.integers(-8, 9, size=(n, 4)) / 4096).astype(np.float32)
+        gt.push(torch.from_numpy(grads).cuda())
+        ot.push(grads)
+        st = gt.stats()
+        assert st.error == 0 and st.size == ot.size and st.last_n_unique == ou.size
+    sample = ou[:: max(1, ou.size // 2000)]
+    close(gt.get(dev(sample))[1].cpu().numpy(), ot.get(sample)[1], "accumulators")
