@@ -87,12 +87,11 @@ def host_description():
 
 STAGE_BITS = {"dedup": 0b00011, "lookup": 0b00100, "pool": 0b01000, "push": 0b10000}
 STAGE_KERNELS = {
-    "dedup": "bucket_count, scan_tiles, scatter_pass (once or twice, with digit_count and "
-             "scan_tiles between), region_borders, region_sort, region_emit (a table's first "
-             "two dedups, and very large ones: sort_prepare, n_pass x onesweep_pass, "
-             "unique_emit, fix_mixed_runs, unique_emit)",
-    "lookup": "lookup_keys<0>, insert_missing",
-    "pool": "pool_bags",
+    "dedup": "bucket_count, scan_buckets, bucket_scatter, group_bucket (a table's first two "
+             "dedups, and very large ones: sort_prepare, n_pass x onesweep_pass, unique_emit, "
+             "fix_mixed_runs, unique_emit)",
+    "lookup": "pull_lookup, pull_missing",
+    "pool": "spread, pool_bags",
     "push": "push_main (short | medium | chunk roles)",
 }
 

@@ -253,7 +253,7 @@ hps_status hps_accumulate(hps_table* t, const uint64_t* d_keys, uint64_t n, cons
  * under HIP graph capture, tight serving loops, harnesses that forbid allocation): the same
  * operation as hps_accumulate, with the call's scratch data (the sorted pairs, the unique keys,
  * their rows, the work lists) in a device array that is part of the library's code object
- * instead of the table's workspace -- 10 MiB per GPU the library runs on, held until the
+ * instead of the table's workspace -- 16 MiB per GPU the library runs on, held until the
  * process ends.  The call allocates nothing, on the device or through the HIP runtime.
  *   n <= HPS_STATIC_MAX_KEYS, else HPS_EINVAL; other arguments and results as hps_accumulate.
  * All tables of a GPU share that GPU's array, and a call leaves its contents behind: the call
