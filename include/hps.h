@@ -43,9 +43,10 @@
  *     "prepared" (its key dedup done ahead of time, see hps_prepare); the workspace
  *     holds both contexts.
  *   - Calls that touch the table (insert, pull, pull_prepared, push, get, dump) must
- *     be issued on one stream at a time (or be ordered by the caller).  hps_prepare
- *     does not touch the table and may run on another stream; the library orders it
- *     against the calls that share its buffers with HIP events.
+ *     be issued on one stream at a time (or be ordered by the caller).  hps_prepare and
+ *     hps_last_unique do not touch the table and may run on other streams; the library orders
+ *     them against the calls that share their buffers with HIP events (hps_last_unique not
+ *     while its stream is being captured: a replay is ordered by the caller).
  *   - Do not capture hps_prepare / hps_pull / hps_accumulate into a HIP graph for replay:
  *     three things about a dedup are chosen on the host when the call is made and would be
  *     frozen by a capture: which of the three lists of frequent keys its kernels read and
@@ -267,7 +268,8 @@ hps_status hps_accumulate_static(hps_table* t, const uint64_t* d_keys, uint64_t 
 /* Section 3 "union of the referenced parameters": copies the outstanding pull's
  * ascending unique keys (d_uniq_out, room for n_keys) and per-occurrence ranks
  * (d_inverse_out [n_keys] int32, uniq[inverse[i]] == keys[i]); either may be NULL.
- * The unique count is hps_stats().last_n_unique. */
+ * The unique count is hps_stats().last_n_unique.  On any stream: it waits for the
+ * mini-batch's dedup, and the next dedup into the same buffers waits for it. */
 hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_inverse_out,
                            void* stream);
 

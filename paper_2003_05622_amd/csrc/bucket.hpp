@@ -87,41 +87,33 @@ __device__ bool slow_radix_pass(const u64* ksrc, const u64* psrc, u64* kdst, u64
 }
 static_assert(kRadix <= 256, "a digit per thread of the smallest block");
 
-// Orders the pairs in [a, b) of (skeys, spay) by full key, equal keys keeping their order.  The
-// passes alternate between two scratch arrays of the same shape; *kres / *pres tell
-// where the result is (the source itself if all keys were equal).
+// Orders the pairs in [a, b) of (keys, pay) by full key, equal keys keeping their order.  The passes go
+// back and forth between them and a second pair of arrays; afterwards keys / pay are the pair that holds the result.
 template <int THREADS>
-__device__ void slow_sort(const u64* skeys, const u64* spay, u64* ka, u64* pa, u64* kb,
-                          u64* pb, u32 a, u32 b, SlowLds<THREADS>& L, const u64** kres,
-                          const u64** pres) {
-  const u64 *kc = skeys, *pc = spay;
-  u64 *kd = ka, *pd = pa;
+__device__ void slow_sort(u64*& keys, u64*& pay, u64* keys2, u64* pay2, u32 a, u32 b, SlowLds<THREADS>& L) {
   for (int shift = 0; shift < 64; shift += kRadixBits) {
-    if (slow_radix_pass<THREADS>(kc, pc, kd, pd, a, b, shift, L)) {
-      kc = kd; pc = pd;
-      kd = kd == ka ? kb : ka;
-      pd = pd == pa ? pb : pa;
+    if (slow_radix_pass<THREADS>(keys, pay, keys2, pay2, a, b, shift, L)) {
+      u64* x = keys; keys = keys2; keys2 = x;
+      x = pay; pay = pay2; pay2 = x;
     }
     __syncthreads();
   }
-  *kres = kc;
-  *pres = pc;
 }
 
-// Scratch of the slow way: three (key, payload) arrays' worth beside the dealt-out keys.
+// Scratch of the slow way beside the dealt-out keys, which nothing reads after it.
 struct SlowScratch {
-  u64 *pay, *ka, *pa, *kb, *pb;
+  u64 *pay, *keys2, *pay2;
 };
 
 template <int THREADS>
-__device__ void group_slow(const u64* __restrict__ keys, u32 start, u32 end, u64* __restrict__ uniq,
+__device__ void group_slow(u64* keys, u32 start, u32 end, u64* __restrict__ uniq,
                            u32* __restrict__ seg_off, u32* __restrict__ bags, u32* __restrict__ upos,
                            u32* __restrict__ count, const SlowScratch& S, PullCtx* __restrict__ ctx, SlowLds<THREADS>& L) {
   const u32 tid = threadIdx.x;
   for (u32 p = start + tid; p < end; p += THREADS) S.pay[p] = (u64)bags[p] | ((u64)p << 32);
   __syncthreads();
-  const u64 *sk, *sp;
-  slow_sort<THREADS>(keys, S.pay, S.ka, S.pa, S.kb, S.pb, start, end, L, &sk, &sp);
+  u64 *sk = keys, *sp = S.pay;
+  slow_sort<THREADS>(sk, sp, S.keys2, S.pay2, start, end, L);
   if (tid == 0) {
     // For the host's choice of the next dedups' form: how much went this way, and how much
     // of that because ONE key fills the bucket (then the sorted bucket's middle element is
@@ -179,10 +171,10 @@ struct GroupLds {
 };
 
 // One natural bucket per block: bucket_start[blockIdx.x] ...  keys / bags: as dealt out; bags are
-// regrouped in place.  ORDERED: how occurrences are ranked (sort.hpp: digit_rank).
+// regrouped in place, keys may be overwritten.  ORDERED: how occurrences are ranked (sort.hpp: digit_rank).
 template <int THREADS, bool ORDERED>
 __global__ void __launch_bounds__(THREADS, 8)
-group_bucket(const u64* __restrict__ keys, const u32* __restrict__ bucket_start, u64* __restrict__ uniq,
+group_bucket(u64* keys, const u32* __restrict__ bucket_start, u64* __restrict__ uniq,
              u32* __restrict__ seg_off, u32* __restrict__ bags, u32* __restrict__ upos, u32* __restrict__ count,
              SlowScratch S, PullCtx* __restrict__ ctx, TableState* __restrict__ st) {
   typedef GroupLds<THREADS> Lds;

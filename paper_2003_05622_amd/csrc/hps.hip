@@ -178,9 +178,10 @@ struct ContextLayout {
 };
 
 struct WorkspaceLayout {
-  size_t keys_a, keys_b, keys_c, idx_a, idx_b, idx_c, hist, prefix, total, tile_bag, heavy_raw, ghist,
+  size_t keys_a, keys_b, idx_a, idx_b, hist, prefix, total, tile_bag, heavy_raw, ghist,
       tickets, tile_rows, group_rows, head_rows, head_groups, evidence, bag_of, id16, by_pos, by_heavy, row_of,
-      bucket_total, med_list, arrived, chunk_items, partials, end;
+      med_list, arrived, chunk_items, partials, end;
+  size_t local_rank, rank_by_pos, rank_by_heavy, bucket_total;     // hps_last_unique's own
   ContextLayout c[2];
   uint64_t max_long, max_items, sort_tiles, head_tiles;
 };
@@ -201,10 +202,8 @@ WorkspaceLayout workspace_layout(uint64_t n, uint64_t bags, uint32_t dim) {
   size_t o = 0;
   L.keys_a = o;      o = align_up(o + n1 * 8);
   L.keys_b = o;      o = align_up(o + n1 * 8);
-  L.keys_c = o;      o = align_up(o + n1 * 8);    // scratch of a bucket ordered the slow way
   L.idx_a = o;       o = align_up(o + n1 * 8);    // payloads: occurrence index | bag << 32
   L.idx_b = o;       o = align_up(o + n1 * 8);
-  L.idx_c = o;       o = align_up(o + n1 * 8);
   L.hist = o;        o = align_up(o + max_counts(n1) * 2);    // bucket form: counts per (tile, bucket)
   L.prefix = o;      o = align_up(o + max_counts(n1) * 4);    // ... and those of the tiles before
   L.total = o;       o = align_up(o + buckets * 4);
@@ -236,7 +235,10 @@ WorkspaceLayout workspace_layout(uint64_t n, uint64_t bags, uint32_t dim) {
   L.by_pos = o;      o = align_up(o + n1 * 4);      // row of the key at every position
   L.by_heavy = o;    o = align_up(o + (kMaxHeavy + 1) * 4);
   L.row_of = o;      o = align_up(o + n1 * 4);      // row of every occurrence
-  L.bucket_total = o; o = align_up(o + buckets * 4);
+  L.local_rank = o;    o = align_up(o + n1 * 4);
+  L.rank_by_pos = o;   o = align_up(o + n1 * 4);
+  L.rank_by_heavy = o; o = align_up(o + (kMaxHeavy + 1) * 4);
+  L.bucket_total = o;  o = align_up(o + buckets * 4);
   L.med_list = o;    o = align_up(o + (n1 / (kShortSeg + 1) + kMaxHeavy + 64) * 4);
   L.arrived = o;     o = align_up(o + L.max_long * 4);
   L.chunk_items = o; o = align_up(o + L.max_items * 16);
@@ -343,14 +345,16 @@ struct hps_table {
     bool buckets;         // its dedup took the bucket form ...
     bool borders;         // ... by sampled borders
     BucketPlan plan;      // ... with these sizes ...
-    u32 heavy_slot;       // ... and this list of frequent keys (common.hpp: HeavyRing)
     hipEvent_t ready;     // recorded after the dedup kernels
     hipEvent_t released;  // recorded after the push that used the context
     bool ready_set, released_set;
+    bool listed;          // hps_last_unique has read this context since its dedup
   } cx[2];
   int current, prepared;
   hipEvent_t scratch_free;   // the last dedup's end: the sort scratch is shared
   bool scratch_set;
+  hipEvent_t listing;        // the last hps_last_unique's end: its scratch, and the context it read
+  bool listing_set;
   uint64_t last_n_keys;      // of the most recent pull, for hps_stats
 
   // stage timing (measurement only)
@@ -469,6 +473,8 @@ static void launch_buckets(hps_table* t, int c, const uint64_t* d_keys, u32 n, c
   u32* tile_bag = t->w<u32>(L.tile_bag);
   u32* bucket_start = t->w<u32>(C.bucket_start);
   u64* keys = t->w<u64>(L.keys_a);
+  u64* uniq = t->w<u64>(C.uniq);
+  u32* seg_off = t->w<u32>(C.seg_off);
   u32* bags = t->w<u32>(C.bags);
   const unsigned bag_blocks = d_offsets ? grid_for(n_bags, kThreads * 4, 256) : 0;
   u64* border = t->w<u64>(C.border);
@@ -489,15 +495,15 @@ static void launch_buckets(hps_table* t, int c, const uint64_t* d_keys, u32 n, c
 #define HPS_ORDERED(ORDERED)                                                                                      \
   do {                                                                                                            \
     bucket_scatter<kThreads, kItems, kMaxBuckets[K], ORDERED, kDirect><<<plan.n_tiles, kThreads, 0, s>>>(         \
-        d_keys, id16, d_offsets, n_bags, tile_bag, n, plan, ctx, hist, prefix, t->w<u32>(L.total), bucket_start, keys, bags,          \
-        t->w<u32>(C.code), t->w<uint16_t>(C.from));                                                               \
+        d_keys, id16, d_offsets, n_bags, tile_bag, n, plan, ctx, hist, prefix, t->w<u32>(L.total), heavy, bucket_start, uniq, seg_off,  \
+        keys, bags, t->w<u32>(C.code), t->w<uint16_t>(C.from));                                                   \
     stage_mark(t, HPS_STAGE_SORT, s);                                                                             \
     stage_mark(t, HPS_STAGE_UNIQUE, s);                                                                           \
     group_bucket<kGroup, ORDERED><<<plan.n_nat, kGroup, 0, s>>>(                                                  \
-        keys, bucket_start, t->w<u64>(C.uniq), t->w<u32>(C.seg_off), bags, t->w<u32>(C.upos),                     \
+        keys, bucket_start, uniq, seg_off, bags, t->w<u32>(C.upos),                                               \
         t->w<u32>(C.count), slow, ctx, t->view.st);                                                               \
   } while (0)
-  const SlowScratch slow = {t->w<u64>(L.idx_a), t->w<u64>(L.keys_b), t->w<u64>(L.idx_b), t->w<u64>(L.keys_c), t->w<u64>(L.idx_c)};
+  const SlowScratch slow = {t->w<u64>(L.idx_a), t->w<u64>(L.keys_b), t->w<u64>(L.idx_b)};
   if (t->ordered_rank) HPS_ORDERED(true);
   else HPS_ORDERED(false);
 #undef HPS_ORDERED
@@ -566,8 +572,7 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
     if (buckets) {
       t->cx[c].plan = bucket_plan(n);
       // the most recent list of frequent keys that is certainly complete (common.hpp)
-      t->cx[c].heavy_slot = (u32)((t->lookup_serial + kHeavyRing - 1) % kHeavyRing);
-      const HeavyRaw* heavy = &t->w<HeavyRing>(L.heavy_raw)->raw[t->cx[c].heavy_slot];
+      const HeavyRaw* heavy = &t->w<HeavyRing>(L.heavy_raw)->raw[(t->lookup_serial + kHeavyRing - 1) % kHeavyRing];
       switch (bucket_class(n)) {
         case 0:
           if (borders) launch_buckets<0, true>(t, c, d_keys, n, d_offsets, n_bags, heavy, s);
@@ -643,7 +648,6 @@ static RowsByPosition rows_by_position_args(const hps_table* t, int c, bool pull
   out.upos = pull && cx.buckets ? t->w<u32>(t->wl.c[c].upos) : nullptr;
   out.by_pos = t->w<u32>(t->wl.by_pos);
   out.by_heavy = t->w<u32>(t->wl.by_heavy);
-  out.heavy_keys = cx.buckets ? t->w<HeavyRing>(t->wl.heavy_raw)->raw[cx.heavy_slot].keys : nullptr;
   return out;
 }
 
@@ -808,12 +812,14 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   t->current = t->prepared = -1;
   t->last_n_keys = 0;
   t->scratch_set = false;
-  bool events_ok = hipEventCreateWithFlags(&t->scratch_free, hipEventDisableTiming) == hipSuccess;
+  t->listing_set = false;
+  bool events_ok = hipEventCreateWithFlags(&t->scratch_free, hipEventDisableTiming) == hipSuccess &&
+                   hipEventCreateWithFlags(&t->listing, hipEventDisableTiming) == hipSuccess;
   for (int k = 0; k < 2; ++k) {
     t->cx[k].n_keys = t->cx[k].n_bags = 0;
     t->cx[k].d_offsets = nullptr;
     t->cx[k].buckets = false;
-    t->cx[k].ready_set = t->cx[k].released_set = false;
+    t->cx[k].ready_set = t->cx[k].released_set = t->cx[k].listed = false;
     events_ok = events_ok &&
                 hipEventCreateWithFlags(&t->cx[k].ready, hipEventDisableTiming) == hipSuccess &&
                 hipEventCreateWithFlags(&t->cx[k].released, hipEventDisableTiming) == hipSuccess;
@@ -873,6 +879,7 @@ hps_status hps_destroy(hps_table* t) {
     for (hipEvent_t e : t->ev_pool[i]) (void)hipEventDestroy(e);
   // (a table whose creation failed half way holds null handles)
   if (t->scratch_free) (void)hipEventDestroy(t->scratch_free);
+  if (t->listing) (void)hipEventDestroy(t->listing);
   for (int k = 0; k < 2; ++k) {
     if (t->cx[k].ready) (void)hipEventDestroy(t->cx[k].ready);
     if (t->cx[k].released) (void)hipEventDestroy(t->cx[k].released);
@@ -920,6 +927,13 @@ static bool mini_batch_ok(const hps_table* t, const uint64_t* d_keys, uint64_t n
   return (uintptr_t)d_keys % 8 == 0 && (uintptr_t)d_offsets % 4 == 0;
 }
 
+// Orders a dedup into context c after the hps_last_unique that read what the context held before.
+static bool after_listing(hps_table* t, int c, hipStream_t s) {
+  if (t->cx[c].listed && hipStreamWaitEvent(s, t->listing, 0) != hipSuccess) return false;
+  t->cx[c].listed = false;
+  return true;
+}
+
 hps_status hps_prepare(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
                        const int32_t* d_offsets, uint32_t n_examples, uint32_t n_slots,
                        void* stream) {
@@ -933,6 +947,7 @@ hps_status hps_prepare(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
   // (the sort scratch is shared); both may have run on other streams
   if (cx.released_set && hipStreamWaitEvent(s, cx.released, 0) != hipSuccess) return HPS_EDEVICE;
   if (t->scratch_set && hipStreamWaitEvent(s, t->scratch_free, 0) != hipSuccess) return HPS_EDEVICE;
+  if (!after_listing(t, c, s)) return HPS_EDEVICE;
 
   launch_dedup(t, c, d_keys, n, d_offsets, (u32)n_bags, s);
   if (!launch_ok()) return HPS_EDEVICE;
@@ -1056,6 +1071,7 @@ hps_status hps_accumulate(hps_table* t, const uint64_t* d_keys, uint64_t n, cons
   for (int k = 0; k < 2; ++k)      // after the last push of either context (shared work lists, table rows)
     if (t->cx[k].released_set && hipStreamWaitEvent(s, t->cx[k].released, 0) != hipSuccess) return HPS_EDEVICE;
   if (t->scratch_set && hipStreamWaitEvent(s, t->scratch_free, 0) != hipSuccess) return HPS_EDEVICE;
+  if (!after_listing(t, 0, s)) return HPS_EDEVICE;
   const hps_status rc = accumulate_launches(t, d_keys, n, d_values, s);
   if (rc != HPS_OK) return rc;
   if (hipEventRecord(cx.released, s) != hipSuccess || hipEventRecord(t->scratch_free, s) != hipSuccess)
@@ -1119,22 +1135,18 @@ hps_status hps_accumulate_static(hps_table* t, const uint64_t* d_keys, uint64_t 
   return rc;
 }
 
-hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_inverse_out,
-                           void* stream) {
-  if (!t) return HPS_EINVAL;
-  if (t->current < 0) return HPS_ESTATE;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  const int c = t->current;
-  const ContextLayout& C = t->wl.c[c];
+// The kernels and copies of an hps_last_unique of context c.  They read what its dedup wrote and nothing
+// else, and write scratch of their own.
+static hps_status list_unique(hps_table* t, int c, uint64_t* d_uniq_out, int32_t* d_inverse_out, hipStream_t s) {
+  const WorkspaceLayout& L = t->wl;
+  const ContextLayout& C = L.c[c];
   const hps_table::Context& cx = t->cx[c];
   const uint64_t n = cx.n_keys;
-  if (n == 0 || (!d_uniq_out && !d_inverse_out)) return HPS_OK;
   if (cx.buckets) {
-    // the pooling is done with by_pos, by_heavy and row_of (calls that touch the table follow each other)
-    u32* local_rank = t->w<u32>(t->wl.row_of);
-    u32* bucket_total = t->w<u32>(t->wl.bucket_total);
-    u32* by_pos = d_inverse_out ? t->w<u32>(t->wl.by_pos) : nullptr;
-    u32* by_heavy = d_inverse_out ? t->w<u32>(t->wl.by_heavy) : nullptr;
+    u32* local_rank = t->w<u32>(L.local_rank);
+    u32* bucket_total = t->w<u32>(L.bucket_total);
+    u32* by_pos = d_inverse_out ? t->w<u32>(L.rank_by_pos) : nullptr;
+    u32* by_heavy = d_inverse_out ? t->w<u32>(L.rank_by_heavy) : nullptr;
     const u32* start = t->w<u32>(C.bucket_start);
     const u32* count = t->w<u32>(C.count);
     const u64* border = cx.borders ? t->w<u64>(C.border) : nullptr;
@@ -1155,6 +1167,29 @@ hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_invers
       hipMemcpyAsync(d_inverse_out, t->w<i32>(C.inverse), n * 4, hipMemcpyDeviceToDevice, s) != hipSuccess)
     return HPS_EDEVICE;
   return HPS_OK;
+}
+
+hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_inverse_out,
+                           void* stream) {
+  if (!t) return HPS_EINVAL;
+  if (t->current < 0) return HPS_ESTATE;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  const int c = t->current;
+  hps_table::Context& cx = t->cx[c];
+  if (cx.n_keys == 0 || (!d_uniq_out && !d_inverse_out)) return HPS_OK;
+  // On any stream: after the dedup whose results it lists and after the call before it (the ranks'
+  // scratch); the next dedup into this context waits for it (after_listing).  Events that were recorded outside a
+  // capture cannot be waited for inside one: what is captured here, the caller orders.
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
+  if (capture != hipStreamCaptureStatusNone) return list_unique(t, c, d_uniq_out, d_inverse_out, s);
+  if (hipStreamWaitEvent(s, cx.ready, 0) != hipSuccess) return HPS_EDEVICE;
+  if (t->listing_set && hipStreamWaitEvent(s, t->listing, 0) != hipSuccess) return HPS_EDEVICE;
+  const hps_status rc = list_unique(t, c, d_uniq_out, d_inverse_out, s);
+  if (hipEventRecord(t->listing, s) != hipSuccess) return HPS_EDEVICE;
+  t->listing_set = true;
+  cx.listed = true;
+  return rc;
 }
 
 static hps_status get_impl(hps_table* t, bool zero, const uint64_t* d_keys, uint64_t n, float* d_weights_out,

@@ -266,13 +266,14 @@ scan_buckets(const uint16_t* __restrict__ hist, BucketPlan plan, u32* __restrict
 // occurrences, 2400 buckets: five occurrences a run, 40 bytes of keys, 20 of bags), which start and end
 // in the middle of memory lines.  Neighbouring tiles' runs lie side by side, so tiles that follow each other
 // go to the same XCD (xcd_piece), whose L2 then puts the pieces of a line together before it
-// writes it: 143 -> 107 us (and 46 -> 37 us for spread, which reads the same runs).  Block 0 also writes bucket_start[0 .. n_nat +
-// max_heavy].  DIRECT: scan_buckets was left out, hist holds all there is.
+// writes it: 143 -> 107 us (and 46 -> 37 us for spread, which reads the same runs).  The first tile's block also writes bucket_start[0 .. n_nat +
+// max_heavy] and the heavy keys' entries of uniq and seg_off (bucket.hpp).  DIRECT: scan_buckets was left out, hist holds all there is.
 template <int THREADS, int ITEMS, int MAX_BUCKETS, bool ORDERED, bool DIRECT>
 __global__ void __launch_bounds__(THREADS)
 bucket_scatter(const u64* __restrict__ keys, const uint16_t* __restrict__ id16, const i32* __restrict__ offsets,
                u32 n_bags, const u32* __restrict__ tile_bag, u32 n, BucketPlan plan, PullCtx* __restrict__ ctx,
-               const uint16_t* __restrict__ hist, const u32* __restrict__ prefix, const u32* __restrict__ total, u32* __restrict__ bucket_start,
+               const uint16_t* __restrict__ hist, const u32* __restrict__ prefix, const u32* __restrict__ total,
+               const HeavyRaw* __restrict__ heavy_raw, u32* __restrict__ bucket_start, u64* __restrict__ uniq, u32* __restrict__ seg_off,
                u64* __restrict__ keys_out, u32* __restrict__ bags_out, u32* __restrict__ code,
                uint16_t* __restrict__ from) {
   constexpr u32 kTile = THREADS * ITEMS;
@@ -397,7 +398,12 @@ bucket_scatter(const u64* __restrict__ keys, const uint16_t* __restrict__ id16, 
       for (int q = 0; q < kPer; ++q) {
         const u32 b = kPer * tid + q;
         if (b < n_all) bucket_start[b] = start[q];
-        if (b >= plan.n_nat && in_bucket[q]) atomicAdd(&ctx->uniq_shard[b % kCountShards], 1u);    // a heavy key that occurs
+        if (b >= plan.n_nat && in_bucket[q]) {       // a heavy key that occurs
+          atomicAdd(&ctx->uniq_shard[b % kCountShards], 1u);
+          uniq[start[q]] = heavy_raw->keys[b - plan.n_nat];
+          seg_off[start[q]] = start[q];
+          seg_off[start[q] + 1] = start[q] + in_bucket[q];
+        }
       }
       if (tid == 0) bucket_start[n_all] = all;
     }

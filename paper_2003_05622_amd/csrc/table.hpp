@@ -495,7 +495,6 @@ struct RowsByPosition {
   const u32* upos;       // null (plain form, accumulate): nothing is handed on
   u32* by_pos;
   u32* by_heavy;
-  const u64* heavy_keys; // the heavy keys this dedup went by
 };
 
 __device__ __forceinline__ void rows_by_position(const UniqueSpans& spans, const RowsByPosition& out, u32 c,
@@ -522,7 +521,7 @@ __device__ __forceinline__ void rows_by_position(const UniqueSpans& spans, const
 // (one key per lane: full waves); in between the group goes through its four keys together
 // (search_keys).
 __global__ void __launch_bounds__(kProbeThreads)
-pull_lookup(TableView t, u64* __restrict__ keys, u32* __restrict__ seg_off, UniqueSpans spans,
+pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ seg_off, UniqueSpans spans,
             u32* __restrict__ rows, RowsByPosition out, u32 create, u32 new_cap, OftenLists often) {
   // new_cap <= kNewLdsCap: how much of the block's list of created keys is used (all of it,
   // except in tests of what happens when it is full)
@@ -581,12 +580,7 @@ pull_lookup(TableView t, u64* __restrict__ keys, u32* __restrict__ seg_off, Uniq
         const u32 end = spans.bucket_start[spans.n_spans + h + 1];
         my_len = end - u;
         on = my_len != 0;                      // a key the hint named and the mini-batch does not hold
-        if (on) {
-          my_key = out.heavy_keys[h];
-          keys[u] = my_key;
-          seg_off[u] = u;
-          seg_off[u + 1] = end;
-        }
+        if (on) my_key = keys[u];
       }
     } else if (on) {
       u = first + k;
