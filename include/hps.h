@@ -269,7 +269,8 @@ hps_status hps_accumulate_static(hps_table* t, const uint64_t* d_keys, uint64_t 
  * ascending unique keys (d_uniq_out, room for n_keys) and per-occurrence ranks
  * (d_inverse_out [n_keys] int32, uniq[inverse[i]] == keys[i]); either may be NULL.
  * The unique count is hps_stats().last_n_unique.  On any stream: it waits for the
- * mini-batch's dedup, and the next dedup into the same buffers waits for it. */
+ * mini-batch's dedup, and the next dedup into the same buffers waits for it.  Also after a pull that failed on
+ * the device (HPS_EFULL, HPS_ERESERVED: the reserved key is listed like any other). */
 hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_inverse_out,
                            void* stream);
 

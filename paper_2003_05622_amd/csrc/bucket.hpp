@@ -167,7 +167,7 @@ struct GroupLds {
     SlowLds<THREADS> slow;
   };
   u32 scratch[THREADS / kWave + 1];
-  u32 full;
+  u32 full;          // the bucket goes the slow way after all
 };
 
 // One natural bucket per block: bucket_start[blockIdx.x] ...  keys / bags: as dealt out; bags are
@@ -212,7 +212,8 @@ group_bucket(u64* keys, const u32* __restrict__ bucket_start, u64* __restrict__ 
     for (int r = 0; r < kGroupItems; ++r) {
       slot[r] = __umulhi(key_hash(key[r]), kSlots);
       if (wave_first + r * kWave + lane < cnt && (u32)r < items) {
-        if (key[r] == kEmptyKey) raise_error(st, kErrReserved);      // (stays on a slot, counts for nothing)
+        // (the reserved key marks free slots here: the slow way takes it as the key it is)
+        if (key[r] == kEmptyKey) { raise_error(st, kErrReserved); L.full = 1; }
         else open |= 1u << r;
       }
     }
@@ -321,7 +322,7 @@ constexpr u32 kOrderCells = 4096;
 constexpr u32 kOrderCellMax = 32;
 __global__ void __launch_bounds__(kOrderThreads)
 order_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start, const u32* __restrict__ count,
-              u32 n_nat, const u64* __restrict__ border, const PullCtx* __restrict__ ctx, const TableState* __restrict__ st,
+              u32 n_nat, const u64* __restrict__ border, const PullCtx* __restrict__ ctx,
               u32* __restrict__ local_rank, u32* __restrict__ bucket_total) {
   constexpr int kPer = kOrderCap / kOrderThreads, kWaves = kOrderThreads / kWave;
   __shared__ u64 key[kOrderCap];
@@ -330,7 +331,6 @@ order_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start
   __shared__ u64 s_lo[kWaves], s_hi[kWaves];
   __shared__ u32 scratch[kWaves + 1];
   __shared__ u32 s_n, s_crowded;
-  if (load_error(st) != 0) return;      // (a reserved key among the distinct ones would be taken for padding)
   const u32 tid = threadIdx.x, c = blockIdx.x;
   const u32 start = bucket_start[c], word = count[c], u = word & ~kSlowBucket;
   const bool slow = (word & kSlowBucket) != 0;       // already in order, and maybe too many for LDS
@@ -418,6 +418,7 @@ order_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start
   } else {
     u32 size = 2;
     while (size < n) size <<= 1;
+    // (the reserved key is never among them: it goes the slow way and is in no list of heavy keys)
     for (u32 i = n + tid; i < size; i += kOrderThreads) { key[i] = ~0ull; num[i] = ~0u; }
     for (u32 k = 2; k <= size; k <<= 1) {
       for (u32 j = k >> 1; j > 0; j >>= 1) {
@@ -457,10 +458,9 @@ order_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start
 __global__ void __launch_bounds__(kOrderThreads)
 emit_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start, const u32* __restrict__ count,
              const u32* __restrict__ upos, u32 n_nat, const u64* __restrict__ border, const PullCtx* __restrict__ ctx,
-             const TableState* __restrict__ st, const u32* __restrict__ local_rank, const u32* __restrict__ bucket_total, u64* __restrict__ uniq_out,
+             const u32* __restrict__ local_rank, const u32* __restrict__ bucket_total, u64* __restrict__ uniq_out,
              u32* __restrict__ rank_by_pos, u32* __restrict__ rank_by_heavy) {
   __shared__ u32 scratch[kOrderThreads / kWave + 1];
-  if (load_error(st) != 0) return;
   const u32 tid = threadIdx.x, c = blockIdx.x;
   const u32 start = bucket_start[c], end = bucket_start[c + 1], word = count[c], u = word & ~kSlowBucket;
   u32 mine = 0, base;

@@ -1150,10 +1150,10 @@ static hps_status list_unique(hps_table* t, int c, uint64_t* d_uniq_out, int32_t
     const u32* start = t->w<u32>(C.bucket_start);
     const u32* count = t->w<u32>(C.count);
     const u64* border = cx.borders ? t->w<u64>(C.border) : nullptr;
-    order_uniques<<<cx.plan.n_nat, kOrderThreads, 0, s>>>(t->w<u64>(C.uniq), start, count, cx.plan.n_nat, border, t->ctx(c), t->view.st,
+    order_uniques<<<cx.plan.n_nat, kOrderThreads, 0, s>>>(t->w<u64>(C.uniq), start, count, cx.plan.n_nat, border, t->ctx(c),
                                                           local_rank, bucket_total);
     emit_uniques<<<cx.plan.n_nat, kOrderThreads, 0, s>>>(t->w<u64>(C.uniq), start, count, t->w<u32>(C.upos), cx.plan.n_nat,
-                                                         border, t->ctx(c), t->view.st, local_rank, bucket_total, d_uniq_out, by_pos, by_heavy);
+                                                         border, t->ctx(c), local_rank, bucket_total, d_uniq_out, by_pos, by_heavy);
     if (d_inverse_out)
       launch_spread(t->w<u32>(C.code), t->w<uint16_t>(C.from), (u32)n, cx.plan.n_tiles, by_pos, by_heavy,
                     reinterpret_cast<u32*>(d_inverse_out), s);

@@ -1,5 +1,5 @@
 """hps_last_unique on streams of its own: beside the pull whose keys it lists, beside the push and the next
-pull, and replayed from a captured graph.  Keys and ranks are the oracle's bit for bit; the pushes carry zero
+pull, after a pull that failed on the device, and replayed from a captured graph.  Keys and ranks are the oracle's bit for bit; the pushes carry zero
 gradients, so the rows stay the initial ones and pooled sums stay within the float32 tolerance of the oracle's."""
 import numpy as np
 import pytest
@@ -102,3 +102,37 @@ def test_replayed_from_a_graph(form):
             assert np.array_equal(inv.cpu().numpy(), oi), "ranks, step %d" % step
         gt.push(zero)
     assert gt.stats().error == 0
+
+
+@pytest.mark.parametrize("n", [300, 70_000])
+def test_after_a_pull_that_failed(form, n):
+    """A table with no room for the mini-batch's keys, a mini-batch with the reserved key in it, and one that is pulled
+    while the status is still set: keys and ranks are listed all the same."""
+    rng = np.random.default_rng(n)
+    n_bags, dim = 16, 4
+    gt = hps.HpsTable(max(64, n // 100), dim, n, n_bags)
+    offsets = torch.from_numpy(even_offsets(n, n_bags)).cuda()
+
+    def listed(keys):
+        gt.pull(dev(keys), offsets, n_bags, 1)
+        uniq, inv = gt.last_unique()
+        ou, oi = oracle.dedup(keys)
+        assert gt.stats().last_n_unique == ou.size
+        assert np.array_equal(uniq.cpu().numpy().view(np.uint64), ou) and np.array_equal(inv.cpu().numpy(), oi)
+        return gt.stats().error
+
+    few = synth.mix64(np.arange(30, dtype=np.uint64))
+    for _ in range(3):              # frequent keys that the next steps' hint names
+        assert listed(few[rng.integers(0, 30, size=n)]) == 0
+        gt.push(torch.zeros((n_bags, dim), device="cuda"))
+    full = batch(rng, n, 0)
+    full[: n // 4] = few[0]
+    assert listed(full) == hps.EFULL
+    gt.push(torch.zeros((n_bags, dim), device="cuda"))
+    assert listed(full[::-1].copy()) == hps.EFULL          # (still set: nothing is looked up)
+    gt.clear_error()
+    reserved = few[rng.integers(0, 30, size=n)]
+    reserved[rng.integers(0, n, size=5)] = np.uint64(2**64 - 1)
+    assert listed(reserved) == hps.ERESERVED
+    gt.clear_error()
+    assert gt.stats().size == 30
