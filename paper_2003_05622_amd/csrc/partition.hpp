@@ -262,6 +262,13 @@ scan_buckets(const uint16_t* __restrict__ hist, BucketPlan plan, u32* __restrict
   if (threadIdx.x < kScanBuckets && b < n_buckets) total[b] = all;
 }
 
+// Where a tile lies beside more than kSparseBags bags per thread, nearly all of them empty, its occurrences' bags are
+// found by a search among the bags' starts: going through them all is a round trip to memory per bag and thread
+// (1000 occurrences in 10^6 bags: a step of 899 us, 63 with the search), the search one per halving, of all the
+// thread's occurrences together.  Up to about a hundred bags per thread going through them is as fast or faster
+// (0.2 M occurrences, 512 threads a tile, 32 bags per thread: 107 us and 117 with the search; 64: 119 and 123; 160: 164 and 143).
+constexpr u32 kSparseBags = 96;
+
 // Deals one tile per block out to the buckets.  What bounds it is the write requests of short runs (9.8 M
 // occurrences, 2400 buckets: five occurrences a run, 40 bytes of keys, 20 of bags), which start and end
 // in the middle of memory lines.  Neighbouring tiles' runs lie side by side, so tiles that follow each other
@@ -337,7 +344,8 @@ bucket_scatter(const u64* __restrict__ keys, const uint16_t* __restrict__ id16, 
 #pragma unroll
   for (int q = 0; q < kPer; ++q) first[q * THREADS + tid] = 0;
   __syncthreads();
-  if (offsets) {
+  const bool sparse = bag_end - bag0 > kSparseBags * THREADS;
+  if (offsets && !sparse) {
     for (u32 b = bag0 + 1 + tid; b <= bag_end; b += THREADS) {
       if (bag_lo < bag_hi && bag_lo - base < kTile) mark[bag_lo - base] = b;      // (before the tile: the difference is huge)
       if (b + THREADS <= bag_end) { bag_lo = (u32)offsets[b + THREADS]; bag_hi = (u32)offsets[b + THREADS + 1]; }
@@ -356,7 +364,18 @@ bucket_scatter(const u64* __restrict__ keys, const uint16_t* __restrict__ id16, 
   }
   // bags: the bag of the last mark at or before the element, in this wave or an earlier one
   u32 bag[ITEMS];
-  if (offsets) {
+  if (sparse) {
+    // the last bag that starts at or before the element
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) bag[r] = bag0;
+    for (u32 step = 1u << (31 - __clz((int)(bag_end - bag0))); step; step >>= 1) {
+#pragma unroll
+      for (int r = 0; r < ITEMS; ++r) {
+        const u32 b = bag[r] + step;
+        if (b <= bag_end && offsets[b] <= (i32)(base + wave_first + r * kWave + lane)) bag[r] = b;
+      }
+    }
+  } else if (offsets) {
     u32 carry = 0;
     u32 m[ITEMS];
 #pragma unroll
