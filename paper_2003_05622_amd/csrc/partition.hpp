@@ -107,8 +107,16 @@ sample_borders(const u64* __restrict__ keys, u32 n, u32 n_nat, u64* __restrict__
   }
 }
 
+// Hash for the LDS tables (top bits): the two halves of the key through MurmurHash3's 32-bit finaliser
+// (Appleby; its last shift leaves the top bits alone).  One multiplication would do for ids and for well-mixed keys, but
+// keys that are multiples of some number (ids spread by a multiplication) can meet it with all keys of a
+// bucket in a row: 30 K distinct keys that are multiples of the multiplier's inverse, a step of 236 us, 59 with this;
+// 1 M that are multiples of a sixteenth of it, 334 and 216 us (of the multiplier itself, which one multiplication
+// spreads evenly: 180 and 217).
 __device__ __forceinline__ u32 key_hash(u64 key) {
-  return (u32)((key * 0x9E3779B97F4A7C15ull) >> 32);
+  u32 h = (u32)key ^ (u32)(key >> 32) * 0x9E3779B1u;
+  h = (h ^ h >> 16) * 0x85EBCA6Bu;
+  return (h ^ h >> 13) * 0xC2B2AE35u;
 }
 
 // The heavy keys in LDS: an open-addressing hash from key to its index in the list.

@@ -99,3 +99,26 @@ def test_bunched_keys(n, form, monkeypatch):
         assert st.error == 0 and st.size == ot.size and st.last_n_unique == ou.size
     sample = ou[:: max(1, ou.size // 2000)]
     close(gt.get(dev(sample))[1].cpu().numpy(), ot.get(sample)[1], "accumulators")
+
+
+@pytest.mark.parametrize("n", [30_000, 1_000_000])
+def test_keys_in_arithmetic_progression(n, monkeypatch):
+    """Multiples of a number, as ids spread by a multiplication: they fill their range evenly, so the bucket form
+    suits them, whatever the number -- here the inverse of the golden ratio's 64-bit fraction (a multiplication
+    by that would undo theirs), and the fraction itself with four bits less."""
+    monkeypatch.setenv("HPS_DEDUP", "auto")
+    rng = np.random.default_rng(n)
+    n_bags = n // 8
+    gt = hps.HpsTable(3 * n, 4, n, n_bags)
+    offsets = (torch.arange(n_bags + 1, device="cuda") * n // n_bags).to(torch.int32)
+    for factor in (pow(0x9E3779B97F4A7C15, -1, 2**64), 0x9E3779B97F4A7C1):
+        gt.clear()
+        for step in range(6):
+            keys = rng.permutation(n).astype(np.uint64) * np.uint64(factor)
+            gt.pull(dev(keys), offsets, n_bags, 1)
+            uniq, inv = gt.last_unique()
+            ou, oi = oracle.dedup(keys)
+            assert np.array_equal(uniq.cpu().numpy().view(np.uint64), ou) and np.array_equal(inv.cpu().numpy(), oi)
+            gt.push(torch.zeros((n_bags, 4), device="cuda"))
+            assert gt.stats().error == 0
+    assert gt.stats().n_plain_fallbacks == 0, "taken for keys that do not suit the buckets"
