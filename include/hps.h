@@ -60,13 +60,14 @@
  *     workgroups (counts per tile, a scan, a scatter into buckets; then every bucket's keys are
  *     grouped inside one workgroup).  The lookups report back, into pinned host memory that
  *     nobody waits for, when the keys did not suit that form, and the next dedups then deal
- *     the keys out by sampled borders (up to 2^19 occurrences, if the keys lie bunched) or take
+ *     the keys out by their hashes instead of by their range (if the keys lie unevenly in that; by
+ *     sampled borders where hps_last_unique is in use, up to 2^19 occurrences), or take
  *     the plain form (radix passes with look-back between tiles), sorting by all 64 key
  *     bits if need be: hps_stats().n_plain_fallbacks, .n_full_fallbacks.  What a pull needs of
  *     a dedup is the occurrences grouped by key; the ascending order of the unique keys is
  *     worked out when hps_last_unique asks for it.
  *   - Environment variables, read by hps_create, for tests and comparison runs:
- *     HPS_DEDUP = "radix" | "bucket" | "borders" pins the dedup's form; HPS_RANK = "ballot" ranks the
+ *     HPS_DEDUP = "radix" | "bucket" | "borders" | "hashed" pins the dedup's form; HPS_RANK = "ballot" ranks the
  *     elements of a sort tile with wave ballots even where the GPU's LDS atomics would
  *     serve (the faster way; hps_create checks on every GPU that they answer the lanes of
  *     an instruction in lane order, and uses ballots where they do not);

@@ -11,12 +11,14 @@
 // counted across buckets.  A heavy key's bucket is one group as it stands; its number is its start.
 //
 // Ascending unique keys and ranks (hps_last_unique) are worked out when they are asked for:
-// the buckets are in key order, so order_uniques sorts each bucket's distinct keys (and the
-// heavy keys that lie among them), emit_uniques adds up the buckets before it.
+// where the buckets are in key order, order_uniques sorts each bucket's distinct keys (and the
+// heavy keys that lie among them), emit_uniques adds up the buckets before it.  Of buckets by hash,
+// gather_uniques collects the distinct keys, the plain form's radix passes sort them, and take_ranks
+// notes every key's rank for emit_uniques.
 //
 // Which keys are heavy is a hint (partition.hpp).  Hot keys of click logs persist from batch to batch, so the hint is
-// nearly always right; when it is not (a new hot key, keys bunched in a small part of their range)
-// some bucket exceeds what fits LDS and its workgroup orders it through global memory
+// nearly always right; when it is not (a new hot key, keys bunched in a small part of their range: the next dedups then go
+// by borders or by hash) some bucket exceeds what fits LDS and its workgroup orders it through global memory
 // instead: slower, same result.
 #pragma once
 
@@ -453,8 +455,52 @@ order_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start
   if (tid == 0) bucket_total[c] = n + (slow ? u : 0);
 }
 
+// Buckets by hash: all distinct keys side by side, with the positions they are numbered by; *n_out = how many.  The block
+// behind the natural buckets' takes the heavy keys.
+__global__ void __launch_bounds__(kOrderThreads)
+gather_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start, const u32* __restrict__ count,
+               u32 n_nat, const PullCtx* __restrict__ ctx, u64* __restrict__ keys_out, u32* __restrict__ pos_out, u32* __restrict__ n_out) {
+  __shared__ u32 scratch[kOrderThreads / kWave + 1];
+  const u32 tid = threadIdx.x, c = blockIdx.x;
+  u32 mine = 0, base;
+  for (u32 i = tid; i < c; i += kOrderThreads) mine += count[i] & ~kSlowBucket;
+  (void)block_excl_sum<kOrderThreads>(mine, scratch, &base);
+  if (c < n_nat) {
+    const u32 start = bucket_start[c], u = count[c] & ~kSlowBucket;
+    for (u32 i = tid; i < u; i += kOrderThreads) { keys_out[base + i] = uniq[start + i]; pos_out[base + i] = start + i; }
+    return;
+  }
+  const u32 n_heavy = ctx->n_heavy;
+  for (u32 h0 = 0; h0 < n_heavy; h0 += kOrderThreads) {
+    const u32 h = h0 + tid;
+    const u32 at = h < n_heavy ? bucket_start[n_nat + h] : 0;
+    const bool on = h < n_heavy && bucket_start[n_nat + h + 1] != at;
+    u32 all;
+    const u32 before = block_excl_sum<kOrderThreads>(on ? 1u : 0u, scratch, &all);
+    if (on) { keys_out[base + before] = uniq[at]; pos_out[base + before] = at; }
+    base += all;
+  }
+  if (tid == 0) *n_out = base;
+}
+
+// From the sorted distinct keys (payload: position in the upper half): the keys, and every key's rank by its position.
+__global__ void __launch_bounds__(kOrderThreads)
+take_ranks(const u64* __restrict__ keys, const u64* __restrict__ pay, const u32* __restrict__ n_dev, const PullCtx* __restrict__ sort_ctx,
+           TableState* __restrict__ st, u64* __restrict__ uniq_out, u32* __restrict__ local_rank) {
+  if (sort_ctx->sort_error) {      // (never expected: a wait of the passes gave up)
+    if (threadIdx.x == 0) raise_error(st, kErrInternal);
+    return;
+  }
+  const u32 n = *n_dev;
+  for (u32 j = blockIdx.x * kOrderThreads + threadIdx.x; j < n; j += gridDim.x * kOrderThreads) {
+    local_rank[(u32)(pay[j] >> 32)] = j;
+    if (uniq_out) uniq_out[j] = keys[j];
+  }
+}
+
 // uniq_out (may be null): the keys in ascending order; rank_by_pos / rank_by_heavy (null: not
-// wanted): every position's and heavy bucket's rank, for spread().
+// wanted): every position's and heavy bucket's rank, for spread().  bucket_total == null: local_rank holds the
+// final ranks already (buckets by hash).
 __global__ void __launch_bounds__(kOrderThreads)
 emit_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start, const u32* __restrict__ count,
              const u32* __restrict__ upos, u32 n_nat, const u64* __restrict__ border, const PullCtx* __restrict__ ctx,
@@ -463,9 +509,11 @@ emit_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start,
   __shared__ u32 scratch[kOrderThreads / kWave + 1];
   const u32 tid = threadIdx.x, c = blockIdx.x;
   const u32 start = bucket_start[c], end = bucket_start[c + 1], word = count[c], u = word & ~kSlowBucket;
-  u32 mine = 0, base;
-  for (u32 i = tid; i < c; i += kOrderThreads) mine += bucket_total[i];
-  (void)block_excl_sum<kOrderThreads>(mine, scratch, &base);
+  u32 mine = 0, base = 0;
+  if (bucket_total) {
+    for (u32 i = tid; i < c; i += kOrderThreads) mine += bucket_total[i];
+    (void)block_excl_sum<kOrderThreads>(mine, scratch, &base);
+  }
   if (uniq_out)
     for (u32 i = tid; i < u; i += kOrderThreads) uniq_out[base + local_rank[start + i]] = uniq[start + i];
   if (rank_by_pos)
@@ -477,7 +525,7 @@ emit_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start,
     const u32 at = bucket_start[n_nat + h];
     if (bucket_start[n_nat + h + 1] == at) continue;
     const u64 k = uniq[at];
-    if (!in_bucket(k, c, range, border, n_nat)) continue;
+    if (bucket_total ? !in_bucket(k, c, range, border, n_nat) : h % n_nat != c) continue;
     const u32 rank = base + local_rank[at];
     if (uniq_out) uniq_out[rank] = k;
     if (rank_by_heavy) rank_by_heavy[h] = rank;

@@ -135,6 +135,8 @@ int bucket_class(uint64_t n) {
   while (k + 1 < kBucketClasses && n > kBucketSizes[k].max_n) ++k;
   return k;
 }
+// Threads of the workgroups that group the buckets of n occurrences.
+u32 group_threads(int form, uint64_t n) { return form == kByBorders ? border_group_threads(n) : kBucketSizes[bucket_class(n)].group_threads; }
 // A key with at least this many occurrences in a mini-batch of n is listed as heavy: an eighth of
 // what a bucket's workgroup holds, so that a few such keys the hint misses still fit one.
 uint32_t heavy_min(uint64_t n) {
@@ -181,7 +183,7 @@ struct WorkspaceLayout {
   size_t keys_a, keys_b, idx_a, idx_b, hist, prefix, total, tile_bag, heavy_raw, ghist,
       tickets, tile_rows, group_rows, head_rows, head_groups, evidence, bag_of, id16, by_pos, by_heavy, row_of,
       med_list, arrived, chunk_items, partials, end;
-  size_t local_rank, rank_by_pos, rank_by_heavy, bucket_total;     // hps_last_unique's own
+  size_t local_rank, rank_by_pos, rank_by_heavy, bucket_total, sort_ctx, sort_n;     // hps_last_unique's own
   ContextLayout c[2];
   uint64_t max_long, max_items, sort_tiles, head_tiles;
 };
@@ -239,6 +241,8 @@ WorkspaceLayout workspace_layout(uint64_t n, uint64_t bags, uint32_t dim) {
   L.rank_by_pos = o;   o = align_up(o + n1 * 4);
   L.rank_by_heavy = o; o = align_up(o + (kMaxHeavy + 1) * 4);
   L.bucket_total = o;  o = align_up(o + buckets * 4);
+  L.sort_ctx = o;      o = align_up(o + sizeof(PullCtx));
+  L.sort_n = o;        o = align_up(o + 4);
   L.med_list = o;    o = align_up(o + (n1 / (kShortSeg + 1) + kMaxHeavy + 64) * 4);
   L.arrived = o;     o = align_up(o + L.max_long * 4);
   L.chunk_items = o; o = align_up(o + L.max_items * 16);
@@ -308,7 +312,7 @@ struct hps_table {
   int lpr;
   bool mean_pooling;        // bags are averaged instead of summed (hps_set_pooling)
   uint64_t lookup_serial;   // lookups so far; lookup s lists its frequent keys in ring slot s % 3
-  int dedup_mode;      // 0: by size and history; 1: plain radix passes always; 2: bucket path whenever it can
+  int dedup_mode;      // 0: by size and history; 1: plain radix passes always; 2, 3, 4: bucket form whenever it can, by range, borders, hash
   bool ordered_rank;   // the GPU's LDS atomics serve a wave's lanes in lane order (sort.hpp: digit_rank)
   // How much of pull_lookup's per-block list of created keys is used: all of it, unless
   // HPS_LOOKUP_NEW_LIST says less (tests of what happens when it is full).
@@ -316,20 +320,20 @@ struct hps_table {
   uint64_t serial;     // number of dedups so far (status words carry it modulo kEpochMod)
   uint64_t plain_serial;   // ... of them in the plain form
   // Pinned host word the lookups report into (table.hpp: OftenLists::report).  When a dedup
-  // of the bucket form had to order much of its input the slow way (keys bunched inside
-  // their range, or frequent keys that change from one mini-batch to the next), the
-  // following dedups take the plain form, which copes with both: for kPlainHold dedups, and
-  // twice as long each time in a row the bucket form then disappoints again.
+  // of the bucket form by key range had to order much of its input the slow way (frequent keys that change from
+  // one mini-batch to the next), or found the keys lying unevenly in their range, the following dedups take
+  // another form: for kPlainHold dedups, and twice as long each time in a row the range then disappoints again.
   unsigned long long* report;
   uint32_t report_seen;     // serial of the last report acted on
   uint32_t strikes;
-  uint64_t plain_until;     // dedups numbered below this take the plain form
-  uint64_t n_fallbacks;     // times plain_until was pushed out
-  // What takes the place of the bucket form until then: where `bunched` keys were the cause and the
-  // mini-batch is small enough, buckets by sampled borders, unless those have disappointed
-  // too (dedups numbered below borders_from); else the plain form.
-  bool bunched;
-  uint64_t borders_from;
+  uint64_t range_from;      // dedups numbered below this do not go by key range
+  uint64_t n_fallbacks;     // times range_from was pushed out
+  // Why, which decides what takes its place: kHotKeys, a few keys that turned frequent without warning; kSlowBuckets,
+  // many frequent keys in some buckets; kUnevenKeys; kCrowdedKeys, very unevenly (launch_dedup).  The plain form while the
+  // stand-ins have disappointed too (dedups numbered below stand_in_from).
+  enum Away { kHotKeys, kSlowBuckets, kUnevenKeys, kCrowdedKeys } away;
+  uint64_t stand_in_from;
+  uint32_t unlisted;        // dedups since the last hps_last_unique
   // The same for the plain form itself: after a dedup whose keys agreed in all the bits the
   // plain form sorts by (table.hpp: kReportMixed), the following ones sort by all 64 bits.
   uint32_t full_strikes;
@@ -343,7 +347,7 @@ struct hps_table {
     const int32_t* d_offsets;
     bool mean;            // pooling of this pull (fixed when it is prepared)
     bool buckets;         // its dedup took the bucket form ...
-    bool borders;         // ... by sampled borders
+    int form;             // ... by range, borders or hash (partition.hpp)
     BucketPlan plan;      // ... with these sizes ...
     hipEvent_t ready;     // recorded after the dedup kernels
     hipEvent_t released;  // recorded after the push that used the context
@@ -458,10 +462,10 @@ static void launch_push(hps_table* t, uint64_t n, PushArgs& a, hipStream_t s) {
 }
 
 // The bucket form's kernels for context c (partition.hpp, bucket.hpp), size class K.
-template <int K, bool BORDERS>
+template <int K, int FORM>
 static void launch_buckets(hps_table* t, int c, const uint64_t* d_keys, u32 n, const int32_t* d_offsets, u32 n_bags,
                            const HeavyRaw* heavy, hipStream_t s) {
-  constexpr int kThreads = kBucketSizes[K].threads, kItems = kBucketSizes[K].items, kGroup = kBucketSizes[K].group_threads;
+  constexpr int kThreads = kBucketSizes[K].threads, kItems = kBucketSizes[K].items;
   constexpr bool kDirect = K == 0;
   const WorkspaceLayout& L = t->wl;
   const ContextLayout& C = L.c[c];
@@ -478,11 +482,11 @@ static void launch_buckets(hps_table* t, int c, const uint64_t* d_keys, u32 n, c
   u32* bags = t->w<u32>(C.bags);
   const unsigned bag_blocks = d_offsets ? grid_for(n_bags, kThreads * 4, 256) : 0;
   u64* border = t->w<u64>(C.border);
-  if constexpr (BORDERS) {
+  if constexpr (FORM == kByBorders) {
     constexpr u32 kSamples = border_samples(kBucketSizes[K].max_nat);
     sample_borders<kSamples><<<kSamples / kWave, kBorderThreads, 0, s>>>(d_keys, n, plan.n_nat, border);
   }
-  bucket_count<kThreads, kItems, kMaxBuckets[K], BORDERS><<<plan.n_tiles + bag_blocks, kThreads, 0, s>>>(
+  bucket_count<kThreads, kItems, kMaxBuckets[K], FORM><<<plan.n_tiles + bag_blocks, kThreads, 0, s>>>(
       d_keys, n, plan, border, ctx, d_offsets, n_bags, tile_bag, heavy, id16, hist);
   if (!kDirect) {
     const unsigned blocks = (plan.n_nat + plan.max_heavy + kScanBuckets - 1) / kScanBuckets;
@@ -499,13 +503,18 @@ static void launch_buckets(hps_table* t, int c, const uint64_t* d_keys, u32 n, c
         keys, bags, t->w<u32>(C.code), t->w<uint16_t>(C.from));                                                   \
     stage_mark(t, HPS_STAGE_SORT, s);                                                                             \
     stage_mark(t, HPS_STAGE_UNIQUE, s);                                                                           \
-    group_bucket<kGroup, ORDERED><<<plan.n_nat, kGroup, 0, s>>>(                                                  \
-        keys, bucket_start, uniq, seg_off, bags, t->w<u32>(C.upos),                                               \
-        t->w<u32>(C.count), slow, ctx, t->view.st);                                                               \
+    if (group == 256) HPS_GROUP(256, ORDERED);                                                                    \
+    else if (group == 512) HPS_GROUP(512, ORDERED);                                                               \
+    else HPS_GROUP(1024, ORDERED);                                                                                \
   } while (0)
+#define HPS_GROUP(THREADS, ORDERED)                                                                               \
+  group_bucket<THREADS, ORDERED><<<plan.n_nat, THREADS, 0, s>>>(keys, bucket_start, uniq, seg_off, bags, t->w<u32>(C.upos), \
+                                                                t->w<u32>(C.count), slow, ctx, t->view.st)
+  const u32 group = group_threads(FORM, n);
   const SlowScratch slow = {t->w<u64>(L.idx_a), t->w<u64>(L.keys_b), t->w<u64>(L.idx_b)};
   if (t->ordered_rank) HPS_ORDERED(true);
   else HPS_ORDERED(false);
+#undef HPS_GROUP
 #undef HPS_ORDERED
 }
 
@@ -528,63 +537,84 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
       fill_u64<<<1024, 256, 0, s>>>(t->w<u64>(L.tile_rows), (L.evidence - L.tile_rows) / 8, 0);
     // The bucket path needs to know the heavy keys, which it learns from the lookups: the
     // first two dedups of a table take the plain passes, as do very large ones.
+    const bool small = n <= kBorderMaxKeys, lists = t->unlisted < 2;       // (the next dedup may come before the call)
+    if (t->unlisted < 2) ++t->unlisted;
     if (t->dedup_mode == 0) {
       const unsigned long long r = __atomic_load_n(t->report, __ATOMIC_RELAXED);
       const uint32_t serial = (uint32_t)r, flags = (uint32_t)(r >> 32);
       if (serial != t->report_seen) {
         t->report_seen = serial;
-        if ((flags & kReportBucket) && (flags & kReportSlow) && (flags & kReportOneKey)) {
-          // a few keys turned frequent without warning: plain until the hint has caught up
-          t->plain_until = t->serial + kHintLag;
-          t->bunched = false;
+        const bool uneven = (flags & kReportUneven) && !(lists && small && !(flags & kReportCrowded));
+        if ((flags & kReportRange) && (uneven || (flags & kReportSlow))) {
           ++t->n_fallbacks;
-        } else if ((flags & kReportBucket) && (flags & kReportSlow)) {
-          t->plain_until = t->serial + ((uint64_t)kPlainHold << (t->strikes < 7 ? t->strikes : 7));
-          ++t->strikes;
-          t->bunched = true;
-          ++t->n_fallbacks;
-        } else if (flags & kReportBucket) {
+          if (uneven) {
+            t->away = (flags & kReportCrowded) ? hps_table::kCrowdedKeys : hps_table::kUnevenKeys;
+          } else {
+            // (a few keys that turned frequent: plain until the hint has caught up)
+            t->away = (flags & kReportOneKey) ? hps_table::kHotKeys : hps_table::kSlowBuckets;
+          }
+          if (t->away == hps_table::kHotKeys) {
+            t->range_from = t->serial + kHintLag;
+          } else {
+            t->range_from = t->serial + ((uint64_t)kPlainHold << (t->strikes < 7 ? t->strikes : 7));
+            ++t->strikes;
+          }
+        } else if (flags & kReportRange) {
           t->strikes = 0;
-        } else if ((flags & kReportBorders) && (flags & kReportSlow)) {
-          t->borders_from = t->serial + ((flags & kReportOneKey) ? kHintLag : kPlainHold);
+        } else if ((flags & kReportStandIn) && (flags & kReportSlow)) {
+          t->stand_in_from = t->serial + ((flags & kReportOneKey) ? kHintLag : kPlainHold);
         }
         if (flags & kReportMixed) {
           // the plain form's sorted bits did not tell the keys apart: all 64 bits for a while
           t->full_until = t->serial + ((uint64_t)kPlainHold << (t->full_strikes < 7 ? t->full_strikes : 7));
           ++t->full_strikes;
           ++t->n_full_fallbacks;
-        } else if (!(flags & (kReportBucket | kReportBorders)) && t->serial >= t->full_until) {
+        } else if (!(flags & (kReportRange | kReportStandIn)) && t->serial >= t->full_until) {
           t->full_strikes = 0;       // the plain form with its usual passes did well
         }
       }
     }
-    // For small mini-batches buckets by sampled borders, one more launch, are the better stand-in for the
-    // plain form's ten (40 K occurrences, raw ids with the frequent ones side by side, dim 100, a
-    // step with its push and lookup: 109 instead of 154 us).  Larger ones would need more samples than one kernel of a few
-    // microseconds can rank.
+    // The stand-ins for the key range.  By hash is the fastest for uneven keys whatever the size, but hps_last_unique then
+    // has to sort all distinct keys.  So a caller who lists the keys of his mini-batches keeps an order of keys: up to
+    // kBorderMaxKeys by range as long as that is not several times slower, else by borders; above, the plain form.
+    // By borders also where frequent keys, not uneven ones, made buckets slow.
+    // (Raw ids, a tenth of the occurrences in a 200th of their range, a step at dim 16 of 105 K, 300 K, 1 M and 4 M occurrences:
+    // by range 327, 402, 1494 and 5822 us, by hash 76, 104, 263 and 940, plain 126, 187, 391 and 1270, by borders 118 and 161; ids whose
+    // density rises from none to twice the mean: by range 90, 125, 740 and 2057, by hash 76, 104, 279 and 900.
+    // Listing the unique keys: 18 to 40 us by borders, in the plain form 5 to 20, by hash 620 for 4 M distinct keys.)
     const bool hinted = n <= kBucketPathMaxKeys && t->dedup_mode != 1 && (t->dedup_mode >= 2 || t->lookup_serial >= 2);
-    const bool by_range = hinted && (t->dedup_mode >= 2 || t->serial >= t->plain_until);
-    const bool borders = hinted && n <= kBorderMaxKeys &&
-                         (t->dedup_mode == 3 || (!by_range && t->bunched && t->serial >= t->borders_from));
-    const bool buckets = by_range || borders;
+    int form = t->dedup_mode == 3 && small ? kByBorders : t->dedup_mode == 4 ? kByHash : kByRange;
+    bool buckets = hinted;
+    if (hinted && t->dedup_mode == 0 && t->serial < t->range_from) {
+      const bool uneven = t->away >= hps_table::kUnevenKeys;
+      if (!(t->away == hps_table::kUnevenKeys && lists && small)) {
+        form = uneven && !lists ? kByHash : kByBorders;
+        buckets = t->away != hps_table::kHotKeys && (small || form == kByHash) && t->serial >= t->stand_in_from;
+      }
+    }
     t->cx[c].buckets = buckets;
-    t->cx[c].borders = borders;
+    t->cx[c].form = form;
     if (buckets) {
       t->cx[c].plan = bucket_plan(n);
       // the most recent list of frequent keys that is certainly complete (common.hpp)
       const HeavyRaw* heavy = &t->w<HeavyRing>(L.heavy_raw)->raw[(t->lookup_serial + kHeavyRing - 1) % kHeavyRing];
+#define HPS_BUCKETS(K, FORM) launch_buckets<K, FORM>(t, c, d_keys, n, d_offsets, n_bags, heavy, s)
+#define HPS_BUCKETS3(K)                                    \
+  if (form == kByBorders) HPS_BUCKETS(K, kByBorders);      \
+  else if (form == kByHash) HPS_BUCKETS(K, kByHash);       \
+  else HPS_BUCKETS(K, kByRange)
+#define HPS_BUCKETS2(K)                                    \
+  if (form == kByHash) HPS_BUCKETS(K, kByHash);            \
+  else HPS_BUCKETS(K, kByRange)
       switch (bucket_class(n)) {
-        case 0:
-          if (borders) launch_buckets<0, true>(t, c, d_keys, n, d_offsets, n_bags, heavy, s);
-          else launch_buckets<0, false>(t, c, d_keys, n, d_offsets, n_bags, heavy, s);
-          break;
-        case 1:
-          if (borders) launch_buckets<1, true>(t, c, d_keys, n, d_offsets, n_bags, heavy, s);
-          else launch_buckets<1, false>(t, c, d_keys, n, d_offsets, n_bags, heavy, s);
-          break;
-        case 2: launch_buckets<2, false>(t, c, d_keys, n, d_offsets, n_bags, heavy, s); break;
-        default: launch_buckets<3, false>(t, c, d_keys, n, d_offsets, n_bags, heavy, s); break;
+        case 0: HPS_BUCKETS3(0); break;
+        case 1: HPS_BUCKETS3(1); break;
+        case 2: HPS_BUCKETS2(2); break;
+        default: HPS_BUCKETS2(3); break;
       }
+#undef HPS_BUCKETS2
+#undef HPS_BUCKETS3
+#undef HPS_BUCKETS
     } else {
       const SortPlan plan = sort_plan(n, t->dedup_mode < 2 && t->serial < t->full_until);
       u64* kcur = t->w<u64>(L.keys_a);
@@ -602,7 +632,7 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
       const unsigned hist_blocks = n_tiles < 768 ? n_tiles : 768;
       sort_prepare<<<hist_blocks + bag_blocks, kPrepThreads, 0, s>>>(
           d_keys, n, plan, ghist, ghist_next, tickets, ctx, d_offsets, n_bags, t->w<i32>(L.bag_of),
-          hist_blocks);
+          hist_blocks, nullptr);
       for (int p = 0; p < plan.n_pass; ++p) {
         u32* tile_rows = t->w<u32>(L.tile_rows) + (size_t)p * L.sort_tiles * kRadix;
         u32* group_rows = t->w<u32>(L.group_rows) + (size_t)p * (L.sort_tiles / kMinTileGroup + 1) * kRadix;
@@ -610,11 +640,11 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
         if (p == 0) {
           onesweep_pass<true><<<n_tiles, kSortThreads, 0, s>>>(
               d_keys, nullptr, t->w<i32>(L.bag_of), kcur, pcur, n, shift, ghist + p * kRadix, tile_rows,
-              group_rows, plan.group, tickets + p, epoch, ctx);
+              group_rows, plan.group, tickets + p, epoch, ctx, nullptr);
         } else {
           onesweep_pass<false><<<n_tiles, kSortThreads, 0, s>>>(
               kcur, pcur, t->w<i32>(L.bag_of), kalt, palt, n, shift, ghist + p * kRadix, tile_rows,
-              group_rows, plan.group, tickets + p, epoch, ctx);
+              group_rows, plan.group, tickets + p, epoch, ctx, nullptr);
           u64* tk = kcur; kcur = kalt; kalt = tk;
           tk = pcur; pcur = palt; palt = tk;
         }
@@ -671,7 +701,7 @@ static void launch_lookup(hps_table* t, int c, uint64_t n_keys, bool create, hip
   often.serial = (u32)t->lookup_serial;
   const UniqueSpans spans = unique_spans(t, c, n_keys);
   const RowsByPosition out = rows_by_position_args(t, c, create);
-  pull_lookup<<<span_blocks(spans), kProbeThreads, 0, s>>>(t->view, t->w<u64>(C.uniq), t->w<u32>(C.seg_off), spans,
+  pull_lookup<<<span_blocks(spans) + 1, kProbeThreads, 0, s>>>(t->view, t->w<u64>(C.uniq), t->w<u32>(C.seg_off), spans,
                                                            t->w<u32>(C.rows), out, create ? 1u : 0u, t->lookup_new_cap, often);
   if (create)
     pull_missing<<<span_blocks(spans), kProbeThreads, 0, s>>>(t->view, t->w<u64>(C.uniq), spans, ctx, t->w<u32>(C.rows), out);
@@ -832,11 +862,12 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   t->plain_serial = 0;
   t->mean_pooling = false;
   t->lookup_serial = 0;
-  t->bunched = false;
-  t->borders_from = 0;
+  t->away = hps_table::kHotKeys;
+  t->stand_in_from = 0;
+  t->unlisted = 2;
   t->report_seen = 0;
   t->strikes = 0;
-  t->plain_until = 0;
+  t->range_from = 0;
   t->n_fallbacks = 0;
   t->full_strikes = 0;
   t->full_until = 0;
@@ -849,10 +880,10 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   }
   *t->report = 0;
   {
-    // HPS_DEDUP=radix / bucket / borders pins the dedup to one of its forms (comparison runs, tests)
+    // HPS_DEDUP=radix / bucket / borders / hashed pins the dedup to one of its forms (comparison runs, tests)
     const char* mode = std::getenv("HPS_DEDUP");
     t->dedup_mode = !mode ? 0 : std::strcmp(mode, "radix") == 0 ? 1 : std::strcmp(mode, "bucket") == 0 ? 2
-                    : std::strcmp(mode, "borders") == 0 ? 3 : 0;
+                    : std::strcmp(mode, "borders") == 0 ? 3 : std::strcmp(mode, "hashed") == 0 ? 4 : 0;
   }
 
   t->lookup_new_cap = kNewLdsCap;
@@ -1135,8 +1166,47 @@ hps_status hps_accumulate_static(hps_table* t, const uint64_t* d_keys, uint64_t 
   return rc;
 }
 
+// Buckets by hash: puts the distinct keys of context c in order (into d_uniq_out, if wanted) and notes every key's rank
+// (local_rank), with the plain form's passes over all 64 bits, in the dedups' scratch.  The number of distinct keys is only
+// known on the device.  The status words and histograms are clear before and after, so that neither this call's
+// sequence of kernels, which a graph may replay, nor a plain dedup meets words of the other.
+static void sort_uniques(hps_table* t, int c, u32 n, uint64_t* d_uniq_out, hipStream_t s) {
+  const WorkspaceLayout& L = t->wl;
+  const ContextLayout& C = L.c[c];
+  const SortPlan plan = sort_plan(n, true);
+  PullCtx* ctx = t->w<PullCtx>(L.sort_ctx);
+  u32* n_dev = t->w<u32>(L.sort_n);
+  u64* in = t->w<u64>(L.keys_b);
+  u64* kout = t->w<u64>(L.keys_a);
+  u64* pin = nullptr;
+  u64* pout = t->w<u64>(L.idx_a);
+  u32* tickets = t->w<u32>(L.tickets);
+  u32* ghist = t->w<u32>(L.ghist);
+  const u32 n_nat = t->cx[c].plan.n_nat;
+  const unsigned n_tiles = (n + kSortTile - 1) / kSortTile, hist_blocks = n_tiles < 768 ? n_tiles : 768;
+  constexpr u32 kEpoch = 1;
+  fill_u64<<<1024, 256, 0, s>>>(t->w<u64>(L.ghist), (L.heavy_raw - L.ghist) / 8, 0);
+  gather_uniques<<<n_nat + 1, kOrderThreads, 0, s>>>(t->w<u64>(C.uniq), t->w<u32>(C.bucket_start), t->w<u32>(C.count), n_nat,
+                                                     t->ctx(c), in, t->w<u32>(L.bag_of), n_dev);
+  sort_prepare<<<hist_blocks, kPrepThreads, 0, s>>>(in, n, plan, ghist, ghist + kHistWords, tickets, ctx, nullptr, 0, nullptr, hist_blocks, n_dev);
+  for (int p = 0; p < plan.n_pass; ++p) {
+    u32* tile_rows = t->w<u32>(L.tile_rows) + (size_t)p * L.sort_tiles * kRadix;
+    u32* group_rows = t->w<u32>(L.group_rows) + (size_t)p * (L.sort_tiles / kMinTileGroup + 1) * kRadix;
+    if (p == 0)
+      onesweep_pass<true><<<n_tiles, kSortThreads, 0, s>>>(in, pin, t->w<i32>(L.bag_of), kout, pout, n, 0, ghist, tile_rows, group_rows,
+                                                           plan.group, tickets, kEpoch, ctx, n_dev);
+    else
+      onesweep_pass<false><<<n_tiles, kSortThreads, 0, s>>>(in, pin, t->w<i32>(L.bag_of), kout, pout, n, p * kRadixBits, ghist + p * kRadix,
+                                                            tile_rows, group_rows, plan.group, tickets + p, kEpoch, ctx, n_dev);
+    u64* x = in; in = kout; kout = x;
+    x = pin ? pin : t->w<u64>(L.idx_b); pin = pout; pout = x;
+  }
+  take_ranks<<<grid_for(n, kOrderThreads * 4, 1024), kOrderThreads, 0, s>>>(in, pin, n_dev, ctx, t->view.st, d_uniq_out, t->w<u32>(L.local_rank));
+  fill_u64<<<1024, 256, 0, s>>>(t->w<u64>(L.ghist), (L.heavy_raw - L.ghist) / 8, 0);
+}
+
 // The kernels and copies of an hps_last_unique of context c.  They read what its dedup wrote and nothing
-// else, and write scratch of their own.
+// else, and write scratch of their own (buckets by hash: and the dedups').
 static hps_status list_unique(hps_table* t, int c, uint64_t* d_uniq_out, int32_t* d_inverse_out, hipStream_t s) {
   const WorkspaceLayout& L = t->wl;
   const ContextLayout& C = L.c[c];
@@ -1149,11 +1219,18 @@ static hps_status list_unique(hps_table* t, int c, uint64_t* d_uniq_out, int32_t
     u32* by_heavy = d_inverse_out ? t->w<u32>(L.rank_by_heavy) : nullptr;
     const u32* start = t->w<u32>(C.bucket_start);
     const u32* count = t->w<u32>(C.count);
-    const u64* border = cx.borders ? t->w<u64>(C.border) : nullptr;
+    const u64* border = cx.form == kByBorders ? t->w<u64>(C.border) : nullptr;
+    if (cx.form == kByHash) {
+      sort_uniques(t, c, (u32)n, d_uniq_out, s);
+      if (d_inverse_out)
+        emit_uniques<<<cx.plan.n_nat, kOrderThreads, 0, s>>>(t->w<u64>(C.uniq), start, count, t->w<u32>(C.upos), cx.plan.n_nat,
+                                                             border, t->ctx(c), local_rank, nullptr, nullptr, by_pos, by_heavy);
+    } else {
     order_uniques<<<cx.plan.n_nat, kOrderThreads, 0, s>>>(t->w<u64>(C.uniq), start, count, cx.plan.n_nat, border, t->ctx(c),
                                                           local_rank, bucket_total);
     emit_uniques<<<cx.plan.n_nat, kOrderThreads, 0, s>>>(t->w<u64>(C.uniq), start, count, t->w<u32>(C.upos), cx.plan.n_nat,
                                                          border, t->ctx(c), local_rank, bucket_total, d_uniq_out, by_pos, by_heavy);
+    }
     if (d_inverse_out)
       launch_spread(t->w<u32>(C.code), t->w<uint16_t>(C.from), (u32)n, cx.plan.n_tiles, by_pos, by_heavy,
                     reinterpret_cast<u32*>(d_inverse_out), s);
@@ -1177,6 +1254,7 @@ hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_invers
   const int c = t->current;
   hps_table::Context& cx = t->cx[c];
   if (cx.n_keys == 0 || (!d_uniq_out && !d_inverse_out)) return HPS_OK;
+  t->unlisted = 0;
   // On any stream: after the dedup whose results it lists and after the call before it (the ranks'
   // scratch); the next dedup into this context waits for it (after_listing).  Events that were recorded outside a
   // capture cannot be waited for inside one: what is captured here, the caller orders.
@@ -1185,7 +1263,10 @@ hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_invers
   if (capture != hipStreamCaptureStatusNone) return list_unique(t, c, d_uniq_out, d_inverse_out, s);
   if (hipStreamWaitEvent(s, cx.ready, 0) != hipSuccess) return HPS_EDEVICE;
   if (t->listing_set && hipStreamWaitEvent(s, t->listing, 0) != hipSuccess) return HPS_EDEVICE;
+  const bool sorts = cx.buckets && cx.form == kByHash;       // in the scratch of the dedups
+  if (sorts && hipStreamWaitEvent(s, t->scratch_free, 0) != hipSuccess) return HPS_EDEVICE;
   const hps_status rc = list_unique(t, c, d_uniq_out, d_inverse_out, s);
+  if (sorts && hipEventRecord(t->scratch_free, s) != hipSuccess) return HPS_EDEVICE;
   if (hipEventRecord(t->listing, s) != hipSuccess) return HPS_EDEVICE;
   t->listing_set = true;
   cx.listed = true;

@@ -1,13 +1,18 @@
 // Key dedup, bucket form, part 1: the key occurrences are dealt into buckets in one stable pass,
 // without any workgroup waiting for another.
 //
-// A bucket is one of n_nat equal parts of the mini-batch's key range (sampled; for hashed keys: of
-// all 64 bits), a few hundred to a few thousand occurrences each, or one frequent ("heavy") key, which a hint from an
-// earlier lookup names (common.hpp): those would make single buckets too large for bucket.hpp,
-// and their occurrences need no grouping.  Buckets 0 .. n_nat-1 are in key order, the heavy
-// ones follow in the order of the hint.  Three launches (two for few tiles):
+// A bucket is one of n_nat parts of the mini-batch's keys, a few hundred to a few thousand occurrences each, or
+// one frequent ("heavy") key, which a hint from an earlier lookup names (common.hpp): those would make single
+// buckets too large for bucket.hpp, and their occurrences need no grouping.  The heavy buckets follow the n_nat
+// natural ones in the order of the hint.  The parts are
+//   by range    equal parts of the mini-batch's key range (sampled; for hashed keys: of all 64 bits): the usual way;
+//   by borders  parts with equal shares of the occurrences, between sampled borders; and
+//   by hash     parts of the keys' hashes: for keys that lie unevenly in their range (raw ids), so that equal parts of
+//               it would hold very different numbers of them.
+// By range and by borders, buckets 0 .. n_nat-1 are in key order, which hps_last_unique builds on.
+// Two launches for few tiles, else three, and one more by borders:
 //
-//   sample_borders   (only where the keys bunch) the borders of buckets of equal shares;
+//   sample_borders   (by borders) the borders of buckets of equal shares;
 //   bucket_count     a tile of consecutive occurrences per block: bucket of every key (id16), counts
 //                    per bucket (hist[tile][bucket]); further blocks note which bag every tile
 //                    starts in;
@@ -43,6 +48,7 @@ constexpr u32 kHeavyCode = 0x80000000u;   // code of an occurrence in heavy buck
 constexpr u32 kDirectTiles = 64;
 constexpr int kHeavySlots = 4096;         // hash slots for the heavy keys (a power of two)
 constexpr u32 kNoHeavy = ~0u;
+constexpr int kByRange = 0, kByBorders = 1, kByHash = 2;      // what the natural buckets are
 
 // Which part of the key range a key lies in.
 __device__ __forceinline__ u32 bucket_of(u64 key, const KeyRange& r) {
@@ -60,10 +66,14 @@ __device__ __forceinline__ KeyRange bucket_range(u64 lo, u64 hi, u32 n_nat) {
 // Sampled borders, for keys that bunch in parts of their range (raw ids, whose frequent ones are often
 // neighbours): bucket b holds the keys from border[b - 1] up to border[b], the quantiles of
 // evenly spaced samples, so that every bucket gets about the same share wherever the keys lie.  n_nat - 1 borders in ascending order, some perhaps equal (a frequent key).
-// Eight samples a bucket: one of four times the mean, which is what LDS holds in the worst case (2^19
-// occurrences in 1024 buckets), has a chance of about 1e-9.
+// Eight samples a bucket: one of s times the mean has fewer than nine where 8 s are expected, a chance of 5e-5 for
+// s = 3 (one mini-batch of 1024 buckets in twenty), 1e-7 for s = 4 and 1e-12 for s = 6.  So the workgroups
+// are chosen to hold six times the mean in distinct keys and eight times in occurrences (border_group_threads).
+// Larger mini-batches would take more samples than one kernel of a few microseconds can rank (with as many, 1 M
+// occurrences took 359 to 372 us by borders, 376 to 396 in the plain form, and listing the unique keys costs 50 us more).
 constexpr u64 kBorderMaxKeys = 1u << 19;
 constexpr u32 kMaxBorders = 1024;
+__host__ constexpr u32 border_group_threads(u64 n) { return n <= (1u << 18) ? 256 : 512; }
 constexpr u32 border_samples(u32 max_nat) { return 8 * max_nat; }
 __device__ __forceinline__ u32 bucket_by_border(u64 key, const u64* border, u32 n_borders) {
   u32 at = 0;
@@ -159,8 +169,8 @@ static_assert(kHeavySlots == 1 << 12, "a slot is the top 12 bits of the hash");
 // first plan.n_tiles blocks; the blocks behind them look through the bag offsets and leave in
 // tile_bag[t] the bag that holds occurrence t * tile (offsets == null: every occurrence is its
 // own bag, nothing to do).  Block 0 also resets the pull context.
-// BORDERS: by sampled borders.
-template <int THREADS, int ITEMS, int MAX_BUCKETS, bool BORDERS>
+// FORM: kByRange, kByBorders or kByHash.
+template <int THREADS, int ITEMS, int MAX_BUCKETS, int FORM>
 __global__ void __launch_bounds__(THREADS, 8)
 bucket_count(const u64* __restrict__ keys, u32 n, BucketPlan plan, const u64* __restrict__ border, PullCtx* __restrict__ ctx,
              const i32* __restrict__ offsets, u32 n_bags, u32* __restrict__ tile_bag,
@@ -178,25 +188,25 @@ bucket_count(const u64* __restrict__ keys, u32 n, BucketPlan plan, const u64* __
   __shared__ HeavyLds hv;
   __shared__ u64 s_lo[THREADS / kWave], s_hi[THREADS / kWave];
   __shared__ KeyRange s_range;
-  __shared__ u64 s_border[BORDERS ? kMaxBorders : 1];
+  __shared__ u64 s_border[FORM == kByBorders ? kMaxBorders : 1];
   // the tile is requested before anything waits for the samples and the list
   const u32 base = blockIdx.x * kTile;
   u64 key[ITEMS];
 #pragma unroll
   for (int k = 0; k < ITEMS; ++k) key[k] = keys[min(base + k * THREADS + threadIdx.x, n - 1)];
   const u32 n_heavy = min(heavy->count, plan.max_heavy);
-  if (BORDERS) {
+  if (FORM == kByBorders) {
     for (u32 b = threadIdx.x; b + 1 < plan.n_nat; b += THREADS) s_border[b] = border[b];
-  } else {
+  } else if (FORM == kByRange) {
     sample_key_range<THREADS>(keys, n, s_lo, s_hi);
   }
   heavy_copy<THREADS>(hv, heavy, n_heavy);
   const u32 n_buckets = plan.n_nat + n_heavy;
   for (u32 b = threadIdx.x; b < n_buckets; b += THREADS) h[b] = 0;
-  if (blockIdx.x == 0) reset_ctx(ctx, n, BORDERS ? 2u : 1u, n_heavy);
+  if (blockIdx.x == 0) reset_ctx(ctx, n, (u32)FORM + 1, n_heavy);
   __syncthreads();
   heavy_index<THREADS>(hv, n_heavy);
-  if (!BORDERS && threadIdx.x == 0) {
+  if (FORM == kByRange && threadIdx.x == 0) {
     u64 lo, hi;
     sampled_ends<THREADS>(s_lo, s_hi, &lo, &hi);
     s_range = bucket_range(lo, hi, plan.n_nat);
@@ -208,7 +218,10 @@ bucket_count(const u64* __restrict__ keys, u32 n, BucketPlan plan, const u64* __
   for (int k = 0; k < ITEMS; ++k) {
     const u32 i = base + k * THREADS + threadIdx.x;
     if (i < n) {
-      u32 id = BORDERS ? bucket_by_border(key[k], s_border, plan.n_nat - 1) : bucket_of(key[k], range);
+      // (by another hash than the groups' LDS tables: the keys of a bucket share its leading bits)
+      u32 id = FORM == kByBorders ? bucket_by_border(key[k], s_border, plan.n_nat - 1)
+               : FORM == kByHash  ? __umulhi((u32)(slot_hash(key[k]) >> 32), plan.n_nat)
+                                  : bucket_of(key[k], range);
       if (n_heavy) {
         const u32 at = heavy_find(hv, key[k]);
         if (at != kNoHeavy) id = plan.n_nat + at;

@@ -385,12 +385,15 @@ __device__ __forceinline__ void sampled_ends(const u64* s_lo, const u64* s_hi, u
 //   ghist      [kHistShards][kMaxPasses][kRadix] of this pull (zero on entry), ghist_next the
 //              buffer the next pull will use (cleared here)
 //   tickets    [kMaxPasses + 2] tile tickets of the passes and of the two unique scans
+//   n_dev      (null: n it is) the number of keys, at most n, at least one
 // Every histogram block first works out the range of the keys from the same kRangeSamples
 // sampled keys (so all agree); block 0 leaves it in ctx->range for the later kernels.
 __global__ void __launch_bounds__(kPrepThreads)
 sort_prepare(const u64* __restrict__ keys, u32 n, SortPlan plan, u32* __restrict__ ghist,
              u32* __restrict__ ghist_next, u32* __restrict__ tickets, PullCtx* __restrict__ ctx,
-             const i32* __restrict__ offsets, u32 n_bags, i32* __restrict__ bag_of, u32 hist_blocks) {
+             const i32* __restrict__ offsets, u32 n_bags, i32* __restrict__ bag_of, u32 hist_blocks,
+             const u32* __restrict__ n_dev) {
+  if (n_dev) n = *n_dev;
   if (blockIdx.x >= hist_blocks) {
     expand_bags(offsets, n_bags, n, bag_of, blockIdx.x - hist_blocks, gridDim.x - hist_blocks);
     return;
@@ -399,7 +402,7 @@ sort_prepare(const u64* __restrict__ keys, u32 n, SortPlan plan, u32* __restrict
   __shared__ KeyRange s_range;
   __shared__ u64 s_lo[kPrepThreads / kWave], s_hi[kPrepThreads / kWave];
   // The block's first tile is requested before anything waits for the samples, so that the
-  // two round trips to memory overlap (hist_blocks <= number of tiles: every block has one).
+  // two round trips to memory overlap (hist_blocks <= number of tiles of n keys: every block has one).
   constexpr int kPrepItems = kSortTile / kPrepThreads;
   u64 first_keys[kPrepItems];
 #pragma unroll
@@ -463,7 +466,8 @@ onesweep_pass(const u64* __restrict__ keys_in, const u64* __restrict__ pay_in,
               u64* __restrict__ pay_out, u32 n, int shift,
               const u32* __restrict__ ghist, u32* __restrict__ tile_rows,
               u32* __restrict__ group_rows, u32 group, u32* __restrict__ ticket, u32 epoch,
-              PullCtx* __restrict__ ctx) {
+              PullCtx* __restrict__ ctx, const u32* __restrict__ n_dev) {
+  if (n_dev) n = *n_dev;
   __shared__ u32 tile_hist[kRadix];              // digit counts of the tile
   __shared__ u32 earlier[kRadix];                // same-digit elements in earlier tiles
   __shared__ u32 wave_cnt[kSortWaves][kRadix];   // per-wave digit counts, then wave offsets
@@ -483,6 +487,7 @@ onesweep_pass(const u64* __restrict__ keys_in, const u64* __restrict__ pay_in,
   const u32 tile = s_tile;
   const u32 wave = tid / kWave, lane = tid & (kWave - 1);
   const u32 tile_base = tile * kSortTile;
+  if (tile_base >= n) return;          // (n_dev; only tiles behind this one would wait for it, and they return too)
   const u32 tile_n = min((u32)kSortTile, n - tile_base);
   const u32 wave_base = tile_base + wave * kSortWaveSpan;
   const KeyRange range = ctx->range;

@@ -187,18 +187,20 @@ struct OftenLists {
   u32 heavy_min;
   HeavyRaw* heavy_next; // the list the next lookup will fill: emptied
   // Host memory (or null) that receives serial | flags << 32 about the dedup before this
-  // lookup: kReportBucket = it took the bucket form, kReportBorders = it did, by sampled borders, kReportSlow = and more than 1/8 of
+  // lookup: kReportRange = it took the bucket form by key range, kReportStandIn = by borders or by hash, kReportSlow = and more than 1/8 of
   // the occurrences lay in buckets that had to be ordered through global memory,
   // kReportOneKey = most of them in buckets that one key fills at least half of (keys
   // that turned frequent without warning, which the next hint will list; otherwise the
-  // keys do not suit the buckets); kReportMixed = it took the plain form and more places
+  // keys do not suit the buckets); kReportUneven = a bucket by range holds far more distinct keys than the mean,
+  // kReportCrowded = so many that it costs several times the others' time (report_dedup); kReportMixed = it took the plain form and more places
   // than fix_mixed_runs can note had different keys agreeing in all sorted bits (keys in
   // clusters far apart), so that one workgroup had to put the whole array in order.  The host looks at it when it chooses the form of a later dedup, without
   // waiting for it.
   unsigned long long* report;
   u32 serial;
 };
-constexpr u32 kReportBucket = 1, kReportSlow = 2, kReportOneKey = 4, kReportMixed = 8, kReportBorders = 16;
+constexpr u32 kReportRange = 1, kReportSlow = 2, kReportOneKey = 4, kReportMixed = 8, kReportStandIn = 16, kReportUneven = 32,
+              kReportCrowded = 64;
 
 // "Updated since the last dirty dump" is kept in the sign bit of a row's first
 // accumulator element: accumulators are sums of squares, never negative, so the bit
@@ -506,6 +508,40 @@ __device__ __forceinline__ void rows_by_position(const UniqueSpans& spans, const
     out.by_pos[first + e] = rows[first + (wide ? out.upos[first + e] : (u32)up[e])];
 }
 
+// What the host is told about the dedup (OftenLists::report).  One block.
+//
+// Buckets by range are uneven if the largest has half as many distinct keys again as the mean (hashed keys stay within a
+// tenth; the slack is for small numbers).  Distinct keys are what counts, not occurrences: frequent keys make
+// lumps in any form.  A block takes a bucket in the grouping, the lookup and the push, so the largest
+// ends late in each: ids whose density rises from none to twice the mean, dim 16, 30 K, 105 K and 520 K
+// occurrences a step of 75, 90 and 208 us by range, 65, 76 and 148 by hash.
+__device__ __forceinline__ void report_dedup(const UniqueSpans& spans, const OftenLists& often) {
+  __shared__ u32 s_sum, s_most;
+  const PullCtx* ctx = often.ctx;
+  if (threadIdx.x == 0) { often.heavy_next->count = 0; s_sum = s_most = 0; }
+  __syncthreads();
+  u32 sum = 0, most = 0;
+  if (spans.bucket_start)
+    for (u32 c = threadIdx.x; c < spans.n_spans; c += kProbeThreads) {
+      const u32 u = spans.count[c] & 0x7FFFFFFFu;
+      sum += u;
+      most = max(most, u);
+    }
+  atomicAdd(&s_sum, sum);
+  atomicMax(&s_most, most);
+  __syncthreads();
+  if (threadIdx.x != 0 || !often.report) return;
+  const u32 mean = s_sum / spans.n_spans;
+  const bool uneven = ctx->by_id == 1 && s_most > mean + mean / 2 + 64;
+  const bool crowded = uneven && (s_most > 3 * mean + 256 || ctx->n_slow > ctx->n_slow_one_key);
+  const u32 flags = (ctx->by_id == 1 ? kReportRange : ctx->by_id ? kReportStandIn : 0u) | ((u64)ctx->n_slow * 8 > ctx->n_total ? kReportSlow : 0u) |
+                    ((u64)ctx->n_slow_one_key * 2 >= ctx->n_slow ? kReportOneKey : 0u) |
+                    (uneven ? kReportUneven : 0u) | (crowded ? kReportCrowded : 0u) |
+                    (!ctx->by_id && ctx->n_evidence > kMaxEvidence ? kReportMixed : 0u);
+  __hip_atomic_store(often.report, (unsigned long long)often.serial | ((unsigned long long)flags << 32),
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // rows[u] = the slot of distinct key u.  Keys the table does not hold:
 //  - create == 0 (accumulate): rows[u] = kNoRow, counted in st->miss_shard;
 //  - create != 0 and the table has room for all the keys even if every one of them is new: the
@@ -514,7 +550,8 @@ __device__ __forceinline__ void rows_by_position(const UniqueSpans& spans, const
 //  - create != 0 otherwise (a pull that might overfill the table): rows[u] = kNoRow, counted in
 //    st->miss_shard, for insert_missing, which creates all of them or none.
 // Also sorts the keys into the push's work lists by their number of occurrences, and (bucket form)
-// hands the rows on by position.  One span of distinct keys or group of heavy keys per block.
+// hands the rows on by position.  One span of distinct keys or group of heavy keys per block; the block behind
+// them reports on the dedup.
 //
 // A group of four lanes looks at a bucket of the table at once and has four keys in flight, one per lane:
 // each lane loads and hashes its own key and, at the end, stores its own key's row and lists it
@@ -533,15 +570,9 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ s
   __shared__ u64 s_new_key[kNewLdsCap];       // keys created by this block, and their rows
   __shared__ u32 s_new_row[kNewLdsCap];
   PullCtx* ctx = often.ctx;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    often.heavy_next->count = 0;
-    if (often.report) {
-      const u32 flags = (ctx->by_id == 1 ? kReportBucket : ctx->by_id ? kReportBorders : 0u) | ((u64)ctx->n_slow * 8 > ctx->n_total ? kReportSlow : 0u) |
-                        ((u64)ctx->n_slow_one_key * 2 >= ctx->n_slow ? kReportOneKey : 0u) |
-                        (!ctx->by_id && ctx->n_evidence > kMaxEvidence ? kReportMixed : 0u);
-      __hip_atomic_store(often.report, (unsigned long long)often.serial | ((unsigned long long)flags << 32),
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
+  if (blockIdx.x == span_blocks(spans)) {
+    report_dedup(spans, often);
+    return;
   }
   if (ctx->sort_error != 0) {     // the dedup before this lookup failed
     if (threadIdx.x == 0) raise_error(t.st, kErrInternal);

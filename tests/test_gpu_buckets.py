@@ -71,7 +71,7 @@ def test_shapes(n, bags, monkeypatch):
 # the sampled borders: mini-batches below and above the number of samples, both size classes that use them (up to
 # 2^16 and up to 2^19 occurrences), the first size beyond; keys the equal parts of a range cannot deal out
 @pytest.mark.parametrize("n", [1, 255, 8191, 20_000, 65_536, 65_537, 1 << 19, (1 << 19) + 1])
-@pytest.mark.parametrize("form", ["borders", "auto"])
+@pytest.mark.parametrize("form", ["borders", "hashed", "auto"])
 def test_bunched_keys(n, form, monkeypatch):
     monkeypatch.setenv("HPS_DEDUP", form)
     rng = np.random.default_rng(n)
@@ -122,3 +122,31 @@ def test_keys_in_arithmetic_progression(n, monkeypatch):
             gt.push(torch.zeros((n_bags, 4), device="cuda"))
             assert gt.stats().error == 0
     assert gt.stats().n_plain_fallbacks == 0, "taken for keys that do not suit the buckets"
+
+
+@pytest.mark.parametrize("listing", [False, True])
+@pytest.mark.parametrize("n", [30_000, 105_000, 530_000, 1_100_000])
+def test_uneven_keys_leave_the_key_range(n, listing, monkeypatch):
+    """Raw ids, a tenth of the occurrences in a two-hundredth of their range: some buckets by key range overflow, though they
+    hold less than an eighth of all occurrences.  Left to itself the library must give the key range up, for buckets by hash, or
+    where unique keys are listed for buckets by borders (530 000: the plain form), and go on giving the same results."""
+    monkeypatch.setenv("HPS_DEDUP", "auto")
+    rng = np.random.default_rng(n)
+    n_bags = n // 3
+    gt = hps.HpsTable(10 * n, 4, n, n_bags)
+    ot = oracle.OracleTable(10 * n, 4)
+    offsets = (np.arange(n_bags + 1, dtype=np.int64) * n // n_bags).astype(np.int32)
+    for step in range(6):
+        ids = np.where(rng.random(n) < 0.1, 7 * n + rng.integers(0, n // 10, size=n), rng.integers(0, 20 * n, size=n)).astype(np.uint64)
+        pooled = gt.pull(dev(ids), torch.from_numpy(offsets).cuda(), n_bags, 1)
+        close(pooled.cpu().numpy(), ot.pull(ids, offsets), "pooled, step %d" % step)
+        if listing or step == 5:
+            uniq, inv = gt.last_unique()
+            ou, oi = ot.last_unique()
+            assert np.array_equal(uniq.cpu().numpy().view(np.uint64), ou), "unique keys, step %d" % step
+            assert np.array_equal(inv.cpu().numpy(), oi), "ranks, step %d" % step
+        gt.push(torch.zeros((n_bags, 4), device="cuda"))
+        ot.push(np.zeros((n_bags, 4), np.float32))
+        st = gt.stats()
+        assert st.error == 0 and st.size == ot.size and st.last_n_unique == ot.n_unique
+    assert gt.stats().n_plain_fallbacks >= 1, "the key range was never given up"

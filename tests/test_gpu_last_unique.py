@@ -11,7 +11,7 @@ import synth
 
 pytestmark = pytest.mark.gpu
 
-FORMS = ["auto", "bucket", "borders", "radix"]
+FORMS = ["auto", "bucket", "borders", "hashed", "radix"]
 
 
 @pytest.fixture(params=FORMS)

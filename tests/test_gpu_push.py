@@ -23,7 +23,7 @@ def close(got, want, what):
 
 
 @pytest.mark.parametrize("dim,fill", [(4, 0), (16, 0), (32, 0), (64, 0), (100, 0), (256, 0), (260, 0), (64, 1 << 19)])
-@pytest.mark.parametrize("form", ["radix", "bucket"])
+@pytest.mark.parametrize("form", ["radix", "bucket", "borders", "hashed"])
 def test_piece_edges(dim, fill, form, monkeypatch):
     monkeypatch.setenv("HPS_DEDUP", form)
     rng = np.random.default_rng(dim + fill)

@@ -17,7 +17,7 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a, dtype=np.uint64).view(np.int64)).cuda()
 
 
-@pytest.mark.parametrize("form", ["bucket", "radix"])
+@pytest.mark.parametrize("form", ["bucket", "hashed", "radix"])
 @pytest.mark.parametrize("n,n_bags", [(1, 30_000), (1000, 24_576), (1000, 24_577), (1000, 24_578), (1024, 100_000), (3000, 70_000),
                                       (3000, 300_000), (70_000, 72_000), (70_000, 840_000), (70_000, 2_000_000)])
 def test_sparse_bags(n, n_bags, form, monkeypatch):
