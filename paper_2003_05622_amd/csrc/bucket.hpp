@@ -309,8 +309,12 @@ __device__ __forceinline__ u32 upos_at(const u32* upos, u32 start, u32 e, u32 co
 
 // ---- ascending unique keys and ranks, on request ----------------------------------------
 constexpr int kOrderThreads = 1024;
-constexpr u32 kOrderCap = 8192;
-static_assert(GroupLds<1024>::kSlots + kMaxHeavy <= kOrderCap, "a bucket's distinct keys and all heavy keys");
+// order_uniques by the threads of the buckets' workgroups: threads of its own, keys it holds in LDS
+constexpr int order_threads(int group) { return group == 256 ? 512 : 1024; }
+constexpr u32 order_cap(int group) { return 8 * order_threads(group); }
+constexpr u32 order_max_heavy(int group) { return group == 256 ? 1023 : kMaxHeavy; }
+static_assert(GroupLds<256>::kSlots + order_max_heavy(256) <= order_cap(256) &&
+                  GroupLds<1024>::kSlots + order_max_heavy(1024) <= order_cap(1024), "a bucket's distinct keys and all heavy keys");
 
 // Bucket c: local_rank[u] = rank of key number u among the bucket's distinct keys and the heavy keys
 // that lie in the bucket's part of the key range; bucket_total[c] = how many those are.
@@ -319,16 +323,19 @@ static_assert(GroupLds<1024>::kSlots + kMaxHeavy <= kOrderCap, "a bucket's disti
 // largest of them), and a key's rank is its cell's start plus the smaller keys of the cell: hashed
 // keys share a cell with one or two others.  Where a cell holds many (keys bunched inside the bucket),
 // a bitonic network sorts them.  9.8 M occurrences, 2.8 M distinct keys: the whole of hps_last_unique
-// takes 175 us; with the network throughout, 485.
-constexpr u32 kOrderCells = 4096;
+// takes 175 us; with the network throughout, 485.  Small buckets (GROUP: threads of their workgroups) are ordered by
+// half the threads, so that three blocks fit a CU and all are under way at once: 0.3 M occurrences, the call 40 us with blocks
+// of 1024 for 8192 keys, 25 with these.
 constexpr u32 kOrderCellMax = 32;
-__global__ void __launch_bounds__(kOrderThreads)
+template <int GROUP>
+__global__ void __launch_bounds__(order_threads(GROUP))
 order_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start, const u32* __restrict__ count,
               u32 n_nat, const u64* __restrict__ border, const PullCtx* __restrict__ ctx,
               u32* __restrict__ local_rank, u32* __restrict__ bucket_total) {
-  constexpr int kPer = kOrderCap / kOrderThreads, kWaves = kOrderThreads / kWave;
-  __shared__ u64 key[kOrderCap];
-  __shared__ u32 num[kOrderCap];
+  constexpr int kThreads = order_threads(GROUP), kPer = order_cap(GROUP) / kThreads, kWaves = kThreads / kWave;
+  constexpr u32 kOrderCells = (GROUP == 256 ? 2 : 4) * kThreads;
+  __shared__ u64 key[order_cap(GROUP)];
+  __shared__ u32 num[order_cap(GROUP)];
   __shared__ u32 cell[kOrderCells + 1];
   __shared__ u64 s_lo[kWaves], s_hi[kWaves];
   __shared__ u32 scratch[kWaves + 1];
@@ -339,9 +346,9 @@ order_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start
   const u32 n_heavy = ctx->n_heavy;
   const KeyRange range = ctx->range;
   if (tid == 0) { s_n = slow ? 0 : u; s_crowded = 0; }
-  if (!slow) for (u32 i = tid; i < u; i += kOrderThreads) { key[i] = uniq[start + i]; num[i] = start + i; }
+  if (!slow) for (u32 i = tid; i < u; i += kThreads) { key[i] = uniq[start + i]; num[i] = start + i; }
   __syncthreads();
-  for (u32 h = tid; h < n_heavy; h += kOrderThreads) {
+  for (u32 h = tid; h < n_heavy; h += kThreads) {
     const u32 at = bucket_start[n_nat + h];
     if (bucket_start[n_nat + h + 1] == at) continue;
     const u64 k = uniq[at];
@@ -350,7 +357,7 @@ order_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start
     key[i] = k;
     num[i] = at;
   }
-  for (u32 i = tid; i <= kOrderCells; i += kOrderThreads) cell[i] = 0;
+  for (u32 i = tid; i <= kOrderCells; i += kThreads) cell[i] = 0;
   __syncthreads();
   const u32 n = s_n;
   // this thread's keys, and the ends of all of them
@@ -359,7 +366,7 @@ order_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start
   u64 lo = ~0ull, hi = 0;
 #pragma unroll
   for (int q = 0; q < kPer; ++q) {
-    const u32 i = q * kOrderThreads + tid;
+    const u32 i = q * kThreads + tid;
     mine[q] = i < n ? key[i] : 0;
     mine_num[q] = i < n ? num[i] : 0;
     if (i < n) { lo = min(lo, mine[q]); hi = max(hi, mine[q]); }
@@ -371,7 +378,7 @@ order_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start
   }
   if (lane_id() == 0) { s_lo[tid / kWave] = lo; s_hi[tid / kWave] = hi; }
   __syncthreads();
-  sampled_ends<kOrderThreads>(s_lo, s_hi, &lo, &hi);
+  sampled_ends<kThreads>(s_lo, s_hi, &lo, &hi);
   KeyRange r;
   r.lo = lo; r.span = hi - lo; r.base = 0;
   r.pre = r.span >> 32 ? 32 - __clzll((long long)r.span) : 0;
@@ -379,28 +386,28 @@ order_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start
   r.mult = r.direct ? 0u : (u32)(((u64)kOrderCells << 32) / ((r.span >> r.pre) + 1));
 #pragma unroll
   for (int q = 0; q < kPer; ++q)
-    if (q * kOrderThreads + tid < n) {
+    if (q * kThreads + tid < n) {
       place[q] = atomicAdd(&cell[bucket_of(mine[q], r)], 1u);
       if (place[q] >= kOrderCellMax) s_crowded = 1;
     }
   __syncthreads();
   if (!s_crowded) {
-    constexpr int kCells = kOrderCells / kOrderThreads;
+    constexpr int kCells = kOrderCells / kThreads;
     u32 v[kCells], sum = 0, total;
 #pragma unroll
     for (int q = 0; q < kCells; ++q) { v[q] = cell[kCells * tid + q]; sum += v[q]; }
-    u32 at = block_excl_sum<kOrderThreads>(sum, scratch, &total);
+    u32 at = block_excl_sum<kThreads>(sum, scratch, &total);
 #pragma unroll
     for (int q = 0; q < kCells; ++q) { cell[kCells * tid + q] = at; at += v[q]; }
     if (tid == 0) cell[kOrderCells] = total;
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < kPer; ++q)
-      if (q * kOrderThreads + tid < n) key[cell[bucket_of(mine[q], r)] + place[q]] = mine[q];
+      if (q * kThreads + tid < n) key[cell[bucket_of(mine[q], r)] + place[q]] = mine[q];
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < kPer; ++q)
-      if (q * kOrderThreads + tid < n) {
+      if (q * kThreads + tid < n) {
         const u32 k = bucket_of(mine[q], r), end = cell[k + 1];
         u32 rank = cell[k];
         for (u32 i = rank; i < end; ++i) rank += key[i] < mine[q] ? 1u : 0u;
@@ -410,22 +417,22 @@ order_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start
     if (!slow) {
 #pragma unroll
       for (int q = 0; q < kPer; ++q)
-        if (q * kOrderThreads + tid < n) local_rank[mine_num[q]] = place[q];
+        if (q * kThreads + tid < n) local_rank[mine_num[q]] = place[q];
     } else {          // the merge below wants the heavy keys in order
 #pragma unroll
       for (int q = 0; q < kPer; ++q)
-        if (q * kOrderThreads + tid < n) { key[place[q]] = mine[q]; num[place[q]] = mine_num[q]; }
+        if (q * kThreads + tid < n) { key[place[q]] = mine[q]; num[place[q]] = mine_num[q]; }
       __syncthreads();
     }
   } else {
     u32 size = 2;
     while (size < n) size <<= 1;
     // (the reserved key is never among them: it goes the slow way and is in no list of heavy keys)
-    for (u32 i = n + tid; i < size; i += kOrderThreads) { key[i] = ~0ull; num[i] = ~0u; }
+    for (u32 i = n + tid; i < size; i += kThreads) { key[i] = ~0ull; num[i] = ~0u; }
     for (u32 k = 2; k <= size; k <<= 1) {
       for (u32 j = k >> 1; j > 0; j >>= 1) {
         __syncthreads();
-        for (u32 i = tid; i < size; i += kOrderThreads) {
+        for (u32 i = tid; i < size; i += kThreads) {
           const u32 partner = i ^ j;
           if (partner > i && (key[i] > key[partner]) == ((i & k) == 0)) {
             const u64 x = key[i]; key[i] = key[partner]; key[partner] = x;
@@ -435,17 +442,17 @@ order_uniques(const u64* __restrict__ uniq, const u32* __restrict__ bucket_start
       }
     }
     __syncthreads();
-    if (!slow) for (u32 i = tid; i < n; i += kOrderThreads) local_rank[num[i]] = i;
+    if (!slow) for (u32 i = tid; i < n; i += kThreads) local_rank[num[i]] = i;
   }
   if (slow) {
     // two ordered lists: the bucket's own keys (global memory) and the heavy ones among them (LDS)
-    for (u32 i = tid; i < u; i += kOrderThreads) {
+    for (u32 i = tid; i < u; i += kThreads) {
       const u64 k = uniq[start + i];
       u32 a = 0, b = n;
       while (a < b) { const u32 m = (a + b) / 2; if (key[m] < k) a = m + 1; else b = m; }
       local_rank[start + i] = i + a;
     }
-    for (u32 i = tid; i < n; i += kOrderThreads) {
+    for (u32 i = tid; i < n; i += kThreads) {
       const u64 k = key[i];
       u32 a = 0, b = u;
       while (a < b) { const u32 m = (a + b) / 2; if (uniq[start + m] < k) a = m + 1; else b = m; }

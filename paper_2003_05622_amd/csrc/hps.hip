@@ -118,6 +118,7 @@ constexpr bool bucket_sizes_ok() {
   for (int k = 0; k < kBucketClasses; ++k) {
     const BucketSizes& z = kBucketSizes[k];
     if (z.max_nat + z.max_heavy > (uint32_t)kMaxBuckets[k] || z.max_nat + z.max_heavy > 8191) return false;
+    if (z.max_heavy > order_max_heavy((int)z.group_threads)) return false;
     if (z.max_nat < z.max_n / z.mean && k != 1) return false;
     if (k == 0 && z.max_n > kDirectTiles * z.threads * z.items) return false;
     if (z.max_n > 1024u * z.threads * z.items) return false;       // scan_buckets: at most 16 tiles per group of lanes
@@ -1226,8 +1227,11 @@ static hps_status list_unique(hps_table* t, int c, uint64_t* d_uniq_out, int32_t
         emit_uniques<<<cx.plan.n_nat, kOrderThreads, 0, s>>>(t->w<u64>(C.uniq), start, count, t->w<u32>(C.upos), cx.plan.n_nat,
                                                              border, t->ctx(c), local_rank, nullptr, nullptr, by_pos, by_heavy);
     } else {
-    order_uniques<<<cx.plan.n_nat, kOrderThreads, 0, s>>>(t->w<u64>(C.uniq), start, count, cx.plan.n_nat, border, t->ctx(c),
-                                                          local_rank, bucket_total);
+#define HPS_ORDER(GROUP) \
+  order_uniques<GROUP><<<cx.plan.n_nat, order_threads(GROUP), 0, s>>>(t->w<u64>(C.uniq), start, count, cx.plan.n_nat, border, t->ctx(c), local_rank, bucket_total)
+    if (group_threads(cx.form, n) == 256) HPS_ORDER(256);
+    else HPS_ORDER(1024);
+#undef HPS_ORDER
     emit_uniques<<<cx.plan.n_nat, kOrderThreads, 0, s>>>(t->w<u64>(C.uniq), start, count, t->w<u32>(C.upos), cx.plan.n_nat,
                                                          border, t->ctx(c), local_rank, bucket_total, d_uniq_out, by_pos, by_heavy);
     }
