@@ -1,16 +1,17 @@
 // The HBM hash table: open addressing over 64-byte lines of 8 slots, linear
-// probing line by line, one 8-lane group per key (each lane looks at one slot of
-// the line), lock-free insertion by 64-bit compare-and-swap on the slot's key.
+// probing line by line from an even line on, lock-free insertion by 64-bit compare-and-swap on the
+// slot's key.  Lookups take four lanes per key, which look at two lines (a 128-byte bucket) at once; the kernels
+// that create keys after a lookup (pull_missing, insert_missing) eight, one slot of a line each.
 //
-// Layout (structure of arrays, row index = slot index):
+// Layout (structure of arrays, row index = slot index; TableView has the variants):
 //   keys[n_slots]            u64, kEmptyKey when free
-//   w[n_slots][dim]          f32
+//   w[n_slots][dim]          f32 or bf16
 //   acc[n_slots][acc_len]    f32
 //
 // A lookup creates missing keys on the spot if the table has room even if every key it
 // looks up were new.  Otherwise creating them is a second kernel, so that the room check
 // against the capacity is one consistent decision and no block has to hit a single
-// counter: the lookup counts the missing keys into sharded counters, insert_missing
+// counter: the lookup counts the missing keys into sharded counters, pull_missing or insert_missing
 // (every block reads the same total) claims slots only if all of them fit and counts
 // the rows it creates.  commit_insert adds the count of created rows to the table size.
 // rows.hpp: the entry points that move rows by key or by slot (insert, get, dump).
@@ -115,7 +116,6 @@ __device__ __forceinline__ float4 init_weight4(u64 base, u32 col4, float range) 
 
 constexpr int kProbeThreads = 256;
 constexpr int kProbeGroups = kProbeThreads / kSlotsPerLine;   // insert: 8-lane groups per block
-constexpr int kProbeInFlight = 8;                             // keys a group probes at a time
 // Lookups take four lanes per key, each reading two of the line's eight slots with one
 // 16-byte load: a wave's load instruction then asks for sixteen lines instead of eight, and
 // the rate at which lines come back follows the lines asked for per instruction.
@@ -125,7 +125,6 @@ constexpr int kLookupLanes = 4;
 // waves per SIMD, a third slower; forcing five or six waves per SIMD by spilling gains nothing).
 constexpr int kPullInFlight = 4;
 static_assert(kPullInFlight % kLookupLanes == 0, "every lane of a group owns the same number of keys");
-constexpr int kLookupGroups = kProbeThreads / kLookupLanes;
 constexpr int kProbeMaxBlocks = 1024;
 constexpr u32 kNoSlot = ~0u;
 constexpr u32 kNewLdsCap = 1024;         // created keys a block lists for its common initialisation
@@ -261,8 +260,8 @@ __global__ void __launch_bounds__(64) set_ctx_empty(PullCtx* ctx, u32* seg_off) 
   if (threadIdx.x < kCountShards) ctx->uniq_shard[threadIdx.x] = 0;
 }
 
-// Adds the rows insert_missing created to the table size and clears the counters.
-// Called by one whole wave, after insert_missing has finished.
+// Adds the rows that were created to the table size and clears the counters.
+// Called by one whole wave, after the kernels that create rows have finished.
 __device__ __forceinline__ void commit_insert_wave(TableState* st) {
   const u32 lane = lane_id();
   u32 made = lane < kCountShards ? st->made_shard[lane] : 0;
@@ -548,7 +547,7 @@ __device__ __forceinline__ void report_dedup(const UniqueSpans& spans, const Oft
 //    key is created right here, with its initial row (the line is at hand, and so are its free
 //    slots), counted in st->made_shard;
 //  - create != 0 otherwise (a pull that might overfill the table): rows[u] = kNoRow, counted in
-//    st->miss_shard, for insert_missing, which creates all of them or none.
+//    st->miss_shard, for pull_missing, which creates all of them or none.
 // Also sorts the keys into the push's work lists by their number of occurrences, and (bucket form)
 // hands the rows on by position.  One span of distinct keys or group of heavy keys per block; the block behind
 // them reports on the dedup.

@@ -1,9 +1,10 @@
-"""The bucket form of the dedup at the sizes where it changes shape: one tile and one more or less of each
-size class, the largest and smallest mini-batch of a class, with bags that start in the middle of tiles, empty
-bags, bags longer than a tile, and heavy keys the hint names, misses, or names in vain.  Unique keys and ranks
-are compared bit for bit, pooled rows and the rows after the push within the float32 tolerance (at most 2^14
-terms of one sign per sum would be off by 2^14 * 2^-24 = 1e-3 relative if added in a chain; the sums here are trees of
-eight-term chains, below 1e-5)."""
+"""The bucket form of the dedup at the sizes where it changes shape: one tile and one more or less, the largest and
+smallest mini-batch of a size class, with bags that start in the middle of tiles, empty bags, bags longer than a tile, and heavy
+keys the hint names, misses, or names in vain.  Unique keys and ranks are compared bit for bit with the oracle's, rows
+after the push within the float32 tolerance.  Pooled rows are compared at every step with the float64 pooling of the
+rows the table itself holds, bags of up to 4096 occurrences: a bag is added up in runs of eight, so 512 additions,
+off by at most 512 * 2^-24 = 3e-5 of the sum of magnitudes if all roundings went one way and by about 1.4e-6 as they
+come: within 1e-6 + 1e-5 |x| for sums whose terms do not nearly cancel, and terms below 0.01 where they do."""
 import numpy as np
 import pytest
 import torch
@@ -22,6 +23,18 @@ def dev(a):
 def close(got, want, what):
     err = np.abs(got.astype(np.float64) - want) - (1e-6 + 1e-5 * np.abs(want))
     assert err.max(initial=-1) <= 0, "%s: excess %g" % (what, err.max())
+
+
+def close_pooled(gt, pooled, uniq, inverse, offsets, mean, what):
+    """pooled against the bags' sums or means, in float64, of the rows the table holds (uniq: ascending, inverse: ranks)."""
+    rows = gt.get(dev(uniq))[0].cpu().numpy().astype(np.float64)
+    total = np.concatenate([np.zeros((1, rows.shape[1])), np.cumsum(rows[inverse], axis=0)])
+    lens = np.diff(offsets)
+    want = total[offsets[1:]] - total[offsets[:-1]]
+    if mean:
+        want /= np.maximum(lens, 1)[:, None]
+    short = lens <= 4096
+    close(pooled.cpu().numpy()[short], want[short], what)
 
 
 # tiles of 1024 (up to 2^16 occurrences), 4096 (up to 2^20), 8192 (up to 3 * 2^20)
@@ -51,14 +64,12 @@ def test_shapes(n, bags, monkeypatch):
             cuts[: n_bags // 2] = cuts[n_bags // 2]
             offsets = np.concatenate([[0], np.sort(cuts), [n]]).astype(np.int32)
         pooled = gt.pull(dev(keys), torch.from_numpy(offsets).cuda(), n_bags, 1)
-        want = ot.pull(keys, offsets)
+        ot.pull(keys, offsets)
         uniq, inv = gt.last_unique()
         ou, oi = ot.last_unique()
         assert np.array_equal(uniq.cpu().numpy().view(np.uint64), ou), "unique keys, step %d" % step
         assert np.array_equal(inv.cpu().numpy(), oi), "ranks, step %d" % step
-        if step == 0 and bags != "one":
-            long = np.diff(offsets) > 4096                 # the oracle sums in double, the library in float32
-            close(pooled.cpu().numpy()[~long], want[~long], "pooled")
+        close_pooled(gt, pooled, ou, oi, offsets, bags == "one", "pooled, step %d" % step)
         grads = (rng.integers(-8, 9, size=(n_bags, dim)) / 4096).astype(np.float32)     # sums of these are exact
         gt.push(torch.from_numpy(grads).cuda())
         ot.push(grads)
@@ -77,7 +88,10 @@ def test_bunched_keys(n, form, monkeypatch):
     rng = np.random.default_rng(n)
     gt = hps.HpsTable(8 * n + 100, 4, n, n, lr=0.05)
     ot = oracle.OracleTable(8 * n + 100, 4, lr=0.05)
-    offsets = np.arange(n + 1, dtype=np.int32)
+    # ragged bags, half of them empty, averaged in one size of two
+    n_bags, mean = n, n % 2 == 1
+    gt.set_pooling(mean)
+    ot.set_pooling(mean)
     # long-tailed raw ids (half of all keys within a thousandth of the range), two crowded places at the
     # ends of the 64 bits, one key over and over, all keys apart
     kinds = [lambda: np.minimum(rng.pareto(1.0, size=n) * 100.0, 1e15).astype(np.uint64),
@@ -86,19 +100,47 @@ def test_bunched_keys(n, form, monkeypatch):
              lambda: rng.permutation(n).astype(np.uint64)]
     for step, kind in enumerate([0, 0, 0, 0, 0, 0, 1, 2, 3, 0, 1]):
         keys = kinds[kind]()
-        gt.pull(dev(keys), torch.from_numpy(offsets).cuda(), n, 1)
+        offsets = np.concatenate([[0], np.sort(rng.choice(np.arange(0, n + 1, 2), size=n_bags - 1)), [n]]).astype(np.int32)
+        pooled = gt.pull(dev(keys), torch.from_numpy(offsets).cuda(), n_bags, 1)
         ot.pull(keys, offsets)
         uniq, inv = gt.last_unique()
         ou, oi = ot.last_unique()
         assert np.array_equal(uniq.cpu().numpy().view(np.uint64), ou), "unique keys, step %d" % step
         assert np.array_equal(inv.cpu().numpy(), oi), "ranks, step %d" % step
-        grads = (rng.integers(-8, 9, size=(n, 4)) / 4096).astype(np.float32)
+        close_pooled(gt, pooled, ou, oi, offsets, mean, "pooled, step %d" % step)
+        grads = (rng.integers(-8, 9, size=(n_bags, 4)) / 4096).astype(np.float32)
         gt.push(torch.from_numpy(grads).cuda())
         ot.push(grads)
         st = gt.stats()
         assert st.error == 0 and st.size == ot.size and st.last_n_unique == ou.size
     sample = ou[:: max(1, ou.size // 2000)]
     close(gt.get(dev(sample))[1].cpu().numpy(), ot.get(sample)[1], "accumulators")
+    if form != "auto":
+        assert gt.stats().n_plain_fallbacks == 0
+    elif n >= 8191:
+        assert gt.stats().n_plain_fallbacks > 0, "the key range was never given up"
+
+
+# the borders between the two largest size classes, and between the largest and the plain form
+@pytest.mark.parametrize("form", ["bucket", "hashed"])
+@pytest.mark.parametrize("n", [3 << 20, (3 << 20) + 1, 12 << 20, (12 << 20) + 1])
+def test_large_size_classes(n, form, monkeypatch):
+    monkeypatch.setenv("HPS_DEDUP", form)
+    rng = np.random.default_rng(n)
+    n_bags = n // 8
+    gt = hps.HpsTable(n, 4, n, n_bags)
+    offsets = (np.arange(n_bags + 1, dtype=np.int64) * n // n_bags).astype(np.int32)
+    for step in range(2):            # the second step with a hint
+        keys = synth.mix64(rng.integers(0, n // 2, size=n).astype(np.uint64))
+        keys[rng.integers(0, n, size=n // 8)] = synth.mix64(np.uint64(10**9))
+        pooled = gt.pull(dev(keys), torch.from_numpy(offsets).cuda(), n_bags, 1)
+        ou, oi = np.unique(keys, return_inverse=True)
+        uniq, inv = gt.last_unique()
+        assert np.array_equal(uniq.cpu().numpy().view(np.uint64), ou), "unique keys, step %d" % step
+        assert np.array_equal(inv.cpu().numpy(), oi), "ranks, step %d" % step
+        close_pooled(gt, pooled, ou, oi, offsets, False, "pooled, step %d" % step)
+        gt.push(torch.zeros((n_bags, 4), device="cuda"))
+    assert gt.stats().error == 0
 
 
 @pytest.mark.parametrize("n", [30_000, 1_000_000])
