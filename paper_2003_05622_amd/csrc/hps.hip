@@ -320,13 +320,19 @@ struct hps_table {
   u32 lookup_new_cap;
   uint64_t serial;     // number of dedups so far (status words carry it modulo kEpochMod)
   uint64_t plain_serial;   // ... of them in the plain form
-  // Pinned host word the lookups report into (table.hpp: OftenLists::report).  When a dedup
+  // Pinned host words the lookups report into (table.hpp: OftenLists::report).  When a dedup
   // of the bucket form by key range had to order much of its input the slow way (frequent keys that change from
   // one mini-batch to the next), or found the keys lying unevenly in their range, the following dedups take
   // another form: for kPlainHold dedups, and twice as long each time in a row the range then disappoints again.
-  unsigned long long* report;
-  uint32_t report_seen;     // serial of the last report acted on
+  unsigned long long* report;             // [0] of the lookup after a dedup in any form but by key range, [1] by key range
+  uint32_t range_seen, other_seen;        // serials of the last reports acted on
+  uint32_t judged;          // reports of lookups up to this one do not count: issued before the range was given up
   uint32_t strikes;
+  // After such a time, one dedup goes by key range again, and the next ones only when the report on that one has
+  // come: a caller who never waits may be dozens of dedups ahead of the GPU (to_probe: it is due; probe: its lookup,
+  // 0: none).  Not after other causes, whose stand-ins are slower than a good key range.
+  bool to_probe;
+  uint32_t probe;
   uint64_t range_from;      // dedups numbered below this do not go by key range
   uint64_t n_fallbacks;     // times range_from was pushed out
   // Why, which decides what takes its place: kHotKeys, a few keys that turned frequent without warning; kSlowBuckets,
@@ -541,28 +547,43 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
     const bool small = n <= kBorderMaxKeys, lists = t->unlisted < 2;       // (the next dedup may come before the call)
     if (t->unlisted < 2) ++t->unlisted;
     if (t->dedup_mode == 0) {
-      const unsigned long long r = __atomic_load_n(t->report, __ATOMIC_RELAXED);
-      const uint32_t serial = (uint32_t)r, flags = (uint32_t)(r >> 32);
-      if (serial != t->report_seen) {
-        t->report_seen = serial;
+      // (the other forms' word first: what it tells of came after whatever the range's word then does not tell of)
+      const unsigned long long other = __atomic_load_n(t->report, __ATOMIC_ACQUIRE), range = __atomic_load_n(t->report + 1, __ATOMIC_RELAXED);
+      if ((uint32_t)range != t->range_seen) {
+        const uint32_t serial = (uint32_t)range, flags = (uint32_t)(range >> 32);
+        t->range_seen = serial;
+        if (t->probe && (int32_t)(serial - t->probe) >= 0) t->probe = 0;
         const bool uneven = (flags & kReportUneven) && !(lists && small && !(flags & kReportCrowded));
-        if ((flags & kReportRange) && (uneven || (flags & kReportSlow))) {
+        if ((int32_t)(serial - t->judged) <= 0) {
+          // (of a dedup that was under way when the range was given up)
+        } else if (uneven || (flags & kReportSlow)) {
           ++t->n_fallbacks;
+          t->judged = (uint32_t)t->lookup_serial;
           if (uneven) {
             t->away = (flags & kReportCrowded) ? hps_table::kCrowdedKeys : hps_table::kUnevenKeys;
           } else {
             // (a few keys that turned frequent: plain until the hint has caught up)
             t->away = (flags & kReportOneKey) ? hps_table::kHotKeys : hps_table::kSlowBuckets;
           }
+          t->to_probe = uneven;
           if (t->away == hps_table::kHotKeys) {
             t->range_from = t->serial + kHintLag;
           } else {
             t->range_from = t->serial + ((uint64_t)kPlainHold << (t->strikes < 7 ? t->strikes : 7));
             ++t->strikes;
           }
-        } else if (flags & kReportRange) {
+        } else {
           t->strikes = 0;
-        } else if ((flags & kReportStandIn) && (flags & kReportSlow)) {
+        }
+      }
+      if ((uint32_t)other != t->other_seen) {
+        const uint32_t serial = (uint32_t)other, flags = (uint32_t)(other >> 32);
+        t->other_seen = serial;
+        if (t->probe && (int32_t)(serial - t->probe) >= 0) {      // its dedup was replaced by another: try again
+          t->probe = 0;
+          t->to_probe = true;
+        }
+        if ((flags & kReportStandIn) && (flags & kReportSlow)) {
           t->stand_in_from = t->serial + ((flags & kReportOneKey) ? kHintLag : kPlainHold);
         }
         if (flags & kReportMixed) {
@@ -570,7 +591,7 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
           t->full_until = t->serial + ((uint64_t)kPlainHold << (t->full_strikes < 7 ? t->full_strikes : 7));
           ++t->full_strikes;
           ++t->n_full_fallbacks;
-        } else if (!(flags & (kReportRange | kReportStandIn)) && t->serial >= t->full_until) {
+        } else if (!(flags & kReportStandIn) && t->serial >= t->full_until) {
           t->full_strikes = 0;       // the plain form with its usual passes did well
         }
       }
@@ -586,7 +607,12 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
     const bool hinted = n <= kBucketPathMaxKeys && t->dedup_mode != 1 && (t->dedup_mode >= 2 || t->lookup_serial >= 2);
     int form = t->dedup_mode == 3 && small ? kByBorders : t->dedup_mode == 4 ? kByHash : kByRange;
     bool buckets = hinted;
-    if (hinted && t->dedup_mode == 0 && t->serial < t->range_from) {
+    const bool away = t->dedup_mode == 0 && (t->serial < t->range_from || t->probe);
+    if (hinted && t->dedup_mode == 0 && !away && t->to_probe) {
+      t->probe = (uint32_t)t->lookup_serial + 1;
+      t->to_probe = false;
+    }
+    if (hinted && away) {
       const bool uneven = t->away >= hps_table::kUnevenKeys;
       if (!(t->away == hps_table::kUnevenKeys && lists && small)) {
         form = uneven && !lists ? kByHash : kByBorders;
@@ -866,7 +892,8 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   t->away = hps_table::kHotKeys;
   t->stand_in_from = 0;
   t->unlisted = 2;
-  t->report_seen = 0;
+  t->range_seen = t->other_seen = t->judged = t->probe = 0;
+  t->to_probe = false;
   t->strikes = 0;
   t->range_from = 0;
   t->n_fallbacks = 0;
@@ -879,7 +906,7 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
     hps_destroy(t);
     return HPS_EDEVICE;
   }
-  *t->report = 0;
+  t->report[0] = t->report[1] = 0;
   {
     // HPS_DEDUP=radix / bucket / borders / hashed pins the dedup to one of its forms (comparison runs, tests)
     const char* mode = std::getenv("HPS_DEDUP");

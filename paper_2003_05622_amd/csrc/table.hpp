@@ -186,7 +186,7 @@ struct OftenLists {
   u32 heavy_min;
   HeavyRaw* heavy_next; // the list the next lookup will fill: emptied
   // Host memory (or null) that receives serial | flags << 32 about the dedup before this
-  // lookup: kReportRange = it took the bucket form by key range, kReportStandIn = by borders or by hash, kReportSlow = and more than 1/8 of
+  // lookup, in its second word if that went by key range, else in its first: kReportStandIn = it went by borders or by hash, kReportSlow = and more than 1/8 of
   // the occurrences lay in buckets that had to be ordered through global memory,
   // kReportOneKey = most of them in buckets that one key fills at least half of (keys
   // that turned frequent without warning, which the next hint will list; otherwise the
@@ -198,7 +198,7 @@ struct OftenLists {
   unsigned long long* report;
   u32 serial;
 };
-constexpr u32 kReportRange = 1, kReportSlow = 2, kReportOneKey = 4, kReportMixed = 8, kReportStandIn = 16, kReportUneven = 32,
+constexpr u32 kReportSlow = 2, kReportOneKey = 4, kReportMixed = 8, kReportStandIn = 16, kReportUneven = 32,
               kReportCrowded = 64;
 
 // "Updated since the last dirty dump" is kept in the sign bit of a row's first
@@ -533,11 +533,11 @@ __device__ __forceinline__ void report_dedup(const UniqueSpans& spans, const Oft
   const u32 mean = s_sum / spans.n_spans;
   const bool uneven = ctx->by_id == 1 && s_most > mean + mean / 2 + 64;
   const bool crowded = uneven && (s_most > 3 * mean + 256 || ctx->n_slow > ctx->n_slow_one_key);
-  const u32 flags = (ctx->by_id == 1 ? kReportRange : ctx->by_id ? kReportStandIn : 0u) | ((u64)ctx->n_slow * 8 > ctx->n_total ? kReportSlow : 0u) |
+  const u32 flags = (ctx->by_id > 1 ? kReportStandIn : 0u) | ((u64)ctx->n_slow * 8 > ctx->n_total ? kReportSlow : 0u) |
                     ((u64)ctx->n_slow_one_key * 2 >= ctx->n_slow ? kReportOneKey : 0u) |
                     (uneven ? kReportUneven : 0u) | (crowded ? kReportCrowded : 0u) |
                     (!ctx->by_id && ctx->n_evidence > kMaxEvidence ? kReportMixed : 0u);
-  __hip_atomic_store(often.report, (unsigned long long)often.serial | ((unsigned long long)flags << 32),
+  __hip_atomic_store(often.report + (ctx->by_id == 1 ? 1 : 0), (unsigned long long)often.serial | ((unsigned long long)flags << 32),
                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
