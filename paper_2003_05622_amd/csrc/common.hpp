@@ -33,10 +33,16 @@ struct TableState {
   int error;                    // sticky: 0 or a negative status
   int absent;                   // distinct keys the last accumulate did not find
   unsigned long long dump_count;  // rows seen by the running dump
-  // Keys the running lookup found missing / rows the running insert created, spread
+  // Keys the running lookup found missing and left / rows the running insert created, spread
   // over shards so that blocks do not all hit one address.
   u32 miss_shard[kCountShards];
   u32 made_shard[kCountShards];
+  // Rows the running pull has created, in the set pulls take in turn (the end of a pull clears the other
+  // one for the next); size before it, and whether it might have overfilled the table (table.hpp: end_pull).
+  u32 pull_made[2][kCountShards];
+  unsigned long long size_before;
+  u32 tight;
+  u32 pad2;
   u32 pad;
   u32 probe_bad;                // result word of probe_lane_order (written once, at creation)
   // hps_probe_lengths: lines looked at to find each stored key, summed / the most for one key

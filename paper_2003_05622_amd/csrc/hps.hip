@@ -181,7 +181,7 @@ struct ContextLayout {
 };
 
 struct WorkspaceLayout {
-  size_t keys_a, keys_b, idx_a, idx_b, hist, prefix, total, tile_bag, heavy_raw, ghist,
+  size_t fresh, keys_a, keys_b, idx_a, idx_b, hist, prefix, total, tile_bag, heavy_raw, ghist,
       tickets, tile_rows, group_rows, head_rows, head_groups, evidence, bag_of, id16, by_pos, by_heavy, row_of,
       med_list, arrived, chunk_items, partials, end;
   size_t local_rank, rank_by_pos, rank_by_heavy, bucket_total, sort_ctx, sort_n;     // hps_last_unique's own
@@ -238,6 +238,7 @@ WorkspaceLayout workspace_layout(uint64_t n, uint64_t bags, uint32_t dim) {
   L.by_pos = o;      o = align_up(o + n1 * 4);      // row of the key at every position
   L.by_heavy = o;    o = align_up(o + (kMaxHeavy + 1) * 4);
   L.row_of = o;      o = align_up(o + n1 * 4);      // row of every occurrence
+  L.fresh = o;       o = align_up(o + n1);          // whether the pull created the key
   L.local_rank = o;    o = align_up(o + n1 * 4);
   L.rank_by_pos = o;   o = align_up(o + n1 * 4);
   L.rank_by_heavy = o; o = align_up(o + (kMaxHeavy + 1) * 4);
@@ -313,6 +314,7 @@ struct hps_table {
   int lpr;
   bool mean_pooling;        // bags are averaged instead of summed (hps_set_pooling)
   uint64_t lookup_serial;   // lookups so far; lookup s lists its frequent keys in ring slot s % 3
+  uint64_t pull_serial;     // pulls with bags so far: they take the two sets of counts in turn (common.hpp: pull_made)
   int dedup_mode;      // 0: by size and history; 1: plain radix passes always; 2, 3, 4: bucket form whenever it can, by range, borders, hash
   bool ordered_rank;   // the GPU's LDS atomics serve a wave's lanes in lane order (sort.hpp: digit_rank)
   // How much of pull_lookup's per-block list of created keys is used: all of it, unless
@@ -446,10 +448,11 @@ static void launch_pool(hps_table* t, int c, float* d_pooled, hipStream_t s) {
   // d = 16 runs the same with 1024 to 3072)
   const unsigned blocks = grid_for(cx.n_bags, kPoolThreads / LPR, kPoolMaxBlocks * (LPR > 4 ? LPR / 4 : 1));
   float* inv_len = cx.mean ? t->w<float>(C.inv_len) : nullptr;
+  const PullEnd end = {(u32)(t->pull_serial & 1), unique_spans(t, c, cx.n_keys), t->ctx(c), t->w<u32>(C.rows), t->w<uint8_t>(t->wl.fresh)};
   if (t->dim <= (uint32_t)LPR * 4)
-    pool_bags<LPR, 1><<<blocks, kPoolThreads, 0, s>>>(t->view, cx.d_offsets, (u32)cx.n_bags, (u32)cx.n_keys, row_of, d_pooled, inv_len);
+    pool_bags<LPR, 1><<<blocks, kPoolThreads, 0, s>>>(t->view, cx.d_offsets, (u32)cx.n_bags, (u32)cx.n_keys, row_of, d_pooled, inv_len, end);
   else
-    pool_bags<LPR, 4><<<blocks, kPoolThreads, 0, s>>>(t->view, cx.d_offsets, (u32)cx.n_bags, (u32)cx.n_keys, row_of, d_pooled, inv_len);
+    pool_bags<LPR, 4><<<blocks, kPoolThreads, 0, s>>>(t->view, cx.d_offsets, (u32)cx.n_bags, (u32)cx.n_keys, row_of, d_pooled, inv_len, end);
 }
 
 template <int LPR>
@@ -728,10 +731,14 @@ static void launch_lookup(hps_table* t, int c, uint64_t n_keys, bool create, hip
   often.serial = (u32)t->lookup_serial;
   const UniqueSpans spans = unique_spans(t, c, n_keys);
   const RowsByPosition out = rows_by_position_args(t, c, create);
+  Creation creation;
+  creation.how = !create ? kCreateNone : n_keys <= t->capacity / 4 ? kCreateAtOnce : kCreateIfRoom;
+  creation.set = (u32)(t->pull_serial & 1);
+  creation.fresh = t->w<uint8_t>(t->wl.fresh);
   pull_lookup<<<span_blocks(spans) + 1, kProbeThreads, 0, s>>>(t->view, t->w<u64>(C.uniq), t->w<u32>(C.seg_off), spans,
-                                                           t->w<u32>(C.rows), out, create ? 1u : 0u, t->lookup_new_cap, often);
-  if (create)
-    pull_missing<<<span_blocks(spans), kProbeThreads, 0, s>>>(t->view, t->w<u64>(C.uniq), spans, ctx, t->w<u32>(C.rows), out);
+                                                           t->w<u32>(C.rows), out, creation, t->lookup_new_cap, often);
+  if (creation.how == kCreateIfRoom)
+    pull_missing<<<span_blocks(spans), kProbeThreads, 0, s>>>(t->view, t->w<u64>(C.uniq), spans, ctx, t->w<u32>(C.rows), out, creation.set);
 }
 
 static void fill_push_args(hps_table* t, int c, uint64_t n_keys, const float* d_rows, int kind, PushArgs& a) {
@@ -888,7 +895,7 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   t->serial = 0;
   t->plain_serial = 0;
   t->mean_pooling = false;
-  t->lookup_serial = 0;
+  t->lookup_serial = t->pull_serial = 0;
   t->away = hps_table::kHotKeys;
   t->stand_in_from = 0;
   t->unlisted = 2;
@@ -1036,6 +1043,7 @@ hps_status hps_pull_prepared(hps_table* t, float* d_pooled, void* stream) {
   const hps_table::Context& other = t->cx[1 - c];
   if (other.released_set && hipStreamWaitEvent(s, other.released, 0) != hipSuccess) return HPS_EDEVICE;
   // a2: look up every unique key, create the missing ones
+  if (cx.n_bags) ++t->pull_serial;
   stage_mark(t, HPS_STAGE_LOOKUP, s);
   if (cx.n_keys) launch_lookup(t, c, cx.n_keys, true, s);
   if (!cx.n_bags) commit_insert<<<1, 64, 0, s>>>(t->view.st);   // else the pooling kernel does it

@@ -4,7 +4,7 @@
 // its share of the bag's gradient).  A group of LPR lanes owns one bag at a time;
 // each lane carries COLS float4 columns (lane*4 + k*LPR*4; COLS = 1 up to dim 256).
 // Eight occurrences are in flight at a time: their row numbers, then their rows.
-// Block 0 also books the rows the preceding lookup created.
+// The kernel also ends the pull (table.hpp: end_pull).
 #pragma once
 
 #include "common.hpp"
@@ -83,9 +83,8 @@ __device__ __forceinline__ void pool_bags_as(const TableView& t, const i32* __re
 template <int LPR, int COLS>
 __global__ void __launch_bounds__(kPoolThreads)
 pool_bags(TableView t, const i32* __restrict__ offsets, u32 n_bags, u32 n, const u32* __restrict__ row_of,
-          float* __restrict__ pooled, float* __restrict__ inv_len) {
-  if (load_error(t.st) != 0) return;
-  if (blockIdx.x == 0 && threadIdx.x < kWave) commit_insert_wave(t.st);
+          float* __restrict__ pooled, float* __restrict__ inv_len, PullEnd end) {
+  if (!end_pull(t, end)) return;
   if (t.bf16) pool_bags_as<LPR, COLS, true>(t, offsets, n_bags, n, row_of, pooled, inv_len);
   else pool_bags_as<LPR, COLS, false>(t, offsets, n_bags, n, row_of, pooled, inv_len);
 }

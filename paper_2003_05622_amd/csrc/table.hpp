@@ -8,12 +8,13 @@
 //   w[n_slots][dim]          f32 or bf16
 //   acc[n_slots][acc_len]    f32
 //
-// A lookup creates missing keys on the spot if the table has room even if every key it
-// looks up were new.  Otherwise creating them is a second kernel, so that the room check
-// against the capacity is one consistent decision and no block has to hit a single
-// counter: the lookup counts the missing keys into sharded counters, pull_missing or insert_missing
-// (every block reads the same total) claims slots only if all of them fit and counts
-// the rows it creates.  commit_insert adds the count of created rows to the table size.
+// A pull's lookup creates missing keys as it finds them.  Whether all of them fitted is known when it is over: the
+// pooling kernel behind it adds up what was created and, if the table ended above its capacity, takes all of it out
+// again (end_pull).  That takes slots for them in the meantime: capacity is 0.7 of the slots, so a mini-batch of up to a
+// quarter of it leaves one slot in eight free.  For larger ones, and in a bulk insert, keys are created on the spot only if the
+// table has room even if every one were new.  Otherwise creating them is a second kernel: the lookup counts
+// the missing keys into sharded counters, pull_missing or insert_missing (every block reads the same total)
+// claims slots only if all of them fit.  commit_insert adds an insert's count of created rows to the table size.
 // rows.hpp: the entry points that move rows by key or by slot (insert, get, dump).
 #pragma once
 
@@ -227,6 +228,10 @@ __global__ void __launch_bounds__(256) fill_u64(u64* __restrict__ p, u64 n, u64 
   for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (u64)gridDim.x * blockDim.x)
     p[i] = v;
 }
+__device__ __forceinline__ void clear_counts(TableState* st) {
+  if (threadIdx.x < kCountShards)
+    st->miss_shard[threadIdx.x] = st->made_shard[threadIdx.x] = st->pull_made[0][threadIdx.x] = st->pull_made[1][threadIdx.x] = 0;
+}
 __global__ void __launch_bounds__(64) reset_state(TableState* st) {
   if (threadIdx.x == 0) {
     st->size = 0;
@@ -234,12 +239,14 @@ __global__ void __launch_bounds__(64) reset_state(TableState* st) {
     st->error = 0;
     st->absent = 0;
     st->dump_count = 0;
+    st->size_before = 0;
+    st->tight = 0;
   }
-  if (threadIdx.x < kCountShards) st->miss_shard[threadIdx.x] = st->made_shard[threadIdx.x] = 0;
+  clear_counts(st);
 }
 __global__ void __launch_bounds__(64) clear_error(TableState* st) {
   if (threadIdx.x == 0) st->error = 0;
-  if (threadIdx.x < kCountShards) st->miss_shard[threadIdx.x] = st->made_shard[threadIdx.x] = 0;
+  clear_counts(st);
 }
 __global__ void clear_dump_count(TableState* st) { st->dump_count = 0; }
 __global__ void __launch_bounds__(64) set_ctx_empty(PullCtx* ctx, u32* seg_off) {
@@ -260,9 +267,8 @@ __global__ void __launch_bounds__(64) set_ctx_empty(PullCtx* ctx, u32* seg_off) 
   if (threadIdx.x < kCountShards) ctx->uniq_shard[threadIdx.x] = 0;
 }
 
-// Adds the rows that were created to the table size and clears the counters.
-// Called by one whole wave, after the kernels that create rows have finished.
-__device__ __forceinline__ void commit_insert_wave(TableState* st) {
+// After an insert's kernels: adds the rows that were created to the table size and clears the counters.
+__global__ void __launch_bounds__(64) commit_insert(TableState* st) {
   const u32 lane = lane_id();
   u32 made = lane < kCountShards ? st->made_shard[lane] : 0;
 #pragma unroll
@@ -273,7 +279,6 @@ __device__ __forceinline__ void commit_insert_wave(TableState* st) {
     st->inserted = made;
   }
 }
-__global__ void __launch_bounds__(64) commit_insert(TableState* st) { commit_insert_wave(st); }
 
 // After a lookup that creates nothing (accumulate): the number of keys not found
 // goes to st->absent, the counters are cleared.
@@ -541,13 +546,21 @@ __device__ __forceinline__ void report_dedup(const UniqueSpans& spans, const Oft
                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// How a lookup treats keys the table does not hold.
+constexpr u32 kCreateNone = 0, kCreateIfRoom = 1, kCreateAtOnce = 2;
+struct Creation {
+  u32 how;
+  u32 set;         // which of st->pull_made counts the created rows
+  uint8_t* fresh;  // per distinct key: created by this pull?  Written where the table might be overfilled
+};
+
 // rows[u] = the slot of distinct key u.  Keys the table does not hold:
-//  - create == 0 (accumulate): rows[u] = kNoRow, counted in st->miss_shard;
-//  - create != 0 and the table has room for all the keys even if every one of them is new: the
-//    key is created right here, with its initial row (the line is at hand, and so are its free
-//    slots), counted in st->made_shard;
-//  - create != 0 otherwise (a pull that might overfill the table): rows[u] = kNoRow, counted in
-//    st->miss_shard, for pull_missing, which creates all of them or none.
+//  - kCreateNone (accumulate): rows[u] = kNoRow, counted in st->miss_shard;
+//  - kCreateAtOnce: the key is created right here, with its initial row (the line is at hand, and so are its free
+//    slots), counted in st->pull_made; end_pull takes them all out again if the table ended above its capacity;
+//  - kCreateIfRoom (a mini-batch too large beside the table for that): the same if the table has room for all the
+//    keys even if every one of them is new, otherwise rows[u] = kNoRow, counted in st->miss_shard, for
+//    pull_missing, which creates all of them or none.
 // Also sorts the keys into the push's work lists by their number of occurrences, and (bucket form)
 // hands the rows on by position.  One span of distinct keys or group of heavy keys per block; the block behind
 // them reports on the dedup.
@@ -558,7 +571,7 @@ __device__ __forceinline__ void report_dedup(const UniqueSpans& spans, const Oft
 // (search_keys).
 __global__ void __launch_bounds__(kProbeThreads)
 pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ seg_off, UniqueSpans spans,
-            u32* __restrict__ rows, RowsByPosition out, u32 create, u32 new_cap, OftenLists often) {
+            u32* __restrict__ rows, RowsByPosition out, Creation create, u32 new_cap, OftenLists often) {
   // new_cap <= kNewLdsCap: how much of the block's list of created keys is used (all of it,
   // except in tests of what happens when it is full)
   constexpr int K = kPullInFlight;            // keys a group has in flight
@@ -569,7 +582,13 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ s
   __shared__ u64 s_new_key[kNewLdsCap];       // keys created by this block, and their rows
   __shared__ u32 s_new_row[kNewLdsCap];
   PullCtx* ctx = often.ctx;
+  // (the size does not change while this kernel runs: every thread decides the same)
+  const bool tight = create.how == kCreateAtOnce && t.st->size + ctx->n_total > t.capacity;
   if (blockIdx.x == span_blocks(spans)) {
+    if (threadIdx.x == 0 && create.how != kCreateNone) {
+      t.st->size_before = t.st->size;
+      t.st->tight = tight ? 1u : 0u;
+    }
     report_dedup(spans, often);
     return;
   }
@@ -586,14 +605,13 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ s
   else unique_span(spans, ctx, c, &first, &count);
   if (count == 0) return;
   if (threadIdx.x == 0) { s_missing = 0; s_med = 0; s_made = 0; s_new = 0; s_long = 0; }
-  if (threadIdx.x < kWave) {
+  if (create.how == kCreateIfRoom && threadIdx.x < kWave) {
     // (kCountShards == kWave) distinct keys of the whole mini-batch
     const u32 u = wave_incl_sum(ctx->uniq_shard[threadIdx.x]);
     if (threadIdx.x == kWave - 1) s_unique = ctx->by_id ? u : ctx->n_unique;
   }
   __syncthreads();
-  // (the size does not change while this kernel runs: every thread decides the same)
-  const bool create_here = create && t.st->size + s_unique <= t.capacity;
+  const bool create_here = create.how == kCreateAtOnce || (create.how == kCreateIfRoom && t.st->size + s_unique <= t.capacity);
   const u32 sub = threadIdx.x % kLookupLanes;
   const u32 lane0 = lane_id() & ~3u;          // the group's first lane
   u32 made = 0, missing = 0;
@@ -602,7 +620,7 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ s
     const u32 k = k0 + sub;
     u64 my_key = kEmptyKey, my_line;
     u32 my_len = 0, my_row, my_free, u = 0;
-    bool on = k < count;
+    bool on = k < count, mine_new = false;
     if (heavies) {
       const u32 h = h0 + k;
       if (on) {
@@ -652,6 +670,7 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ s
         u32 at = 0;
         if (sub == (u32)q) {
           my_row = row;
+          mine_new = true;
           ++made;
           at = atomicAdd(&s_new, 1u);
           if (at < new_cap) { s_new_key[at] = key; s_new_row[at] = row; }
@@ -667,6 +686,7 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ s
     // every lane: the row of its own key, and the push's work lists
     if (!on) continue;
     rows[u] = my_row;
+    if (tight) create.fresh[u] = mine_new ? 1 : 0;
     if (heavies && out.upos) out.by_heavy[h0 + k] = my_row;
     if (my_row == kNoRow) ++missing;
     if (my_len >= often.heavy_min && my_key != kEmptyKey) {
@@ -696,7 +716,7 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ s
   if (missing) atomicAdd(&s_missing, missing);
   __syncthreads();
   if (threadIdx.x == 0) {
-    if (s_made) atomicAdd(&t.st->made_shard[blockIdx.x % kCountShards], s_made);
+    if (s_made) atomicAdd(&t.st->pull_made[create.set][blockIdx.x % kCountShards], s_made);
     if (s_missing) atomicAdd(&t.st->miss_shard[blockIdx.x % kCountShards], s_missing);
     if (s_med) s_med_base = atomicAdd(&ctx->n_med, min(s_med, kMedLdsCap));
   }
@@ -783,7 +803,7 @@ insert_missing(TableView t, const u64* __restrict__ keys, u64 n_keys, const floa
 // keys of 2.8 M, 140 us; 278 with every group looking for its own).
 __global__ void __launch_bounds__(kProbeThreads)
 pull_missing(TableView t, const u64* __restrict__ keys, UniqueSpans spans, const PullCtx* __restrict__ ctx,
-             u32* __restrict__ rows, RowsByPosition out) {
+             u32* __restrict__ rows, RowsByPosition out, u32 set) {
   constexpr u32 kList = 1024;
   __shared__ u32 s_word, s_made, s_n;
   __shared__ u32 s_list[kList];
@@ -823,8 +843,55 @@ pull_missing(TableView t, const u64* __restrict__ keys, UniqueSpans spans, const
   }
   if (sub == 0 && made) atomicAdd(&s_made, made);
   __syncthreads();
-  if (threadIdx.x == 0 && s_made) atomicAdd(&t.st->made_shard[blockIdx.x % kCountShards], s_made);
+  if (threadIdx.x == 0 && s_made) atomicAdd(&t.st->pull_made[set][blockIdx.x % kCountShards], s_made);
   if (out.upos && !heavies) rows_by_position(spans, out, c, first, rows);
+}
+
+// What the pooling kernel, the last one of a pull, needs to end it.
+struct PullEnd {
+  u32 set;                 // of st->pull_made
+  UniqueSpans spans;
+  const PullCtx* ctx;
+  const u32* rows;
+  const uint8_t* fresh;
+};
+// All threads of all blocks, before anything else.  Books the rows the lookup created -- or, if the table ended above
+// its capacity, raises kErrFull and takes them out of it (nothing else has been put behind them: the table
+// is as before).  Every block adds up the same counts, so all come to the same end, whichever raises the error
+// first.  Returns false if the pull has failed, now or before.
+__device__ __forceinline__ bool end_pull(const TableView& t, const PullEnd& e) {
+  static_assert(kCountShards == kWave, "a count per lane");
+  const int error = load_error(t.st);
+  const u32 tight = t.st->tight, mine = t.st->pull_made[e.set][lane_id()];
+  if (!tight && blockIdx.x != 0) return error == 0;
+  const u32 made = (u32)__builtin_amdgcn_readlane((int)wave_incl_sum(mine), kWave - 1);
+  const bool overfull = tight && t.st->size_before + made > t.capacity;
+  if (blockIdx.x == 0 && threadIdx.x < kWave) {
+    t.st->pull_made[1 - e.set][threadIdx.x] = 0;
+    t.st->miss_shard[threadIdx.x] = 0;
+    if (threadIdx.x == 0 && error == 0 && !overfull) {
+      t.st->size += made;
+      t.st->inserted = made;
+    }
+  }
+  if (!overfull) return error == 0;
+  if (threadIdx.x == 0) raise_error(t.st, kErrFull);
+  for (u32 b = blockIdx.x; b < span_blocks(e.spans); b += gridDim.x) {
+    const bool heavies = b < heavy_blocks(e.spans);
+    const u32 h0 = b * kHeavyGroup;
+    u32 first = 0, count;
+    if (heavies) count = e.ctx->n_heavy > h0 ? min(kHeavyGroup, e.ctx->n_heavy - h0) : 0u;
+    else unique_span(e.spans, e.ctx, b - heavy_blocks(e.spans), &first, &count);
+    for (u32 k = threadIdx.x; k < count; k += blockDim.x) {
+      u32 u = first + k;
+      if (heavies) {
+        u = e.spans.bucket_start[e.spans.n_spans + h0 + k];
+        if (e.spans.bucket_start[e.spans.n_spans + h0 + k + 1] == u) continue;
+      }
+      if (e.fresh[u]) t.keys[e.rows[u]] = kEmptyKey;
+    }
+  }
+  return false;
 }
 
 // How many buckets (pairs of lines: 128 bytes) a lookup reads to find each stored key (1 = the

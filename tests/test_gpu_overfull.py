@@ -1,0 +1,65 @@
+"""Pulls that end with more keys than the table's capacity: nothing of them stays in the table, whatever the dedup's form, and
+pulls that just fit go through.  Bags of 18 to 100 initial rows |w| <= 0.01, changed by few steps: sums of at most 100 terms,
+within the float32 tolerance of the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2003_05622_amd as hps
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.uint64).view(np.int64)).cuda()
+
+
+@pytest.mark.parametrize("form", ["auto", "bucket", "hashed", "radix"])
+@pytest.mark.parametrize("n", [900, 5000, 70_000])
+def test_overfull_pulls_leave_no_trace(n, form, monkeypatch):
+    monkeypatch.setenv("HPS_DEDUP", form)
+    dim, n_bags, cap = 4, max(50, n // 100), 5 * n - n // 3        # (n is less than a quarter of the capacity)
+    rng = np.random.default_rng(n)
+    gt, ot = hps.HpsTable(cap, dim, n, n_bags), oracle.OracleTable(cap, dim)
+    offsets = (np.arange(n_bags + 1, dtype=np.int64) * n // n_bags).astype(np.int32)
+    d_offsets = torch.from_numpy(offsets).cuda()
+
+    def ids(first, last):
+        return synth.mix64(np.arange(first, last, dtype=np.uint64))
+
+    def pull(keys, fits):
+        pooled = gt.pull(dev(keys), d_offsets, n_bags, 1)
+        st = gt.stats()
+        if not fits:
+            assert st.error == hps.EFULL and st.size == ot.size
+            gt.clear_error()
+            assert gt.stats().size == ot.size
+            found = gt.get(dev(keys))[2].cpu().numpy()
+            assert np.array_equal(found, ot.get(keys)[2])
+            return
+        want = ot.pull(keys, offsets)
+        assert st.error == 0 and st.size == ot.size
+        assert np.all(np.abs(pooled.cpu().numpy() - want) <= 1e-6 + 1e-5 * np.abs(want))
+        grads = rng.normal(size=(n_bags, dim)).astype(np.float32) * 1e-3
+        gt.push(torch.from_numpy(grads).cuda())
+        ot.push(grads)
+
+    at = 0
+    while ot.size + n <= cap:
+        pull(ids(at, at + n), True)
+        at += n
+    room = cap - ot.size
+    pull(rng.permutation(np.concatenate([ids(at, at + room + 1), ids(0, n - room - 1)])), False)
+    pull(rng.permutation(np.resize(ids(at, at + room - 3), n)), True)
+    pull(rng.permutation(np.resize(ids(at, at + room + 1), n)), False)
+    pull(rng.permutation(np.resize(ids(at, at + room), n)), True)
+    pull(rng.permutation(np.resize(ids(at, at + room), n)), True)
+    pull(rng.permutation(np.resize(ids(at, at + room + 1), n)), False)
+    k, w, a = gt.dump()
+    order = np.argsort(k.cpu().numpy().view(np.uint64))
+    ok, ow, oa = ot.dump()
+    assert np.array_equal(k.cpu().numpy().view(np.uint64)[order], ok)
+    assert np.all(np.abs(w.cpu().numpy()[order] - ow) <= 1e-6 + 1e-5 * np.abs(ow))
+    assert np.all(np.abs(a.cpu().numpy()[order] - oa) <= 1e-6 + 1e-5 * np.abs(oa))
