@@ -67,7 +67,8 @@
  *     a dedup is the occurrences grouped by key; the ascending order of the unique keys is
  *     worked out when hps_last_unique asks for it.
  *   - Environment variables, read by hps_create, for tests and comparison runs:
- *     HPS_DEDUP = "radix" | "bucket" | "borders" | "hashed" pins the dedup's form; HPS_RANK = "ballot" ranks the
+ *     HPS_DEDUP = "radix" | "bucket" | "borders" | "hashed" | "small" (up to 65536 occurrences, beyond "hashed") pins the
+ *     dedup's form; HPS_RANK = "ballot" ranks the
  *     elements of a sort tile with wave ballots even where the GPU's LDS atomics would
  *     serve (the faster way; hps_create checks on every GPU that they answer the lanes of
  *     an instruction in lane order, and uses ballots where they do not);

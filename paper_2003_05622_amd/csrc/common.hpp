@@ -135,6 +135,10 @@ __device__ __forceinline__ float init_weight(u64 base, u32 j, float a) {
 
 __device__ __forceinline__ u32 lane_id() { return threadIdx.x & (kWave - 1); }
 
+// The value a lane of the wave holds (`lane` the same in all of them).
+__device__ __forceinline__ u32 wave_lane(u32 v, int lane) { return (u32)__builtin_amdgcn_readlane((int)v, lane); }
+__device__ __forceinline__ u64 wave_lane(u64 v, int lane) { return wave_lane((u32)v, lane) | (u64)wave_lane((u32)(v >> 32), lane) << 32; }
+
 __device__ __forceinline__ u64 lanemask_lt() {
   const u32 l = lane_id();
   return l == 0 ? 0ull : (~0ull >> (64 - l));

@@ -24,6 +24,7 @@
 #include "pool.hpp"
 #include "push.hpp"
 #include "rows.hpp"
+#include "small.hpp"
 #include "sort.hpp"
 #include "table.hpp"
 #include "mem_tier.hpp"
@@ -177,6 +178,7 @@ int lanes_per_row(uint32_t dim) {
 struct ContextLayout {
   size_t ctx, uniq, rows, bags, seg_off, inv_len;
   size_t code, from, upos, bucket_start, count, border;      // bucket form
+  size_t places;                                     // small form
   size_t inverse;                                    // plain form (shares its memory with `code`)
 };
 
@@ -207,7 +209,7 @@ WorkspaceLayout workspace_layout(uint64_t n, uint64_t bags, uint32_t dim) {
   L.keys_b = o;      o = align_up(o + n1 * 8);
   L.idx_a = o;       o = align_up(o + n1 * 8);    // payloads: occurrence index | bag << 32
   L.idx_b = o;       o = align_up(o + n1 * 8);
-  L.hist = o;        o = align_up(o + max_counts(n1) * 2);    // bucket form: counts per (tile, bucket)
+  L.hist = o;        o = align_up(o + std::max<uint64_t>(max_counts(n1), kSmallHistWords) * 2);    // bucket and small form: counts per (tile, bucket)
   L.prefix = o;      o = align_up(o + max_counts(n1) * 4);    // ... and those of the tiles before
   L.total = o;       o = align_up(o + buckets * 4);
   L.tile_bag = o;    o = align_up(o + 1025 * 4);
@@ -234,6 +236,7 @@ WorkspaceLayout workspace_layout(uint64_t n, uint64_t bags, uint32_t dim) {
     L.c[k].bucket_start = o; o = align_up(o + (buckets + 1) * 4);
     L.c[k].count = o;   o = align_up(o + buckets * 4);
     L.c[k].border = o;  o = align_up(o + kMaxBorders * 8);
+    L.c[k].places = o;  o = align_up(o + std::min<uint64_t>(n1, kSmallMax) * 16);
   }
   L.by_pos = o;      o = align_up(o + n1 * 4);      // row of the key at every position
   L.by_heavy = o;    o = align_up(o + (kMaxHeavy + 1) * 4);
@@ -260,6 +263,7 @@ uint32_t tile_group(uint64_t n_tiles) {
   return g;
 }
 
+constexpr uint32_t kQuiet = 3;           // dedups without an hps_last_unique until a caller is taken not to want it
 constexpr uint64_t kPlainHold = 32;      // dedups in the plain form after the bucket form disappointed
 constexpr uint64_t kHintLag = 3;         // ... after a surprise that the next lists of frequent keys will cover
 
@@ -315,7 +319,8 @@ struct hps_table {
   bool mean_pooling;        // bags are averaged instead of summed (hps_set_pooling)
   uint64_t lookup_serial;   // lookups so far; lookup s lists its frequent keys in ring slot s % 3
   uint64_t pull_serial;     // pulls with bags so far: they take the two sets of counts in turn (common.hpp: pull_made)
-  int dedup_mode;      // 0: by size and history; 1: plain radix passes always; 2, 3, 4: bucket form whenever it can, by range, borders, hash
+  int dedup_mode;      // 0: by size and history; 1: plain radix passes always; 2, 3, 4: bucket form whenever it can, by range, borders, hash;
+                       // 5: small form up to kSmallMax, beyond by hash
   bool ordered_rank;   // the GPU's LDS atomics serve a wave's lanes in lane order (sort.hpp: digit_rank)
   // How much of pull_lookup's per-block list of created keys is used: all of it, unless
   // HPS_LOOKUP_NEW_LIST says less (tests of what happens when it is full).
@@ -342,7 +347,8 @@ struct hps_table {
   // stand-ins have disappointed too (dedups numbered below stand_in_from).
   enum Away { kHotKeys, kSlowBuckets, kUnevenKeys, kCrowdedKeys } away;
   uint64_t stand_in_from;
-  uint32_t unlisted;        // dedups since the last hps_last_unique
+  uint32_t unlisted;        // dedups since the last hps_last_unique (or the creation)
+  int listing_pinned;       // 0, or since an hps_last_unique was captured: 1 in an order of keys, 2 by hash
   // The same for the plain form itself: after a dedup whose keys agreed in all the bits the
   // plain form sorts by (table.hpp: kReportMixed), the following ones sort by all 64 bits.
   uint32_t full_strikes;
@@ -355,8 +361,9 @@ struct hps_table {
     uint64_t n_keys, n_bags;
     const int32_t* d_offsets;
     bool mean;            // pooling of this pull (fixed when it is prepared)
+    bool looked_up;       // its dedup included the lookup (small form)
     bool buckets;         // its dedup took the bucket form ...
-    int form;             // ... by range, borders or hash (partition.hpp)
+    int form;             // ... by range, borders or hash (partition.hpp), or the small form (kSmallForm)
     BucketPlan plan;      // ... with these sizes ...
     hipEvent_t ready;     // recorded after the dedup kernels
     hipEvent_t released;  // recorded after the push that used the context
@@ -380,6 +387,7 @@ struct hps_table {
 };
 
 namespace {
+constexpr int kSmallForm = 3;        // beside kByRange, kByBorders, kByHash
 constexpr size_t kMaxEventPairs = 4096;
 
 void stage_mark(hps_table* t, int stage, hipStream_t s) {
@@ -435,9 +443,13 @@ static void launch_pool(hps_table* t, int c, float* d_pooled, hipStream_t s) {
   const hps_table::Context& cx = t->cx[c];
   const ContextLayout& C = t->wl.c[c];
   u32* row_of = t->w<u32>(t->wl.row_of);
+  uint4* places = t->w<uint4>(C.places);
+  const bool small = cx.n_keys && cx.buckets && cx.form == kSmallForm;
   if (cx.n_keys) {
     const u32 n = (u32)cx.n_keys;
-    if (cx.buckets)
+    if (small) {
+      if (!cx.looked_up) small_rows<<<grid_for(n, 256, 256), 256, 0, s>>>(t->view.st, t->w<u32>(C.rows), n, places);
+    } else if (cx.buckets)
       launch_spread(t->w<u32>(C.code), t->w<uint16_t>(C.from), n, cx.plan.n_tiles, t->w<u32>(t->wl.by_pos),
                     t->w<u32>(t->wl.by_heavy), row_of, s);
     else
@@ -449,10 +461,12 @@ static void launch_pool(hps_table* t, int c, float* d_pooled, hipStream_t s) {
   const unsigned blocks = grid_for(cx.n_bags, kPoolThreads / LPR, kPoolMaxBlocks * (LPR > 4 ? LPR / 4 : 1));
   float* inv_len = cx.mean ? t->w<float>(C.inv_len) : nullptr;
   const PullEnd end = {(u32)(t->pull_serial & 1), unique_spans(t, c, cx.n_keys), t->ctx(c), t->w<u32>(C.rows), t->w<uint8_t>(t->wl.fresh)};
-  if (t->dim <= (uint32_t)LPR * 4)
-    pool_bags<LPR, 1><<<blocks, kPoolThreads, 0, s>>>(t->view, cx.d_offsets, (u32)cx.n_bags, (u32)cx.n_keys, row_of, d_pooled, inv_len, end);
-  else
-    pool_bags<LPR, 4><<<blocks, kPoolThreads, 0, s>>>(t->view, cx.d_offsets, (u32)cx.n_bags, (u32)cx.n_keys, row_of, d_pooled, inv_len, end);
+  u32* bags = t->w<u32>(C.bags);
+#define HPS_POOL(COLS, SMALL) \
+  pool_bags<LPR, COLS, SMALL><<<blocks, kPoolThreads, 0, s>>>(t->view, cx.d_offsets, (u32)cx.n_bags, (u32)cx.n_keys, row_of, d_pooled, inv_len, places, bags, end)
+  if (t->dim <= (uint32_t)LPR * 4) { if (small) HPS_POOL(1, true); else HPS_POOL(1, false); }
+  else { if (small) HPS_POOL(4, true); else HPS_POOL(4, false); }
+#undef HPS_POOL
 }
 
 template <int LPR>
@@ -528,14 +542,83 @@ static void launch_buckets(hps_table* t, int c, const uint64_t* d_keys, u32 n, c
 #undef HPS_ORDERED
 }
 
+// Whether a pull's lookup may create keys as it finds them (table.hpp: end_pull).
+static bool creates_at_once(const hps_table* t, uint64_t n_keys) { return n_keys <= t->capacity / 4; }
+
+// What a lookup of context c, of n_keys occurrences, works with besides the keys: the lists it fills (it counts as a lookup) and
+// how it treats missing keys.
+static OftenLists start_lookup(hps_table* t, int c, uint64_t n_keys) {
+  HeavyRing* ring = t->w<HeavyRing>(t->wl.heavy_raw);
+  OftenLists often;
+  often.ctx = t->ctx(c);
+  often.med_list = t->w<u32>(t->wl.med_list);
+  often.chunk_items = t->w<uint4>(t->wl.chunk_items);
+  often.arrived = t->w<u32>(t->wl.arrived);
+  often.pieces = piece_sizes((u32)t->lpr, n_keys);
+  ++t->lookup_serial;
+  often.heavy_raw = &ring->raw[t->lookup_serial % kHeavyRing];
+  often.heavy_next = &ring->raw[(t->lookup_serial + 1) % kHeavyRing];
+  often.heavy_min = heavy_min(n_keys);
+  often.report = t->report;
+  often.serial = (u32)t->lookup_serial;
+  return often;
+}
+static Creation creation_of(const hps_table* t, uint64_t n_keys, bool create) {
+  Creation k;
+  k.how = !create ? kCreateNone : creates_at_once(t, n_keys) ? kCreateAtOnce : kCreateIfRoom;
+  k.set = (u32)(t->pull_serial & 1);
+  k.new_cap = t->lookup_new_cap;
+  k.fresh = t->w<uint8_t>(t->wl.fresh);
+  return k;
+}
+
+// What a dedup includes besides (small form).
+enum Include { kDedupOnly, kWithPullLookup, kWithAddLookup };
+
+// The small form (small.hpp).
+template <bool LOOKUP>
+static void launch_small(hps_table* t, int c, const uint64_t* d_keys, u32 n, bool own_bags, Include include, hipStream_t s) {
+  const WorkspaceLayout& L = t->wl;
+  const ContextLayout& C = L.c[c];
+  SmallArgs a;
+  a.keys = d_keys;
+  a.n = n;
+  a.log2_nat = kSmallMinLog2;
+  while (n > kSmallMean << a.log2_nat) ++a.log2_nat;
+  a.n_tiles = (n + kSmallTile - 1) / kSmallTile;
+  a.own_bags = own_bags ? 1u : 0u;
+  a.ctx = t->ctx(c);
+  a.ids = t->w<uint8_t>(L.id16);
+  a.hist = t->w<uint16_t>(L.hist);
+  a.bucket_start = t->w<u32>(C.bucket_start);
+  a.count = t->w<u32>(C.count);
+  a.uniq = t->w<u64>(C.uniq);
+  a.seg_off = t->w<u32>(C.seg_off);
+  a.bags = t->w<u32>(C.bags);
+  a.places = own_bags ? nullptr : t->w<uint4>(C.places);
+  a.dealt = t->w<u64>(L.keys_a);
+  a.upos = t->w<u32>(C.upos);
+  a.slow = {t->w<u64>(L.idx_a), t->w<u64>(L.keys_b), t->w<u64>(L.idx_b)};
+  a.rows = t->w<u32>(C.rows);
+  a.create = LOOKUP ? creation_of(t, n, include == kWithPullLookup) : Creation();
+  a.often = LOOKUP ? start_lookup(t, c, n) : OftenLists();
+  BucketPlan& plan = t->cx[c].plan;
+  plan.n_nat = 1u << a.log2_nat;
+  plan.max_heavy = plan.stride = plan.n_tiles = 0;
+  small_ids<<<a.n_tiles, kSmallTile, 0, s>>>(t->view, a);
+  if (t->ordered_rank) small_group<LOOKUP, true><<<plan.n_nat, kSmallThreads, 0, s>>>(t->view, a);
+  else small_group<LOOKUP, false><<<plan.n_nat, kSmallThreads, 0, s>>>(t->view, a);
+}
+
 // a1 for context c: the kernels that turn (keys, offsets) into the distinct keys and the
 // occurrences' bags grouped by key.  d_offsets == nullptr: every occurrence is its own bag.
+// `include`: what the small form may do besides; cx[c].looked_up tells whether it did.
 static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
-                         const int32_t* d_offsets, u32 n_bags, hipStream_t s) {
+                         const int32_t* d_offsets, u32 n_bags, Include include, hipStream_t s) {
   const WorkspaceLayout& L = t->wl;
   const ContextLayout& C = L.c[c];
   PullCtx* ctx = t->ctx(c);
-  t->cx[c].buckets = false;
+  t->cx[c].buckets = t->cx[c].looked_up = false;
   if (n == 0) {
     set_ctx_empty<<<1, 64, 0, s>>>(ctx, t->w<u32>(C.seg_off));
   } else {
@@ -548,7 +631,8 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
     // The bucket path needs to know the heavy keys, which it learns from the lookups: the
     // first two dedups of a table take the plain passes, as do very large ones.
     const bool small = n <= kBorderMaxKeys, lists = t->unlisted < 2;       // (the next dedup may come before the call)
-    if (t->unlisted < 2) ++t->unlisted;
+    const bool quiet = t->listing_pinned ? t->listing_pinned == 2 : t->unlisted >= kQuiet;
+    if (t->unlisted < kQuiet) ++t->unlisted;
     if (t->dedup_mode == 0) {
       // (the other forms' word first: what it tells of came after whatever the range's word then does not tell of)
       const unsigned long long other = __atomic_load_n(t->report, __ATOMIC_ACQUIRE), range = __atomic_load_n(t->report + 1, __ATOMIC_RELAXED);
@@ -607,8 +691,21 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
     // by range 327, 402, 1494 and 5822 us, by hash 76, 104, 263 and 940, plain 126, 187, 391 and 1270, by borders 118 and 161; ids whose
     // density rises from none to twice the mean: by range 90, 125, 740 and 2057, by hash 76, 104, 279 and 900.
     // Listing the unique keys: 18 to 40 us by borders, in the plain form 5 to 20, by hash 620 for 4 M distinct keys.)
+    if (n <= kSmallMax && (t->dedup_mode == 5 || (t->dedup_mode == 0 && quiet && t->serial >= t->stand_in_from))) {
+      t->cx[c].buckets = true;
+      t->cx[c].form = kSmallForm;
+      t->cx[c].looked_up = include != kDedupOnly;
+      if (include == kWithPullLookup) ++t->pull_serial;
+      const bool own_bags = d_offsets == nullptr;
+      if (include == kDedupOnly) launch_small<false>(t, c, d_keys, n, own_bags, include, s);
+      else launch_small<true>(t, c, d_keys, n, own_bags, include, s);
+      stage_mark(t, HPS_STAGE_SORT, s);
+      stage_mark(t, HPS_STAGE_UNIQUE, s);
+      stage_mark(t, HPS_STAGE_UNIQUE, s);
+      return;
+    }
     const bool hinted = n <= kBucketPathMaxKeys && t->dedup_mode != 1 && (t->dedup_mode >= 2 || t->lookup_serial >= 2);
-    int form = t->dedup_mode == 3 && small ? kByBorders : t->dedup_mode == 4 ? kByHash : kByRange;
+    int form = t->dedup_mode == 3 && small ? kByBorders : t->dedup_mode >= 4 ? kByHash : kByRange;
     bool buckets = hinted;
     const bool away = t->dedup_mode == 0 && (t->serial < t->range_from || t->probe);
     if (hinted && t->dedup_mode == 0 && !away && t->to_probe) {
@@ -705,7 +802,7 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
 static RowsByPosition rows_by_position_args(const hps_table* t, int c, bool pull) {
   const hps_table::Context& cx = t->cx[c];
   RowsByPosition out;
-  out.upos = pull && cx.buckets ? t->w<u32>(t->wl.c[c].upos) : nullptr;
+  out.upos = pull && cx.buckets && cx.form != kSmallForm ? t->w<u32>(t->wl.c[c].upos) : nullptr;
   out.by_pos = t->w<u32>(t->wl.by_pos);
   out.by_heavy = t->w<u32>(t->wl.by_heavy);
   return out;
@@ -715,30 +812,15 @@ static RowsByPosition rows_by_position_args(const hps_table* t, int c, bool pull
 // `create`, does not get) and the push's work lists.
 static void launch_lookup(hps_table* t, int c, uint64_t n_keys, bool create, hipStream_t s) {
   const ContextLayout& C = t->wl.c[c];
-  PullCtx* ctx = t->ctx(c);
-  HeavyRing* ring = t->w<HeavyRing>(t->wl.heavy_raw);
-  OftenLists often;
-  often.ctx = ctx;
-  often.med_list = t->w<u32>(t->wl.med_list);
-  often.chunk_items = t->w<uint4>(t->wl.chunk_items);
-  often.arrived = t->w<u32>(t->wl.arrived);
-  often.pieces = piece_sizes((u32)t->lpr, n_keys);
-  ++t->lookup_serial;
-  often.heavy_raw = &ring->raw[t->lookup_serial % kHeavyRing];
-  often.heavy_next = &ring->raw[(t->lookup_serial + 1) % kHeavyRing];
-  often.heavy_min = heavy_min(n_keys);
-  often.report = t->report;
-  often.serial = (u32)t->lookup_serial;
+  if (t->cx[c].looked_up) return;
+  const OftenLists often = start_lookup(t, c, n_keys);
+  const Creation creation = creation_of(t, n_keys, create);
   const UniqueSpans spans = unique_spans(t, c, n_keys);
   const RowsByPosition out = rows_by_position_args(t, c, create);
-  Creation creation;
-  creation.how = !create ? kCreateNone : n_keys <= t->capacity / 4 ? kCreateAtOnce : kCreateIfRoom;
-  creation.set = (u32)(t->pull_serial & 1);
-  creation.fresh = t->w<uint8_t>(t->wl.fresh);
   pull_lookup<<<span_blocks(spans) + 1, kProbeThreads, 0, s>>>(t->view, t->w<u64>(C.uniq), t->w<u32>(C.seg_off), spans,
-                                                           t->w<u32>(C.rows), out, creation, t->lookup_new_cap, often);
+                                                           t->w<u32>(C.rows), out, creation, often);
   if (creation.how == kCreateIfRoom)
-    pull_missing<<<span_blocks(spans), kProbeThreads, 0, s>>>(t->view, t->w<u64>(C.uniq), spans, ctx, t->w<u32>(C.rows), out, creation.set);
+    pull_missing<<<span_blocks(spans), kProbeThreads, 0, s>>>(t->view, t->w<u64>(C.uniq), spans, t->ctx(c), t->w<u32>(C.rows), out, creation.set);
 }
 
 static void fill_push_args(hps_table* t, int c, uint64_t n_keys, const float* d_rows, int kind, PushArgs& a) {
@@ -882,7 +964,7 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   for (int k = 0; k < 2; ++k) {
     t->cx[k].n_keys = t->cx[k].n_bags = 0;
     t->cx[k].d_offsets = nullptr;
-    t->cx[k].buckets = false;
+    t->cx[k].buckets = t->cx[k].looked_up = false;
     t->cx[k].ready_set = t->cx[k].released_set = t->cx[k].listed = false;
     events_ok = events_ok &&
                 hipEventCreateWithFlags(&t->cx[k].ready, hipEventDisableTiming) == hipSuccess &&
@@ -898,7 +980,8 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   t->lookup_serial = t->pull_serial = 0;
   t->away = hps_table::kHotKeys;
   t->stand_in_from = 0;
-  t->unlisted = 2;
+  t->unlisted = 0;
+  t->listing_pinned = 0;
   t->range_seen = t->other_seen = t->judged = t->probe = 0;
   t->to_probe = false;
   t->strikes = 0;
@@ -915,10 +998,11 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   }
   t->report[0] = t->report[1] = 0;
   {
-    // HPS_DEDUP=radix / bucket / borders / hashed pins the dedup to one of its forms (comparison runs, tests)
+    // HPS_DEDUP=radix / bucket / borders / hashed / small pins the dedup to one of its forms (comparison runs, tests)
     const char* mode = std::getenv("HPS_DEDUP");
     t->dedup_mode = !mode ? 0 : std::strcmp(mode, "radix") == 0 ? 1 : std::strcmp(mode, "bucket") == 0 ? 2
-                    : std::strcmp(mode, "borders") == 0 ? 3 : std::strcmp(mode, "hashed") == 0 ? 4 : 0;
+                    : std::strcmp(mode, "borders") == 0 ? 3 : std::strcmp(mode, "hashed") == 0 ? 4
+                    : std::strcmp(mode, "small") == 0 ? 5 : 0;
   }
 
   t->lookup_new_cap = kNewLdsCap;
@@ -1000,9 +1084,10 @@ static bool after_listing(hps_table* t, int c, hipStream_t s) {
   return true;
 }
 
-hps_status hps_prepare(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
-                       const int32_t* d_offsets, uint32_t n_examples, uint32_t n_slots,
-                       void* stream) {
+// include: kDedupOnly, or kWithPullLookup where hps_pull_prepared follows on the same stream at once.
+static hps_status prepare(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
+                          const int32_t* d_offsets, uint32_t n_examples, uint32_t n_slots,
+                          Include include, void* stream) {
   if (!mini_batch_ok(t, d_keys, n_keys, d_offsets, n_examples, n_slots)) return HPS_EINVAL;
   const uint64_t n_bags = (uint64_t)n_examples * n_slots;
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1014,8 +1099,11 @@ hps_status hps_prepare(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
   if (cx.released_set && hipStreamWaitEvent(s, cx.released, 0) != hipSuccess) return HPS_EDEVICE;
   if (t->scratch_set && hipStreamWaitEvent(s, t->scratch_free, 0) != hipSuccess) return HPS_EDEVICE;
   if (!after_listing(t, c, s)) return HPS_EDEVICE;
+  // (a lookup among it: what hps_pull_prepared orders it after)
+  const hps_table::Context& other = t->cx[1 - c];
+  if (include != kDedupOnly && other.released_set && hipStreamWaitEvent(s, other.released, 0) != hipSuccess) return HPS_EDEVICE;
 
-  launch_dedup(t, c, d_keys, n, d_offsets, (u32)n_bags, s);
+  launch_dedup(t, c, d_keys, n, d_offsets, (u32)n_bags, include, s);
   if (!launch_ok()) return HPS_EDEVICE;
   if (hipEventRecord(cx.ready, s) != hipSuccess || hipEventRecord(t->scratch_free, s) != hipSuccess)
     return HPS_EDEVICE;
@@ -1027,6 +1115,12 @@ hps_status hps_prepare(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
   cx.mean = t->mean_pooling;
   t->prepared = c;
   return HPS_OK;
+}
+
+hps_status hps_prepare(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
+                       const int32_t* d_offsets, uint32_t n_examples, uint32_t n_slots,
+                       void* stream) {
+  return prepare(t, d_keys, n_keys, d_offsets, n_examples, n_slots, kDedupOnly, stream);
 }
 
 hps_status hps_pull_prepared(hps_table* t, float* d_pooled, void* stream) {
@@ -1043,7 +1137,7 @@ hps_status hps_pull_prepared(hps_table* t, float* d_pooled, void* stream) {
   const hps_table::Context& other = t->cx[1 - c];
   if (other.released_set && hipStreamWaitEvent(s, other.released, 0) != hipSuccess) return HPS_EDEVICE;
   // a2: look up every unique key, create the missing ones
-  if (cx.n_bags) ++t->pull_serial;
+  if (cx.n_bags && !cx.looked_up) ++t->pull_serial;
   stage_mark(t, HPS_STAGE_LOOKUP, s);
   if (cx.n_keys) launch_lookup(t, c, cx.n_keys, true, s);
   if (!cx.n_bags) commit_insert<<<1, 64, 0, s>>>(t->view.st);   // else the pooling kernel does it
@@ -1070,7 +1164,8 @@ hps_status hps_pull(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
   if ((uintptr_t)d_pooled % 16) return HPS_EINVAL;
   if (!mini_batch_ok(t, d_keys, n_keys, d_offsets, n_examples, n_slots)) return HPS_EINVAL;
   if (t->current >= 0) return HPS_ESTATE;
-  const hps_status rc = hps_prepare(t, d_keys, n_keys, d_offsets, n_examples, n_slots, stream);
+  const Include include = creates_at_once(t, n_keys) ? kWithPullLookup : kDedupOnly;
+  const hps_status rc = prepare(t, d_keys, n_keys, d_offsets, n_examples, n_slots, include, stream);
   return rc != HPS_OK ? rc : hps_pull_prepared(t, d_pooled, stream);
 }
 
@@ -1113,7 +1208,7 @@ static hps_status accumulate_launches(hps_table* t, const uint64_t* d_keys, uint
   const int c = 0;
   // every (key, value row) pair is a bag of its own: the dedup groups the pairs by key,
   // the push kernels sum each group's value rows and add the sum onto the row
-  launch_dedup(t, c, d_keys, (u32)n, nullptr, (u32)n, s);
+  launch_dedup(t, c, d_keys, (u32)n, nullptr, (u32)n, kWithAddLookup, s);
   if (n) {
     launch_lookup(t, c, n, false, s);
     commit_absent<<<1, 64, 0, s>>>(t->view.st);
@@ -1256,6 +1351,12 @@ static hps_status list_unique(hps_table* t, int c, uint64_t* d_uniq_out, int32_t
     const u32* start = t->w<u32>(C.bucket_start);
     const u32* count = t->w<u32>(C.count);
     const u64* border = cx.form == kByBorders ? t->w<u64>(C.border) : nullptr;
+    if (cx.form == kSmallForm) {
+      sort_uniques(t, c, (u32)n, d_uniq_out, s);
+      if (d_inverse_out)
+        small_ranks<<<grid_for(n, 256, 256), 256, 0, s>>>(t->w<uint4>(C.places), local_rank, (u32)n, reinterpret_cast<u32*>(d_inverse_out));
+      return launch_ok() ? HPS_OK : HPS_EDEVICE;
+    }
     if (cx.form == kByHash) {
       sort_uniques(t, c, (u32)n, d_uniq_out, s);
       if (d_inverse_out)
@@ -1299,10 +1400,14 @@ hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_invers
   // capture cannot be waited for inside one: what is captured here, the caller orders.
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
-  if (capture != hipStreamCaptureStatusNone) return list_unique(t, c, d_uniq_out, d_inverse_out, s);
+  if (capture != hipStreamCaptureStatusNone) {
+    // (a replay lists a later mini-batch the way this one is: its dedup has to take the same form)
+    if (!t->listing_pinned) t->listing_pinned = cx.buckets && (cx.form == kByHash || cx.form == kSmallForm) ? 2 : 1;
+    return list_unique(t, c, d_uniq_out, d_inverse_out, s);
+  }
   if (hipStreamWaitEvent(s, cx.ready, 0) != hipSuccess) return HPS_EDEVICE;
   if (t->listing_set && hipStreamWaitEvent(s, t->listing, 0) != hipSuccess) return HPS_EDEVICE;
-  const bool sorts = cx.buckets && cx.form == kByHash;       // in the scratch of the dedups
+  const bool sorts = cx.buckets && (cx.form == kByHash || cx.form == kSmallForm);       // in the scratch of the dedups
   if (sorts && hipStreamWaitEvent(s, t->scratch_free, 0) != hipSuccess) return HPS_EDEVICE;
   const hps_status rc = list_unique(t, c, d_uniq_out, d_inverse_out, s);
   if (sorts && hipEventRecord(t->scratch_free, s) != hipSuccess) return HPS_EDEVICE;

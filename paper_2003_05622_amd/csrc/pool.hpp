@@ -16,10 +16,11 @@ constexpr int kPoolThreads = 256;
 constexpr int kPoolMaxBlocks = 1024;   // the groups loop over the bags (1536 to 3072 blocks measured no faster)
 constexpr int kPoolInFlight = 8;
 
-template <int LPR, int COLS, bool BF16>
+template <int LPR, int COLS, bool BF16, bool SMALL>
 __device__ __forceinline__ void pool_bags_as(const TableView& t, const i32* __restrict__ offsets,
                                              u32 n_bags, u32 n, const u32* __restrict__ row_of,
-                                             float* __restrict__ pooled, float* __restrict__ inv_len) {
+                                             float* __restrict__ pooled, float* __restrict__ inv_len,
+                                             const uint4* __restrict__ places, u32* __restrict__ bags) {
   const u32 sub = threadIdx.x % LPR;
   const u32 dim4 = t.dim >> 2;
   const u32 n_groups = gridDim.x * (kPoolThreads / LPR);
@@ -32,7 +33,16 @@ __device__ __forceinline__ void pool_bags_as(const TableView& t, const i32* __re
     for (i32 i0 = lo; i0 < hi; i0 += kPoolInFlight) {
       u32 r[kPoolInFlight];
 #pragma unroll
-      for (int k = 0; k < kPoolInFlight; ++k) r[k] = i0 + k < hi ? row_of[i0 + k] : kNoRow;
+      for (int k = 0; k < kPoolInFlight; ++k) {
+        if (SMALL) {
+          const uint2 p = i0 + k < hi ? *reinterpret_cast<const uint2*>(places + i0 + k) : make_uint2(kNoRow, 0u);
+          r[k] = p.x;
+          // (the lanes of the group share the stores)
+          if (i0 + k < hi && (u32)k % LPR == sub) bags[p.y] = b;
+        } else {
+          r[k] = i0 + k < hi ? row_of[i0 + k] : kNoRow;
+        }
+      }
       // the rows as stored (all loads first: nothing between them that needs their data) ...
       StoredW4<BF16> raw[kPoolInFlight][COLS];
 #pragma unroll
@@ -79,14 +89,16 @@ __device__ __forceinline__ void pool_bags_as(const TableView& t, const i32* __re
   }
 }
 
-// row_of[i]: the row of occurrence i's key.
-template <int LPR, int COLS>
+// row_of[i]: the row of occurrence i's key.  SMALL (small.hpp): that is in places[i], with its position in the order grouped
+// by key, for which its bag is put down.
+template <int LPR, int COLS, bool SMALL>
 __global__ void __launch_bounds__(kPoolThreads)
 pool_bags(TableView t, const i32* __restrict__ offsets, u32 n_bags, u32 n, const u32* __restrict__ row_of,
-          float* __restrict__ pooled, float* __restrict__ inv_len, PullEnd end) {
+          float* __restrict__ pooled, float* __restrict__ inv_len, const uint4* __restrict__ places, u32* __restrict__ bags,
+          PullEnd end) {
   if (!end_pull(t, end)) return;
-  if (t.bf16) pool_bags_as<LPR, COLS, true>(t, offsets, n_bags, n, row_of, pooled, inv_len);
-  else pool_bags_as<LPR, COLS, false>(t, offsets, n_bags, n, row_of, pooled, inv_len);
+  if (t.bf16) pool_bags_as<LPR, COLS, true, SMALL>(t, offsets, n_bags, n, row_of, pooled, inv_len, places, bags);
+  else pool_bags_as<LPR, COLS, false, SMALL>(t, offsets, n_bags, n, row_of, pooled, inv_len, places, bags);
 }
 
 // Plain form of the dedup: row_of[i] = rows[inverse[i]].

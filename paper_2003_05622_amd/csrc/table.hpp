@@ -128,9 +128,9 @@ constexpr int kPullInFlight = 4;
 static_assert(kPullInFlight % kLookupLanes == 0, "every lane of a group owns the same number of keys");
 constexpr int kProbeMaxBlocks = 1024;
 constexpr u32 kNoSlot = ~0u;
-constexpr u32 kNewLdsCap = 1024;         // created keys a block lists for its common initialisation
+constexpr u32 kNewLdsCap = 1024;         // created keys a block of the lookup lists for its common initialisation
 constexpr u32 kLongLdsCap = 64;          // very frequent keys whose chunk items whole waves write (>= kHeavyGroup)
-constexpr u32 kMedLdsCap = 512;          // medium keys a block buffers before it appends
+constexpr u32 kMedLdsCap = 512;          // medium keys it buffers before it appends
 constexpr u32 kShortSeg = 16;            // occurrences handled serially by one lane group
 
 // How the push shares out the occurrences of a key with more than kShortSeg, by lanes per row: up to
@@ -551,8 +551,157 @@ constexpr u32 kCreateNone = 0, kCreateIfRoom = 1, kCreateAtOnce = 2;
 struct Creation {
   u32 how;
   u32 set;         // which of st->pull_made counts the created rows
+  u32 new_cap;     // entries used of a block's list of created keys: all, except in tests of what happens when it is full
   uint8_t* fresh;  // per distinct key: created by this pull?  Written where the table might be overfilled
 };
+// (the size does not change while a pull's kernels run: every thread decides the same)
+__device__ __forceinline__ bool is_tight(const TableView& t, const Creation& create, u32 n) {
+  return create.how == kCreateAtOnce && t.st->size + n > t.capacity;
+}
+// One thread of a pull's lookup: what end_pull decides by.
+__device__ __forceinline__ void note_tight(const TableView& t, const Creation& create, bool tight) {
+  if (create.how == kCreateNone) return;
+  t.st->size_before = t.st->size;
+  t.st->tight = tight ? 1u : 0u;
+}
+
+// What the threads of a block that looks up keys gather, to be written out together at the end.
+template <u32 NEW, u32 MED, u32 LONG>
+struct LookupLds {
+  static constexpr u32 kNew = NEW, kMed = MED, kLong = LONG;
+  u32 missing, n_new, n_med, med_base, n_long;
+  uint4 long_list[LONG];  // (unique index, first chunk item, chunks, number) of very frequent keys
+  u64 new_key[NEW];       // created keys, and their rows
+  u32 new_row[NEW];
+  u32 med_list[MED];
+  __device__ __forceinline__ void clear() { missing = n_new = n_med = n_long = 0; }
+};
+
+// The row of my_key (kEmptyKey: none), one key per lane of a group of four; *mine_new: it was created just now.
+//
+// A group of four lanes looks at a bucket of the table at once and has four keys in flight, one per lane:
+// each lane loads and hashes its own key and, at the end, stores its own key's row and lists it
+// (one key per lane: full waves); in between the group goes through its four keys together
+// (search_keys).
+template <typename LDS>
+__device__ __forceinline__ u32 lookup_key(const TableView& t, u64 my_key, bool create_here, u32 new_cap, LDS& L, bool* mine_new) {
+  constexpr int K = kPullInFlight;            // keys a group has in flight
+  static_assert(K == kLookupLanes, "one key per lane");
+  const u32 sub = threadIdx.x % kLookupLanes;
+  const u32 lane0 = lane_id() & ~3u;          // the group's first lane
+  u64 my_line;
+  u32 my_row, my_free;
+  *mine_new = false;
+  const u32 to_create = search_keys<K>(t, &my_key, &my_line, &my_row, &my_free, sub);
+  // keys to create: all first attempts in flight together, then whatever is left of each
+  if (create_here && __any(to_create != 0)) {
+    u64 seen[K];
+    my_line += my_free >> 3;        // the line of the free slot
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      const u64 key = quad_lane(my_key, q);
+      const u64 line = quad_lane(my_line, q);
+      const u32 slot = quad_lane(my_free, q) & 7u;
+      seen[q] = 0;
+      if ((to_create >> q & 1u) && sub == slot >> 1)
+        seen[q] = atomicCAS((unsigned long long*)&t.keys[line * kSlotsPerLine + slot],
+                            (unsigned long long)kEmptyKey, (unsigned long long)key);
+    }
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      const u64 key = quad_lane(my_key, q);
+      const u64 line = quad_lane(my_line, q);
+      const u32 slot = quad_lane(my_free, q) & 7u;
+      if (!(to_create >> q & 1u)) continue;
+      const u64 got = __shfl(seen[q], (int)(lane0 + (slot >> 1)), kWave);
+      bool created;
+      const u32 row = claim_after4<true>(t, key, sub, line, slot, got, &created);
+      if (row == kNoRow) {
+        raise_error(t.st, kErrInternal);            // (cannot happen: the table has room)
+        continue;
+      }
+      // The new row's initial values are left to the end of the kernel, where all lanes of
+      // the block share the work (here four lanes of the wave would do it while sixty wait);
+      // only a key that finds the block's list full gets them right away.
+      u32 at = 0;
+      if (sub == (u32)q) {
+        my_row = row;
+        *mine_new = true;
+        at = atomicAdd(&L.n_new, 1u);
+        if (at < new_cap) { L.new_key[at] = key; L.new_row[at] = row; }
+      }
+      if (quad_lane(at, q) >= new_cap) {
+        const u64 base = mix64(key ^ t.init_seed);
+        for (u32 j = sub; j < t.dim; j += kLookupLanes) store_w(t, row, j, init_weight(base, j, t.init_range));
+        float* ar = acc_row(t, row);
+        for (u32 j = sub; j < t.acc_len; j += kLookupLanes) ar[j] = t.init_acc;
+      }
+    }
+  }
+  return my_row;
+}
+
+// Puts distinct key number u into the push's work lists, by its number of occurrences, and into the hint for later dedups.
+template <typename LDS>
+__device__ __forceinline__ void list_key(const OftenLists& often, u32 u, u64 key, u32 len, LDS& L) {
+  PullCtx* ctx = often.ctx;
+  if (len >= often.heavy_min && key != kEmptyKey) {
+    const u32 at = atomicAdd(&often.heavy_raw->count, 1u);
+    if (at < (u32)kMaxHeavy) often.heavy_raw->keys[at] = key;
+  }
+  if (len > often.pieces.medium) {
+    const u32 n_chunks = (len + often.pieces.chunk - 1) / often.pieces.chunk;
+    const u32 item = atomicAdd(&ctx->n_chunk_items, n_chunks);
+    const u32 number = atomicAdd(&ctx->n_long, 1u);
+    often.arrived[number] = 0;
+    // the key's chunk items are written at the end of the kernel by all lanes of a wave
+    // (a key that fills thousands of chunks would keep this lane, and its wave, for long)
+    const u32 at = atomicAdd(&L.n_long, 1u);
+    if (at < LDS::kLong) {
+      L.long_list[at] = make_uint4(u, item, n_chunks, number);
+    } else {
+      for (u32 i = 0; i < n_chunks; ++i) often.chunk_items[item + i] = make_uint4(u, i, number, item);
+    }
+  } else if (len > kShortSeg) {
+    const u32 at = atomicAdd(&L.n_med, 1u);
+    if (at < LDS::kMed) L.med_list[at] = u;
+    else often.med_list[atomicAdd(&ctx->n_med, 1u)] = u;      // buffer full: append straight to the list
+  }
+}
+
+// After a barrier: writes out what the block's threads have gathered, in two steps with a barrier between them.
+template <typename LDS>
+__device__ __forceinline__ void end_lookup_counts(const TableView& t, const OftenLists& often, const Creation& create, LDS& L) {
+  if (threadIdx.x == 0) {
+    if (L.n_new) atomicAdd(&t.st->pull_made[create.set][blockIdx.x % kCountShards], L.n_new);
+    if (L.missing) atomicAdd(&t.st->miss_shard[blockIdx.x % kCountShards], L.missing);
+    if (L.n_med) L.med_base = atomicAdd(&often.ctx->n_med, min(L.n_med, LDS::kMed));
+  }
+}
+template <int THREADS, typename LDS>
+__device__ __forceinline__ void end_lookup_lists(const TableView& t, const OftenLists& often, const Creation& create, LDS& L) {
+  {
+    const u32 n_long_here = min(L.n_long, LDS::kLong);
+    for (u32 e = threadIdx.x / kWave; e < n_long_here; e += THREADS / kWave) {
+      const uint4 it = L.long_list[e];
+      for (u32 i = lane_id(); i < it.z; i += kWave) often.chunk_items[it.y + i] = make_uint4(it.x, i, it.w, it.y);
+    }
+  }
+  // the initial rows of the keys created above: one float4 of one row per lane and turn
+  const u32 n_new = min(L.n_new, min(create.new_cap, LDS::kNew));
+  const u32 dim4 = t.dim >> 2;
+  for (u32 e = threadIdx.x; e < n_new * dim4; e += THREADS) {
+    const u32 i = e / dim4, col = e % dim4;
+    store_w4(t, L.new_row[i], col, init_weight4(mix64(L.new_key[i] ^ t.init_seed), col, t.init_range));
+  }
+  for (u32 e = threadIdx.x; e < n_new * t.acc_len; e += THREADS)
+    acc_row(t, L.new_row[e / t.acc_len])[e % t.acc_len] = t.init_acc;
+  const u32 n_med = min(L.n_med, LDS::kMed);
+  if (n_med) {
+    __syncthreads();
+    for (u32 i = threadIdx.x; i < n_med; i += THREADS) often.med_list[L.med_base + i] = L.med_list[i];
+  }
+}
 
 // rows[u] = the slot of distinct key u.  Keys the table does not hold:
 //  - kCreateNone (accumulate): rows[u] = kNoRow, counted in st->miss_shard;
@@ -564,31 +713,16 @@ struct Creation {
 // Also sorts the keys into the push's work lists by their number of occurrences, and (bucket form)
 // hands the rows on by position.  One span of distinct keys or group of heavy keys per block; the block behind
 // them reports on the dedup.
-//
-// A group of four lanes looks at a bucket of the table at once and has four keys in flight, one per lane:
-// each lane loads and hashes its own key and, at the end, stores its own key's row and lists it
-// (one key per lane: full waves); in between the group goes through its four keys together
-// (search_keys).
 __global__ void __launch_bounds__(kProbeThreads)
 pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ seg_off, UniqueSpans spans,
-            u32* __restrict__ rows, RowsByPosition out, Creation create, u32 new_cap, OftenLists often) {
-  // new_cap <= kNewLdsCap: how much of the block's list of created keys is used (all of it,
-  // except in tests of what happens when it is full)
-  constexpr int K = kPullInFlight;            // keys a group has in flight
-  static_assert(K == kLookupLanes, "one key per lane");
-  __shared__ u32 s_missing, s_med, s_med_base, s_made, s_new, s_long, s_unique;
-  __shared__ uint4 s_long_list[kLongLdsCap];  // (unique index, first chunk item, chunks, number) of the block's very frequent keys
-  __shared__ u32 s_med_list[kMedLdsCap];
-  __shared__ u64 s_new_key[kNewLdsCap];       // keys created by this block, and their rows
-  __shared__ u32 s_new_row[kNewLdsCap];
+            u32* __restrict__ rows, RowsByPosition out, Creation create, OftenLists often) {
+  typedef LookupLds<kNewLdsCap, kMedLdsCap, kLongLdsCap> Lds;
+  __shared__ Lds L;
+  __shared__ u32 s_unique;
   PullCtx* ctx = often.ctx;
-  // (the size does not change while this kernel runs: every thread decides the same)
-  const bool tight = create.how == kCreateAtOnce && t.st->size + ctx->n_total > t.capacity;
+  const bool tight = is_tight(t, create, ctx->n_total);
   if (blockIdx.x == span_blocks(spans)) {
-    if (threadIdx.x == 0 && create.how != kCreateNone) {
-      t.st->size_before = t.st->size;
-      t.st->tight = tight ? 1u : 0u;
-    }
+    if (threadIdx.x == 0) note_tight(t, create, tight);
     report_dedup(spans, often);
     return;
   }
@@ -604,7 +738,7 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ s
   if (heavies) count = ctx->n_heavy > h0 ? min(kHeavyGroup, ctx->n_heavy - h0) : 0u;
   else unique_span(spans, ctx, c, &first, &count);
   if (count == 0) return;
-  if (threadIdx.x == 0) { s_missing = 0; s_med = 0; s_made = 0; s_new = 0; s_long = 0; }
+  if (threadIdx.x == 0) L.clear();
   if (create.how == kCreateIfRoom && threadIdx.x < kWave) {
     // (kCountShards == kWave) distinct keys of the whole mini-batch
     const u32 u = wave_incl_sum(ctx->uniq_shard[threadIdx.x]);
@@ -612,15 +746,13 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ s
   }
   __syncthreads();
   const bool create_here = create.how == kCreateAtOnce || (create.how == kCreateIfRoom && t.st->size + s_unique <= t.capacity);
-  const u32 sub = threadIdx.x % kLookupLanes;
-  const u32 lane0 = lane_id() & ~3u;          // the group's first lane
-  u32 made = 0, missing = 0;
+  u32 missing = 0;
   // (the bound is the same for all lanes of a group, so a group stays together)
   for (u32 k0 = threadIdx.x & ~3u; k0 < count; k0 += kProbeThreads) {
-    const u32 k = k0 + sub;
-    u64 my_key = kEmptyKey, my_line;
-    u32 my_len = 0, my_row, my_free, u = 0;
-    bool on = k < count, mine_new = false;
+    const u32 k = k0 + threadIdx.x % kLookupLanes;
+    u64 my_key = kEmptyKey;
+    u32 my_len = 0, u = 0;
+    bool on = k < count, mine_new;
     if (heavies) {
       const u32 h = h0 + k;
       if (on) {
@@ -636,112 +768,20 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ s
       my_len = seg_off[u + 1] - seg_off[u];
       if (my_key == kEmptyKey) raise_error(t.st, kErrReserved);
     }
-    const u32 to_create = search_keys<K>(t, &my_key, &my_line, &my_row, &my_free, sub);
-    // keys to create: all first attempts in flight together, then whatever is left of each
-    if (create_here && __any(to_create != 0)) {
-      u64 seen[K];
-      my_line += my_free >> 3;        // the line of the free slot
-#pragma unroll
-      for (int q = 0; q < K; ++q) {
-        const u64 key = quad_lane(my_key, q);
-        const u64 line = quad_lane(my_line, q);
-        const u32 slot = quad_lane(my_free, q) & 7u;
-        seen[q] = 0;
-        if ((to_create >> q & 1u) && sub == slot >> 1)
-          seen[q] = atomicCAS((unsigned long long*)&t.keys[line * kSlotsPerLine + slot],
-                              (unsigned long long)kEmptyKey, (unsigned long long)key);
-      }
-#pragma unroll
-      for (int q = 0; q < K; ++q) {
-        const u64 key = quad_lane(my_key, q);
-        const u64 line = quad_lane(my_line, q);
-        const u32 slot = quad_lane(my_free, q) & 7u;
-        if (!(to_create >> q & 1u)) continue;
-        const u64 got = __shfl(seen[q], (int)(lane0 + (slot >> 1)), kWave);
-        bool created;
-        const u32 row = claim_after4<true>(t, key, sub, line, slot, got, &created);
-        if (row == kNoRow) {
-          raise_error(t.st, kErrInternal);            // (cannot happen: the table has room)
-          continue;
-        }
-        // The new row's initial values are left to the end of the kernel, where all lanes of
-        // the block share the work (here four lanes of the wave would do it while sixty wait);
-        // only a key that finds the block's list full gets them right away.
-        u32 at = 0;
-        if (sub == (u32)q) {
-          my_row = row;
-          mine_new = true;
-          ++made;
-          at = atomicAdd(&s_new, 1u);
-          if (at < new_cap) { s_new_key[at] = key; s_new_row[at] = row; }
-        }
-        if (quad_lane(at, q) >= new_cap) {
-          const u64 base = mix64(key ^ t.init_seed);
-          for (u32 j = sub; j < t.dim; j += kLookupLanes) store_w(t, row, j, init_weight(base, j, t.init_range));
-          float* ar = acc_row(t, row);
-          for (u32 j = sub; j < t.acc_len; j += kLookupLanes) ar[j] = t.init_acc;
-        }
-      }
-    }
+    const u32 my_row = lookup_key(t, my_key, create_here, create.new_cap, L, &mine_new);
     // every lane: the row of its own key, and the push's work lists
     if (!on) continue;
     rows[u] = my_row;
     if (tight) create.fresh[u] = mine_new ? 1 : 0;
     if (heavies && out.upos) out.by_heavy[h0 + k] = my_row;
     if (my_row == kNoRow) ++missing;
-    if (my_len >= often.heavy_min && my_key != kEmptyKey) {
-      const u32 at = atomicAdd(&often.heavy_raw->count, 1u);
-      if (at < (u32)kMaxHeavy) often.heavy_raw->keys[at] = my_key;
-    }
-    if (my_len > often.pieces.medium) {
-      const u32 n_chunks = (my_len + often.pieces.chunk - 1) / often.pieces.chunk;
-      const u32 item = atomicAdd(&ctx->n_chunk_items, n_chunks);
-      const u32 number = atomicAdd(&ctx->n_long, 1u);
-      often.arrived[number] = 0;
-      // the key's chunk items are written at the end of the kernel by all lanes of a wave
-      // (a key that fills thousands of chunks would keep this lane, and its wave, for long)
-      const u32 at = atomicAdd(&s_long, 1u);
-      if (at < kLongLdsCap) {
-        s_long_list[at] = make_uint4(u, item, n_chunks, number);
-      } else {
-        for (u32 i = 0; i < n_chunks; ++i) often.chunk_items[item + i] = make_uint4(u, i, number, item);
-      }
-    } else if (my_len > kShortSeg) {
-      const u32 at = atomicAdd(&s_med, 1u);
-      if (at < kMedLdsCap) s_med_list[at] = u;
-      else often.med_list[atomicAdd(&ctx->n_med, 1u)] = u;      // buffer full: append straight to the list
-    }
+    list_key(often, u, my_key, my_len, L);
   }
-  if (made) atomicAdd(&s_made, made);
-  if (missing) atomicAdd(&s_missing, missing);
+  if (missing) atomicAdd(&L.missing, missing);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    if (s_made) atomicAdd(&t.st->pull_made[create.set][blockIdx.x % kCountShards], s_made);
-    if (s_missing) atomicAdd(&t.st->miss_shard[blockIdx.x % kCountShards], s_missing);
-    if (s_med) s_med_base = atomicAdd(&ctx->n_med, min(s_med, kMedLdsCap));
-  }
+  end_lookup_counts(t, often, create, L);
   if (out.upos && !heavies) rows_by_position(spans, out, c, first, rows);      // (this block's own rows[])
-  {
-    const u32 n_long_here = min(s_long, kLongLdsCap);
-    for (u32 e = threadIdx.x / kWave; e < n_long_here; e += kProbeThreads / kWave) {
-      const uint4 it = s_long_list[e];
-      for (u32 i = lane_id(); i < it.z; i += kWave) often.chunk_items[it.y + i] = make_uint4(it.x, i, it.w, it.y);
-    }
-  }
-  // the initial rows of the keys created above: one float4 of one row per lane and turn
-  const u32 n_new = min(s_new, new_cap);
-  const u32 dim4 = t.dim >> 2;
-  for (u32 e = threadIdx.x; e < n_new * dim4; e += kProbeThreads) {
-    const u32 i = e / dim4, col = e % dim4;
-    store_w4(t, s_new_row[i], col, init_weight4(mix64(s_new_key[i] ^ t.init_seed), col, t.init_range));
-  }
-  for (u32 e = threadIdx.x; e < n_new * t.acc_len; e += kProbeThreads)
-    acc_row(t, s_new_row[e / t.acc_len])[e % t.acc_len] = t.init_acc;
-  const u32 n_med = min(s_med, kMedLdsCap);
-  if (n_med) {
-    __syncthreads();
-    for (u32 i = threadIdx.x; i < n_med; i += kProbeThreads) often.med_list[s_med_base + i] = s_med_list[i];
-  }
+  end_lookup_lists<kProbeThreads>(t, often, create, L);
 }
 
 // Whether the keys a lookup found missing (st->miss_shard) may be created: 0 there are none, 1 yes,

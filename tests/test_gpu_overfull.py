@@ -16,7 +16,7 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a, dtype=np.uint64).view(np.int64)).cuda()
 
 
-@pytest.mark.parametrize("form", ["auto", "bucket", "hashed", "radix"])
+@pytest.mark.parametrize("form", ["auto", "bucket", "hashed", "small", "radix"])
 @pytest.mark.parametrize("n", [900, 5000, 70_000])
 def test_overfull_pulls_leave_no_trace(n, form, monkeypatch):
     monkeypatch.setenv("HPS_DEDUP", form)
