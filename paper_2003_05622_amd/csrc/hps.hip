@@ -375,6 +375,10 @@ struct hps_table {
   bool scratch_set;
   hipEvent_t listing;        // the last hps_last_unique's end: its scratch, and the context it read
   bool listing_set;
+  // While all calls come on one stream, its order is all they need, and none of these events is recorded (a record
+  // takes the stream 3 us in which nothing runs, three of them a step); the *_set flags are kept all the same.  See enter().
+  bool many_streams, stream_known;
+  hipStream_t stream;
   uint64_t last_n_keys;      // of the most recent pull, for hps_stats
 
   // stage timing (measurement only)
@@ -402,6 +406,52 @@ void stage_mark(hps_table* t, int stage, hipStream_t s) {
   (void)hipEventRecord(pool[t->ev_used[stage]++], s);
 }
 }  // namespace
+
+// ---- order between streams ---------------------------------------------------------------
+// From now on calls come on several streams.  On the one stream there has been, s, the events that have been left out are put
+// down now (later than they ask for).  On another one all work is waited for instead: the first stream may be gone.
+static bool leave_single_stream(hps_table* t, hipStream_t s) {
+  t->many_streams = true;
+  if (!t->stream_known) return true;
+  struct { hipEvent_t event; bool* set; } left_out[] = {
+      {t->scratch_free, &t->scratch_set}, {t->listing, &t->listing_set}, {t->cx[0].ready, &t->cx[0].ready_set},
+      {t->cx[1].ready, &t->cx[1].ready_set}, {t->cx[0].released, &t->cx[0].released_set}, {t->cx[1].released, &t->cx[1].released_set}};
+  if (s == t->stream) {
+    for (auto& e : left_out)
+      if (*e.set && hipEventRecord(e.event, s) != hipSuccess) return false;
+    return true;
+  }
+  if (hipDeviceSynchronize() != hipSuccess) return false;
+  for (auto& e : left_out) *e.set = false;
+  t->cx[0].listed = t->cx[1].listed = false;
+  return true;
+}
+
+// Before any wait or mark of a call on stream s.  several: the call is one that is made for work on several streams.
+//
+// The stream is known by its handle.  A handle comes to stand for another stream only after the first one has been
+// destroyed, and that waits for the stream's work (a stream with 42 ms of work: 42 ms in hipStreamDestroy).
+static bool enter(hps_table* t, hipStream_t s, bool several) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
+  if (capture != hipStreamCaptureStatusNone) {
+    // (what ran before the capture cannot be waited for inside it)
+    if (!t->many_streams && (t->scratch_set || t->listing_set || t->cx[0].released_set || t->cx[1].released_set)) return false;
+    t->many_streams = true;
+    return true;
+  }
+  if (t->many_streams) return true;
+  if (!t->stream_known) { t->stream = s; t->stream_known = true; }
+  // (hipStreamPerThread is another stream in every thread)
+  return (s == t->stream && s != hipStreamPerThread && !several) || leave_single_stream(t, s);
+}
+static bool mark(hps_table* t, hipEvent_t e, bool* set, hipStream_t s) {
+  *set = true;
+  return !t->many_streams || hipEventRecord(e, s) == hipSuccess;
+}
+static bool wait_for(const hps_table* t, hipEvent_t e, bool set, hipStream_t s) {
+  return !set || !t->many_streams || hipStreamWaitEvent(s, e, 0) == hipSuccess;
+}
 
 static UniqueSpans unique_spans(const hps_table* t, int c, uint64_t n) {
   const hps_table::Context& cx = t->cx[c];
@@ -959,6 +1009,7 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   t->last_n_keys = 0;
   t->scratch_set = false;
   t->listing_set = false;
+  t->many_streams = t->stream_known = false;
   bool events_ok = hipEventCreateWithFlags(&t->scratch_free, hipEventDisableTiming) == hipSuccess &&
                    hipEventCreateWithFlags(&t->listing, hipEventDisableTiming) == hipSuccess;
   for (int k = 0; k < 2; ++k) {
@@ -1079,15 +1130,16 @@ static bool mini_batch_ok(const hps_table* t, const uint64_t* d_keys, uint64_t n
 
 // Orders a dedup into context c after the hps_last_unique that read what the context held before.
 static bool after_listing(hps_table* t, int c, hipStream_t s) {
-  if (t->cx[c].listed && hipStreamWaitEvent(s, t->listing, 0) != hipSuccess) return false;
+  if (!wait_for(t, t->listing, t->cx[c].listed, s)) return false;
   t->cx[c].listed = false;
   return true;
 }
 
-// include: kDedupOnly, or kWithPullLookup where hps_pull_prepared follows on the same stream at once.
+// include: kDedupOnly, or kWithPullLookup where hps_pull_prepared follows on the same stream at once.  ahead: it is a call
+// of its own, perhaps beside others.
 static hps_status prepare(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
                           const int32_t* d_offsets, uint32_t n_examples, uint32_t n_slots,
-                          Include include, void* stream) {
+                          Include include, bool ahead, void* stream) {
   if (!mini_batch_ok(t, d_keys, n_keys, d_offsets, n_examples, n_slots)) return HPS_EINVAL;
   const uint64_t n_bags = (uint64_t)n_examples * n_slots;
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1096,19 +1148,16 @@ static hps_status prepare(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
   const u32 n = (u32)n_keys;
   // order after the push that last read this context, and after the previous dedup
   // (the sort scratch is shared); both may have run on other streams
-  if (cx.released_set && hipStreamWaitEvent(s, cx.released, 0) != hipSuccess) return HPS_EDEVICE;
-  if (t->scratch_set && hipStreamWaitEvent(s, t->scratch_free, 0) != hipSuccess) return HPS_EDEVICE;
+  if (!enter(t, s, ahead)) return HPS_EDEVICE;
+  if (!wait_for(t, cx.released, cx.released_set, s) || !wait_for(t, t->scratch_free, t->scratch_set, s)) return HPS_EDEVICE;
   if (!after_listing(t, c, s)) return HPS_EDEVICE;
   // (a lookup among it: what hps_pull_prepared orders it after)
   const hps_table::Context& other = t->cx[1 - c];
-  if (include != kDedupOnly && other.released_set && hipStreamWaitEvent(s, other.released, 0) != hipSuccess) return HPS_EDEVICE;
+  if (include != kDedupOnly && !wait_for(t, other.released, other.released_set, s)) return HPS_EDEVICE;
 
   launch_dedup(t, c, d_keys, n, d_offsets, (u32)n_bags, include, s);
   if (!launch_ok()) return HPS_EDEVICE;
-  if (hipEventRecord(cx.ready, s) != hipSuccess || hipEventRecord(t->scratch_free, s) != hipSuccess)
-    return HPS_EDEVICE;
-  cx.ready_set = true;
-  t->scratch_set = true;
+  if (!mark(t, cx.ready, &cx.ready_set, s) || !mark(t, t->scratch_free, &t->scratch_set, s)) return HPS_EDEVICE;
   cx.n_keys = n_keys;
   cx.n_bags = n_bags;
   cx.d_offsets = d_offsets;
@@ -1120,7 +1169,7 @@ static hps_status prepare(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
 hps_status hps_prepare(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
                        const int32_t* d_offsets, uint32_t n_examples, uint32_t n_slots,
                        void* stream) {
-  return prepare(t, d_keys, n_keys, d_offsets, n_examples, n_slots, kDedupOnly, stream);
+  return prepare(t, d_keys, n_keys, d_offsets, n_examples, n_slots, kDedupOnly, true, stream);
 }
 
 hps_status hps_pull_prepared(hps_table* t, float* d_pooled, void* stream) {
@@ -1131,11 +1180,11 @@ hps_status hps_pull_prepared(hps_table* t, float* d_pooled, void* stream) {
   if (cx.n_bags && !d_pooled) return HPS_EINVAL;
   if ((uintptr_t)d_pooled % 16) return HPS_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (hipStreamWaitEvent(s, cx.ready, 0) != hipSuccess) return HPS_EDEVICE;
+  if (!enter(t, s, false) || !wait_for(t, cx.ready, cx.ready_set, s)) return HPS_EDEVICE;
   // the lookup rewrites the work lists that both contexts share and the pooling reads rows: order
   // them after the push of the mini-batch before, should that have run on another stream
   const hps_table::Context& other = t->cx[1 - c];
-  if (other.released_set && hipStreamWaitEvent(s, other.released, 0) != hipSuccess) return HPS_EDEVICE;
+  if (!wait_for(t, other.released, other.released_set, s)) return HPS_EDEVICE;
   // a2: look up every unique key, create the missing ones
   if (cx.n_bags && !cx.looked_up) ++t->pull_serial;
   stage_mark(t, HPS_STAGE_LOOKUP, s);
@@ -1165,7 +1214,7 @@ hps_status hps_pull(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
   if (!mini_batch_ok(t, d_keys, n_keys, d_offsets, n_examples, n_slots)) return HPS_EINVAL;
   if (t->current >= 0) return HPS_ESTATE;
   const Include include = creates_at_once(t, n_keys) ? kWithPullLookup : kDedupOnly;
-  const hps_status rc = prepare(t, d_keys, n_keys, d_offsets, n_examples, n_slots, include, stream);
+  const hps_status rc = prepare(t, d_keys, n_keys, d_offsets, n_examples, n_slots, include, false, stream);
   return rc != HPS_OK ? rc : hps_pull_prepared(t, d_pooled, stream);
 }
 
@@ -1177,6 +1226,7 @@ hps_status hps_push(hps_table* t, const float* d_pooled_grads, void* stream) {
   if (cx.n_bags && cx.n_keys && !d_pooled_grads) return HPS_EINVAL;
   if ((uintptr_t)d_pooled_grads % 16) return HPS_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  if (!enter(t, s, false)) return HPS_EDEVICE;
   t->current = -1;
   if (cx.n_keys && cx.n_bags) {
     PushArgs a;
@@ -1190,9 +1240,7 @@ hps_status hps_push(hps_table* t, const float* d_pooled_grads, void* stream) {
     stage_mark(t, HPS_STAGE_PUSH, s);
     if (!launch_ok()) return HPS_EDEVICE;
   }
-  if (hipEventRecord(cx.released, s) != hipSuccess) return HPS_EDEVICE;
-  cx.released_set = true;
-  return HPS_OK;
+  return mark(t, cx.released, &cx.released_set, s) ? HPS_OK : HPS_EDEVICE;
 }
 
 hps_status hps_set_pooling(hps_table* t, int mean) {
@@ -1230,17 +1278,14 @@ hps_status hps_accumulate(hps_table* t, const uint64_t* d_keys, uint64_t n, cons
   if (t->current >= 0 || t->prepared >= 0) return HPS_ESTATE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hps_table::Context& cx = t->cx[0];
+  if (!enter(t, s, false)) return HPS_EDEVICE;
   for (int k = 0; k < 2; ++k)      // after the last push of either context (shared work lists, table rows)
-    if (t->cx[k].released_set && hipStreamWaitEvent(s, t->cx[k].released, 0) != hipSuccess) return HPS_EDEVICE;
-  if (t->scratch_set && hipStreamWaitEvent(s, t->scratch_free, 0) != hipSuccess) return HPS_EDEVICE;
+    if (!wait_for(t, t->cx[k].released, t->cx[k].released_set, s)) return HPS_EDEVICE;
+  if (!wait_for(t, t->scratch_free, t->scratch_set, s)) return HPS_EDEVICE;
   if (!after_listing(t, 0, s)) return HPS_EDEVICE;
   const hps_status rc = accumulate_launches(t, d_keys, n, d_values, s);
   if (rc != HPS_OK) return rc;
-  if (hipEventRecord(cx.released, s) != hipSuccess || hipEventRecord(t->scratch_free, s) != hipSuccess)
-    return HPS_EDEVICE;
-  cx.released_set = true;
-  t->scratch_set = true;
-  return HPS_OK;
+  return mark(t, cx.released, &cx.released_set, s) && mark(t, t->scratch_free, &t->scratch_set, s) ? HPS_OK : HPS_EDEVICE;
 }
 
 hps_status hps_accumulate_static(hps_table* t, const uint64_t* d_keys, uint64_t n,
@@ -1405,14 +1450,12 @@ hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_invers
     if (!t->listing_pinned) t->listing_pinned = cx.buckets && (cx.form == kByHash || cx.form == kSmallForm) ? 2 : 1;
     return list_unique(t, c, d_uniq_out, d_inverse_out, s);
   }
-  if (hipStreamWaitEvent(s, cx.ready, 0) != hipSuccess) return HPS_EDEVICE;
-  if (t->listing_set && hipStreamWaitEvent(s, t->listing, 0) != hipSuccess) return HPS_EDEVICE;
+  if (!enter(t, s, false) || !wait_for(t, cx.ready, cx.ready_set, s) || !wait_for(t, t->listing, t->listing_set, s)) return HPS_EDEVICE;
   const bool sorts = cx.buckets && (cx.form == kByHash || cx.form == kSmallForm);       // in the scratch of the dedups
-  if (sorts && hipStreamWaitEvent(s, t->scratch_free, 0) != hipSuccess) return HPS_EDEVICE;
+  if (sorts && !wait_for(t, t->scratch_free, t->scratch_set, s)) return HPS_EDEVICE;
   const hps_status rc = list_unique(t, c, d_uniq_out, d_inverse_out, s);
-  if (sorts && hipEventRecord(t->scratch_free, s) != hipSuccess) return HPS_EDEVICE;
-  if (hipEventRecord(t->listing, s) != hipSuccess) return HPS_EDEVICE;
-  t->listing_set = true;
+  if (sorts && !mark(t, t->scratch_free, &t->scratch_set, s)) return HPS_EDEVICE;
+  if (!mark(t, t->listing, &t->listing_set, s)) return HPS_EDEVICE;
   cx.listed = true;
   return rc;
 }

@@ -1,0 +1,76 @@
+"""A table whose calls come on one stream, and then on several: the order between its calls holds from the first call on
+another stream on, also if the first stream has been destroyed by then.  Zero gradients: pooled sums stay the initial rows'."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2003_05622_amd as hps
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.uint64).view(np.int64)).cuda()
+
+
+@pytest.mark.parametrize("form", ["auto", "small", "hashed", "bucket"])
+@pytest.mark.parametrize("first", ["default", "torch", "destroyed"])
+def test_from_one_stream_to_several(first, form, monkeypatch):
+    monkeypatch.setenv("HPS_DEDUP", form)
+    rng = np.random.default_rng(1)
+    n, n_bags, dim, steps = 20_000, 2000, 8, 12
+    keys = [synth.mix64(rng.integers(0, n, size=n).astype(np.uint64)) for _ in range(steps)]
+    offsets = (np.arange(n_bags + 1, dtype=np.int64) * n // n_bags).astype(np.int32)
+    dk, do = [dev(k) for k in keys], torch.from_numpy(offsets).cuda()
+    pooled = [torch.empty((n_bags, dim), device="cuda") for _ in keys]
+    zero = torch.zeros((n_bags, dim), device="cuda")
+    gt, ot = hps.HpsTable(20 * n, dim, n, n_bags), oracle.OracleTable(20 * n, dim)
+    hip, raw = ctypes.CDLL("libamdhip64.so"), ctypes.c_void_p()
+    if first == "default":
+        a = torch.cuda.default_stream()
+    elif first == "torch":
+        a = torch.cuda.Stream()
+    else:
+        assert hip.hipStreamCreate(ctypes.byref(raw)) == 0
+        a = torch.cuda.ExternalStream(raw.value)
+    b, c = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    uniq, inv = torch.zeros(n, dtype=torch.int64, device="cuda"), torch.zeros(n, dtype=torch.int32, device="cuda")
+    with torch.cuda.stream(a):
+        for i in range(6):
+            torch.cuda._sleep(300_000)
+            gt.pull(dk[i], do, n_bags, 1, pooled[i])
+            gt.push(zero)
+    if first == "destroyed":
+        a.synchronize()
+        assert hip.hipStreamDestroy(raw) == 0
+        a = torch.cuda.Stream()
+    # prepared beside the last calls above, pulled and listed elsewhere
+    with torch.cuda.stream(b):
+        gt.prepare(dk[6], do, n_bags, 1)
+    for i in range(6, steps):
+        with torch.cuda.stream(c if i % 2 else a):
+            torch.cuda._sleep(300_000)
+            gt.pull_prepared(pooled[i])
+        if i == 8:
+            assert hps.lib().hps_last_unique(gt._h, uniq.data_ptr(), inv.data_ptr(), b.cuda_stream) == hps.OK
+        if i + 1 < steps:
+            with torch.cuda.stream(b):
+                gt.prepare(dk[i + 1], do, n_bags, 1)
+        with torch.cuda.stream(a if i % 2 else c):          # (the push reads what the pull on the other stream left)
+            (a if i % 2 else c).wait_stream(c if i % 2 else a)
+            gt.push(zero)
+    torch.cuda.synchronize()
+    assert gt.stats().error == 0
+    for i in range(steps):
+        want = ot.pull(keys[i], offsets)
+        ou, oi = ot.last_unique()
+        ot.push(np.zeros((n_bags, dim), np.float32))
+        assert np.all(np.abs(pooled[i].cpu().numpy() - want) <= 1e-6 + 1e-5 * np.abs(want)), "step %d" % i
+        if i == 8:
+            assert np.array_equal(uniq.cpu().numpy().view(np.uint64)[: ou.size], ou) and np.array_equal(inv.cpu().numpy(), oi)
+    assert gt.stats().size == ot.size
