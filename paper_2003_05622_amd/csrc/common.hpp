@@ -73,9 +73,8 @@ struct PullCtx {
   u32 sort_error;      // set if a look-back wait gave up (never expected)
   u32 n_total;         // occurrences of this dedup
   u32 by_id;           // 0: this dedup took the plain form, else 1 + the bucket form's kByRange, kByBorders, kByHash
-  u32 n_med;           // keys the push handles with one wave each
   u32 n_heavy;         // bucket form: frequent keys with a bucket of their own
-  u32 pad;
+  u32 pad[2];
   u32 n_slow_one_key;  // ... of n_slow, in buckets that one key fills at least half of
   KeyRange range;      // plain form: for the kernels after the first
   u32 uniq_shard[kCountShards];   // bucket form: distinct keys, spread over shards

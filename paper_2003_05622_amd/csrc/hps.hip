@@ -185,13 +185,14 @@ struct ContextLayout {
 struct WorkspaceLayout {
   size_t fresh, keys_a, keys_b, idx_a, idx_b, hist, prefix, total, tile_bag, heavy_raw, ghist,
       tickets, tile_rows, group_rows, head_rows, head_groups, evidence, bag_of, id16, by_pos, by_heavy, row_of,
-      med_list, arrived, chunk_items, partials, end;
+      med_list, med_span, arrived, chunk_items, partials, end;
   size_t local_rank, rank_by_pos, rank_by_heavy, bucket_total, sort_ctx, sort_n;     // hps_last_unique's own
   ContextLayout c[2];
   uint64_t max_long, max_items, sort_tiles, head_tiles;
 };
 
-WorkspaceLayout workspace_layout(uint64_t n, uint64_t bags, uint32_t dim) {
+// small: with what the small form needs (an accumulate on the static scratch does not take it).
+WorkspaceLayout workspace_layout(uint64_t n, uint64_t bags, uint32_t dim, bool small = true) {
   WorkspaceLayout L;
   const uint64_t n1 = n ? n : 1;
   const uint64_t buckets = (uint64_t)kMaxBuckets[kBucketClasses - 1] + 1;
@@ -236,7 +237,7 @@ WorkspaceLayout workspace_layout(uint64_t n, uint64_t bags, uint32_t dim) {
     L.c[k].bucket_start = o; o = align_up(o + (buckets + 1) * 4);
     L.c[k].count = o;   o = align_up(o + buckets * 4);
     L.c[k].border = o;  o = align_up(o + kMaxBorders * 8);
-    L.c[k].places = o;  o = align_up(o + std::min<uint64_t>(n1, kSmallMax) * 16);
+    L.c[k].places = o;  o = align_up(o + (small ? std::min<uint64_t>(n1, kSmallMax) * 16 : 0));
   }
   L.by_pos = o;      o = align_up(o + n1 * 4);      // row of the key at every position
   L.by_heavy = o;    o = align_up(o + (kMaxHeavy + 1) * 4);
@@ -249,6 +250,7 @@ WorkspaceLayout workspace_layout(uint64_t n, uint64_t bags, uint32_t dim) {
   L.sort_ctx = o;      o = align_up(o + sizeof(PullCtx));
   L.sort_n = o;        o = align_up(o + 4);
   L.med_list = o;    o = align_up(o + (n1 / (kShortSeg + 1) + kMaxHeavy + 64) * 4);
+  L.med_span = o;    o = align_up(o + (std::max<uint64_t>(buckets, n1 / 1024 + 2049) + kMaxHeavy / kHeavyGroup + 1) * 8);    // (unique_spans)
   L.arrived = o;     o = align_up(o + L.max_long * 4);
   L.chunk_items = o; o = align_up(o + L.max_items * 16);
   L.partials = o;    o = align_up(o + L.max_items * (size_t)dim * 4);
@@ -524,7 +526,7 @@ static void launch_push(hps_table* t, uint64_t n, PushArgs& a, hipStream_t s) {
   // (a span's distinct keys are fewer than its occurrences; about four keys per lane group)
   const uint64_t per_span = (n + a.spans.n_spans - 1) / a.spans.n_spans;
   a.parts = grid_for(per_span, 4 * kPushThreads / LPR, std::max(1u, std::min((unsigned)kPushMaxParts, kPushSplitBlocks / a.spans.n_spans)));
-  a.medium_blocks = kPushMediumBlocks;
+  a.medium_blocks = std::min(std::max(kPushMediumBlocks, a.spans.n_spans / 2), kPushMaxMediumBlocks);
   a.chunk = piece_sizes(LPR, n).chunk;
   a.chunk_blocks = grid_for(n / a.chunk + 1, 1, kPushChunkBlocks);
   const unsigned main_blocks = a.chunk_blocks + a.medium_blocks + heavy_blocks(a.spans) + a.spans.n_spans * a.parts;
@@ -602,6 +604,7 @@ static OftenLists start_lookup(hps_table* t, int c, uint64_t n_keys) {
   OftenLists often;
   often.ctx = t->ctx(c);
   often.med_list = t->w<u32>(t->wl.med_list);
+  often.med_span = t->w<uint2>(t->wl.med_span);
   often.chunk_items = t->w<uint4>(t->wl.chunk_items);
   often.arrived = t->w<u32>(t->wl.arrived);
   often.pieces = piece_sizes((u32)t->lpr, n_keys);
@@ -890,6 +893,7 @@ static void fill_push_args(hps_table* t, int c, uint64_t n_keys, const float* d_
   a.inv_len = nullptr;
   a.ctx = t->ctx(c);
   a.med_list = t->w<u32>(L.med_list);
+  a.med_span = t->w<uint2>(L.med_span);
   a.chunk_items = t->w<uint4>(L.chunk_items);
   a.arrived = t->w<u32>(L.arrived);
   a.partials = t->w<float>(L.partials);
@@ -1300,7 +1304,7 @@ hps_status hps_accumulate_static(hps_table* t, const uint64_t* d_keys, uint64_t 
   if (!t || (n && (!d_keys || !d_values))) return HPS_EINVAL;
   if (n > HPS_STATIC_MAX_KEYS || (uintptr_t)d_keys % 8 || (uintptr_t)d_values % 16) return HPS_EINVAL;
   if (t->current >= 0 || t->prepared >= 0) return HPS_ESTATE;
-  const WorkspaceLayout wl = workspace_layout(HPS_STATIC_MAX_KEYS, HPS_STATIC_MAX_KEYS, t->dim);
+  const WorkspaceLayout wl = workspace_layout(HPS_STATIC_MAX_KEYS, HPS_STATIC_MAX_KEYS, t->dim, false);
   if (wl.end > kStaticScratchBytes) return HPS_EINVAL;       // rows too wide for the static array
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) { (void)hipGetLastError(); return HPS_EDEVICE; }

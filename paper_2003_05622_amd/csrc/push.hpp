@@ -29,7 +29,7 @@
 namespace hps {
 
 constexpr int kPushThreads = 256;
-constexpr int kPushMediumBlocks = 512;   // fixed grids: waves and blocks loop
+constexpr u32 kPushMediumBlocks = 512, kPushMaxMediumBlocks = 2048;      // waves loop; about two waves a span
 // (one block per chunk, as many as the mini-batch could have, up to this: with 512 the skewed
 // workload, most of whose occurrences are chunks of very frequent keys, ran its push at two
 // waves per SIMD, 0.55 ms instead of 0.32; blocks without a chunk return at once)
@@ -55,6 +55,7 @@ struct PushArgs {
   const float* inv_len;   // != null (mean pooling): per bag, the share of its gradient an occurrence gets
   const PullCtx* ctx;
   const u32* med_list;        // unique indices
+  const uint2* med_span;      // per block of the lookup: its part of the list
   const uint4* chunk_items;   // (unique index, chunk number, number of the chunked key, its first chunk item)
   u32* arrived;               // per chunked key: chunks summed so far
   u32 chunk_blocks, medium_blocks;      // roles of push_main's blocks: chunks, medium, short
@@ -208,9 +209,32 @@ __device__ __forceinline__ void push_medium_role(const TableView& t, const PushA
   constexpr u32 kGroups = kWave / LPR;
   constexpr u32 kWavesPerBlock = kPushThreads / kWave;
   const u32 group = lane_id() / LPR, sub = lane_id() % LPR;
-  const u32 count = a.ctx->n_med;
-  for (u32 m = block * kWavesPerBlock + threadIdx.x / kWave; m < count; m += a.medium_blocks * kWavesPerBlock) {
-    const u32 u = a.med_list[m];
+  // The waves go through the parts of the list, a part at a time by `sharers` waves: a span's by a few, a group of heavy keys'
+  // (up to 64, of hundreds of occurrences each) by as many as it has entries.
+  const u32 n_heavy = heavy_blocks(a.spans), n_waves = a.medium_blocks * kWavesPerBlock;
+  const u32 heavy_work = n_heavy * kHeavyGroup, sharers = max(1u, n_waves / max(1u, a.spans.n_spans));
+  const u32 work = heavy_work + a.spans.n_spans * sharers;
+  u32 at = block * kWavesPerBlock + threadIdx.x / kWave, m = 0, step = 1;
+  uint2 part = make_uint2(0u, 0u);
+  bool fresh = true;
+  while (true) {
+    if (fresh) {
+      if (at >= work) break;
+      if (at < heavy_work) {
+        part = a.med_span[at / kHeavyGroup];
+        m = at % kHeavyGroup;
+        step = kHeavyGroup;
+      } else {
+        part = a.med_span[n_heavy + (at - heavy_work) / sharers];
+        m = (at - heavy_work) % sharers;
+        step = sharers;
+      }
+      at += n_waves;
+      fresh = false;
+    }
+    if (m >= part.y) { fresh = true; continue; }
+    const u32 u = a.med_list[part.x + m];
+    m += step;
     float4 g[COLS];
 #pragma unroll
     for (int c = 0; c < COLS; ++c) g[c] = make_float4(0.f, 0.f, 0.f, 0.f);

@@ -97,7 +97,7 @@ struct SmallLds {
     };
     SlowLds<kSmallThreads> slow;
   };
-  LookupLds<kSmallNewCap, 256, 64> look;
+  LookupLds<kSmallNewCap, 64> look;
   u32 scratch[kSmallWaves + 1];
   u32 wave_cnt[kSmallWaves], low[kSmallWaves];
   u32 full;
@@ -230,7 +230,10 @@ small_group(TableView t, SmallArgs a) {
   if (tid == 0) {
     a.bucket_start[c] = start;
     if (c + 1 == gridDim.x) a.bucket_start[c + 1] = n;
-    if (cnt == 0) a.count[c] = 0;
+    if (cnt == 0) {
+      a.count[c] = 0;
+      if (LOOKUP) a.often.med_span[c] = make_uint2(0u, 0u);
+    }
   }
   if (cnt == 0) return;
 
@@ -336,11 +339,10 @@ small_group(TableView t, SmallArgs a) {
       if (!slow) L.ukey[k] = row;
       if (tight) a.create.fresh[u] = mine_new ? 1 : 0;
       if (row == kNoRow) ++missing;
-      list_key(a.often, u, my_key, len, L.look);
+      list_key(a.often, med_first(start), u, my_key, len, L.look);
     }
     if (missing) atomicAdd(&L.look.missing, missing);
     __syncthreads();
-    end_lookup_counts(t, a.often, a.create, L.look);
   }
 
   // per occurrence: its key's number and row, its place in the grouped order
@@ -393,7 +395,7 @@ small_group(TableView t, SmallArgs a) {
   }
   if (look) {
     __syncthreads();
-    end_lookup_lists<kSmallThreads>(t, a.often, a.create, L.look);
+    end_lookup<kSmallThreads>(t, a.often, a.create, med_first(start), L.look);
   }
 }
 

@@ -307,7 +307,6 @@ __device__ __forceinline__ void reset_ctx(PullCtx* ctx, u32 n, u32 by_id, u32 n_
     ctx->sort_error = 0;
     ctx->n_slow = 0;
     ctx->n_slow_one_key = 0;
-    ctx->n_med = 0;
     ctx->n_heavy = n_heavy;
     ctx->n_total = n;
     ctx->by_id = by_id;

@@ -130,7 +130,6 @@ constexpr int kProbeMaxBlocks = 1024;
 constexpr u32 kNoSlot = ~0u;
 constexpr u32 kNewLdsCap = 1024;         // created keys a block of the lookup lists for its common initialisation
 constexpr u32 kLongLdsCap = 64;          // very frequent keys whose chunk items whole waves write (>= kHeavyGroup)
-constexpr u32 kMedLdsCap = 512;          // medium keys it buffers before it appends
 constexpr u32 kRowsLdsCap = 2048;        // distinct keys whose rows it keeps to hand them on by position
 constexpr u32 kShortSeg = 16;            // occurrences handled serially by one lane group
 
@@ -177,10 +176,13 @@ __device__ __forceinline__ void unique_span(const UniqueSpans& s, const PullCtx*
 
 // What the lookup leaves for the push about keys that occur often (push.hpp): keys with
 // kShortSeg < occurrences <= pieces.medium are listed, keys with more are cut into
-// chunks of pieces.chunk positions.
+// chunks of pieces.chunk positions.  Every block has its part of the list, with room for as many such keys as its
+// occurrences could be (their count goes to med_span, beside where the part starts): with one counter for all, two thousand blocks
+// queued up at it for 8 ns each.
 struct OftenLists {
   PullCtx* ctx;
   u32* med_list;
+  uint2* med_span;      // per block of a span or group of heavy keys: first entry, entries
   uint4* chunk_items;   // (unique index, chunk number, number of the chunked key, its first chunk item)
   u32* arrived;         // per chunked key: chunks the push has summed (cleared here)
   PieceSizes pieces;
@@ -259,7 +261,6 @@ __global__ void __launch_bounds__(64) set_ctx_empty(PullCtx* ctx, u32* seg_off) 
     ctx->sort_error = 0;
     ctx->n_slow = 0;
     ctx->n_slow_one_key = 0;
-    ctx->n_med = 0;
     ctx->n_heavy = 0;
     ctx->n_total = 0;
     ctx->by_id = 0;
@@ -588,15 +589,19 @@ __device__ __forceinline__ void note_tight(const TableView& t, const Creation& c
   t.st->tight = tight ? 1u : 0u;
 }
 
+// Where in med_list the part of a block starts whose first occurrence (in the grouped order) is `first`; that of a group of heavy
+// keys, h0 the first one's number, lies behind those of n occurrences.
+__host__ __device__ constexpr u32 med_first(u32 first) { return first / (kShortSeg + 1); }
+__host__ __device__ constexpr u32 med_first_heavy(u32 n, u32 h0) { return n / (kShortSeg + 1) + 1 + h0; }
+
 // What the threads of a block that looks up keys gather, to be written out together at the end.
-template <u32 NEW, u32 MED, u32 LONG>
+template <u32 NEW, u32 LONG>
 struct LookupLds {
-  static constexpr u32 kNew = NEW, kMed = MED, kLong = LONG;
-  u32 missing, n_new, n_med, med_base, n_long;
+  static constexpr u32 kNew = NEW, kLong = LONG;
+  u32 missing, n_new, n_med, n_long;
   uint4 long_list[LONG];  // (unique index, first chunk item, chunks, number) of very frequent keys
   u64 new_key[NEW];       // created keys, and their rows
   u32 new_row[NEW];
-  u32 med_list[MED];
   __device__ __forceinline__ void clear() { missing = n_new = n_med = n_long = 0; }
 };
 
@@ -666,7 +671,7 @@ __device__ __forceinline__ u32 lookup_key(const TableView& t, u64 my_key, bool c
 
 // Puts distinct key number u into the push's work lists, by its number of occurrences, and into the hint for later dedups.
 template <typename LDS>
-__device__ __forceinline__ void list_key(const OftenLists& often, u32 u, u64 key, u32 len, LDS& L) {
+__device__ __forceinline__ void list_key(const OftenLists& often, u32 med_base, u32 u, u64 key, u32 len, LDS& L) {
   PullCtx* ctx = often.ctx;
   if (len >= often.heavy_min && key != kEmptyKey) {
     const u32 at = atomicAdd(&often.heavy_raw->count, 1u);
@@ -686,23 +691,18 @@ __device__ __forceinline__ void list_key(const OftenLists& often, u32 u, u64 key
       for (u32 i = 0; i < n_chunks; ++i) often.chunk_items[item + i] = make_uint4(u, i, number, item);
     }
   } else if (len > kShortSeg) {
-    const u32 at = atomicAdd(&L.n_med, 1u);
-    if (at < LDS::kMed) L.med_list[at] = u;
-    else often.med_list[atomicAdd(&ctx->n_med, 1u)] = u;      // buffer full: append straight to the list
+    often.med_list[med_base + atomicAdd(&L.n_med, 1u)] = u;
   }
 }
 
-// After a barrier: writes out what the block's threads have gathered, in two steps with a barrier between them.
-template <typename LDS>
-__device__ __forceinline__ void end_lookup_counts(const TableView& t, const OftenLists& often, const Creation& create, LDS& L) {
+// After a barrier: writes out what the block's threads have gathered.
+template <int THREADS, typename LDS>
+__device__ __forceinline__ void end_lookup(const TableView& t, const OftenLists& often, const Creation& create, u32 med_base, LDS& L) {
   if (threadIdx.x == 0) {
     if (L.n_new) atomicAdd(&t.st->pull_made[create.set][blockIdx.x % kCountShards], L.n_new);
     if (L.missing) atomicAdd(&t.st->miss_shard[blockIdx.x % kCountShards], L.missing);
-    if (L.n_med) L.med_base = atomicAdd(&often.ctx->n_med, min(L.n_med, LDS::kMed));
+    often.med_span[blockIdx.x] = make_uint2(med_base, L.n_med);
   }
-}
-template <int THREADS, typename LDS>
-__device__ __forceinline__ void end_lookup_lists(const TableView& t, const OftenLists& often, const Creation& create, LDS& L) {
   {
     const u32 n_long_here = min(L.n_long, LDS::kLong);
     for (u32 e = threadIdx.x / kWave; e < n_long_here; e += THREADS / kWave) {
@@ -719,11 +719,6 @@ __device__ __forceinline__ void end_lookup_lists(const TableView& t, const Often
   }
   for (u32 e = threadIdx.x; e < n_new * t.acc_len; e += THREADS)
     acc_row(t, L.new_row[e / t.acc_len])[e % t.acc_len] = t.init_acc;
-  const u32 n_med = min(L.n_med, LDS::kMed);
-  if (n_med) {
-    __syncthreads();
-    for (u32 i = threadIdx.x; i < n_med; i += THREADS) often.med_list[L.med_base + i] = L.med_list[i];
-  }
 }
 
 // rows[u] = the slot of distinct key u.  Keys the table does not hold:
@@ -739,7 +734,7 @@ __device__ __forceinline__ void end_lookup_lists(const TableView& t, const Often
 __global__ void __launch_bounds__(kProbeThreads)
 pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ seg_off, UniqueSpans spans,
             u32* __restrict__ rows, RowsByPosition out, Creation create, OftenLists often) {
-  typedef LookupLds<kNewLdsCap, kMedLdsCap, kLongLdsCap> Lds;
+  typedef LookupLds<kNewLdsCap, kLongLdsCap> Lds;
   __shared__ Lds L;
   __shared__ u32 s_rows[kRowsLdsCap];
   __shared__ u32 s_unique;
@@ -761,7 +756,11 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ s
   u32 first = 0, count;
   if (heavies) count = ctx->n_heavy > h0 ? min(kHeavyGroup, ctx->n_heavy - h0) : 0u;
   else unique_span(spans, ctx, c, &first, &count);
-  if (count == 0) return;
+  if (count == 0) {
+    if (threadIdx.x == 0) often.med_span[blockIdx.x] = make_uint2(0u, 0u);
+    return;
+  }
+  const u32 med_base = heavies ? med_first_heavy(ctx->n_total, h0) : med_first(spans.bucket_start ? first : seg_off[first]);
   if (threadIdx.x == 0) L.clear();
   if (create.how == kCreateIfRoom && threadIdx.x < kWave) {
     // (kCountShards == kWave) distinct keys of the whole mini-batch
@@ -800,13 +799,12 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ s
     if (tight) create.fresh[u] = mine_new ? 1 : 0;
     if (heavies && out.upos) out.by_heavy[h0 + k] = my_row;
     if (my_row == kNoRow) ++missing;
-    list_key(often, u, my_key, my_len, L);
+    list_key(often, med_base, u, my_key, my_len, L);
   }
   if (missing) atomicAdd(&L.missing, missing);
   __syncthreads();
-  end_lookup_counts(t, often, create, L);
   if (out.upos && !heavies) rows_by_position(spans, out, c, first, rows, count <= kRowsLdsCap ? s_rows : nullptr);      // (this block's own rows[])
-  end_lookup_lists<kProbeThreads>(t, often, create, L);
+  end_lookup<kProbeThreads>(t, often, create, med_base, L);
 }
 
 // Whether the keys a lookup found missing (st->miss_shard) may be created: 0 there are none, 1 yes,

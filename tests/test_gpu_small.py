@@ -103,3 +103,13 @@ def test_accumulate(n, rank):
         st = gt.stats()
         assert st.error == 0 and st.last_n_absent == absent
         close(gt.get(dev(known))[0].cpu().numpy(), ot.get(known)[0], "weights, step %d" % step)
+
+
+def test_static_scratch_holds_the_widest_rows():
+    n, dim = 1000, 1024
+    gt = hps.HpsTable(4 * n, dim, n, 1)
+    keys = dev(synth.mix64(np.arange(n, dtype=np.uint64)))
+    gt.insert(keys)
+    before = gt.get(keys)[0]
+    gt.accumulate_static(keys, torch.full((n, dim), 0.5, device="cuda"))
+    assert torch.equal(gt.get(keys)[0], before + 0.5) and gt.stats().error == 0
