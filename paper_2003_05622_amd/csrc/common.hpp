@@ -151,6 +151,43 @@ __device__ __forceinline__ u32 dpp_or_zero(u32 v) {
   return (u32)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
 }
 
+// The value lane k (a constant after unrolling, below eight) of each group of LPR lanes holds, in all its lanes: full-rate moves.
+template <int LPR>
+__device__ __forceinline__ u32 group_lane(u32 v, int k) {
+  static_assert(LPR == 1 || LPR == 2 || LPR == 4 || LPR == 8 || LPR == 16 || LPR == 32 || LPR == 64, "");
+  if (LPR == 1) return v;
+  if (LPR == 2) return (u32)(k == 0 ? __builtin_amdgcn_mov_dpp((int)v, 0xA0, 0xF, 0xF, true) : __builtin_amdgcn_mov_dpp((int)v, 0xF5, 0xF, 0xF, true));
+#define HPS_LANE(K)                                                                                                           \
+  case K:                                                                                                                     \
+    if (LPR == 4) return (u32)__builtin_amdgcn_mov_dpp((int)v, (K & 3) * 0x55, 0xF, 0xF, true);             /* within four */  \
+    if (LPR == 16) return (u32)__builtin_amdgcn_mov_dpp((int)v, 0x150 + K, 0xF, 0xF, true);                 /* within 16 */    \
+    if (LPR == 8)                                                                                           /* half by half */ \
+      return (u32)__builtin_amdgcn_update_dpp(__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + K, 0xF, 0x3, false), (int)v, 0x158 + K, 0xF, 0xC, false); \
+    break;
+  switch (k) { HPS_LANE(0) HPS_LANE(1) HPS_LANE(2) HPS_LANE(3) HPS_LANE(4) HPS_LANE(5) HPS_LANE(6) HPS_LANE(7) }
+#undef HPS_LANE
+  const u32 low = (u32)__builtin_amdgcn_readlane((int)v, k);
+  if (LPR == 64) return low;
+  const u32 high = (u32)__builtin_amdgcn_readlane((int)v, 32 + k);
+  return lane_id() < 32 ? low : high;
+}
+
+// Eight items a group of LPR lanes has in flight, each known to one lane (item j to lane j % LPR, as its number j / LPR): where
+// they lie, as byte offsets.
+constexpr u64 kNowhere = ~0ull;
+template <int LPR>
+struct GroupOffsets {
+  static constexpr int kOwn = LPR < 8 ? 8 / LPR : 1;
+  u64 own[kOwn];
+  // The offset of item k; false: there is none.
+  __device__ __forceinline__ bool get(int k, u64* offset) const {
+    const u64 v = own[k / LPR];
+    const u32 high = group_lane<LPR>((u32)(v >> 32), k % LPR);
+    *offset = (u64)high << 32 | group_lane<LPR>((u32)v, k % LPR);
+    return high != 0xFFFFFFFFu;
+  }
+};
+
 // Inclusive sum over the 64 lanes of a wave.
 __device__ __forceinline__ u32 wave_incl_sum(u32 v) {
   v += dpp_or_zero<0x111, 0xF>(v);

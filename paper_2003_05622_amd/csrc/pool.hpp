@@ -3,7 +3,10 @@
 // also receives 1 / (bag length) per bag, which the push needs to hand every occurrence
 // its share of the bag's gradient).  A group of LPR lanes owns one bag at a time;
 // each lane carries COLS float4 columns (lane*4 + k*LPR*4; COLS = 1 up to dim 256).
-// Eight occurrences are in flight at a time: their row numbers, then their rows.
+// Eight occurrences are in flight at a time.  Wide rows (dim 64, keys that repeat: the caches serve nearly all of them) are bound by
+// the instructions per row, so a row's number and place are worked out by one lane of the group and handed to the others by moves; narrow
+// ones by the lines they ask for (9.8 M occurrences, dim 16: 170 us, 58 G rows/s) and by the round trips of a turn, which
+// overlap.  8.4 M occurrences, dim 64: 215 us with every lane loading every number, 208 now; 40 K, dim 100: 8.9 and 7.6.
 // The kernel also ends the pull (table.hpp: end_pull).
 #pragma once
 
@@ -16,75 +19,111 @@ constexpr int kPoolThreads = 256;
 constexpr int kPoolMaxBlocks = 1024;   // the groups loop over the bags (1536 to 3072 blocks measured no faster)
 constexpr int kPoolInFlight = 8;
 
+// A bag's occurrences, clamped so that no offsets array can make the kernel read outside row_of[0, n).
+struct BagRange {
+  i32 lo, hi;
+};
+__device__ __forceinline__ BagRange load_bag(const i32* __restrict__ offsets, u32 b, u32 n_bags, u32 n) {
+  BagRange r = {0, 0};
+  if (b < n_bags) { r.lo = max(offsets[b], 0); r.hi = min(offsets[b + 1], (i32)n); }
+  return r;
+}
+
+// A group's bags are b, b + n_groups, ...; `bag` and `next` the first two's occurrences.
 template <int LPR, int COLS, bool BF16, bool SMALL>
-__device__ __forceinline__ void pool_bags_as(const TableView& t, const i32* __restrict__ offsets,
+__device__ __forceinline__ void pool_bags_as(const TableView& t, const i32* __restrict__ offsets, u32 b, BagRange bag, BagRange next,
                                              u32 n_bags, u32 n, const u32* __restrict__ row_of,
                                              float* __restrict__ pooled, float* __restrict__ inv_len,
                                              const uint4* __restrict__ places, u32* __restrict__ bags) {
   const u32 sub = threadIdx.x % LPR;
   const u32 dim4 = t.dim >> 2;
   const u32 n_groups = gridDim.x * (kPoolThreads / LPR);
-  for (u32 b = (blockIdx.x * kPoolThreads + threadIdx.x) / LPR; b < n_bags; b += n_groups) {
-    float4 acc[COLS];
+  float4 acc[COLS];
 #pragma unroll
-    for (int c = 0; c < COLS; ++c) acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-    // clamped, so that no offsets array can make the kernel read outside row_of[0, n)
-    const i32 lo = max(offsets[b], 0), hi = min(offsets[b + 1], (i32)n);
-    for (i32 i0 = lo; i0 < hi; i0 += kPoolInFlight) {
-      u32 r[kPoolInFlight];
+  for (int c = 0; c < COLS; ++c) acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+  // the rows of the next eight occurrences; each lane looks up its share of them
+  GroupOffsets<LPR> rows;
+  u32 at[GroupOffsets<LPR>::kOwn];      // SMALL: positions in the grouped order
+  auto load_rows = [&](i32 i0, i32 hi) {
 #pragma unroll
-      for (int k = 0; k < kPoolInFlight; ++k) {
-        if (SMALL) {
-          const uint2 p = i0 + k < hi ? *reinterpret_cast<const uint2*>(places + i0 + k) : make_uint2(kNoRow, 0u);
-          r[k] = p.x;
-          // (the lanes of the group share the stores)
-          if (i0 + k < hi && (u32)k % LPR == sub) bags[p.y] = b;
-        } else {
-          r[k] = i0 + k < hi ? row_of[i0 + k] : kNoRow;
-        }
+    for (int q = 0; q < GroupOffsets<LPR>::kOwn; ++q) {
+      const u32 j = q * LPR + sub;
+      const bool on = j < (u32)kPoolInFlight && i0 + (i32)j < hi;
+      u32 r = kNoRow;
+      if (SMALL) {
+        const uint2 p = on ? *reinterpret_cast<const uint2*>(places + i0 + j) : make_uint2(kNoRow, kNoRow);
+        r = p.x;
+        at[q] = p.y;
+      } else if (on) {
+        r = row_of[i0 + j];
       }
-      // the rows as stored (all loads first: nothing between them that needs their data) ...
-      StoredW4<BF16> raw[kPoolInFlight][COLS];
+      rows.own[q] = r == kNoRow ? kNowhere : (u64)r * t.w_pitch;
+    }
+  };
+  i32 i0 = bag.lo;
+  load_rows(i0, bag.hi);
+  // Eight rows a turn, of one bag.  The row numbers of the next turn, whichever bag that is in, and the bounds of the bag after
+  // it are requested behind the rows of this one, so that a turn is one round trip and not three.
+  while (b < n_bags) {
+    // the rows as stored (all loads first: nothing between them that needs their data) ...
+    StoredW4<BF16> raw[kPoolInFlight][COLS];
 #pragma unroll
-      for (int k = 0; k < kPoolInFlight; ++k) {
-#pragma unroll
-        for (int c = 0; c < COLS; ++c) {
-          const u32 col = sub + c * LPR;
-          raw[k][c] = (r[k] != kNoRow && col < dim4) ? load_stored_w4<BF16>(t, r[k], col) : StoredW4<BF16>();
-        }
-      }
-      // ... then as float32 (all-zero bits are 0.0 in both formats)
-      float4 v[kPoolInFlight][COLS];
-#pragma unroll
-      for (int k = 0; k < kPoolInFlight; ++k)
-#pragma unroll
-        for (int c = 0; c < COLS; ++c) v[k][c] = raw[k][c].value();
-      // the (up to) eight rows as a balanced tree, then onto the running sum: a fixed shape,
-      // and a smaller rounding error than adding one row after the other
+    for (int k = 0; k < kPoolInFlight; ++k) {
+      u64 offset;
+      const bool on = rows.get(k, &offset);
 #pragma unroll
       for (int c = 0; c < COLS; ++c) {
-#pragma unroll
-        for (int w = 1; w < kPoolInFlight; w <<= 1) {
-#pragma unroll
-          for (int k = 0; k + w < kPoolInFlight; k += 2 * w) {
-            v[k][c].x += v[k + w][c].x; v[k][c].y += v[k + w][c].y;
-            v[k][c].z += v[k + w][c].z; v[k][c].w += v[k + w][c].w;
-          }
-        }
-        acc[c].x += v[0][c].x; acc[c].y += v[0][c].y; acc[c].z += v[0][c].z; acc[c].w += v[0][c].w;
+        const u32 col = sub + c * LPR;
+        if (on && col < dim4) raw[k][c].raw = reinterpret_cast<const decltype(raw[k][c].raw)*>(t.w + offset)[col];
       }
     }
-    if (inv_len) {
-      const float len = (float)max(hi - lo, 1);
-      if (sub == 0) inv_len[b] = 1.0f / len;
+    if (SMALL) {
 #pragma unroll
-      for (int c = 0; c < COLS; ++c) { acc[c].x /= len; acc[c].y /= len; acc[c].z /= len; acc[c].w /= len; }
+      for (int q = 0; q < GroupOffsets<LPR>::kOwn; ++q)
+        if (at[q] != kNoRow) bags[at[q]] = b;
     }
-    float4* out = reinterpret_cast<float4*>(pooled + (u64)b * t.dim);
+    const bool last = i0 + kPoolInFlight >= bag.hi;
+    i0 = last ? next.lo : i0 + kPoolInFlight;
+    load_rows(i0, last ? next.hi : bag.hi);
+    BagRange after = next;
+    if (last) after = load_bag(offsets, b + 2 * n_groups, n_bags, n);
+    // ... then as float32 (all-zero bits are 0.0 in both formats)
+    float4 v[kPoolInFlight][COLS];
+#pragma unroll
+    for (int k = 0; k < kPoolInFlight; ++k)
+#pragma unroll
+      for (int c = 0; c < COLS; ++c) v[k][c] = raw[k][c].value();
+    // the (up to) eight rows as a balanced tree, then onto the running sum: a fixed shape,
+    // and a smaller rounding error than adding one row after the other
 #pragma unroll
     for (int c = 0; c < COLS; ++c) {
-      const u32 col = sub + c * LPR;
-      if (col < dim4) out[col] = acc[c];
+#pragma unroll
+      for (int w = 1; w < kPoolInFlight; w <<= 1) {
+#pragma unroll
+        for (int k = 0; k + w < kPoolInFlight; k += 2 * w) {
+          v[k][c].x += v[k + w][c].x; v[k][c].y += v[k + w][c].y;
+          v[k][c].z += v[k + w][c].z; v[k][c].w += v[k + w][c].w;
+        }
+      }
+      acc[c].x += v[0][c].x; acc[c].y += v[0][c].y; acc[c].z += v[0][c].z; acc[c].w += v[0][c].w;
+    }
+    if (last) {
+      if (inv_len) {
+        const float len = (float)max(bag.hi - bag.lo, 1);
+        if (sub == 0) inv_len[b] = 1.0f / len;
+#pragma unroll
+        for (int c = 0; c < COLS; ++c) { acc[c].x /= len; acc[c].y /= len; acc[c].z /= len; acc[c].w /= len; }
+      }
+      float4* out = reinterpret_cast<float4*>(pooled + (u64)b * t.dim);
+#pragma unroll
+      for (int c = 0; c < COLS; ++c) {
+        const u32 col = sub + c * LPR;
+        if (col < dim4) out[col] = acc[c];
+        acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+      b += n_groups;
+      bag = next;
+      next = after;
     }
   }
 }
@@ -96,9 +135,11 @@ __global__ void __launch_bounds__(kPoolThreads)
 pool_bags(TableView t, const i32* __restrict__ offsets, u32 n_bags, u32 n, const u32* __restrict__ row_of,
           float* __restrict__ pooled, float* __restrict__ inv_len, const uint4* __restrict__ places, u32* __restrict__ bags,
           PullEnd end) {
+  const u32 b = (blockIdx.x * kPoolThreads + threadIdx.x) / LPR, n_groups = gridDim.x * (kPoolThreads / LPR);
+  const BagRange bag = load_bag(offsets, b, n_bags, n), next = load_bag(offsets, b + n_groups, n_bags, n);
   if (!end_pull(t, end)) return;
-  if (t.bf16) pool_bags_as<LPR, COLS, true, SMALL>(t, offsets, n_bags, n, row_of, pooled, inv_len, places, bags);
-  else pool_bags_as<LPR, COLS, false, SMALL>(t, offsets, n_bags, n, row_of, pooled, inv_len, places, bags);
+  if (t.bf16) pool_bags_as<LPR, COLS, true, SMALL>(t, offsets, b, bag, next, n_bags, n, row_of, pooled, inv_len, places, bags);
+  else pool_bags_as<LPR, COLS, false, SMALL>(t, offsets, b, bag, next, n_bags, n, row_of, pooled, inv_len, places, bags);
 }
 
 // Plain form of the dedup: row_of[i] = rows[inverse[i]].

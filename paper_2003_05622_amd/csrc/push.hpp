@@ -132,35 +132,41 @@ template <int LPR, int COLS>
 __device__ __forceinline__ void add_positions(float4* g, const PushArgs& a, u32 lo, u32 hi,
                                               u32 stride, u32 dim, u32 sub) {
   const u32 dim4 = dim >> 2;
+  typedef GroupOffsets<LPR> Offsets;
   for (u32 j0 = lo; j0 < hi; j0 += kPushInFlight * stride) {
-    u32 bag[kPushInFlight];
-    bool on[kPushInFlight];
+    // (Each lane looks up its share of the bags.  Requesting the next ones behind the rows, as the pooling does, costs two waves per SIMD
+    // and more: 4.2 M occurrences, dim 64, bfloat16 rows, 218 -> 417 us.)
+    Offsets rows;
+    float own_share[Offsets::kOwn];
 #pragma unroll
-    for (int k = 0; k < kPushInFlight; ++k) {
-      const u32 j = j0 + k * stride;
-      on[k] = j < hi;
-      bag[k] = on[k] ? a.bags[j] : 0u;
+    for (int q = 0; q < Offsets::kOwn; ++q) {
+      const u32 k = q * LPR + sub, j = j0 + k * stride;
+      const bool on = k < (u32)kPushInFlight && j < hi;
+      const u32 bag = on ? a.bags[j] : 0u;
+      rows.own[q] = on ? (u64)bag * (dim * sizeof(float)) : kNowhere;
+      own_share[q] = a.inv_len && on ? a.inv_len[bag] : 1.0f;
     }
     float4 v[kPushInFlight][COLS];
-    float share[kPushInFlight];
-#pragma unroll
-    for (int k = 0; k < kPushInFlight; ++k) share[k] = (a.inv_len && on[k]) ? a.inv_len[bag[k]] : 1.0f;
 #pragma unroll
     for (int k = 0; k < kPushInFlight; ++k) {
-      const float4* row = reinterpret_cast<const float4*>(a.grads + (u64)bag[k] * dim);
+      u64 offset;
+      const bool on = rows.get(k, &offset);
+      const float4* row = reinterpret_cast<const float4*>(reinterpret_cast<const char*>(a.grads) + offset);
 #pragma unroll
       for (int c = 0; c < COLS; ++c) {
         const u32 col = sub + c * LPR;
-        v[k][c] = (on[k] && col < dim4) ? row[col] : make_float4(0.f, 0.f, 0.f, 0.f);
+        v[k][c] = (on && col < dim4) ? row[col] : make_float4(0.f, 0.f, 0.f, 0.f);
       }
     }
     if (a.inv_len) {
 #pragma unroll
-      for (int k = 0; k < kPushInFlight; ++k)
+      for (int k = 0; k < kPushInFlight; ++k) {
+        const float share = __uint_as_float(group_lane<LPR>(__float_as_uint(own_share[k / LPR < Offsets::kOwn ? k / LPR : 0]), k % LPR));
 #pragma unroll
         for (int c = 0; c < COLS; ++c) {
-          v[k][c].x *= share[k]; v[k][c].y *= share[k]; v[k][c].z *= share[k]; v[k][c].w *= share[k];
+          v[k][c].x *= share; v[k][c].y *= share; v[k][c].z *= share; v[k][c].w *= share;
         }
+      }
     }
 #pragma unroll
     for (int c = 0; c < COLS; ++c) {
