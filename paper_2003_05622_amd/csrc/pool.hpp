@@ -118,7 +118,10 @@ __device__ __forceinline__ void pool_bags_as(const TableView& t, const i32* __re
 #pragma unroll
       for (int c = 0; c < COLS; ++c) {
         const u32 col = sub + c * LPR;
-        if (col < dim4) out[col] = acc[c];
+        // (past the L2, which is left to the rows: 8.4 M occurrences, dim 64: 208.5 -> 204 us, and the push after it 309 -> 303)
+        typedef float Words4 __attribute__((ext_vector_type(4)));
+        const Words4 x = {acc[c].x, acc[c].y, acc[c].z, acc[c].w};
+        if (col < dim4) __builtin_nontemporal_store(x, reinterpret_cast<Words4*>(out + col));
         acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
       }
       b += n_groups;
