@@ -320,6 +320,7 @@ struct hps_table {
   int lpr;
   bool mean_pooling;        // bags are averaged instead of summed (hps_set_pooling)
   uint64_t lookup_serial;   // lookups so far; lookup s lists its frequent keys in ring slot s % 3
+  uint64_t dumped;          // TableState::dump_count after the last dump (~0: not known, that dump failed)
   uint64_t pull_serial;     // pulls with bags so far: they take the two sets of counts in turn (common.hpp: pull_made)
   int dedup_mode;      // 0: by size and history; 1: plain radix passes always; 2, 3, 4: bucket form whenever it can, by range, borders, hash;
                        // 5: small form up to kSmallMax, beyond by hash
@@ -1039,7 +1040,7 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   t->serial = 0;
   t->plain_serial = 0;
   t->mean_pooling = false;
-  t->lookup_serial = t->pull_serial = 0;
+  t->lookup_serial = t->pull_serial = t->dumped = 0;
   t->away = hps_table::kHotKeys;
   t->stand_in_from = 0;
   t->unlisted = 0;
@@ -1109,6 +1110,7 @@ hps_status hps_clear(hps_table* t, void* stream) {
   // claimed, and the marks of updated rows live in the accumulators
   fill_u64<<<4096, 256, 0, s>>>(t->view.keys, t->n_slots, kEmptyKey);
   reset_state<<<1, 64, 0, s>>>(t->view.st);
+  t->dumped = 0;
   return launch_ok() ? HPS_OK : HPS_EDEVICE;
 }
 
@@ -1270,8 +1272,7 @@ static hps_status accumulate_launches(hps_table* t, const uint64_t* d_keys, uint
   launch_dedup(t, c, d_keys, (u32)n, nullptr, (u32)n, kWithAddLookup, s);
   if (n) {
     launch_lookup(t, c, n, false, s);
-    commit_absent<<<1, 64, 0, s>>>(t->view.st);
-    PushArgs a;
+    PushArgs a;                      // (its kernel also books the keys that were not found)
     fill_push_args(t, c, n, d_values, kStepAdd, a);
 #define CALL(LPR) launch_push<LPR>(t, n, a, s)
     HPS_DISPATCH_LPR(t->lpr, CALL)
@@ -1500,10 +1501,15 @@ static hps_status dump_impl(hps_table* t, bool dirty, uint64_t* d_keys_out, floa
   if (!t || !h_n_rows) return HPS_EINVAL;
   if (max_rows && (!d_keys_out || !d_weights_out || !d_acc_out)) return HPS_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  clear_dump_count<<<1, 1, 0, s>>>(t->view.st);
+  if (t->dumped == ~0ull) {
+    fill_u64<<<1, 64, 0, s>>>(reinterpret_cast<u64*>(&t->view.st->dump_count), 1, 0);
+    t->dumped = 0;
+  }
+  const uint64_t counted = t->dumped;
+  t->dumped = ~0ull;
 #define HPS_DUMP(DIRTY, ROUNDS)                                                                                     \
   dump_rows<DIRTY, ROUNDS><<<grid_for(t->n_slots, kDumpSlots * ROUNDS, kDumpMaxBlocks), kRowThreads, 0, s>>>(        \
-      t->view, d_keys_out, d_weights_out, d_acc_out, max_rows, &t->view.st->dump_count)
+      t->view, d_keys_out, d_weights_out, d_acc_out, max_rows, &t->view.st->dump_count, counted)
   if (t->n_slots < kDumpSmall) { if (dirty) HPS_DUMP(true, 1); else HPS_DUMP(false, 1); }
   else { if (dirty) HPS_DUMP(true, kDumpRounds); else HPS_DUMP(false, kDumpRounds); }
 #undef HPS_DUMP
@@ -1512,6 +1518,8 @@ static hps_status dump_impl(hps_table* t, bool dirty, uint64_t* d_keys_out, floa
   if (hipMemcpyAsync(&count, &t->view.st->dump_count, sizeof(count), hipMemcpyDeviceToHost, s) != hipSuccess)
     return HPS_EDEVICE;
   if (hipStreamSynchronize(s) != hipSuccess) return HPS_EDEVICE;
+  t->dumped = count;
+  count -= counted;
   *h_n_rows = count;
   return count > max_rows ? HPS_ENOMEM : HPS_OK;
 }

@@ -198,10 +198,8 @@ __device__ __forceinline__ void push_short_role(const TableView& t, const PushAr
       u = a.spans.bucket_start[a.spans.n_spans + h0 + k];
       if (a.spans.bucket_start[a.spans.n_spans + h0 + k + 1] == u) continue;
     }
-    const u32 lo = a.seg_off[u], hi = a.seg_off[u + 1];
-    if (hi - lo > kShortSeg) continue;      // on one of the lists
-    const u32 r = a.rows[u];
-    if (r == kNoRow) continue;
+    const u32 lo = a.seg_off[u], hi = a.seg_off[u + 1], r = a.rows[u];
+    if (hi - lo > kShortSeg || r == kNoRow) continue;      // on one of the lists, or nowhere
     float4 g[COLS];
 #pragma unroll
     for (int c = 0; c < COLS; ++c) g[c] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -364,6 +362,7 @@ template <int LPR, int COLS>
 __global__ void __launch_bounds__(kPushThreads) push_main(TableView t, PushArgs a) {
   __shared__ float4 lds[kPushThreads];
   __shared__ u32 s_last;
+  if (a.kind == kStepAdd && blockIdx.x == 0 && threadIdx.x < kWave) commit_absent_wave(t.st);
   if (load_error(t.st) != 0) return;
   const u32 b = blockIdx.x;
   const u32 n_short = heavy_blocks(a.spans) + a.spans.n_spans * a.parts;

@@ -241,7 +241,7 @@ insert_rows(TableView t, const u64* __restrict__ keys, u64 n_keys, const float* 
 // dump: every occupied slot (DIRTY: every occupied slot whose row is marked as updated; the mark
 // of a row that is written out is cleared), order unspecified.  A block looks at kDumpSlots * ROUNDS
 // slots at a time, lists the rows to go out in LDS, takes places for them from one counter and
-// moves them with all lanes.
+// moves them with all lanes.  The counter goes on from dump to dump: `counted` is where it stood.
 //
 // What bounds it is the read of every slot's key or mark, and the one counter, whose additions the memory
 // side takes one after the other: kDumpRounds = 4 keeps them few.  Where the accumulators lie in an array
@@ -256,7 +256,7 @@ constexpr u64 kDumpSmall = 1u << 20;      // fewer slots: one round a block, so 
 template <bool DIRTY, int ROUNDS>
 __global__ void __launch_bounds__(kRowThreads)
 dump_rows(TableView t, u64* __restrict__ keys_out, float* __restrict__ w_out,
-          float* __restrict__ acc_out, u64 max_rows, unsigned long long* __restrict__ counter) {
+          float* __restrict__ acc_out, u64 max_rows, unsigned long long* __restrict__ counter, u64 counted) {
   __shared__ u32 scratch[kRowThreads / kWave + 1];
   __shared__ unsigned long long s_base;
   __shared__ u32 s_slot[kDumpSlots * ROUNDS];
@@ -312,7 +312,7 @@ dump_rows(TableView t, u64* __restrict__ keys_out, float* __restrict__ w_out,
       const u32 q = __ffs(left) - 1;
       s_slot[at++] = (u32)(first + q / kDumpItems * kDumpSlots + q % kDumpItems);
     }
-    if (threadIdx.x == 0 && total) s_base = atomicAdd(counter, (unsigned long long)total);
+    if (threadIdx.x == 0 && total) s_base = atomicAdd(counter, (unsigned long long)total) - counted;
     __syncthreads();
     if (total) {
       const u64 base = s_base;

@@ -251,7 +251,6 @@ __global__ void __launch_bounds__(64) clear_error(TableState* st) {
   if (threadIdx.x == 0) st->error = 0;
   clear_counts(st);
 }
-__global__ void clear_dump_count(TableState* st) { st->dump_count = 0; }
 __global__ void __launch_bounds__(64) set_ctx_empty(PullCtx* ctx, u32* seg_off) {
   if (threadIdx.x == 0) {
     ctx->n_unique = 0;
@@ -283,8 +282,8 @@ __global__ void __launch_bounds__(64) commit_insert(TableState* st) {
 }
 
 // After a lookup that creates nothing (accumulate): the number of keys not found
-// goes to st->absent, the counters are cleared.
-__global__ void __launch_bounds__(64) commit_absent(TableState* st) {
+// goes to st->absent, the counters are cleared.  One wave; of the push, or where there is nothing to push a kernel.
+__device__ __forceinline__ void commit_absent_wave(TableState* st) {
   const u32 lane = lane_id();
   u32 missing = lane < kCountShards ? st->miss_shard[lane] : 0;
 #pragma unroll
@@ -292,6 +291,7 @@ __global__ void __launch_bounds__(64) commit_absent(TableState* st) {
   if (lane < kCountShards) st->miss_shard[lane] = 0;
   if (lane == 0) st->absent = (int)missing;
 }
+__global__ void __launch_bounds__(64) commit_absent(TableState* st) { commit_absent_wave(st); }
 
 // Where a key's probe sequence starts: an even line (n_lines is even), so that a 128-byte
 // memory line holds the first two lines of the sequence.
