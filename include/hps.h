@@ -54,18 +54,23 @@
  *     reads a list that is still being written), which form the dedup takes (below), and,
  *     in the plain form, the sequence number that tells its kernels which of the
  *     workspace's hand-off words are theirs.
- *   - The key dedup has two forms with identical results; the library picks one per call
+ *   - The key dedup has three forms with identical results; the library picks one per call
  *     from the mini-batch's size and the table's history.  A table's third and later dedups
  *     use the keys that earlier lookups found frequent and run without any waits between
  *     workgroups (counts per tile, a scan, a scatter into buckets; then every bucket's keys are
- *     grouped inside one workgroup).  The lookups report back, into pinned host memory that
- *     nobody waits for, when the keys did not suit that form, and the next dedups then deal
- *     the keys out by their hashes instead of by their range (if the keys lie unevenly in that; by
+ *     grouped inside one workgroup).  The buckets are parts of the keys' hashes, and up to 65536
+ *     occurrences each bucket's workgroup picks its keys out by itself and looks them up in the same launch,
+ *     unless hps_last_unique was called within the last three dedups: then they are parts of the keys' range.  The lookups report
+ *     back, into pinned host memory that nobody waits for, when the keys did not suit that, and the next dedups then deal
+ *     the keys out by their hashes instead (by
  *     sampled borders where hps_last_unique is in use, up to 2^19 occurrences), or take
  *     the plain form (radix passes with look-back between tiles), sorting by all 64 key
  *     bits if need be: hps_stats().n_plain_fallbacks, .n_full_fallbacks.  What a pull needs of
  *     a dedup is the occurrences grouped by key; the ascending order of the unique keys is
  *     worked out when hps_last_unique asks for it.
+ *   - Calls on one stream are ordered by it.  hps_prepare, hps_pull, hps_pull_prepared, hps_push, hps_accumulate and hps_last_unique
+ *     of one table may also come on several streams and are ordered by events; the first of them that comes on another stream
+ *     than the ones before waits for the device, unless hps_prepare has been called before.
  *   - Environment variables, read by hps_create, for tests and comparison runs:
  *     HPS_DEDUP = "radix" | "bucket" | "borders" | "hashed" | "small" (up to 65536 occurrences, beyond "hashed") pins the
  *     dedup's form; HPS_RANK = "ballot" ranks the
