@@ -11,7 +11,7 @@
 //                 per wave, so that afterwards every wave can place its occurrences in their order without waiting for
 //                 the others.  Then the distinct keys are looked up.
 //
-// 20 and 40 thousand occurrences (dim 8 and 100, a key with an eighth of them): 17 and 23 us in the two launches, 40 and 43 in the
+// 20 and 40 thousand occurrences (dim 8 and 100, a key with an eighth of them): 18 and 25 us in the two launches, 37 and 42 in the
 // six (dedup, lookup, missing keys, rows by occurrence) they stand for.  What bounds it is the chain of round trips (ids, keys, slots) and,
 // in the block with the most frequent key, that key's occurrences.  (Hashing all keys in every block instead, with no launch
 // before it: 24 and 41 us, of which 8 and 12 are the hashes.)

@@ -60,10 +60,6 @@ __device__ __forceinline__ float* acc_row(const TableView& t, u64 row) {
   return reinterpret_cast<float*>(t.acc + row * t.acc_pitch);
 }
 // Element j of row `row`.
-__device__ __forceinline__ float load_w(const TableView& t, u64 row, u32 j) {
-  if (t.bf16) return bf16_value(reinterpret_cast<const unsigned short*>(w_row(t, row))[j]);
-  return reinterpret_cast<const float*>(w_row(t, row))[j];
-}
 __device__ __forceinline__ void store_w(const TableView& t, u64 row, u32 j, float v) {
   if (t.bf16) reinterpret_cast<unsigned short*>(w_row(t, row))[j] = (unsigned short)bf16_nearest(v);
   else reinterpret_cast<float*>(w_row(t, row))[j] = v;
@@ -127,7 +123,6 @@ constexpr int kLookupLanes = 4;
 constexpr int kPullInFlight = 4;
 static_assert(kPullInFlight % kLookupLanes == 0, "every lane of a group owns the same number of keys");
 constexpr int kProbeMaxBlocks = 1024;
-constexpr u32 kNoSlot = ~0u;
 constexpr u32 kNewLdsCap = 1024;         // created keys a block of the lookup lists for its common initialisation
 constexpr u32 kLongLdsCap = 64;          // very frequent keys whose chunk items whole waves write (>= kHeavyGroup)
 constexpr u32 kRowsLdsCap = 2048;        // distinct keys whose rows it keeps to hand them on by position
