@@ -32,7 +32,7 @@ struct TableState {
   unsigned long long inserted;  // keys created by the last pull / insert call
   int error;                    // sticky: 0 or a negative status
   int absent;                   // distinct keys the last accumulate did not find
-  unsigned long long dump_count;  // rows seen by all dumps so far (the host knows how many before the running one)
+  unsigned long long dump_count;  // rows seen by all dumps since the creation (the host knows how many before the running one)
   // Keys the running lookup found missing and left / rows the running insert created, spread
   // over shards so that blocks do not all hit one address.
   u32 miss_shard[kCountShards];

@@ -1079,6 +1079,7 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   // look-back status words, digit histograms and the lists of frequent keys start at zero
   fill_u64<<<1024, 256, 0, s>>>(t->w<u64>(wl.ghist), (wl.bag_of - wl.ghist) / 8, 0);
   reset_state<<<1, 64, 0, s>>>(t->view.st);
+  fill_u64<<<1, 64, 0, s>>>(reinterpret_cast<u64*>(&t->view.st->dump_count), 1, 0);
   for (int k = 0; k < 2; ++k)
     set_ctx_empty<<<1, 64, 0, s>>>(t->ctx(k), t->w<u32>(wl.c[k].seg_off));
   if (!launch_ok()) { hps_destroy(t); return HPS_EDEVICE; }
@@ -1110,7 +1111,6 @@ hps_status hps_clear(hps_table* t, void* stream) {
   // claimed, and the marks of updated rows live in the accumulators
   fill_u64<<<4096, 256, 0, s>>>(t->view.keys, t->n_slots, kEmptyKey);
   reset_state<<<1, 64, 0, s>>>(t->view.st);
-  t->dumped = 0;
   return launch_ok() ? HPS_OK : HPS_EDEVICE;
 }
 

@@ -230,13 +230,13 @@ __device__ __forceinline__ void clear_counts(TableState* st) {
   if (threadIdx.x < kCountShards)
     st->miss_shard[threadIdx.x] = st->made_shard[threadIdx.x] = st->pull_made[0][threadIdx.x] = st->pull_made[1][threadIdx.x] = 0;
 }
+// (not dump_count: the host counts on from it, and a captured hps_clear runs when the host does not see it)
 __global__ void __launch_bounds__(64) reset_state(TableState* st) {
   if (threadIdx.x == 0) {
     st->size = 0;
     st->inserted = 0;
     st->error = 0;
     st->absent = 0;
-    st->dump_count = 0;
     st->size_before = 0;
     st->tight = 0;
   }
