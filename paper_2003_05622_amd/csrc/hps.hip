@@ -191,7 +191,7 @@ struct WorkspaceLayout {
   uint64_t max_long, max_items, sort_tiles, head_tiles;
 };
 
-// small: with what the small form needs (an accumulate on the static scratch does not take it).
+// small: with what the small form and pulls need (an accumulate on the static scratch is neither).
 WorkspaceLayout workspace_layout(uint64_t n, uint64_t bags, uint32_t dim, bool small = true) {
   WorkspaceLayout L;
   const uint64_t n1 = n ? n : 1;
@@ -242,7 +242,7 @@ WorkspaceLayout workspace_layout(uint64_t n, uint64_t bags, uint32_t dim, bool s
   L.by_pos = o;      o = align_up(o + n1 * 4);      // row of the key at every position
   L.by_heavy = o;    o = align_up(o + (kMaxHeavy + 1) * 4);
   L.row_of = o;      o = align_up(o + n1 * 4);      // row of every occurrence
-  L.fresh = o;       o = align_up(o + n1);          // whether the pull created the key
+  L.fresh = o;       o = align_up(o + (small ? n1 * 4 : 0));      // the pull that created the key
   L.local_rank = o;    o = align_up(o + n1 * 4);
   L.rank_by_pos = o;   o = align_up(o + n1 * 4);
   L.rank_by_heavy = o; o = align_up(o + (kMaxHeavy + 1) * 4);
@@ -476,6 +476,9 @@ static UniqueSpans unique_spans(const hps_table* t, int c, uint64_t n) {
   return u;
 }
 
+// The number the running pull marks the keys it creates with: never 0, which hps_create leaves in the marks.
+static u32 pull_stamp(const hps_table* t) { return (u32)(t->pull_serial % 0xFFFFFFFFu) + 1; }
+
 // spread (partition.hpp) with the tiles of a bucket-form dedup of n occurrences.
 static void launch_spread(const u32* code, const uint16_t* from, u32 n, u32 n_tiles, const u32* by_pos,
                           const u32* by_heavy, u32* out, hipStream_t s) {
@@ -513,7 +516,7 @@ static void launch_pool(hps_table* t, int c, float* d_pooled, hipStream_t s) {
   // d = 16 runs the same with 1024 to 3072)
   const unsigned blocks = grid_for(cx.n_bags, kPoolThreads / LPR, kPoolMaxBlocks * (LPR > 4 ? LPR / 4 : 1));
   float* inv_len = cx.mean ? t->w<float>(C.inv_len) : nullptr;
-  const PullEnd end = {(u32)(t->pull_serial & 1), unique_spans(t, c, cx.n_keys), t->ctx(c), t->w<u32>(C.rows), t->w<uint8_t>(t->wl.fresh)};
+  const PullEnd end = {(u32)(t->pull_serial & 1), unique_spans(t, c, cx.n_keys), t->ctx(c), t->w<u32>(C.rows), t->w<u32>(t->wl.fresh), pull_stamp(t)};
   u32* bags = t->w<u32>(C.bags);
 #define HPS_POOL(COLS, SMALL) \
   pool_bags<LPR, COLS, SMALL><<<blocks, kPoolThreads, 0, s>>>(t->view, cx.d_offsets, (u32)cx.n_bags, (u32)cx.n_keys, row_of, d_pooled, inv_len, places, bags, end)
@@ -622,7 +625,8 @@ static Creation creation_of(const hps_table* t, uint64_t n_keys, bool create) {
   k.how = !create ? kCreateNone : creates_at_once(t, n_keys) ? kCreateAtOnce : kCreateIfRoom;
   k.set = (u32)(t->pull_serial & 1);
   k.new_cap = t->lookup_new_cap;
-  k.fresh = t->w<uint8_t>(t->wl.fresh);
+  k.fresh = t->w<u32>(t->wl.fresh);
+  k.stamp = pull_stamp(t);
   return k;
 }
 
@@ -1078,6 +1082,7 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   fill_u64<<<4096, 256, 0, s>>>(t->view.keys, n_slots, kEmptyKey);
   // look-back status words, digit histograms and the lists of frequent keys start at zero
   fill_u64<<<1024, 256, 0, s>>>(t->w<u64>(wl.ghist), (wl.bag_of - wl.ghist) / 8, 0);
+  fill_u64<<<1024, 256, 0, s>>>(t->w<u64>(wl.fresh), (wl.local_rank - wl.fresh) / 8, 0);      // (aligned to kAlign)
   reset_state<<<1, 64, 0, s>>>(t->view.st);
   fill_u64<<<1, 64, 0, s>>>(reinterpret_cast<u64*>(&t->view.st->dump_count), 1, 0);
   for (int k = 0; k < 2; ++k)

@@ -337,7 +337,7 @@ small_group(TableView t, SmallArgs a) {
       if (!on) continue;
       a.rows[u] = row;
       if (!slow) L.ukey[k] = row;
-      if (tight) a.create.fresh[u] = mine_new ? 1 : 0;
+      if (tight && mine_new) a.create.fresh[u] = a.create.stamp;
       if (row == kNoRow) ++missing;
       list_key(a.often, med_first(start), u, my_key, len, L.look);
     }

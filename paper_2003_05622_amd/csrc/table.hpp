@@ -571,7 +571,10 @@ struct Creation {
   u32 how;
   u32 set;         // which of st->pull_made counts the created rows
   u32 new_cap;     // entries used of a block's list of created keys: all, except in tests of what happens when it is full
-  uint8_t* fresh;  // per distinct key: created by this pull?  Written where the table might be overfilled
+  // Per distinct key: `stamp`, the pull's number, if this pull created it.  Written where the table might be overfilled.  What is
+  // left of other pulls carries their numbers: a block that stops early, at an error, leaves its part as it was.
+  u32* fresh;
+  u32 stamp;
 };
 // (the size does not change while a pull's kernels run: every thread decides the same)
 __device__ __forceinline__ bool is_tight(const TableView& t, const Creation& create, u32 n) {
@@ -791,7 +794,7 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ s
     if (!on) continue;
     rows[u] = my_row;
     if (!heavies && k < kRowsLdsCap) s_rows[k] = my_row;
-    if (tight) create.fresh[u] = mine_new ? 1 : 0;
+    if (tight && mine_new) create.fresh[u] = create.stamp;
     if (heavies && out.upos) out.by_heavy[h0 + k] = my_row;
     if (my_row == kNoRow) ++missing;
     list_key(often, med_base, u, my_key, my_len, L);
@@ -911,12 +914,14 @@ struct PullEnd {
   UniqueSpans spans;
   const PullCtx* ctx;
   const u32* rows;
-  const uint8_t* fresh;
+  const u32* fresh;        // (Creation)
+  u32 stamp;
 };
 // All threads of all blocks, before anything else.  Books the rows the lookup created -- or, if the table ended above
 // its capacity, raises kErrFull and takes them out of it (nothing else has been put behind them: the table
 // is as before).  Every block adds up the same counts, so all come to the same end, whichever raises the error
-// first.  Returns false if the pull has failed, now or before.
+// first.  What was created stays booked if an error has come from elsewhere meanwhile (a mini-batch being prepared beside this
+// pull, with the reserved key in it): the rows are in the table.  Returns false if the pull has failed, now or before.
 __device__ __forceinline__ bool end_pull(const TableView& t, const PullEnd& e) {
   static_assert(kCountShards == kWave, "a count per lane");
   const int error = load_error(t.st);
@@ -927,7 +932,7 @@ __device__ __forceinline__ bool end_pull(const TableView& t, const PullEnd& e) {
   if (blockIdx.x == 0 && threadIdx.x < kWave) {
     t.st->pull_made[1 - e.set][threadIdx.x] = 0;
     t.st->miss_shard[threadIdx.x] = 0;
-    if (threadIdx.x == 0 && error == 0 && !overfull) {
+    if (threadIdx.x == 0 && !overfull && (error == 0 || made != 0)) {
       t.st->size += made;
       t.st->inserted = made;
     }
@@ -946,7 +951,7 @@ __device__ __forceinline__ bool end_pull(const TableView& t, const PullEnd& e) {
         u = e.spans.bucket_start[e.spans.n_spans + h0 + k];
         if (e.spans.bucket_start[e.spans.n_spans + h0 + k + 1] == u) continue;
       }
-      if (e.fresh[u]) t.keys[e.rows[u]] = kEmptyKey;
+      if (e.fresh[u] == e.stamp) t.keys[e.rows[u]] = kEmptyKey;
     }
   }
   return false;

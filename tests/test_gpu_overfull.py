@@ -63,3 +63,54 @@ def test_overfull_pulls_leave_no_trace(n, form, monkeypatch):
     assert np.array_equal(k.cpu().numpy().view(np.uint64)[order], ok)
     assert np.all(np.abs(w.cpu().numpy()[order] - ow) <= 1e-6 + 1e-5 * np.abs(ow))
     assert np.all(np.abs(a.cpu().numpy()[order] - oa) <= 1e-6 + 1e-5 * np.abs(oa))
+
+
+@pytest.mark.parametrize("form", ["auto", "hashed", "bucket", "radix"])
+@pytest.mark.parametrize("n", [5000, 70_000])
+def test_overfull_while_the_next_mini_batch_fails(n, form, monkeypatch):
+    """A prepared pull ends above the capacity, or just fits, and the mini-batch prepared beside it holds the reserved key: its
+    error comes before, in the midst of or after the pull's kernels, by how long either stream sleeps.  Whatever is left undone,
+    no key that was in the table goes missing, and all that are in it are counted."""
+    monkeypatch.setenv("HPS_DEDUP", form)
+    dim, n_bags, cap = 4, n // 100, 5 * n
+    rng = np.random.default_rng(n)
+    gt = hps.HpsTable(cap, dim, n, n_bags)
+    d_offsets = torch.from_numpy((np.arange(n_bags + 1, dtype=np.int64) * n // n_bags).astype(np.int32)).cuda()
+    side, zero = torch.cuda.Stream(), torch.zeros((n_bags, dim), device="cuda")
+    ids = lambda first, last: synth.mix64(np.arange(first, last, dtype=np.uint64))
+    known, at = ids(0, cap - n), cap - n
+    gt.insert(dev(known))
+    reserved = rng.permutation(known)[:n].copy()
+    reserved[::101] = np.uint64(2**64 - 1)
+    d_reserved = dev(reserved)
+    errors = set()
+    for turn in range(30):
+        room = cap - known.size
+        new = room // 4 if turn % 2 else n                # fits, and leaves its marks; or does not
+        keys = rng.permutation(np.concatenate([ids(at, at + new), known[: n - new]]))
+        at += new
+        d_keys = dev(keys)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            gt.prepare(d_keys, d_offsets, n_bags, 1)
+        torch.cuda._sleep(100_000)
+        gt.pull_prepared()
+        with torch.cuda.stream(side):
+            if turn % 3:
+                torch.cuda._sleep(30_000 + 5000 * turn)
+            gt.prepare(d_reserved, d_offsets, n_bags, 1)
+        torch.cuda.synchronize()
+        errors.add(gt.stats().error)
+        gt.clear_error()
+        size = gt.stats().size
+        stored = gt.dump(max_rows=size)[0].cpu().numpy().view(np.uint64)
+        assert size <= cap and stored.size == size and np.unique(stored).size == size
+        assert np.isin(known, stored).all() and np.isin(stored, np.concatenate([known, keys])).all()
+        known = stored
+        # a pull beside nothing: what is stored is found, with its initial rows
+        pooled = gt.pull(dev(stored[:n]), d_offsets, n_bags, 1)
+        rows = gt.get(dev(stored[:n]))[0]
+        gt.push(zero)
+        assert gt.stats().error == 0 and gt.stats().size == size
+        torch.testing.assert_close(pooled, rows.reshape(n_bags, -1, dim).sum(dim=1), rtol=1e-5, atol=1e-6)
+    assert hps.ERESERVED in errors
