@@ -19,13 +19,18 @@ constexpr int kPoolThreads = 256;
 constexpr int kPoolMaxBlocks = 1024;   // the groups loop over the bags (1536 to 3072 blocks measured no faster)
 constexpr int kPoolInFlight = 8;
 
-// A bag's occurrences, clamped so that no offsets array can make the kernel read outside row_of[0, n).
+// A bag's occurrences: 0 <= lo <= hi <= n whatever the offsets array holds, so that the kernel reads nothing outside row_of[0, n)
+// and no sum of a place and a few more overflows (n < 2^30).
 struct BagRange {
   i32 lo, hi;
 };
-__device__ __forceinline__ BagRange load_bag(const i32* __restrict__ offsets, u32 b, u32 n_bags, u32 n) {
+__host__ __device__ __forceinline__ BagRange load_bag(const i32* __restrict__ offsets, u32 b, u32 n_bags, u32 n) {
   BagRange r = {0, 0};
-  if (b < n_bags) { r.lo = max(offsets[b], 0); r.hi = min(offsets[b + 1], (i32)n); }
+  if (b < n_bags) {
+    const i32 lo = offsets[b], hi = offsets[b + 1], most = (i32)n;
+    r.lo = lo < 0 ? 0 : lo > most ? most : lo;
+    r.hi = hi < r.lo ? r.lo : hi > most ? most : hi;
+  }
   return r;
 }
 
