@@ -69,8 +69,10 @@
  *     a dedup is the occurrences grouped by key; the ascending order of the unique keys is
  *     worked out when hps_last_unique asks for it.
  *   - Calls on one stream are ordered by it.  hps_prepare, hps_pull, hps_pull_prepared, hps_push, hps_accumulate and hps_last_unique
- *     of one table may also come on several streams and are ordered by events; the first of them that comes on another stream
- *     than the ones before waits for the device, unless hps_prepare has been called before.
+ *     of one table may also come on several streams and are ordered by events (a push that comes on another stream than its pull:
+ *     by the caller).  As long as all of them come on the null stream no event is recorded, which saves about 3 us each
+ *     (three a step); the first one on another stream records them on the null stream and goes on from there.
+ *   - A push may be captured into a graph by itself, its pull made outside, and replayed in its place; the caller orders the replay.
  *   - Environment variables, read by hps_create, for tests and comparison runs:
  *     HPS_DEDUP = "radix" | "bucket" | "borders" | "hashed" | "small" (up to 65536 occurrences, beyond "hashed") pins the
  *     dedup's form; HPS_RANK = "ballot" ranks the

@@ -378,10 +378,9 @@ struct hps_table {
   bool scratch_set;
   hipEvent_t listing;        // the last hps_last_unique's end: its scratch, and the context it read
   bool listing_set;
-  // While all calls come on one stream, its order is all they need, and none of these events is recorded (a record
+  // While all calls come on the null stream, its order is all they need, and none of these events is recorded (a record
   // takes the stream 3 us in which nothing runs, three of them a step); the *_set flags are kept all the same.  See enter().
-  bool many_streams, stream_known;
-  hipStream_t stream;
+  bool many_streams;
   uint64_t last_n_keys;      // of the most recent pull, for hps_stats
 
   // stage timing (measurement only)
@@ -411,42 +410,36 @@ void stage_mark(hps_table* t, int stage, hipStream_t s) {
 }  // namespace
 
 // ---- order between streams ---------------------------------------------------------------
-// From now on calls come on several streams.  On the one stream there has been, s, the events that have been left out are put
-// down now (later than they ask for).  On another one all work is waited for instead: the first stream may be gone.
-static bool leave_single_stream(hps_table* t, hipStream_t s) {
+// From the first call on another stream than the null stream on, the events are recorded.  Those that have been left out are put down
+// on the null stream now (later than they ask for).  Only calls on the null stream may leave them out: it can always be
+// recorded on, while a stream of the caller's may be gone by the time another one comes, its handle
+// perhaps in use for a new stream, and hipStreamDestroy need not wait for the work on it.
+static bool leave_null_stream(hps_table* t) {
+  const struct { hipEvent_t event; bool set; } left_out[] = {
+      {t->scratch_free, t->scratch_set}, {t->listing, t->listing_set}, {t->cx[0].ready, t->cx[0].ready_set},
+      {t->cx[1].ready, t->cx[1].ready_set}, {t->cx[0].released, t->cx[0].released_set}, {t->cx[1].released, t->cx[1].released_set}};
+  for (const auto& e : left_out)
+    if (e.set && hipEventRecord(e.event, nullptr) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;             // (nothing has changed: the next call tries again)
+    }
   t->many_streams = true;
-  if (!t->stream_known) return true;
-  struct { hipEvent_t event; bool* set; } left_out[] = {
-      {t->scratch_free, &t->scratch_set}, {t->listing, &t->listing_set}, {t->cx[0].ready, &t->cx[0].ready_set},
-      {t->cx[1].ready, &t->cx[1].ready_set}, {t->cx[0].released, &t->cx[0].released_set}, {t->cx[1].released, &t->cx[1].released_set}};
-  if (s == t->stream) {
-    for (auto& e : left_out)
-      if (*e.set && hipEventRecord(e.event, s) != hipSuccess) return false;
-    return true;
-  }
-  if (hipDeviceSynchronize() != hipSuccess) return false;
-  for (auto& e : left_out) *e.set = false;
-  t->cx[0].listed = t->cx[1].listed = false;
   return true;
 }
 
-// Before any wait or mark of a call on stream s.  several: the call is one that is made for work on several streams.
-//
-// The stream is known by its handle.  A handle comes to stand for another stream only after the first one has been
-// destroyed, and that waits for the stream's work (a stream with 42 ms of work: 42 ms in hipStreamDestroy).
-static bool enter(hps_table* t, hipStream_t s, bool several) {
+// Before any wait or mark of a call on stream s.  waits: the call has to come after earlier ones (a push is part of its pull:
+// where it comes on another stream, the caller orders it).
+static bool enter(hps_table* t, hipStream_t s, bool waits) {
+  if (t->many_streams) return true;
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
   if (capture != hipStreamCaptureStatusNone) {
     // (what ran before the capture cannot be waited for inside it)
-    if (!t->many_streams && (t->scratch_set || t->listing_set || t->cx[0].released_set || t->cx[1].released_set)) return false;
+    if (t->scratch_set || t->listing_set || t->cx[0].released_set || t->cx[1].released_set) return !waits;
     t->many_streams = true;
     return true;
   }
-  if (t->many_streams) return true;
-  if (!t->stream_known) { t->stream = s; t->stream_known = true; }
-  // (hipStreamPerThread is another stream in every thread)
-  return (s == t->stream && s != hipStreamPerThread && !several) || leave_single_stream(t, s);
+  return s == nullptr || leave_null_stream(t);
 }
 static bool mark(hps_table* t, hipEvent_t e, bool* set, hipStream_t s) {
   *set = true;
@@ -1025,7 +1018,7 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   t->last_n_keys = 0;
   t->scratch_set = false;
   t->listing_set = false;
-  t->many_streams = t->stream_known = false;
+  t->many_streams = false;
   bool events_ok = hipEventCreateWithFlags(&t->scratch_free, hipEventDisableTiming) == hipSuccess &&
                    hipEventCreateWithFlags(&t->listing, hipEventDisableTiming) == hipSuccess;
   for (int k = 0; k < 2; ++k) {
@@ -1153,11 +1146,10 @@ static bool after_listing(hps_table* t, int c, hipStream_t s) {
   return true;
 }
 
-// include: kDedupOnly, or kWithPullLookup where hps_pull_prepared follows on the same stream at once.  ahead: it is a call
-// of its own, perhaps beside others.
+// include: kDedupOnly, or kWithPullLookup where hps_pull_prepared follows on the same stream at once.
 static hps_status prepare(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
                           const int32_t* d_offsets, uint32_t n_examples, uint32_t n_slots,
-                          Include include, bool ahead, void* stream) {
+                          Include include, void* stream) {
   if (!mini_batch_ok(t, d_keys, n_keys, d_offsets, n_examples, n_slots)) return HPS_EINVAL;
   const uint64_t n_bags = (uint64_t)n_examples * n_slots;
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1166,7 +1158,7 @@ static hps_status prepare(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
   const u32 n = (u32)n_keys;
   // order after the push that last read this context, and after the previous dedup
   // (the sort scratch is shared); both may have run on other streams
-  if (!enter(t, s, ahead)) return HPS_EDEVICE;
+  if (!enter(t, s, true)) return HPS_EDEVICE;
   if (!wait_for(t, cx.released, cx.released_set, s) || !wait_for(t, t->scratch_free, t->scratch_set, s)) return HPS_EDEVICE;
   if (!after_listing(t, c, s)) return HPS_EDEVICE;
   // (a lookup among it: what hps_pull_prepared orders it after)
@@ -1187,7 +1179,7 @@ static hps_status prepare(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
 hps_status hps_prepare(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
                        const int32_t* d_offsets, uint32_t n_examples, uint32_t n_slots,
                        void* stream) {
-  return prepare(t, d_keys, n_keys, d_offsets, n_examples, n_slots, kDedupOnly, true, stream);
+  return prepare(t, d_keys, n_keys, d_offsets, n_examples, n_slots, kDedupOnly, stream);
 }
 
 hps_status hps_pull_prepared(hps_table* t, float* d_pooled, void* stream) {
@@ -1198,7 +1190,7 @@ hps_status hps_pull_prepared(hps_table* t, float* d_pooled, void* stream) {
   if (cx.n_bags && !d_pooled) return HPS_EINVAL;
   if ((uintptr_t)d_pooled % 16) return HPS_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (!enter(t, s, false) || !wait_for(t, cx.ready, cx.ready_set, s)) return HPS_EDEVICE;
+  if (!enter(t, s, true) || !wait_for(t, cx.ready, cx.ready_set, s)) return HPS_EDEVICE;
   // the lookup rewrites the work lists that both contexts share and the pooling reads rows: order
   // them after the push of the mini-batch before, should that have run on another stream
   const hps_table::Context& other = t->cx[1 - c];
@@ -1232,7 +1224,7 @@ hps_status hps_pull(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
   if (!mini_batch_ok(t, d_keys, n_keys, d_offsets, n_examples, n_slots)) return HPS_EINVAL;
   if (t->current >= 0) return HPS_ESTATE;
   const Include include = creates_at_once(t, n_keys) ? kWithPullLookup : kDedupOnly;
-  const hps_status rc = prepare(t, d_keys, n_keys, d_offsets, n_examples, n_slots, include, false, stream);
+  const hps_status rc = prepare(t, d_keys, n_keys, d_offsets, n_examples, n_slots, include, stream);
   return rc != HPS_OK ? rc : hps_pull_prepared(t, d_pooled, stream);
 }
 
@@ -1295,7 +1287,7 @@ hps_status hps_accumulate(hps_table* t, const uint64_t* d_keys, uint64_t n, cons
   if (t->current >= 0 || t->prepared >= 0) return HPS_ESTATE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hps_table::Context& cx = t->cx[0];
-  if (!enter(t, s, false)) return HPS_EDEVICE;
+  if (!enter(t, s, true)) return HPS_EDEVICE;
   for (int k = 0; k < 2; ++k)      // after the last push of either context (shared work lists, table rows)
     if (!wait_for(t, t->cx[k].released, t->cx[k].released_set, s)) return HPS_EDEVICE;
   if (!wait_for(t, t->scratch_free, t->scratch_set, s)) return HPS_EDEVICE;
@@ -1467,7 +1459,7 @@ hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_invers
     if (!t->listing_pinned) t->listing_pinned = cx.buckets && (cx.form == kByHash || cx.form == kSmallForm) ? 2 : 1;
     return list_unique(t, c, d_uniq_out, d_inverse_out, s);
   }
-  if (!enter(t, s, false) || !wait_for(t, cx.ready, cx.ready_set, s) || !wait_for(t, t->listing, t->listing_set, s)) return HPS_EDEVICE;
+  if (!enter(t, s, true) || !wait_for(t, cx.ready, cx.ready_set, s) || !wait_for(t, t->listing, t->listing_set, s)) return HPS_EDEVICE;
   const bool sorts = cx.buckets && (cx.form == kByHash || cx.form == kSmallForm);       // in the scratch of the dedups
   if (sorts && !wait_for(t, t->scratch_free, t->scratch_set, s)) return HPS_EDEVICE;
   const hps_status rc = list_unique(t, c, d_uniq_out, d_inverse_out, s);
