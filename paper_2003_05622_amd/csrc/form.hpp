@@ -1,0 +1,150 @@
+// Which form a dedup takes (host code; nothing here needs a GPU).
+//
+// All forms give the same results, so this is about time only: by size, by whether the caller lists the distinct keys
+// (hps_last_unique), and by what the lookups report about the dedups before, in pinned host words that nobody waits for.
+#pragma once
+
+#include <stdint.h>
+
+namespace hps {
+
+// The bucket form, by what its natural buckets are; the small form (small.hpp); the plain form (sort.hpp, dedup.hpp).
+constexpr int kByRange = 0, kByBorders = 1, kByHash = 2, kSmallForm = 3, kPlainForm = 4;
+
+constexpr uint32_t kSmallMax = 1u << 16;                  // occurrences the small form takes, at most
+constexpr uint64_t kBorderMaxKeys = 1u << 19;             // ... the bucket form by sampled borders
+constexpr uint64_t kBucketPathMaxKeys = 12u << 20;        // ... the bucket form
+
+// What a lookup reports about the dedup before it (table.hpp: OftenLists::report).
+constexpr uint32_t kReportSlow = 2, kReportOneKey = 4, kReportMixed = 8, kReportStandIn = 16, kReportUneven = 32,
+                   kReportCrowded = 64;
+
+constexpr uint32_t kQuiet = 3;           // dedups without an hps_last_unique until a caller is taken not to want it
+constexpr uint64_t kPlainHold = 32;      // dedups in another form after one disappointed
+constexpr uint64_t kHintLag = 3;         // ... after a surprise that the next lists of frequent keys will cover
+
+struct FormChoice {
+  int mode;            // 0: by size and history; 1: plain radix passes always; 2, 3, 4: bucket form whenever it can, by range, borders, hash;
+                       // 5: small form up to kSmallMax, beyond by hash
+  // When a dedup
+  // of the bucket form by key range had to order much of its input the slow way (frequent keys that change from
+  // one mini-batch to the next), or found the keys lying unevenly in their range, the following dedups take
+  // another form: for kPlainHold dedups, and twice as long each time in a row the range then disappoints again.
+  uint32_t range_seen, other_seen;        // serials of the last reports acted on
+  uint32_t judged;          // reports of lookups up to this one do not count: issued before the range was given up
+  uint32_t strikes;
+  // After such a time, one dedup goes by key range again, and the next ones only when the report on that one has
+  // come: a caller who never waits may be dozens of dedups ahead of the GPU (to_probe: it is due; probe: its lookup,
+  // 0: none).  Not after other causes, whose stand-ins are slower than a good key range.
+  bool to_probe;
+  uint32_t probe;
+  uint64_t range_from;      // dedups numbered below this do not go by key range
+  uint64_t n_fallbacks;     // times range_from was pushed out
+  // Why, which decides what takes its place: kHotKeys, a few keys that turned frequent without warning; kSlowBuckets,
+  // many frequent keys in some buckets; kUnevenKeys; kCrowdedKeys, very unevenly (next).  The plain form while the
+  // stand-ins have disappointed too (dedups numbered below stand_in_from).
+  enum Away { kHotKeys, kSlowBuckets, kUnevenKeys, kCrowdedKeys } away;
+  uint64_t stand_in_from;
+  uint32_t unlisted;        // dedups since the last hps_last_unique (or the creation)
+  int listing_pinned;       // 0, or since an hps_last_unique was captured: 1 in an order of keys, 2 by hash
+  // The same for the plain form itself: after a dedup whose keys agreed in all the bits the
+  // plain form sorts by (kReportMixed), the following ones sort by all 64 bits.
+  uint32_t full_strikes;
+  uint64_t full_until;
+  uint64_t n_full_fallbacks;
+
+  // The words the lookups report into: of dedups by key range, of dedups in any other form.
+  struct Reports {
+    unsigned long long range, other;
+  };
+
+  // The form of dedup number `serial`, of n occurrences, with lookup_serial lookups issued so far.
+  int next(uint32_t n, uint64_t serial, uint64_t lookup_serial, Reports reports) {
+    // The bucket path needs to know the heavy keys, which it learns from the lookups: the
+    // first two dedups of a table take the plain passes, as do very large ones.
+    const bool small = n <= kBorderMaxKeys, lists = unlisted < 2;       // (the next dedup may come before the call)
+    const bool quiet = listing_pinned ? listing_pinned == 2 : unlisted >= kQuiet;
+    if (unlisted < kQuiet) ++unlisted;
+    if (mode == 0) take(reports, serial, lookup_serial, small, lists);
+    // The stand-ins for the key range.  By hash is the fastest for uneven keys whatever the size, but hps_last_unique then
+    // has to sort all distinct keys.  So a caller who lists the keys of his mini-batches keeps an order of keys: up to
+    // kBorderMaxKeys by range as long as that is not several times slower, else by borders; above, the plain form.
+    // By borders also where frequent keys, not uneven ones, made buckets slow.
+    // (Raw ids, a tenth of the occurrences in a 200th of their range, a step at dim 16 of 105 K, 300 K, 1 M and 4 M occurrences:
+    // by range 327, 402, 1494 and 5822 us, by hash 76, 104, 263 and 940, plain 126, 187, 391 and 1270, by borders 118 and 161; ids whose
+    // density rises from none to twice the mean: by range 90, 125, 740 and 2057, by hash 76, 104, 279 and 900.
+    // Listing the unique keys: 18 to 40 us by borders, in the plain form 5 to 20, by hash 620 for 4 M distinct keys.)
+    if (n <= kSmallMax && (mode == 5 || (mode == 0 && quiet && serial >= stand_in_from))) return kSmallForm;
+    if (n > kBucketPathMaxKeys || mode == 1 || (mode == 0 && lookup_serial < 2)) return kPlainForm;
+    if (mode != 0) return mode == 3 && small ? kByBorders : mode >= 4 ? kByHash : kByRange;
+    // (Nobody wants the keys in order: by hash.  The first kernel has no key range to sample, and a bucket's rows lie in one
+    // part of the table.  Hashed keys, dim 16, four steps of 2 M and 9.8 M occurrences: by range 1104 and 4787 us, by hash 1080 and
+    // 4735; 0.3 M accumulated, 77 and 73.  With hps_last_unique it is the other way round: above.)
+    if (quiet) return serial >= stand_in_from ? kByHash : kPlainForm;
+    if (serial >= range_from && !probe) {
+      if (to_probe) {
+        probe = (uint32_t)lookup_serial + 1;
+        to_probe = false;
+      }
+      return kByRange;
+    }
+    if (away == kUnevenKeys && lists && small) return kByRange;
+    const int form = away >= kUnevenKeys && !lists ? kByHash : kByBorders;
+    return away != kHotKeys && (small || form == kByHash) && serial >= stand_in_from ? form : kPlainForm;
+  }
+
+  // Whether a plain dedup sorts by all 64 bits of the keys.
+  bool all_bits(uint64_t serial) const { return mode < 2 && serial < full_until; }
+
+ private:
+  void take(Reports reports, uint64_t serial, uint64_t lookup_serial, bool small, bool lists) {
+    if ((uint32_t)reports.range != range_seen) {
+      const uint32_t at = (uint32_t)reports.range, flags = (uint32_t)(reports.range >> 32);
+      range_seen = at;
+      if (probe && (int32_t)(at - probe) >= 0) probe = 0;
+      const bool uneven = (flags & kReportUneven) && !(lists && small && !(flags & kReportCrowded));
+      if ((int32_t)(at - judged) <= 0) {
+        // (of a dedup that was under way when the range was given up)
+      } else if (uneven || (flags & kReportSlow)) {
+        ++n_fallbacks;
+        judged = (uint32_t)lookup_serial;
+        if (uneven) {
+          away = (flags & kReportCrowded) ? kCrowdedKeys : kUnevenKeys;
+        } else {
+          // (a few keys that turned frequent: plain until the hint has caught up)
+          away = (flags & kReportOneKey) ? kHotKeys : kSlowBuckets;
+        }
+        to_probe = uneven;
+        if (away == kHotKeys) {
+          range_from = serial + kHintLag;
+        } else {
+          range_from = serial + (kPlainHold << (strikes < 7 ? strikes : 7));
+          ++strikes;
+        }
+      } else {
+        strikes = 0;
+      }
+    }
+    if ((uint32_t)reports.other != other_seen) {
+      const uint32_t at = (uint32_t)reports.other, flags = (uint32_t)(reports.other >> 32);
+      other_seen = at;
+      if (probe && (int32_t)(at - probe) >= 0) {      // its dedup was replaced by another: try again
+        probe = 0;
+        to_probe = true;
+      }
+      if ((flags & kReportStandIn) && (flags & kReportSlow)) {
+        stand_in_from = serial + ((flags & kReportOneKey) ? kHintLag : kPlainHold);
+      }
+      if (flags & kReportMixed) {
+        // the plain form's sorted bits did not tell the keys apart: all 64 bits for a while
+        full_until = serial + (kPlainHold << (full_strikes < 7 ? full_strikes : 7));
+        ++full_strikes;
+        ++n_full_fallbacks;
+      } else if (!(flags & kReportStandIn) && serial >= full_until) {
+        full_strikes = 0;       // the plain form with its usual passes did well
+      }
+    }
+  }
+};
+
+}  // namespace hps

@@ -20,6 +20,7 @@
 #include "common.hpp"
 #include "bucket.hpp"
 #include "dedup.hpp"
+#include "form.hpp"
 #include "partition.hpp"
 #include "pool.hpp"
 #include "push.hpp"
@@ -129,8 +130,7 @@ constexpr bool bucket_sizes_ok() {
 static_assert(kBucketSizes[0].max_nat <= kMaxBorders && kBucketSizes[1].max_nat <= kMaxBorders &&
                   kBorderMaxKeys <= kBucketSizes[1].max_n, "buckets by sampled borders");
 static_assert(bucket_sizes_ok(), "the kernels' limits");
-// Largest dedup the bucket form takes.
-constexpr uint64_t kBucketPathMaxKeys = kBucketSizes[kBucketClasses - 1].max_n;
+static_assert(kBucketPathMaxKeys == kBucketSizes[kBucketClasses - 1].max_n, "the largest class");
 
 int bucket_class(uint64_t n) {
   int k = 0;
@@ -265,10 +265,6 @@ uint32_t tile_group(uint64_t n_tiles) {
   return g;
 }
 
-constexpr uint32_t kQuiet = 3;           // dedups without an hps_last_unique until a caller is taken not to want it
-constexpr uint64_t kPlainHold = 32;      // dedups in the plain form after the bucket form disappointed
-constexpr uint64_t kHintLag = 3;         // ... after a surprise that the next lists of frequent keys will cover
-
 // Plain form.  How many 8-bit digits to sort for n occurrences: enough that two different
 // keys rarely agree in all sorted bits.  With b sorted bits about n^2 / 2^(b+1) pairs of
 // distinct hashed keys collide; b >= 2*log2(n) - 2 keeps that near one in a few
@@ -322,41 +318,14 @@ struct hps_table {
   uint64_t lookup_serial;   // lookups so far; lookup s lists its frequent keys in ring slot s % 3
   uint64_t dumped;          // TableState::dump_count after the last dump (~0: not known, that dump failed)
   uint64_t pull_serial;     // pulls with bags so far: they take the two sets of counts in turn (common.hpp: pull_made)
-  int dedup_mode;      // 0: by size and history; 1: plain radix passes always; 2, 3, 4: bucket form whenever it can, by range, borders, hash;
-                       // 5: small form up to kSmallMax, beyond by hash
   bool ordered_rank;   // the GPU's LDS atomics serve a wave's lanes in lane order (sort.hpp: digit_rank)
   // How much of pull_lookup's per-block list of created keys is used: all of it, unless
   // HPS_LOOKUP_NEW_LIST says less (tests of what happens when it is full).
   u32 lookup_new_cap;
   uint64_t serial;     // number of dedups so far (status words carry it modulo kEpochMod)
   uint64_t plain_serial;   // ... of them in the plain form
-  // Pinned host words the lookups report into (table.hpp: OftenLists::report).  When a dedup
-  // of the bucket form by key range had to order much of its input the slow way (frequent keys that change from
-  // one mini-batch to the next), or found the keys lying unevenly in their range, the following dedups take
-  // another form: for kPlainHold dedups, and twice as long each time in a row the range then disappoints again.
-  unsigned long long* report;             // [0] of the lookup after a dedup in any form but by key range, [1] by key range
-  uint32_t range_seen, other_seen;        // serials of the last reports acted on
-  uint32_t judged;          // reports of lookups up to this one do not count: issued before the range was given up
-  uint32_t strikes;
-  // After such a time, one dedup goes by key range again, and the next ones only when the report on that one has
-  // come: a caller who never waits may be dozens of dedups ahead of the GPU (to_probe: it is due; probe: its lookup,
-  // 0: none).  Not after other causes, whose stand-ins are slower than a good key range.
-  bool to_probe;
-  uint32_t probe;
-  uint64_t range_from;      // dedups numbered below this do not go by key range
-  uint64_t n_fallbacks;     // times range_from was pushed out
-  // Why, which decides what takes its place: kHotKeys, a few keys that turned frequent without warning; kSlowBuckets,
-  // many frequent keys in some buckets; kUnevenKeys; kCrowdedKeys, very unevenly (launch_dedup).  The plain form while the
-  // stand-ins have disappointed too (dedups numbered below stand_in_from).
-  enum Away { kHotKeys, kSlowBuckets, kUnevenKeys, kCrowdedKeys } away;
-  uint64_t stand_in_from;
-  uint32_t unlisted;        // dedups since the last hps_last_unique (or the creation)
-  int listing_pinned;       // 0, or since an hps_last_unique was captured: 1 in an order of keys, 2 by hash
-  // The same for the plain form itself: after a dedup whose keys agreed in all the bits the
-  // plain form sorts by (table.hpp: kReportMixed), the following ones sort by all 64 bits.
-  uint32_t full_strikes;
-  uint64_t full_until;
-  uint64_t n_full_fallbacks;
+  unsigned long long* report;             // pinned host words the lookups report into: [0] of the lookup after a dedup in any form but by key range, [1] by key range
+  FormChoice choice;        // the dedups' form
 
   // Pull contexts.  `current` is the context of the outstanding pull (-1: none),
   // `prepared` the one whose dedup has been enqueued but not yet pulled (-1: none).
@@ -365,9 +334,9 @@ struct hps_table {
     const int32_t* d_offsets;
     bool mean;            // pooling of this pull (fixed when it is prepared)
     bool looked_up;       // its dedup included the lookup (small form)
-    bool buckets;         // its dedup took the bucket form ...
-    int form;             // ... by range, borders or hash (partition.hpp), or the small form (kSmallForm)
-    BucketPlan plan;      // ... with these sizes ...
+    int form;             // of its dedup (form.hpp)
+    bool buckets;         // ... and whether that is the bucket or the small form ...
+    BucketPlan plan;      // ... with these sizes
     hipEvent_t ready;     // recorded after the dedup kernels
     hipEvent_t released;  // recorded after the push that used the context
     bool ready_set, released_set;
@@ -393,7 +362,6 @@ struct hps_table {
 };
 
 namespace {
-constexpr int kSmallForm = 3;        // beside kByRange, kByBorders, kByHash
 constexpr size_t kMaxEventPairs = 4096;
 
 void stage_mark(hps_table* t, int stage, hipStream_t s) {
@@ -679,72 +647,16 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
     const u32 epoch = (u32)(t->serial % kEpochMod) + 1;
     if (epoch == 1 && t->serial >= kEpochMod)   // the epochs start over: forget the old words
       fill_u64<<<1024, 256, 0, s>>>(t->w<u64>(L.tile_rows), (L.evidence - L.tile_rows) / 8, 0);
-    // The bucket path needs to know the heavy keys, which it learns from the lookups: the
-    // first two dedups of a table take the plain passes, as do very large ones.
-    const bool small = n <= kBorderMaxKeys, lists = t->unlisted < 2;       // (the next dedup may come before the call)
-    const bool quiet = t->listing_pinned ? t->listing_pinned == 2 : t->unlisted >= kQuiet;
-    if (t->unlisted < kQuiet) ++t->unlisted;
-    if (t->dedup_mode == 0) {
-      // (the other forms' word first: what it tells of came after whatever the range's word then does not tell of)
-      const unsigned long long other = __atomic_load_n(t->report, __ATOMIC_ACQUIRE), range = __atomic_load_n(t->report + 1, __ATOMIC_RELAXED);
-      if ((uint32_t)range != t->range_seen) {
-        const uint32_t serial = (uint32_t)range, flags = (uint32_t)(range >> 32);
-        t->range_seen = serial;
-        if (t->probe && (int32_t)(serial - t->probe) >= 0) t->probe = 0;
-        const bool uneven = (flags & kReportUneven) && !(lists && small && !(flags & kReportCrowded));
-        if ((int32_t)(serial - t->judged) <= 0) {
-          // (of a dedup that was under way when the range was given up)
-        } else if (uneven || (flags & kReportSlow)) {
-          ++t->n_fallbacks;
-          t->judged = (uint32_t)t->lookup_serial;
-          if (uneven) {
-            t->away = (flags & kReportCrowded) ? hps_table::kCrowdedKeys : hps_table::kUnevenKeys;
-          } else {
-            // (a few keys that turned frequent: plain until the hint has caught up)
-            t->away = (flags & kReportOneKey) ? hps_table::kHotKeys : hps_table::kSlowBuckets;
-          }
-          t->to_probe = uneven;
-          if (t->away == hps_table::kHotKeys) {
-            t->range_from = t->serial + kHintLag;
-          } else {
-            t->range_from = t->serial + ((uint64_t)kPlainHold << (t->strikes < 7 ? t->strikes : 7));
-            ++t->strikes;
-          }
-        } else {
-          t->strikes = 0;
-        }
-      }
-      if ((uint32_t)other != t->other_seen) {
-        const uint32_t serial = (uint32_t)other, flags = (uint32_t)(other >> 32);
-        t->other_seen = serial;
-        if (t->probe && (int32_t)(serial - t->probe) >= 0) {      // its dedup was replaced by another: try again
-          t->probe = 0;
-          t->to_probe = true;
-        }
-        if ((flags & kReportStandIn) && (flags & kReportSlow)) {
-          t->stand_in_from = t->serial + ((flags & kReportOneKey) ? kHintLag : kPlainHold);
-        }
-        if (flags & kReportMixed) {
-          // the plain form's sorted bits did not tell the keys apart: all 64 bits for a while
-          t->full_until = t->serial + ((uint64_t)kPlainHold << (t->full_strikes < 7 ? t->full_strikes : 7));
-          ++t->full_strikes;
-          ++t->n_full_fallbacks;
-        } else if (!(flags & kReportStandIn) && t->serial >= t->full_until) {
-          t->full_strikes = 0;       // the plain form with its usual passes did well
-        }
-      }
+    // (the other forms' word first: what it tells of came after whatever the range's word then does not tell of)
+    FormChoice::Reports reports = {0, 0};
+    if (t->report) {
+      reports.other = __atomic_load_n(t->report, __ATOMIC_ACQUIRE);
+      reports.range = __atomic_load_n(t->report + 1, __ATOMIC_RELAXED);
     }
-    // The stand-ins for the key range.  By hash is the fastest for uneven keys whatever the size, but hps_last_unique then
-    // has to sort all distinct keys.  So a caller who lists the keys of his mini-batches keeps an order of keys: up to
-    // kBorderMaxKeys by range as long as that is not several times slower, else by borders; above, the plain form.
-    // By borders also where frequent keys, not uneven ones, made buckets slow.
-    // (Raw ids, a tenth of the occurrences in a 200th of their range, a step at dim 16 of 105 K, 300 K, 1 M and 4 M occurrences:
-    // by range 327, 402, 1494 and 5822 us, by hash 76, 104, 263 and 940, plain 126, 187, 391 and 1270, by borders 118 and 161; ids whose
-    // density rises from none to twice the mean: by range 90, 125, 740 and 2057, by hash 76, 104, 279 and 900.
-    // Listing the unique keys: 18 to 40 us by borders, in the plain form 5 to 20, by hash 620 for 4 M distinct keys.)
-    if (n <= kSmallMax && (t->dedup_mode == 5 || (t->dedup_mode == 0 && quiet && t->serial >= t->stand_in_from))) {
-      t->cx[c].buckets = true;
-      t->cx[c].form = kSmallForm;
+    const int form = t->choice.next(n, t->serial, t->lookup_serial, reports);
+    t->cx[c].form = form;
+    t->cx[c].buckets = form != kPlainForm;
+    if (form == kSmallForm) {
       t->cx[c].looked_up = include != kDedupOnly;
       if (include == kWithPullLookup) ++t->pull_serial;
       const bool own_bags = d_offsets == nullptr;
@@ -755,31 +667,7 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
       stage_mark(t, HPS_STAGE_UNIQUE, s);
       return;
     }
-    const bool hinted = n <= kBucketPathMaxKeys && t->dedup_mode != 1 && (t->dedup_mode >= 2 || t->lookup_serial >= 2);
-    int form = t->dedup_mode == 3 && small ? kByBorders : t->dedup_mode >= 4 ? kByHash : kByRange;
-    bool buckets = hinted;
-    const bool away = t->dedup_mode == 0 && (t->serial < t->range_from || t->probe);
-    // (Nobody wants the keys in order: by hash.  The first kernel has no key range to sample, and a bucket's rows lie in one
-    // part of the table.  Hashed keys, dim 16, four steps of 2 M and 9.8 M occurrences: by range 1104 and 4787 us, by hash 1080 and
-    // 4735; 0.3 M accumulated, 77 and 73.  With hps_last_unique it is the other way round: below.)
-    const bool by_hash = t->dedup_mode == 0 && quiet;
-    if (hinted && t->dedup_mode == 0 && !away && !by_hash && t->to_probe) {
-      t->probe = (uint32_t)t->lookup_serial + 1;
-      t->to_probe = false;
-    }
-    if (hinted && by_hash) {
-      form = kByHash;
-      buckets = t->serial >= t->stand_in_from;
-    } else if (hinted && away) {
-      const bool uneven = t->away >= hps_table::kUnevenKeys;
-      if (!(t->away == hps_table::kUnevenKeys && lists && small)) {
-        form = uneven && !lists ? kByHash : kByBorders;
-        buckets = t->away != hps_table::kHotKeys && (small || form == kByHash) && t->serial >= t->stand_in_from;
-      }
-    }
-    t->cx[c].buckets = buckets;
-    t->cx[c].form = form;
-    if (buckets) {
+    if (form != kPlainForm) {
       t->cx[c].plan = bucket_plan(n);
       // the most recent list of frequent keys that is certainly complete (common.hpp)
       const HeavyRaw* heavy = &t->w<HeavyRing>(L.heavy_raw)->raw[(t->lookup_serial + kHeavyRing - 1) % kHeavyRing];
@@ -801,7 +689,7 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
 #undef HPS_BUCKETS3
 #undef HPS_BUCKETS
     } else {
-      const SortPlan plan = sort_plan(n, t->dedup_mode < 2 && t->serial < t->full_until);
+      const SortPlan plan = sort_plan(n, t->choice.all_bits(t->serial));
       u64* kcur = t->w<u64>(L.keys_a);
       u64* kalt = t->w<u64>(L.keys_b);
       u64* pcur = t->w<u64>(L.idx_a);
@@ -1038,18 +926,7 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   t->plain_serial = 0;
   t->mean_pooling = false;
   t->lookup_serial = t->pull_serial = t->dumped = 0;
-  t->away = hps_table::kHotKeys;
-  t->stand_in_from = 0;
-  t->unlisted = 0;
-  t->listing_pinned = 0;
-  t->range_seen = t->other_seen = t->judged = t->probe = 0;
-  t->to_probe = false;
-  t->strikes = 0;
-  t->range_from = 0;
-  t->n_fallbacks = 0;
-  t->full_strikes = 0;
-  t->full_until = 0;
-  t->n_full_fallbacks = 0;
+  t->choice = FormChoice();
   t->report = nullptr;
   if (hipHostMalloc(reinterpret_cast<void**>(&t->report), 64, hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
@@ -1060,7 +937,7 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   {
     // HPS_DEDUP=radix / bucket / borders / hashed / small pins the dedup to one of its forms (comparison runs, tests)
     const char* mode = std::getenv("HPS_DEDUP");
-    t->dedup_mode = !mode ? 0 : std::strcmp(mode, "radix") == 0 ? 1 : std::strcmp(mode, "bucket") == 0 ? 2
+    t->choice.mode = !mode ? 0 : std::strcmp(mode, "radix") == 0 ? 1 : std::strcmp(mode, "bucket") == 0 ? 2
                     : std::strcmp(mode, "borders") == 0 ? 3 : std::strcmp(mode, "hashed") == 0 ? 4
                     : std::strcmp(mode, "small") == 0 ? 5 : 0;
   }
@@ -1318,16 +1195,15 @@ hps_status hps_accumulate_static(hps_table* t, const uint64_t* d_keys, uint64_t 
   // The table works on the static array for the length of this call: its own workspace, and
   // what the host keeps about it, stay as they are.
   struct Saved {
-    char* ws; WorkspaceLayout wl; uint64_t serial, plain_serial, lookup_serial, full_until;
-    int dedup_mode; unsigned long long* report; uint32_t timing_mask;
-  } keep = {t->ws, t->wl, t->serial, t->plain_serial, t->lookup_serial, t->full_until,
-            t->dedup_mode, t->report, t->timing_mask};
+    char* ws; WorkspaceLayout wl; uint64_t serial, plain_serial, lookup_serial;
+    FormChoice choice; unsigned long long* report; uint32_t timing_mask;
+  } keep = {t->ws, t->wl, t->serial, t->plain_serial, t->lookup_serial, t->choice, t->report, t->timing_mask};
   t->ws = ss.ptr;
   t->wl = wl;
   t->serial = t->plain_serial = 0;            // the status words are cleared below: any epoch will do
   t->lookup_serial = ss.lookup_serial;
-  t->dedup_mode = 1;                           // plain passes ...
-  t->full_until = ~0ull;                       // ... over all 64 key bits: exact whatever the keys, no history needed
+  t->choice.mode = 1;                          // plain passes ...
+  t->choice.full_until = ~0ull;                // ... over all 64 key bits: exact whatever the keys, no history needed
   t->report = nullptr;
   t->timing_mask = 0;
   // what must start at zero: digit histograms, tickets, status words; once per device: the lists of frequent keys
@@ -1344,8 +1220,7 @@ hps_status hps_accumulate_static(hps_table* t, const uint64_t* d_keys, uint64_t 
   t->serial = keep.serial;
   t->plain_serial = keep.plain_serial;
   t->lookup_serial = keep.lookup_serial;
-  t->full_until = keep.full_until;
-  t->dedup_mode = keep.dedup_mode;
+  t->choice = keep.choice;
   t->report = keep.report;
   t->timing_mask = keep.timing_mask;
   return rc;
@@ -1448,7 +1323,7 @@ hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_invers
   const int c = t->current;
   hps_table::Context& cx = t->cx[c];
   if (cx.n_keys == 0 || (!d_uniq_out && !d_inverse_out)) return HPS_OK;
-  t->unlisted = 0;
+  t->choice.unlisted = 0;
   // On any stream: after the dedup whose results it lists and after the call before it (the ranks'
   // scratch); the next dedup into this context waits for it (after_listing).  Events that were recorded outside a
   // capture cannot be waited for inside one: what is captured here, the caller orders.
@@ -1456,7 +1331,7 @@ hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_invers
   if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
   if (capture != hipStreamCaptureStatusNone) {
     // (a replay lists a later mini-batch the way this one is: its dedup has to take the same form)
-    if (!t->listing_pinned) t->listing_pinned = cx.buckets && (cx.form == kByHash || cx.form == kSmallForm) ? 2 : 1;
+    if (!t->choice.listing_pinned) t->choice.listing_pinned = cx.buckets && (cx.form == kByHash || cx.form == kSmallForm) ? 2 : 1;
     return list_unique(t, c, d_uniq_out, d_inverse_out, s);
   }
   if (!enter(t, s, true) || !wait_for(t, cx.ready, cx.ready_set, s) || !wait_for(t, t->listing, t->listing_set, s)) return HPS_EDEVICE;
@@ -1554,8 +1429,8 @@ hps_status hps_stats(hps_table* t, hps_stats_t* h_out, void* stream) {
   }
   h_out->last_n_inserted = st.inserted;
   h_out->last_n_absent = (uint64_t)st.absent;
-  h_out->n_plain_fallbacks = t->n_fallbacks;
-  h_out->n_full_fallbacks = t->n_full_fallbacks;
+  h_out->n_plain_fallbacks = t->choice.n_fallbacks;
+  h_out->n_full_fallbacks = t->choice.n_full_fallbacks;
   h_out->load_factor = (double)st.size / (double)t->n_slots;
   h_out->error = st.error;
   h_out->pull_outstanding = t->current >= 0 ? 1 : 0;

@@ -33,6 +33,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "form.hpp"
 #include "sort.hpp"
 
 namespace hps {
@@ -48,7 +49,6 @@ constexpr u32 kHeavyCode = 0x80000000u;   // code of an occurrence in heavy buck
 constexpr u32 kDirectTiles = 64;
 constexpr int kHeavySlots = 4096;         // hash slots for the heavy keys (a power of two)
 constexpr u32 kNoHeavy = ~0u;
-constexpr int kByRange = 0, kByBorders = 1, kByHash = 2;      // what the natural buckets are
 
 // Which part of the key range a key lies in.
 __device__ __forceinline__ u32 bucket_of(u64 key, const KeyRange& r) {
@@ -71,7 +71,6 @@ __device__ __forceinline__ KeyRange bucket_range(u64 lo, u64 hi, u32 n_nat) {
 // are chosen to hold six times the mean in distinct keys and eight times in occurrences (border_group_threads).
 // Larger mini-batches would take more samples than one kernel of a few microseconds can rank (with as many, 1 M
 // occurrences took 359 to 372 us by borders, 376 to 396 in the plain form, and listing the unique keys costs 50 us more).
-constexpr u64 kBorderMaxKeys = 1u << 19;
 constexpr u32 kMaxBorders = 1024;
 __host__ constexpr u32 border_group_threads(u64 n) { return n <= (1u << 18) ? 256 : 512; }
 constexpr u32 border_samples(u32 max_nat) { return 8 * max_nat; }

@@ -29,7 +29,6 @@
 
 namespace hps {
 
-constexpr u32 kSmallMax = 1u << 16;        // occurrences
 constexpr u32 kSmallTile = 1024;           // occurrences and threads of a block of small_ids
 constexpr int kSmallThreads = 1024;
 constexpr u32 kSmallWaves = kSmallThreads / kWave;

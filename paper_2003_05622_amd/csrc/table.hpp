@@ -19,6 +19,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "form.hpp"
 
 namespace hps {
 
@@ -197,8 +198,6 @@ struct OftenLists {
   unsigned long long* report;
   u32 serial;
 };
-constexpr u32 kReportSlow = 2, kReportOneKey = 4, kReportMixed = 8, kReportStandIn = 16, kReportUneven = 32,
-              kReportCrowded = 64;
 
 // "Updated since the last dirty dump" is kept in the sign bit of a row's first
 // accumulator element: accumulators are sums of squares, never negative, so the bit
