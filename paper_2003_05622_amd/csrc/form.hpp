@@ -46,7 +46,10 @@ struct FormChoice {
   enum Away { kHotKeys, kSlowBuckets, kUnevenKeys, kCrowdedKeys } away;
   uint64_t stand_in_from;
   uint32_t unlisted;        // dedups since the last hps_last_unique (or the creation)
-  int listing_pinned;       // 0, or since an hps_last_unique was captured: 1 in an order of keys, 2 by hash
+  // Since an hps_last_unique was captured: the form, plus 1, of the mini-batch it was captured for.  A replay lists a later
+  // mini-batch of as many occurrences with the kernels of that form, so all of these have to take it, whatever is
+  // reported and listed.  By sizes that have the same forms to choose from (pin_of), 0: none.
+  uint8_t pinned[3];
   // The same for the plain form itself: after a dedup whose keys agreed in all the bits the
   // plain form sorts by (kReportMixed), the following ones sort by all 64 bits.
   uint32_t full_strikes;
@@ -58,14 +61,24 @@ struct FormChoice {
     unsigned long long range, other;
   };
 
-  // The form of dedup number `serial`, of n occurrences, with lookup_serial lookups issued so far.
-  int next(uint32_t n, uint64_t serial, uint64_t lookup_serial, Reports reports) {
+  static int pin_of(uint64_t n) { return n <= kSmallMax ? 0 : n <= kBorderMaxKeys ? 1 : n <= kBucketPathMaxKeys ? 2 : -1; }
+  // hps_last_unique is captured for a mini-batch of n occurrences that was dealt out in this form.
+  void captured(uint64_t n, int form) {
+    const int p = pin_of(n);            // (beyond there is the plain form only)
+    if (p >= 0 && !pinned[p]) pinned[p] = (uint8_t)(form + 1);
+  }
+
+  // The form of dedup number `serial`, of n occurrences, with lookup_serial lookups issued so far.  listable: of a
+  // mini-batch whose distinct keys may be listed (a pull's).
+  int next(uint32_t n, bool listable, uint64_t serial, uint64_t lookup_serial, Reports reports) {
     // The bucket path needs to know the heavy keys, which it learns from the lookups: the
     // first two dedups of a table take the plain passes, as do very large ones.
     const bool small = n <= kBorderMaxKeys, lists = unlisted < 2;       // (the next dedup may come before the call)
-    const bool quiet = listing_pinned ? listing_pinned == 2 : unlisted >= kQuiet;
+    const bool quiet = unlisted >= kQuiet;
     if (unlisted < kQuiet) ++unlisted;
     if (mode == 0) take(reports, serial, lookup_serial, small, lists);
+    const int pin = pin_of(n);
+    if (mode == 0 && listable && pin >= 0 && pinned[pin]) return pinned[pin] - 1;
     // The stand-ins for the key range.  By hash is the fastest for uneven keys whatever the size, but hps_last_unique then
     // has to sort all distinct keys.  So a caller who lists the keys of his mini-batches keeps an order of keys: up to
     // kBorderMaxKeys by range as long as that is not several times slower, else by borders; above, the plain form.

@@ -653,7 +653,7 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
       reports.other = __atomic_load_n(t->report, __ATOMIC_ACQUIRE);
       reports.range = __atomic_load_n(t->report + 1, __ATOMIC_RELAXED);
     }
-    const int form = t->choice.next(n, t->serial, t->lookup_serial, reports);
+    const int form = t->choice.next(n, d_offsets != nullptr, t->serial, t->lookup_serial, reports);
     t->cx[c].form = form;
     t->cx[c].buckets = form != kPlainForm;
     if (form == kSmallForm) {
@@ -1330,8 +1330,7 @@ hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_invers
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
   if (capture != hipStreamCaptureStatusNone) {
-    // (a replay lists a later mini-batch the way this one is: its dedup has to take the same form)
-    if (!t->choice.listing_pinned) t->choice.listing_pinned = cx.buckets && (cx.form == kByHash || cx.form == kSmallForm) ? 2 : 1;
+    t->choice.captured(cx.n_keys, cx.form);
     return list_unique(t, c, d_uniq_out, d_inverse_out, s);
   }
   if (!enter(t, s, true) || !wait_for(t, cx.ready, cx.ready_set, s) || !wait_for(t, t->listing, t->listing_set, s)) return HPS_EDEVICE;

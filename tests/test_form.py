@@ -1,0 +1,109 @@
+"""The choice of a dedup's form (csrc/form.hpp), compiled for the host: no GPU, no library."""
+import ctypes
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+RANGE, BORDERS, HASH, SMALL, PLAIN = range(5)
+SLOW, ONE_KEY, MIXED, STAND_IN, UNEVEN, CROWDED = 2, 4, 8, 16, 32, 64
+
+SOURCE = r"""
+#include "form.hpp"
+using namespace hps;
+extern "C" {
+FormChoice* make() { return new FormChoice(); }
+void drop(FormChoice* c) { delete c; }
+int next(FormChoice* c, uint32_t n, int listable, uint64_t serial, uint64_t lookups, unsigned long long range, unsigned long long other) {
+  return c->next(n, listable != 0, serial, lookups, {range, other});
+}
+void listed(FormChoice* c) { c->unlisted = 0; }
+void captured(FormChoice* c, uint64_t n, int form) { c->captured(n, form); }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("no g++ here")
+    d = tmp_path_factory.mktemp("form")
+    (d / "form.cpp").write_text(SOURCE)
+    so = str(d / "libform.so")
+    subprocess.check_call([gxx, "-O1", "-std=c++17", "-fPIC", "-shared", "-fsanitize=undefined", "-fsanitize-undefined-trap-on-error",
+                           "-I", os.path.join(ROOT, "paper_2003_05622_amd", "csrc"), "-o", so, str(d / "form.cpp")])
+    L = ctypes.CDLL(so)
+    u64, vp = ctypes.c_uint64, ctypes.c_void_p
+    L.make.restype = vp
+    L.drop.argtypes = [vp]
+    L.next.argtypes = [vp, ctypes.c_uint32, ctypes.c_int, u64, u64, u64, u64]
+    L.listed.argtypes = [vp]
+    L.captured.argtypes = [vp, u64, ctypes.c_int]
+    return L
+
+
+class Caller:
+    """A table's dedups, one after the other, each with its lookup, and the reports of the lookups as they arrive."""
+
+    def __init__(self, lib):
+        self.L, self.c = lib, lib.make()
+        self.serial = self.lookups = self.range = self.other = 0
+
+    def __del__(self):
+        self.L.drop(self.c)
+
+    def dedup(self, n, flags=0, listable=True):
+        """The form of the next dedup.  `flags`: what its lookup reports."""
+        self.serial += 1
+        form = self.L.next(self.c, n, listable, self.serial, self.lookups, self.range, self.other)
+        self.lookups += 1
+        if form == RANGE:
+            self.range = self.lookups | flags << 32
+        elif form != SMALL:
+            self.other = self.lookups | (flags & (SLOW | ONE_KEY) | STAND_IN if form != PLAIN else flags & MIXED) << 32
+        return form
+
+    def list(self):
+        self.L.listed(self.c)
+
+    def capture(self, n, form):
+        self.list()
+        self.L.captured(self.c, n, form)
+
+
+def test_captured_listing_keeps_the_form_of_uneven_keys_by_hash(lib):
+    """At most 65536 occurrences by hash, the third dedup after a listing: the fourth would take the small form."""
+    t, n = Caller(lib), 30_000
+    assert [t.dedup(n, UNEVEN | CROWDED) for _ in range(3)] == [PLAIN, PLAIN, RANGE]
+    t.list()
+    assert [t.dedup(n) for _ in range(2)] == [BORDERS, BORDERS] and t.dedup(n) == HASH
+    t.capture(n, HASH)
+    assert {t.dedup(n, SLOW) for _ in range(300)} == {HASH}
+
+
+def test_captured_listings_keep_their_forms_whatever_comes(lib):
+    rng = random.Random(1)
+    seen = set()
+    for turn in range(300):
+        t, pins = Caller(lib), {}
+        sizes = rng.choice([[500, 30_000], [65_536, 65_537], [100_000, 524_288, 524_289], [30_000, 300_000, 3_000_000], [2_000_000, 13_000_000]])
+        period = rng.choice([0, 1, 2, 4, 9])
+        for k in range(200):
+            n, listable = rng.choice(sizes), rng.random() < 0.9
+            flags = rng.choice([0, 0, 0, SLOW, SLOW | ONE_KEY, UNEVEN, UNEVEN | CROWDED, MIXED])
+            form = t.dedup(n, flags, listable)
+            group = sum(n > most for most in (65_536, 524_288, 12 << 20))
+            assert group < 3 or form == PLAIN
+            if listable and group in pins:
+                assert form == pins[group]
+            if listable and group < 3 and rng.random() < 0.02:
+                t.capture(n, form)
+                pins.setdefault(group, form)
+                seen.add((group, form))
+            elif listable and period and k % period == 0:
+                t.list()
+    assert len(seen) >= 9, seen           # every form was captured, at several sizes

@@ -104,6 +104,45 @@ def test_replayed_from_a_graph(form):
     assert gt.stats().error == 0
 
 
+def test_replayed_after_a_capture_by_hash(monkeypatch):
+    """Raw ids crowded in a part of their range: by hash on the third dedup after a listing, when nobody is taken not to list yet.
+    The mini-batches after the capture keep to that."""
+    monkeypatch.delenv("HPS_DEDUP", raising=False)
+    rng = np.random.default_rng(5)
+    n, n_bags, dim = 30_000, 1000, 4
+    gt = hps.HpsTable(20 * n, dim, n, n_bags)
+    offsets = torch.from_numpy(even_offsets(n, n_bags)).cuda()
+    uniq = torch.zeros(n, dtype=torch.int64, device="cuda")
+    inv = torch.zeros(n, dtype=torch.int32, device="cuda")
+    zero = torch.zeros((n_bags, dim), device="cuda")
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    for step in range(16):
+        keys = rng.integers(0, 10**9, size=n).astype(np.uint64)
+        keys[rng.random(n) < 0.4] = rng.integers(0, 5000, dtype=np.uint64) + np.uint64(7000)
+        crowd = rng.random(n) < 0.5
+        keys[crowd] = rng.integers(10**6, 2 * 10**6, size=int(crowd.sum())).astype(np.uint64)
+        gt.pull(dev(keys), offsets, n_bags, 1)
+        ou, oi = oracle.dedup(keys)
+        if step == 2:
+            u, i = gt.last_unique()
+            assert np.array_equal(u.cpu().numpy().view(np.uint64), ou) and np.array_equal(i.cpu().numpy(), oi)
+        if step == 5:
+            torch.cuda.synchronize()
+            with torch.cuda.graph(graph, stream=stream):
+                assert hps.lib().hps_last_unique(gt._h, uniq.data_ptr(), inv.data_ptr(), stream.cuda_stream) == hps.OK
+        if step >= 5:
+            uniq.fill_(-1)
+            inv.fill_(-1)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(uniq.cpu().numpy().view(np.uint64)[: ou.size], ou), "unique keys, step %d" % step
+            assert np.array_equal(inv.cpu().numpy(), oi), "ranks, step %d" % step
+        gt.push(zero)
+        gt.stats()                # (what the lookup has to report arrives)
+    st = gt.stats()
+    assert st.error == 0 and st.n_plain_fallbacks > 0
+
+
 @pytest.mark.parametrize("n", [300, 70_000])
 def test_after_a_pull_that_failed(form, n):
     """A table with no room for the mini-batch's keys, a mini-batch with the reserved key in it, and one that is pulled
