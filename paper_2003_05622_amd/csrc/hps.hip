@@ -335,6 +335,7 @@ struct hps_table {
     bool mean;            // pooling of this pull (fixed when it is prepared)
     bool looked_up;       // its dedup included the lookup (small form)
     int form;             // of its dedup (form.hpp)
+    bool guessed;         // ... taken because nobody is taken to list keys
     bool buckets;         // ... and whether that is the bucket or the small form ...
     BucketPlan plan;      // ... with these sizes
     hipEvent_t ready;     // recorded after the dedup kernels
@@ -655,6 +656,7 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
     }
     const int form = t->choice.next(n, d_offsets != nullptr, t->serial, t->lookup_serial, reports);
     t->cx[c].form = form;
+    t->cx[c].guessed = t->choice.guessed;
     t->cx[c].buckets = form != kPlainForm;
     if (form == kSmallForm) {
       t->cx[c].looked_up = include != kDedupOnly;
@@ -912,7 +914,7 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   for (int k = 0; k < 2; ++k) {
     t->cx[k].n_keys = t->cx[k].n_bags = 0;
     t->cx[k].d_offsets = nullptr;
-    t->cx[k].buckets = t->cx[k].looked_up = false;
+    t->cx[k].buckets = t->cx[k].looked_up = t->cx[k].guessed = false;
     t->cx[k].ready_set = t->cx[k].released_set = t->cx[k].listed = false;
     events_ok = events_ok &&
                 hipEventCreateWithFlags(&t->cx[k].ready, hipEventDisableTiming) == hipSuccess &&
@@ -1323,7 +1325,8 @@ hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_invers
   const int c = t->current;
   hps_table::Context& cx = t->cx[c];
   if (cx.n_keys == 0 || (!d_uniq_out && !d_inverse_out)) return HPS_OK;
-  t->choice.unlisted = 0;
+  t->choice.listed(cx.guessed);
+  cx.guessed = false;           // (listed again: that tells nothing new)
   // On any stream: after the dedup whose results it lists and after the call before it (the ranks'
   // scratch); the next dedup into this context waits for it (after_listing).  Events that were recorded outside a
   // capture cannot be waited for inside one: what is captured here, the caller orders.

@@ -20,7 +20,8 @@ void drop(FormChoice* c) { delete c; }
 int next(FormChoice* c, uint32_t n, int listable, uint64_t serial, uint64_t lookups, unsigned long long range, unsigned long long other) {
   return c->next(n, listable != 0, serial, lookups, {range, other});
 }
-void listed(FormChoice* c) { c->unlisted = 0; }
+void listed(FormChoice* c, int guessed) { c->listed(guessed != 0); }
+int guessed(FormChoice* c) { return c->guessed; }
 void captured(FormChoice* c, uint64_t n, int form) { c->captured(n, form); }
 }
 """
@@ -41,7 +42,8 @@ def lib(tmp_path_factory):
     L.make.restype = vp
     L.drop.argtypes = [vp]
     L.next.argtypes = [vp, ctypes.c_uint32, ctypes.c_int, u64, u64, u64, u64]
-    L.listed.argtypes = [vp]
+    L.listed.argtypes = [vp, ctypes.c_int]
+    L.guessed.argtypes = [vp]
     L.captured.argtypes = [vp, u64, ctypes.c_int]
     return L
 
@@ -61,6 +63,8 @@ class Caller:
         self.serial += 1
         form = self.L.next(self.c, n, listable, self.serial, self.lookups, self.range, self.other)
         self.lookups += 1
+        if listable:
+            self.guessed = self.L.guessed(self.c)          # (kept with the mini-batch)
         if form == RANGE:
             self.range = self.lookups | flags << 32
         elif form != SMALL:
@@ -68,7 +72,7 @@ class Caller:
         return form
 
     def list(self):
-        self.L.listed(self.c)
+        self.L.listed(self.c, self.guessed)
 
     def capture(self, n, form):
         self.list()
@@ -107,3 +111,30 @@ def test_captured_listings_keep_their_forms_whatever_comes(lib):
             elif listable and period and k % period == 0:
                 t.list()
     assert len(seen) >= 9, seen           # every form was captured, at several sizes
+
+
+@pytest.mark.parametrize("n", [20_000, 300_000, 5_000_000])
+def test_who_lists_now_and_then_gets_an_order_of_keys(lib, n):
+    """Whatever the period, a handful of listings find their keys dealt out by hash, and none once the caller is known."""
+    for period in [1, 2, 3, 4, 5, 7, 12, 33, 64, 65, 100, 250]:
+        t, dear = Caller(lib), []
+        for k in range(6000):
+            form = t.dedup(n)
+            for _ in range(k % 4):
+                t.dedup(n, listable=False)              # accumulates in between count for nothing
+            if k % period == period - 1:
+                if form in (HASH, SMALL):
+                    dear.append(k)
+                t.list()
+        assert len(dear) <= (0 if period < 4 else 1 if period < 65 else 3), (period, dear)
+
+
+@pytest.mark.parametrize("n", [20_000, 300_000, 5_000_000])
+def test_who_never_lists_goes_by_hash(lib, n):
+    t = Caller(lib)
+    forms = [t.dedup(n) for _ in range(50)]
+    assert RANGE in forms[:3] and set(forms[3:]) == {SMALL if n <= 65_536 else HASH}
+    t.list()                                             # once
+    assert {t.dedup(n) for _ in range(64)} == {RANGE}
+    assert {t.dedup(n) for _ in range(50)} == {SMALL if n <= 65_536 else HASH}
+    assert t.dedup(n, listable=False) == (SMALL if n <= 65_536 else HASH)
