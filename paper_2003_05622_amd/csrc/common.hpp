@@ -72,7 +72,7 @@ struct PullCtx {
   u32 n_evidence;      // plain form: sorted positions where a run of equal sorted bits mixes keys
   u32 sort_error;      // set if a look-back wait gave up (never expected)
   u32 n_total;         // occurrences of this dedup
-  u32 by_id;           // 0: this dedup took the plain form, else 1 + the bucket form's kByRange, kByBorders, kByHash
+  u32 by_id;           // 0: this dedup took the plain form, else 1 + its form (form.hpp)
   u32 n_heavy;         // bucket form: frequent keys with a bucket of their own
   u32 pad[2];
   u32 n_slow_one_key;  // ... of n_slow, in buckets that one key fills at least half of

@@ -46,6 +46,15 @@ struct FormChoice {
   // stand-ins have disappointed too (dedups numbered below stand_in_from).
   enum Away { kHotKeys, kSlowBuckets, kUnevenKeys, kCrowdedKeys } away;
   uint64_t stand_in_from;
+  // After a mini-batch that did not suit the small form (small.hpp), the next ones that would take it go by hash: for kPlainHold
+  // dedups, and twice as long each time the small form disappoints again before as many have gone well.  Then one dedup tries it,
+  // and the next ones wait for what comes of that, as above.
+  uint32_t small_seen;      // serial (of the dedup) of the last report acted on
+  uint32_t small_judged;    // reports of dedups up to this one do not count: issued before the form was given up
+  uint32_t small_strikes;
+  bool small_doubted;       // it has disappointed, and no try since then has gone well
+  uint32_t small_try;       // the lookup of the dedup that tries it, 0: none
+  uint64_t small_from;      // dedups numbered below this do not take the small form
   uint32_t unlisted;        // dedups of pulls since the last hps_last_unique (or the creation)
   // Times the call came for a mini-batch dealt out by hash because nobody was taken to want it.  Its keys are then sorted, which
   // costs more than many mini-batches by hash gain, so the patience with the next ones doubles each time: whoever
@@ -69,9 +78,9 @@ struct FormChoice {
   uint64_t full_until;
   uint64_t n_full_fallbacks;
 
-  // The words the lookups report into: of dedups by key range, of dedups in any other form.
+  // The words the lookups report into: of dedups by key range, of dedups in any other form; and the one of the small form.
   struct Reports {
-    unsigned long long range, other;
+    unsigned long long range, other, small;
   };
 
   static int pin_of(uint64_t n) { return n <= kSmallMax ? 0 : n <= kBorderMaxKeys ? 1 : n <= kBucketPathMaxKeys ? 2 : -1; }
@@ -102,7 +111,7 @@ struct FormChoice {
     // density rises from none to twice the mean: by range 90, 125, 740 and 2057, by hash 76, 104, 279 and 900.
     // Listing the unique keys: 18 to 40 us by borders, in the plain form 5 to 20, by hash 620 for 4 M distinct keys.)
     guessed = mode == 0 && quiet && listable;
-    if (n <= kSmallMax && (mode == 5 || (mode == 0 && quiet && serial >= stand_in_from))) return kSmallForm;
+    if (n <= kSmallMax && (mode == 5 || (mode == 0 && quiet && small_suits(serial, lookup_serial)))) return kSmallForm;
     if (n > kBucketPathMaxKeys || mode == 1 || (mode == 0 && lookup_serial < 2)) return kPlainForm;
     if (mode != 0) return mode == 3 && small ? kByBorders : mode >= 4 ? kByHash : kByRange;
     // (Nobody wants the keys in order: by hash.  The first kernel has no key range to sample, and a bucket's rows lie in one
@@ -125,6 +134,12 @@ struct FormChoice {
   bool all_bits(uint64_t serial) const { return mode < 2 && serial < full_until; }
 
  private:
+  bool small_suits(uint64_t serial, uint64_t lookup_serial) {
+    if (serial < small_from || small_try) return false;
+    if (small_doubted) small_try = (uint32_t)lookup_serial + 1;
+    return true;
+  }
+
   void take(Reports reports, uint64_t serial, uint64_t lookup_serial, bool small, bool lists) {
     if ((uint32_t)reports.range != range_seen) {
       const uint32_t at = (uint32_t)reports.range, flags = (uint32_t)(reports.range >> 32);
@@ -153,9 +168,25 @@ struct FormChoice {
         strikes = 0;
       }
     }
+    if ((uint32_t)reports.small != small_seen) {
+      const uint32_t at = small_seen = (uint32_t)reports.small;
+      if ((int32_t)(at - small_judged) > 0) {
+        if (!small_doubted && (int32_t)(at - (uint32_t)small_from) > (int32_t)kPlainHold) small_strikes = 0;
+        small_judged = (uint32_t)serial - 1;
+        small_doubted = true;
+        small_try = 0;
+        small_from = serial + (kPlainHold << (small_strikes < 7 ? small_strikes : 7));
+        ++small_strikes;
+      }
+    }
     if ((uint32_t)reports.other != other_seen) {
       const uint32_t at = (uint32_t)reports.other, flags = (uint32_t)(reports.other >> 32);
       other_seen = at;
+      // (of a lookup after the try's: what that had to report would be here)
+      if (small_try && (int32_t)(at - small_try) > 0) {
+        small_try = 0;
+        small_doubted = false;
+      }
       if (probe && (int32_t)(at - probe) >= 0) {      // its dedup was replaced by another: try again
         probe = 0;
         to_probe = true;

@@ -324,7 +324,7 @@ struct hps_table {
   u32 lookup_new_cap;
   uint64_t serial;     // number of dedups so far (status words carry it modulo kEpochMod)
   uint64_t plain_serial;   // ... of them in the plain form
-  unsigned long long* report;             // pinned host words the lookups report into: [0] of the lookup after a dedup in any form but by key range, [1] by key range
+  unsigned long long* report;             // pinned host words the lookups report into: [0] of the lookup after a dedup in any form but by key range, [1] by key range, [2] of the small form
   FormChoice choice;        // the dedups' form
 
   // Pull contexts.  `current` is the context of the outstanding pull (-1: none),
@@ -619,6 +619,8 @@ static void launch_small(hps_table* t, int c, const uint64_t* d_keys, u32 n, boo
   a.dealt = t->w<u64>(L.keys_a);
   a.upos = t->w<u32>(C.upos);
   a.slow = {t->w<u64>(L.idx_a), t->w<u64>(L.keys_b), t->w<u64>(L.idx_b)};
+  a.report = t->report ? t->report + 2 : nullptr;
+  a.serial = (u32)t->serial;
   a.rows = t->w<u32>(C.rows);
   a.create = LOOKUP ? creation_of(t, n, include == kWithPullLookup) : Creation();
   a.often = LOOKUP ? start_lookup(t, c, n) : OftenLists();
@@ -649,10 +651,11 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
     if (epoch == 1 && t->serial >= kEpochMod)   // the epochs start over: forget the old words
       fill_u64<<<1024, 256, 0, s>>>(t->w<u64>(L.tile_rows), (L.evidence - L.tile_rows) / 8, 0);
     // (the other forms' word first: what it tells of came after whatever the range's word then does not tell of)
-    FormChoice::Reports reports = {0, 0};
+    FormChoice::Reports reports = {0, 0, 0};
     if (t->report) {
       reports.other = __atomic_load_n(t->report, __ATOMIC_ACQUIRE);
       reports.range = __atomic_load_n(t->report + 1, __ATOMIC_RELAXED);
+      reports.small = __atomic_load_n(t->report + 2, __ATOMIC_RELAXED);
     }
     const int form = t->choice.next(n, d_offsets != nullptr, t->serial, t->lookup_serial, reports);
     t->cx[c].form = form;
@@ -935,7 +938,7 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
     hps_destroy(t);
     return HPS_EDEVICE;
   }
-  t->report[0] = t->report[1] = 0;
+  t->report[0] = t->report[1] = t->report[2] = 0;
   {
     // HPS_DEDUP=radix / bucket / borders / hashed / small pins the dedup to one of its forms (comparison runs, tests)
     const char* mode = std::getenv("HPS_DEDUP");

@@ -38,6 +38,12 @@ constexpr u32 kSmallMean = 256;            // occurrences of a bucket on average
 constexpr u32 kSmallMinLog2 = 1, kSmallMaxLog2 = 8;
 constexpr u32 kSmallBuckets = 1u << kSmallMaxLog2;
 constexpr u32 kSmallPiece = 8 * kWave;     // occurrences of its bucket a wave lists at a time
+// The block of a key that makes up much of the mini-batch places all its occurrences, 9 ns each on end, while the bucket form gives such a
+// key a bucket that needs no grouping.  A bucket this long is reported, and the next mini-batches go by hash.  (us a step, dim 8,
+// small form and by hash, one key with a share of 3, 12, 30, 50, 95 %: 20 K occurrences 23, 29, 39, 50, 77 and 39 to 41; 40 K 29, 34,
+// 51, 74, 132 and 40 to 42; 65 K 34, 45, 68, 105, 196 and 43 to 47; 5 K 20, 23, 28, 34, 41 and 35 to 38.)
+constexpr u32 kSmallLong = 7168;
+__device__ __forceinline__ bool small_too_long(u32 cnt, u32 n) { return cnt > kSmallLong || (n >= 2048 && cnt > n / 4 * 3); }
 constexpr u64 kSmallHistWords = (u64)(kSmallMax / kSmallTile) * kSmallBuckets;
 static_assert(kSmallMax <= kSmallMean << kSmallMaxLog2, "a byte per occurrence");
 static_assert(kSmallMax <= kSmallThreads * 64, "a bit per occurrence in a lane's mask");
@@ -58,6 +64,8 @@ struct SmallArgs {
   u64* dealt;            // group_slow: the bucket's keys, upos, its scratch
   u32* upos;
   SlowScratch slow;
+  unsigned long long* report;      // host memory (or null): receives `serial`, the dedup's number, if the mini-batch does not suit this form
+  u32 serial;
   // with the lookup
   u32* rows;
   Creation create;
@@ -70,7 +78,7 @@ small_ids(TableView t, SmallArgs a) {
   const u32 tid = threadIdx.x, i = blockIdx.x * kSmallTile + tid;
   const u64 key = a.keys[min(i, a.n - 1)];
   if (tid < kSmallBuckets) h[tid] = 0;
-  if (blockIdx.x == 0) reset_ctx(a.ctx, a.n, (u32)kByHash + 1, 0);
+  if (blockIdx.x == 0) reset_ctx(a.ctx, a.n, (u32)kSmallForm + 1, 0);
   __syncthreads();
   if (i < a.n) {
     const u32 id = key_hash(key) >> (32 - a.log2_nat);
@@ -158,6 +166,10 @@ __device__ __forceinline__ void small_list(uint16_t* list, const SmallMine& m, u
   __builtin_amdgcn_wave_barrier();
 }
 
+__device__ __forceinline__ void small_report(const SmallArgs& a) {
+  if (a.report) __hip_atomic_store(a.report, (unsigned long long)a.serial, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // LOOKUP: with the lookup.  ORDERED: how occurrences are ranked (sort.hpp: digit_rank).
 template <bool LOOKUP, bool ORDERED>
 __global__ void __launch_bounds__(kSmallThreads)
@@ -233,6 +245,7 @@ small_group(TableView t, SmallArgs a) {
       a.count[c] = 0;
       if (LOOKUP) a.often.med_span[c] = make_uint2(0u, 0u);
     }
+    if (small_too_long(cnt, n)) small_report(a);
   }
   if (cnt == 0) return;
 
@@ -284,9 +297,8 @@ small_group(TableView t, SmallArgs a) {
     group_slow<kSmallThreads>(a.dealt, start, start + cnt, a.uniq, a.seg_off, a.bags, a.upos, a.count, a.slow, a.ctx, L.slow);
     __syncthreads();
     u_count = a.count[c] & ~kSlowBucket;
-    if (LOOKUP && tid == 0 && cnt * 8 > n && a.often.report)
-      __hip_atomic_store(a.often.report, (unsigned long long)a.often.serial | ((unsigned long long)(kReportStandIn | kReportSlow) << 32),
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    // (more than an eighth of the occurrences in such buckets: whichever block adds the last of them sees it)
+    if (tid == 0 && (u64)__hip_atomic_load(&a.ctx->n_slow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) * 8 > n) small_report(a);
   } else {
     // per slot: the key's number in the bucket, its group's start, and the occurrences in earlier waves
     u32 here = 0;

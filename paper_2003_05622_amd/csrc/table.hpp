@@ -556,7 +556,8 @@ __device__ __forceinline__ void report_dedup(const UniqueSpans& spans, const Oft
   const u32 mean = s_sum / spans.n_spans;
   const bool uneven = ctx->by_id == 1 && s_most > mean + mean / 2 + 64;
   const bool crowded = uneven && (s_most > 3 * mean + 256 || ctx->n_slow > ctx->n_slow_one_key);
-  const u32 flags = (ctx->by_id > 1 ? kReportStandIn : 0u) | ((u64)ctx->n_slow * 8 > ctx->n_total ? kReportSlow : 0u) |
+  const u32 flags = (ctx->by_id > 1 ? kReportStandIn : 0u) |
+                    (ctx->by_id != kSmallForm + 1 && (u64)ctx->n_slow * 8 > ctx->n_total ? kReportSlow : 0u) |      // (small.hpp reports by itself)
                     ((u64)ctx->n_slow_one_key * 2 >= ctx->n_slow ? kReportOneKey : 0u) |
                     (uneven ? kReportUneven : 0u) | (crowded ? kReportCrowded : 0u) |
                     (!ctx->by_id && ctx->n_evidence > kMaxEvidence ? kReportMixed : 0u);

@@ -17,8 +17,8 @@ using namespace hps;
 extern "C" {
 FormChoice* make() { return new FormChoice(); }
 void drop(FormChoice* c) { delete c; }
-int next(FormChoice* c, uint32_t n, int listable, uint64_t serial, uint64_t lookups, unsigned long long range, unsigned long long other) {
-  return c->next(n, listable != 0, serial, lookups, {range, other});
+int next(FormChoice* c, uint32_t n, int listable, uint64_t serial, uint64_t lookups, unsigned long long range, unsigned long long other, unsigned long long small) {
+  return c->next(n, listable != 0, serial, lookups, {range, other, small});
 }
 void listed(FormChoice* c, int guessed) { c->listed(guessed != 0); }
 int guessed(FormChoice* c) { return c->guessed; }
@@ -41,7 +41,7 @@ def lib(tmp_path_factory):
     u64, vp = ctypes.c_uint64, ctypes.c_void_p
     L.make.restype = vp
     L.drop.argtypes = [vp]
-    L.next.argtypes = [vp, ctypes.c_uint32, ctypes.c_int, u64, u64, u64, u64]
+    L.next.argtypes = [vp, ctypes.c_uint32, ctypes.c_int, u64, u64, u64, u64, u64]
     L.listed.argtypes = [vp, ctypes.c_int]
     L.guessed.argtypes = [vp]
     L.captured.argtypes = [vp, u64, ctypes.c_int]
@@ -53,7 +53,7 @@ class Caller:
 
     def __init__(self, lib):
         self.L, self.c = lib, lib.make()
-        self.serial = self.lookups = self.range = self.other = 0
+        self.serial = self.lookups = self.range = self.other = self.small = 0
 
     def __del__(self):
         self.L.drop(self.c)
@@ -61,13 +61,16 @@ class Caller:
     def dedup(self, n, flags=0, listable=True):
         """The form of the next dedup.  `flags`: what its lookup reports."""
         self.serial += 1
-        form = self.L.next(self.c, n, listable, self.serial, self.lookups, self.range, self.other)
+        form = self.L.next(self.c, n, listable, self.serial, self.lookups, self.range, self.other, self.small)
         self.lookups += 1
         if listable:
             self.guessed = self.L.guessed(self.c)          # (kept with the mini-batch)
         if form == RANGE:
             self.range = self.lookups | flags << 32
-        elif form != SMALL:
+        elif form == SMALL:
+            if flags & SLOW:
+                self.small = self.serial
+        else:
             self.other = self.lookups | (flags & (SLOW | ONE_KEY) | STAND_IN if form != PLAIN else flags & MIXED) << 32
         return form
 
@@ -138,3 +141,33 @@ def test_who_never_lists_goes_by_hash(lib, n):
     assert {t.dedup(n) for _ in range(64)} == {RANGE}
     assert {t.dedup(n) for _ in range(50)} == {SMALL if n <= 65_536 else HASH}
     assert t.dedup(n, listable=False) == (SMALL if n <= 65_536 else HASH)
+
+
+@pytest.mark.parametrize("ahead", [1, 20, 300])
+def test_mini_batches_the_small_form_does_not_suit_go_by_hash(lib, ahead):
+    """The GPU is `ahead` dedups behind with what it reports.  The small form is tried again ever more rarely, one mini-batch at a
+    time, and is back for good once it does well."""
+    t, n, hold = Caller(lib), 20_000, 32
+    written = [(0, 0)]                   # the report words after every dedup
+
+    def dedup(suits):
+        small, other = written[-1]
+        seen = written[max(0, len(written) - 1 - ahead)]
+        t.small, t.other = seen
+        form = t.dedup(n)
+        written.append((t.serial if form == SMALL and not suits else small, t.other if t.other != seen[1] else other))
+        return form
+
+    forms = [dedup(False) for _ in range(4000)]
+    assert set(forms[3:]) == {SMALL, HASH}
+    assert forms.count(SMALL) <= ahead + 1 + 7 and SMALL in forms[ahead + 30 : 2 * ahead + 120]
+    assert set([dedup(True) for _ in range(6000)][-1000:]) == {SMALL}
+    forms = [dedup(False) for _ in range(ahead + 2)] + [dedup(True) for _ in range(3 * ahead + hold + 8)]
+    assert HASH in forms and forms[-1] == SMALL          # (the strikes are forgotten)
+
+
+def test_mini_batches_that_suit_the_small_form_every_other_time(lib):
+    """It is given up ever longer all the same."""
+    t, n = Caller(lib), 20_000
+    forms = [t.dedup(n, SLOW if k % 16 < 8 else 0) for k in range(8000)]
+    assert forms[1000:].count(SMALL) < 400
