@@ -18,6 +18,12 @@ namespace hps {
 constexpr int kPoolThreads = 256;
 constexpr int kPoolMaxBlocks = 1024;   // the groups loop over the bags (1536 to 3072 blocks measured no faster)
 constexpr int kPoolInFlight = 8;
+// Pooled rows are stored past the L2, which is left to the table's rows, where they are more than it holds for the kernel that reads
+// them next; never in small mini-batches, whose rows fit beside them.  (us a step of pull, a kernel that reads the pooled rows, push,
+// stored past the L2 and into it; that kernel a matrix product: 256 KB 53.4 and 52.5, 2 MB 63 and 61, 4 MB 67.6 and 64.9, 4.8 MB 94.1 and 92.3,
+// 8 MB 73.8 and 72.9, 16 MB 87.0 and 88.1, 33 MB 90.8 and 92.1, 102 MB 371 and 374, 262 MB 869 and 879; a product by element: 5 MB 44.6 and 43.4,
+// 10 MB 67.8 and 68.6, 33 MB 86.7 and 87.4, 102 MB 368 and 373, 262 MB 886 and 893; small form, 15 MB: 50.8 and 49.0, a matrix product 58.2 and 56.8.)
+constexpr u64 kPoolPastL2 = 8u << 20;
 
 // A bag's occurrences: 0 <= lo <= hi <= n whatever the offsets array holds, so that the kernel reads nothing outside row_of[0, n)
 // and no sum of a place and a few more overflows (n < 2^30).
@@ -39,7 +45,7 @@ template <int LPR, int COLS, bool BF16, bool SMALL>
 __device__ __forceinline__ void pool_bags_as(const TableView& t, const i32* __restrict__ offsets, u32 b, BagRange bag, BagRange next,
                                              u32 n_bags, u32 n, const u32* __restrict__ row_of,
                                              float* __restrict__ pooled, float* __restrict__ inv_len,
-                                             const uint4* __restrict__ places, u32* __restrict__ bags) {
+                                             const uint4* __restrict__ places, u32* __restrict__ bags, bool past_l2) {
   const u32 sub = threadIdx.x % LPR;
   const u32 dim4 = t.dim >> 2;
   const u32 n_groups = gridDim.x * (kPoolThreads / LPR);
@@ -123,10 +129,18 @@ __device__ __forceinline__ void pool_bags_as(const TableView& t, const i32* __re
 #pragma unroll
       for (int c = 0; c < COLS; ++c) {
         const u32 col = sub + c * LPR;
-        // (past the L2, which is left to the rows: 8.4 M occurrences, dim 64: 208.5 -> 204 us, and the push after it 309 -> 303)
         typedef float Words4 __attribute__((ext_vector_type(4)));
         const Words4 x = {acc[c].x, acc[c].y, acc[c].z, acc[c].w};
-        if (col < dim4) __builtin_nontemporal_store(x, reinterpret_cast<Words4*>(out + col));
+        if (col < dim4) {
+          if (past_l2) {
+            // (an instruction of its own on either side: the compiler would make one store of the two, and an ordinary one)
+            asm volatile("s_nop 0");
+            __builtin_nontemporal_store(x, reinterpret_cast<Words4*>(out + col));
+            asm volatile("s_nop 0");
+          } else {
+            *reinterpret_cast<Words4*>(out + col) = x;
+          }
+        }
         acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
       }
       b += n_groups;
@@ -146,8 +160,9 @@ pool_bags(TableView t, const i32* __restrict__ offsets, u32 n_bags, u32 n, const
   const u32 b = (blockIdx.x * kPoolThreads + threadIdx.x) / LPR, n_groups = gridDim.x * (kPoolThreads / LPR);
   const BagRange bag = load_bag(offsets, b, n_bags, n), next = load_bag(offsets, b + n_groups, n_bags, n);
   if (!end_pull(t, end)) return;
-  if (t.bf16) pool_bags_as<LPR, COLS, true, SMALL>(t, offsets, b, bag, next, n_bags, n, row_of, pooled, inv_len, places, bags);
-  else pool_bags_as<LPR, COLS, false, SMALL>(t, offsets, b, bag, next, n_bags, n, row_of, pooled, inv_len, places, bags);
+  const bool past_l2 = !SMALL && (u64)n_bags * t.dim * sizeof(float) > kPoolPastL2;
+  if (t.bf16) pool_bags_as<LPR, COLS, true, SMALL>(t, offsets, b, bag, next, n_bags, n, row_of, pooled, inv_len, places, bags, past_l2);
+  else pool_bags_as<LPR, COLS, false, SMALL>(t, offsets, b, bag, next, n_bags, n, row_of, pooled, inv_len, places, bags, past_l2);
 }
 
 // Plain form of the dedup: row_of[i] = rows[inverse[i]].
