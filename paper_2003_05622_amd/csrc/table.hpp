@@ -787,7 +787,6 @@ pull_lookup(TableView t, const u64* __restrict__ keys, const u32* __restrict__ s
       u = first + k;
       my_key = keys[u];
       my_len = seg_off[u + 1] - seg_off[u];
-      if (my_key == kEmptyKey) raise_error(t.st, kErrReserved);
     }
     const u32 my_row = lookup_key(t, my_key, create_here, create.new_cap, L, &mine_new);
     // every lane: the row of its own key, and the push's work lists

@@ -113,3 +113,31 @@ def test_static_scratch_holds_the_widest_rows():
     before = gt.get(keys)[0]
     gt.accumulate_static(keys, torch.full((n, dim), 0.5, device="cuda"))
     assert torch.equal(gt.get(keys)[0], before + 0.5) and gt.stats().error == 0
+
+
+@pytest.mark.parametrize("how", ["pull", "prepared", "accumulate"])
+@pytest.mark.parametrize("n", [1, 1025, 40_001])
+def test_reserved_key(n, how, rank):
+    """Refused by the dedup itself: nothing of the mini-batch gets into the table."""
+    rng = np.random.default_rng(n)
+    dim, n_bags = 8, max(1, n // 3)
+    gt = hps.HpsTable(20 * n + 100, dim, n, n_bags)
+    known = synth.mix64(np.arange(n, dtype=np.uint64))
+    gt.insert(dev(known))
+    before = gt.get(dev(known))[0]
+    keys = synth.mix64(rng.integers(0, 2 * n, size=n).astype(np.uint64))
+    keys[rng.integers(0, n)] = np.uint64(2**64 - 1)
+    offsets = torch.from_numpy((np.arange(n_bags + 1, dtype=np.int64) * n // n_bags).astype(np.int32)).cuda()
+    if how == "pull":
+        gt.pull(dev(keys), offsets, n_bags, 1)
+    elif how == "prepared":
+        gt.prepare(dev(keys), offsets, n_bags, 1)
+        gt.pull_prepared()
+    else:
+        gt.accumulate(dev(keys), torch.ones((n, dim), device="cuda"))
+    assert gt.stats().error == hps.ERESERVED
+    gt.clear_error()
+    assert gt.stats().size == n and torch.equal(gt.get(dev(known))[0], before)
+    keys = known[rng.integers(0, n, size=n)]
+    gt.pull(dev(keys), offsets, n_bags, 1)
+    assert gt.stats().error == 0 and gt.stats().size == n
