@@ -344,8 +344,7 @@ struct hps_table {
     bool listed;          // hps_last_unique has read this context since its dedup
   } cx[2];
   int current, prepared;
-  hipEvent_t scratch_free;   // the last dedup's end: the sort scratch is shared
-  bool scratch_set;
+  hipEvent_t scratch_free;   // the one of the other events that marks the end of the last work on the dedups' scratch, which is shared; or null
   hipEvent_t listing;        // the last hps_last_unique's end: its scratch, and the context it read
   bool listing_set;
   // While all calls come on the null stream, its order is all they need, and none of these events is recorded (a record
@@ -385,7 +384,7 @@ void stage_mark(hps_table* t, int stage, hipStream_t s) {
 // perhaps in use for a new stream, and hipStreamDestroy need not wait for the work on it.
 static bool leave_null_stream(hps_table* t) {
   const struct { hipEvent_t event; bool set; } left_out[] = {
-      {t->scratch_free, t->scratch_set}, {t->listing, t->listing_set}, {t->cx[0].ready, t->cx[0].ready_set},
+      {t->listing, t->listing_set}, {t->cx[0].ready, t->cx[0].ready_set},
       {t->cx[1].ready, t->cx[1].ready_set}, {t->cx[0].released, t->cx[0].released_set}, {t->cx[1].released, t->cx[1].released_set}};
   for (const auto& e : left_out)
     if (e.set && hipEventRecord(e.event, nullptr) != hipSuccess) {
@@ -404,7 +403,7 @@ static bool enter(hps_table* t, hipStream_t s, bool waits) {
   if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
   if (capture != hipStreamCaptureStatusNone) {
     // (what ran before the capture cannot be waited for inside it)
-    if (t->scratch_set || t->listing_set || t->cx[0].released_set || t->cx[1].released_set) return !waits;
+    if (t->scratch_free || t->listing_set || t->cx[0].released_set || t->cx[1].released_set) return !waits;
     t->many_streams = true;
     return true;
   }
@@ -417,6 +416,8 @@ static bool mark(hps_table* t, hipEvent_t e, bool* set, hipStream_t s) {
 static bool wait_for(const hps_table* t, hipEvent_t e, bool set, hipStream_t s) {
   return !set || !t->many_streams || hipStreamWaitEvent(s, e, 0) == hipSuccess;
 }
+
+static bool wait_for_scratch(const hps_table* t, hipStream_t s) { return wait_for(t, t->scratch_free, t->scratch_free != nullptr, s); }
 
 static UniqueSpans unique_spans(const hps_table* t, int c, uint64_t n) {
   const hps_table::Context& cx = t->cx[c];
@@ -909,11 +910,10 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   t->lpr = lanes_per_row(dim);
   t->current = t->prepared = -1;
   t->last_n_keys = 0;
-  t->scratch_set = false;
+  t->scratch_free = nullptr;
   t->listing_set = false;
   t->many_streams = false;
-  bool events_ok = hipEventCreateWithFlags(&t->scratch_free, hipEventDisableTiming) == hipSuccess &&
-                   hipEventCreateWithFlags(&t->listing, hipEventDisableTiming) == hipSuccess;
+  bool events_ok = hipEventCreateWithFlags(&t->listing, hipEventDisableTiming) == hipSuccess;
   for (int k = 0; k < 2; ++k) {
     t->cx[k].n_keys = t->cx[k].n_bags = 0;
     t->cx[k].d_offsets = nullptr;
@@ -972,7 +972,6 @@ hps_status hps_destroy(hps_table* t) {
   for (int i = 0; i < HPS_N_STAGES; ++i)
     for (hipEvent_t e : t->ev_pool[i]) (void)hipEventDestroy(e);
   // (a table whose creation failed half way holds null handles)
-  if (t->scratch_free) (void)hipEventDestroy(t->scratch_free);
   if (t->listing) (void)hipEventDestroy(t->listing);
   for (int k = 0; k < 2; ++k) {
     if (t->cx[k].ready) (void)hipEventDestroy(t->cx[k].ready);
@@ -1041,7 +1040,7 @@ static hps_status prepare(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
   // order after the push that last read this context, and after the previous dedup
   // (the sort scratch is shared); both may have run on other streams
   if (!enter(t, s, true)) return HPS_EDEVICE;
-  if (!wait_for(t, cx.released, cx.released_set, s) || !wait_for(t, t->scratch_free, t->scratch_set, s)) return HPS_EDEVICE;
+  if (!wait_for(t, cx.released, cx.released_set, s) || !wait_for_scratch(t, s)) return HPS_EDEVICE;
   if (!after_listing(t, c, s)) return HPS_EDEVICE;
   // (a lookup among it: what hps_pull_prepared orders it after)
   const hps_table::Context& other = t->cx[1 - c];
@@ -1049,7 +1048,8 @@ static hps_status prepare(hps_table* t, const uint64_t* d_keys, uint64_t n_keys,
 
   launch_dedup(t, c, d_keys, n, d_offsets, (u32)n_bags, include, s);
   if (!launch_ok()) return HPS_EDEVICE;
-  if (!mark(t, cx.ready, &cx.ready_set, s) || !mark(t, t->scratch_free, &t->scratch_set, s)) return HPS_EDEVICE;
+  if (!mark(t, cx.ready, &cx.ready_set, s)) return HPS_EDEVICE;
+  t->scratch_free = cx.ready;
   cx.n_keys = n_keys;
   cx.n_bags = n_bags;
   cx.d_offsets = d_offsets;
@@ -1172,11 +1172,13 @@ hps_status hps_accumulate(hps_table* t, const uint64_t* d_keys, uint64_t n, cons
   if (!enter(t, s, true)) return HPS_EDEVICE;
   for (int k = 0; k < 2; ++k)      // after the last push of either context (shared work lists, table rows)
     if (!wait_for(t, t->cx[k].released, t->cx[k].released_set, s)) return HPS_EDEVICE;
-  if (!wait_for(t, t->scratch_free, t->scratch_set, s)) return HPS_EDEVICE;
+  if (!wait_for_scratch(t, s)) return HPS_EDEVICE;
   if (!after_listing(t, 0, s)) return HPS_EDEVICE;
   const hps_status rc = accumulate_launches(t, d_keys, n, d_values, s);
   if (rc != HPS_OK) return rc;
-  return mark(t, cx.released, &cx.released_set, s) && mark(t, t->scratch_free, &t->scratch_set, s) ? HPS_OK : HPS_EDEVICE;
+  if (!mark(t, cx.released, &cx.released_set, s)) return HPS_EDEVICE;
+  t->scratch_free = cx.released;
+  return HPS_OK;
 }
 
 hps_status hps_accumulate_static(hps_table* t, const uint64_t* d_keys, uint64_t n,
@@ -1341,10 +1343,10 @@ hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_invers
   }
   if (!enter(t, s, true) || !wait_for(t, cx.ready, cx.ready_set, s) || !wait_for(t, t->listing, t->listing_set, s)) return HPS_EDEVICE;
   const bool sorts = cx.buckets && (cx.form == kByHash || cx.form == kSmallForm);       // in the scratch of the dedups
-  if (sorts && !wait_for(t, t->scratch_free, t->scratch_set, s)) return HPS_EDEVICE;
+  if (sorts && !wait_for_scratch(t, s)) return HPS_EDEVICE;
   const hps_status rc = list_unique(t, c, d_uniq_out, d_inverse_out, s);
-  if (sorts && !mark(t, t->scratch_free, &t->scratch_set, s)) return HPS_EDEVICE;
   if (!mark(t, t->listing, &t->listing_set, s)) return HPS_EDEVICE;
+  if (sorts) t->scratch_free = t->listing;
   cx.listed = true;
   return rc;
 }
