@@ -60,14 +60,16 @@
  *     workgroups (counts per tile, a scan, a scatter into buckets; then every bucket's keys are
  *     grouped inside one workgroup).  The buckets are parts of the keys' hashes, and up to 65536
  *     occurrences each bucket's workgroup picks its keys out by itself and looks them up in the same launch,
- *     unless hps_last_unique was called within the last three dedups: then they are parts of the keys' range.  The lookups report
+ *     unless hps_last_unique was called within the last three dedups of pulls (64 and more once it has been
+ *     called for keys dealt out by hash, which it has to sort): then they are parts of the keys' range.  The kernels report
  *     back, into pinned host memory that nobody waits for, when the keys did not suit that, and the next dedups then deal
  *     the keys out by their hashes instead (by
  *     sampled borders where hps_last_unique is in use, up to 2^19 occurrences), or take
  *     the plain form (radix passes with look-back between tiles), sorting by all 64 key
  *     bits if need be: hps_stats().n_plain_fallbacks, .n_full_fallbacks.  What a pull needs of
  *     a dedup is the occurrences grouped by key; the ascending order of the unique keys is
- *     worked out when hps_last_unique asks for it.
+ *     worked out when hps_last_unique asks for it.  Once that call has been captured into a graph, mini-batches
+ *     of like size keep to the form of the one it was captured for, so that a replay lists what a later pull left.
  *   - Calls on one stream are ordered by it.  hps_prepare, hps_pull, hps_pull_prepared, hps_push, hps_accumulate and hps_last_unique
  *     of one table may also come on several streams and are ordered by events (a push that comes on another stream than its pull:
  *     by the caller).  As long as all of them come on the null stream no event is recorded, which saves about 3 us each

@@ -1,7 +1,7 @@
 // Which form a dedup takes (host code; nothing here needs a GPU).
 //
 // All forms give the same results, so this is about time only: by size, by whether the caller lists the distinct keys
-// (hps_last_unique), and by what the lookups report about the dedups before, in pinned host words that nobody waits for.
+// (hps_last_unique), and by what the kernels report about the dedups before, in pinned host words that nobody waits for.
 #pragma once
 
 #include <stdint.h>
@@ -27,9 +27,8 @@ constexpr uint64_t kHintLag = 3;         // ... after a surprise that the next l
 struct FormChoice {
   int mode;            // 0: by size and history; 1: plain radix passes always; 2, 3, 4: bucket form whenever it can, by range, borders, hash;
                        // 5: small form up to kSmallMax, beyond by hash
-  // When a dedup
-  // of the bucket form by key range had to order much of its input the slow way (frequent keys that change from
-  // one mini-batch to the next), or found the keys lying unevenly in their range, the following dedups take
+  // When a dedup of the bucket form by key range had to order much of its input the slow way (frequent keys that change
+  // from one mini-batch to the next), or found the keys lying unevenly in their range, the following dedups take
   // another form: for kPlainHold dedups, and twice as long each time in a row the range then disappoints again.
   uint32_t range_seen, other_seen;        // serials of the last reports acted on
   uint32_t judged;          // reports of lookups up to this one do not count: issued before the range was given up

@@ -506,7 +506,8 @@ __device__ __forceinline__ void rows_by_position(const UniqueSpans& spans, const
   const bool wide = (spans.count[c] & 0x80000000u) != 0;       // (bucket.hpp: upos_at)
   if (lds_rows && !wide) {
     // (two positions a lane and load, four loads in flight: one after the other, with rows[] from the L2, a block spent a fifth
-    // of its time here; the whole lookup, 8.4 M occurrences of 0.27 M keys: 52 us, 44 now)
+    // of its time here; the whole lookup, 8.4 M occurrences of 0.27 M keys: 52 us, 44 with this; 20 since the blocks have
+    // their own parts of the list of medium keys: OftenLists)
     constexpr int kTurns = 4;
     const u32* up = out.upos + first;
     for (u32 e0 = 2 * threadIdx.x; e0 < end - first; e0 += 2 * kProbeThreads * kTurns) {
