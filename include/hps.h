@@ -60,8 +60,8 @@
  *     workgroups (counts per tile, a scan, a scatter into buckets; then every bucket's keys are
  *     grouped inside one workgroup).  The buckets are parts of the keys' hashes, and up to 65536
  *     occurrences each bucket's workgroup picks its keys out by itself and looks them up in the same launch,
- *     unless hps_last_unique was called within the last three dedups of pulls (64 and more once it has been
- *     called for keys dealt out by hash, which it has to sort): then they are parts of the keys' range.  The kernels report
+ *     unless hps_last_unique was called within the last three dedups of pulls (the last 10, beyond 65536
+ *     occurrences 24, if it was called as often the time before; keys dealt out by hash it has to sort): then they are parts of the keys' range.  The kernels report
  *     back, into pinned host memory that nobody waits for, when the keys did not suit that, and the next dedups then deal
  *     the keys out by their hashes instead (by
  *     sampled borders where hps_last_unique is in use, up to 2^19 occurrences), or take

@@ -20,7 +20,7 @@ constexpr uint32_t kReportSlow = 2, kReportOneKey = 4, kReportMixed = 8, kReport
                    kReportCrowded = 64;
 
 constexpr uint32_t kQuiet = 3;           // dedups without an hps_last_unique until a caller is taken not to want it ...
-constexpr uint32_t kQuietAgain = 64;     // ... once he has called it all the same
+constexpr uint32_t kOftenSmall = 10, kOften = 24;      // ... if he calls it often: up to kSmallMax occurrences, beyond
 constexpr uint64_t kPlainHold = 32;      // dedups in another form after one disappointed
 constexpr uint64_t kHintLag = 3;         // ... after a surprise that the next lists of frequent keys will cover
 
@@ -55,18 +55,20 @@ struct FormChoice {
   uint32_t small_try;       // the lookup of the dedup that tries it, 0: none
   uint64_t small_from;      // dedups numbered below this do not take the small form
   uint32_t unlisted;        // dedups of pulls since the last hps_last_unique (or the creation)
-  // Times the call came for a mini-batch dealt out by hash because nobody was taken to want it.  Its keys are then sorted, which
-  // costs more than many mini-batches by hash gain, so the patience with the next ones doubles each time: whoever
-  // lists every so many mini-batches is caught a few times and then never again.  (us a step, a listing every fourth step, patience
-  // of 3 dedups and after 64: 1000 occurrences 58 and 38, 20 K 74 and 45, 0.3 M 99 and 71, 2 M 206 and 162, 9 M 719 and 629.)
-  uint32_t caught;
-  uint32_t patience() const { return caught ? kQuietAgain << (caught < 7 ? caught - 1 : 6) : kQuiet; }
-  // hps_last_unique is called for a mini-batch for which next() left `guessed` so.
-  void listed(bool guessed_then) {
+  // ... and how many there were the time before.  Keys dealt out by hash have to be sorted when they are listed, which costs as much as
+  // so many mini-batches by hash gain (often).  Whoever has just listed after no more than that keeps an order of keys for as many
+  // dedups again, so that a caller with such a period is caught once; whoever lists more rarely is better off by hash all the same.
+  // (us a step, hashed keys, dim 16, by range always and by hash from the fourth dedup after a listing on, a listing every
+  // 4, 12, 48 steps: 1000 occurrences 38, 37, 36 and 59, 37, 29; 20 K 49, 47, 46 and 73, 42, 30; 0.3 M 81, 77, 76 and 112, 83, 73;
+  // 2 M 297, 287, 283 and 358, 302, 281; 9 M 1314, 1283, 1271 and 1500, 1316, 1246.  The two meet at 13, 9, 23, 34 and 20.)
+  uint32_t period;
+  static uint32_t often(uint64_t n) { return n <= kSmallMax ? kOftenSmall : kOften; }
+  uint32_t patience(uint64_t n) const { return period && period <= often(n) ? often(n) : kQuiet; }
+  // hps_last_unique is called for a mini-batch for the first time.
+  void listed() {
+    period = unlisted ? unlisted : 1;       // (0: a dedup may have come before the listing of the one before it)
     unlisted = 0;
-    if (guessed_then && caught < 7) ++caught;
   }
-  bool guessed;             // the last form was taken because nobody is taken to list keys
   // Since an hps_last_unique was captured: the form, plus 1, of the mini-batch it was captured for.  A replay lists a later
   // mini-batch of as many occurrences with the kernels of that form, so all of these have to take it, whatever is
   // reported and listed.  By sizes that have the same forms to choose from (pin_of), 0: none.
@@ -95,9 +97,8 @@ struct FormChoice {
     // The bucket path needs to know the heavy keys, which it learns from the lookups: the
     // first two dedups of a table take the plain passes, as do very large ones.
     const bool small = n <= kBorderMaxKeys, lists = unlisted < 2;       // (the next dedup may come before the call)
-    const bool quiet = !listable || unlisted >= patience();
+    const bool quiet = !listable || unlisted >= patience(n);
     if (listable && unlisted < ~0u) ++unlisted;
-    guessed = false;
     if (mode == 0) take(reports, serial, lookup_serial, small, lists);
     const int pin = pin_of(n);
     if (mode == 0 && listable && pin >= 0 && pinned[pin]) return pinned[pin] - 1;
@@ -109,7 +110,6 @@ struct FormChoice {
     // by range 327, 402, 1494 and 5822 us, by hash 76, 104, 263 and 940, plain 126, 187, 391 and 1270, by borders 118 and 161; ids whose
     // density rises from none to twice the mean: by range 90, 125, 740 and 2057, by hash 76, 104, 279 and 900.
     // Listing the unique keys: 18 to 40 us by borders, in the plain form 5 to 20, by hash 620 for 4 M distinct keys.)
-    guessed = mode == 0 && quiet && listable;
     if (n <= kSmallMax && (mode == 5 || (mode == 0 && quiet && small_suits(serial, lookup_serial)))) return kSmallForm;
     if (n > kBucketPathMaxKeys || mode == 1 || (mode == 0 && lookup_serial < 2)) return kPlainForm;
     if (mode != 0) return mode == 3 && small ? kByBorders : mode >= 4 ? kByHash : kByRange;

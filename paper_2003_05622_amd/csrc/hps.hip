@@ -335,13 +335,13 @@ struct hps_table {
     bool mean;            // pooling of this pull (fixed when it is prepared)
     bool looked_up;       // its dedup included the lookup (small form)
     int form;             // of its dedup (form.hpp)
-    bool guessed;         // ... taken because nobody is taken to list keys
     bool buckets;         // ... and whether that is the bucket or the small form ...
     BucketPlan plan;      // ... with these sizes
     hipEvent_t ready;     // recorded after the dedup kernels
     hipEvent_t released;  // recorded after the push that used the context
     bool ready_set, released_set;
     bool listed;          // hps_last_unique has read this context since its dedup
+    bool counted;         // ... was called for it, captured or not
   } cx[2];
   int current, prepared;
   hipEvent_t scratch_free;   // the one of the other events that marks the end of the last work on the dedups' scratch, which is shared; or null
@@ -641,7 +641,7 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
   const WorkspaceLayout& L = t->wl;
   const ContextLayout& C = L.c[c];
   PullCtx* ctx = t->ctx(c);
-  t->cx[c].buckets = t->cx[c].looked_up = false;
+  t->cx[c].buckets = t->cx[c].looked_up = t->cx[c].counted = false;
   if (n == 0) {
     set_ctx_empty<<<1, 64, 0, s>>>(ctx, t->w<u32>(C.seg_off));
   } else {
@@ -660,7 +660,6 @@ static void launch_dedup(hps_table* t, int c, const uint64_t* d_keys, u32 n,
     }
     const int form = t->choice.next(n, d_offsets != nullptr, t->serial, t->lookup_serial, reports);
     t->cx[c].form = form;
-    t->cx[c].guessed = t->choice.guessed;
     t->cx[c].buckets = form != kPlainForm;
     if (form == kSmallForm) {
       t->cx[c].looked_up = include != kDedupOnly;
@@ -917,8 +916,8 @@ hps_status hps_create(hps_table** out, uint64_t capacity_keys, uint32_t dim,
   for (int k = 0; k < 2; ++k) {
     t->cx[k].n_keys = t->cx[k].n_bags = 0;
     t->cx[k].d_offsets = nullptr;
-    t->cx[k].buckets = t->cx[k].looked_up = t->cx[k].guessed = false;
-    t->cx[k].ready_set = t->cx[k].released_set = t->cx[k].listed = false;
+    t->cx[k].buckets = t->cx[k].looked_up = false;
+    t->cx[k].ready_set = t->cx[k].released_set = t->cx[k].listed = t->cx[k].counted = false;
     events_ok = events_ok &&
                 hipEventCreateWithFlags(&t->cx[k].ready, hipEventDisableTiming) == hipSuccess &&
                 hipEventCreateWithFlags(&t->cx[k].released, hipEventDisableTiming) == hipSuccess;
@@ -1330,8 +1329,8 @@ hps_status hps_last_unique(hps_table* t, uint64_t* d_uniq_out, int32_t* d_invers
   const int c = t->current;
   hps_table::Context& cx = t->cx[c];
   if (cx.n_keys == 0 || (!d_uniq_out && !d_inverse_out)) return HPS_OK;
-  t->choice.listed(cx.guessed);
-  cx.guessed = false;           // (listed again: that tells nothing new)
+  if (!cx.counted) t->choice.listed();          // (listed again: that tells nothing new)
+  cx.counted = true;
   // On any stream: after the dedup whose results it lists and after the call before it (the ranks'
   // scratch); the next dedup into this context waits for it (after_listing).  Events that were recorded outside a
   // capture cannot be waited for inside one: what is captured here, the caller orders.
