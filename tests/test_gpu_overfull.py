@@ -114,3 +114,45 @@ def test_overfull_while_the_next_mini_batch_fails(n, form, monkeypatch):
         assert gt.stats().error == 0 and gt.stats().size == size
         torch.testing.assert_close(pooled, rows.reshape(n_bags, -1, dim).sum(dim=1), rtol=1e-5, atol=1e-6)
     assert hps.ERESERVED in errors
+
+
+@pytest.mark.parametrize("form", ["auto", "small", "hashed", "bucket", "radix"])
+@pytest.mark.parametrize("n", [900, 5000, 70_000])
+def test_marks_of_earlier_pulls_are_not_rolled_back(n, form, monkeypatch):
+    """The state in which an error finds a pull whose first blocks have created more than fits, put there by hand: the error is
+    set and keys are counted as created before the lookup runs, so that all its blocks stop and leave the marks and rows of the pulls
+    before, which fitted.  Their keys stay."""
+    monkeypatch.setenv("HPS_DEDUP", form)
+    dim, n_bags, cap = 4, max(9, n // 100), 5 * n
+    rng = np.random.default_rng(n)
+    gt = hps.HpsTable(cap, dim, n, n_bags)
+    d_offsets = torch.from_numpy((np.arange(n_bags + 1, dtype=np.int64) * n // n_bags).astype(np.int32)).cuda()
+    zero = torch.zeros((n_bags, dim), device="cuda")
+    ids = lambda first, last: synth.mix64(np.arange(first, last, dtype=np.uint64))
+    at = cap - n + n // 10
+    gt.insert(dev(ids(0, at)))
+    for _ in range(4):                                    # (above the capacity if all its occurrences were new keys: marked)
+        new = n // 10
+        gt.pull(dev(rng.permutation(np.concatenate([ids(at, at + new), ids(0, n - new)]))), d_offsets, n_bags, 1)
+        gt.push(zero)
+        at += new
+    stored = ids(0, at)
+    # the table's state lies at the end of its storage: size, rows created last; the error after these; the counts of created rows
+    state = gt.storage[-1280:].view(torch.int32)
+    assert gt.stats().size == at and state[:4].tolist() == [at, 0, n // 10, 0] and state[4] == 0
+    for _ in range(3):                                    # (both contexts, both sets of counts)
+        gt.prepare(dev(rng.permutation(stored)[:n]), d_offsets, n_bags, 1)
+        state[4] = hps.ERESERVED
+        state[136] = state[200] = 2 * n
+        gt.pull_prepared()
+        assert gt.stats().error == hps.ERESERVED
+        gt.clear_error()
+        assert gt.stats().size == at and gt.get(dev(stored))[2].all()
+    keys = gt.dump()[0].cpu().numpy().view(np.uint64)
+    assert np.array_equal(np.sort(keys), np.sort(stored))
+    keys = rng.permutation(stored)[:n]
+    pooled = gt.pull(dev(keys), d_offsets, n_bags, 1)
+    gt.push(zero)
+    total = torch.cat([torch.zeros((1, dim), dtype=torch.float64, device="cuda"), gt.get(dev(keys))[0].double().cumsum(dim=0)])[d_offsets.long()]
+    torch.testing.assert_close(pooled, (total[1:] - total[:-1]).float(), rtol=1e-5, atol=1e-6)
+    assert gt.stats().error == 0 and gt.stats().size == at
